@@ -132,3 +132,33 @@ def test_longest_message_the_encoder_takes(dq, b):
         dq.dq_sparse_encode(torch.zeros((nw1 + 3) // 4 * 4, dtype=torch.int32, device="cuda"), d1, b,
                             torch.zeros(dq.dq_sparse_stream_words(d1, b), dtype=torch.int32, device="cuda"), nnz[:1])
     assert e.value.code == dq.ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("M,d,b", [(1, 1279, 8), (2, 1281, 8), (300, 700, 4), (1, 24576, 4), (8, 47236, 4), (1, 49152, 8),
+                                   (2, 62080, 2)])
+def test_encode_decode_where_a_row_is_cut(dq, M, d, b):
+    """Rows of one word more and less than a span, rows past 256, the widest streams: bits across the cuts, dense rows."""
+    rng = np.random.default_rng(d)
+    nw, cap = dq.packed_words(d, b), dq.dq_sparse_stream_words(d, b)
+    ldw = (nw + 3) // 4 * 4
+    codes = rng.integers(-(2 ** (b - 1)), 2 ** (b - 1), size=(M, d)).astype(np.int8)
+    codes[0][codes[0] == 0] = 1                          # every coordinate sent: the whole capacity is used
+    if M > 1:
+        codes[1, rng.random(d) < 0.97] = 0
+    pw = np.zeros((M, ldw), dtype=np.uint32)
+    for m in range(M):
+        pw[m, :nw] = oracle.pack(codes[m], b)
+    left = d * b % 32
+    dirty = pw.copy()
+    if left:
+        dirty[:, nw - 1] |= np.uint32((0xFFFFFFFF << left) & 0xFFFFFFFF)      # what lies past the last coordinate is not sent
+    stream = torch.full((M, cap), -1, dtype=torch.int32, device="cuda")
+    nnz = torch.full((M,), -1, dtype=torch.int32, device="cuda")
+    dq.dq_sparse_encode(dev(dirty.view(np.int32)), d, b, stream, nnz)
+    for m in range(min(M, 4)):
+        want, k = oracle.sparse_encode(codes[m], b)
+        assert host(nnz)[m] == k
+        assert np.array_equal(words(stream)[m, :cap], want)
+    back = torch.full((M, ldw), -1, dtype=torch.int32, device="cuda")
+    dq.dq_sparse_decode(stream, nnz, d, b, back)
+    assert np.array_equal(words(back)[:, :nw], pw[:, :nw])
