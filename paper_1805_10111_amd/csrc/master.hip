@@ -1,6 +1,7 @@
 // Master side of a round (Alg. 1, master (ii) then (i); Alg. 3 momentum update),
 // the epoch-boundary vector operations of Alg. 3, mini-batch index sampling and the
 // stand-alone gradient sparsifier of eq. (3).
+#include <algorithm>
 #include <type_traits>
 
 #include "dq_common.h"
@@ -426,9 +427,28 @@ __global__ __launch_bounds__(kThreads) void sample_indices_kernel(uint32_t n, in
     idx[static_cast<int64_t>(blockIdx.y) * B + j] = static_cast<int32_t>(__umulhi(w, n));
 }
 
-// ------------------------------------------------------------------ sparsifier, one block per row
+// ------------------------------------------------------------------ sparsifier
 constexpr int kSparsifyThreads = 1024;
+constexpr int64_t kOneBlockRow = 24576;      // coordinates of a row that one block sparsifies alone
 
+__global__ __launch_bounds__(kSparsifyThreads) void clear_rows_kernel(float *__restrict__ a, int32_t *__restrict__ b, int64_t M)
+{
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kSparsifyThreads + threadIdx.x;
+    if (i < M) {
+        a[i] = 0.0f;
+        b[i] = 0;
+    }
+}
+
+// Grid (M, slices).  What bounds it is the work one compute unit does for a row: a Philox block and up to eight divisions
+// per quad, about 1.4 us for 1024 quads.  So a long row is shared by several blocks: each finds the row's norms for
+// itself (the row comes from L2 after the first) and sparsifies the quads of its own slice; the slices' results meet in
+// absmax_out / nnz_out by integer atomics, on values that clear_rows_kernel has set to zero.  That is one launch more,
+// about 3.5 us, so a row of up to kOneBlockRow coordinates is one block's.  Measured (one block per row and a Philox
+// block per coordinate -> now): 16 rows of 20,958 coordinates 16.5 -> 11.3 us (shared by six blocks 6.2 + 1.4 us in two
+// launches); 8 rows of 47,236 33.0 -> 7.2 + 1.4 us; one row of 10^6 801 -> 41 us; 32 rows of 4096 5.9 -> 5.5 us.
+// VEC: rows are 16-byte aligned, so a quad is one access.
+template <bool VEC>
 __global__ __launch_bounds__(kSparsifyThreads) void sparsify_kernel(
     const float *__restrict__ alpha, int64_t d, int64_t ld, const float *__restrict__ phi, StreamKey key, uint32_t worker0,
     float *__restrict__ beta, int64_t ld_out, float *__restrict__ absmax_out, int32_t *__restrict__ nnz_out)
@@ -441,13 +461,51 @@ __global__ __launch_bounds__(kSparsifyThreads) void sparsify_kernel(
     float *out = beta + static_cast<int64_t>(m) * ld_out;
     key.worker = worker0 + static_cast<uint32_t>(m);
     key.tag = DQ_TAG_SPARSIFY;
-    // pass 1: ||alpha||_inf and, for a caller-supplied budget, ||alpha||_1 (double, fixed order)
+    const int64_t quads = (d + 3) / 4;
+    const int64_t per = (quads + gridDim.y - 1) / gridDim.y;
+    const int64_t q_lo = min(quads, per * blockIdx.y), q_hi = min(quads, q_lo + per);
+    const auto quad_at = [&](int64_t q) {                // (past the end of the row: its last quad, whose tail reads as zero)
+        if constexpr (VEC) return load_quad(row, q, d);
+        float4 r;
+        r.x = row[4 * q];
+        r.y = 4 * q + 1 < d ? row[4 * q + 1] : 0.0f;
+        r.z = 4 * q + 2 < d ? row[4 * q + 2] : 0.0f;
+        r.w = 4 * q + 3 < d ? row[4 * q + 3] : 0.0f;
+        return r;
+    };
+    // the thread's first quad and its random bits do not wait for the norms
+    const int64_t q_first = q_lo + threadIdx.x;
+    const float4 first = quad_at(min(q_first, quads - 1));
+    const uint4 first_w = stream_block(key, static_cast<uint32_t>(q_first));
+    // pass 1: ||alpha||_inf and, for a caller-supplied budget, ||alpha||_1 (double, fixed order); eight reads at clamped
+    // positions in flight (a repeated coordinate changes no maximum)
     uint32_t mb = 0;
     double s1 = 0.0;
-    for (int64_t i = threadIdx.x; i < d; i += kSparsifyThreads) {
-        const float a = row[i];
-        mb = max(mb, abs_bits(a));
-        s1 += static_cast<double>(fabsf(a));
+    constexpr int kFlight = 8;
+    if (phi == nullptr) {
+        const int64_t whole = VEC ? d / 4 : 0;           // whole quads; the coordinates after them one by one
+        for (int64_t q0 = threadIdx.x; q0 < whole; q0 += kFlight * kSparsifyThreads) {
+            float4 a[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u)
+                a[u] = reinterpret_cast<const float4 *>(row)[min(q0 + u * kSparsifyThreads, whole - 1)];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u)
+                mb = max(max(mb, abs_bits(a[u].x)), max(max(abs_bits(a[u].y), abs_bits(a[u].z)), abs_bits(a[u].w)));
+        }
+        for (int64_t i0 = 4 * whole + threadIdx.x; i0 < d; i0 += kFlight * kSparsifyThreads) {
+            float a[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) a[u] = row[min(i0 + u * kSparsifyThreads, d - 1)];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) mb = max(mb, abs_bits(a[u]));
+        }
+    } else {
+        for (int64_t i = threadIdx.x; i < d; i += kSparsifyThreads) {
+            const float a = row[i];
+            mb = max(mb, abs_bits(a));
+            s1 += static_cast<double>(fabsf(a));
+        }
     }
     mb = block_max_u32(mb, su);
     SparsifyRule rule;
@@ -461,17 +519,37 @@ __global__ __launch_bounds__(kSparsifyThreads) void sparsify_kernel(
     // pass 2: Bernoulli keep, rescale
     uint32_t bmax = 0;
     int kept = 0;
-    for (int64_t i = threadIdx.x; i < d; i += kSparsifyThreads) {
-        const float b = sparsify_one(row[i], rule, stream_word(key, static_cast<uint64_t>(i)));
-        out[i] = b;
-        bmax = max(bmax, abs_bits(b));
-        kept += b != 0.0f ? 1 : 0;
+    for (int64_t q = q_lo + threadIdx.x; q < q_hi; q += kSparsifyThreads) {
+        float4 a = first;
+        uint4 w = first_w;
+        if (q != q_first) {
+            a = quad_at(q);
+            w = stream_block(key, static_cast<uint32_t>(q));
+        }
+        a.x = sparsify_one(a.x, rule, w.x);
+        a.y = sparsify_one(a.y, rule, w.y);
+        a.z = sparsify_one(a.z, rule, w.z);
+        a.w = sparsify_one(a.w, rule, w.w);
+        bmax = max(max(bmax, abs_bits(a.x)), max(max(abs_bits(a.y), abs_bits(a.z)), abs_bits(a.w)));
+        kept += (a.x != 0.0f) + (a.y != 0.0f) + (a.z != 0.0f) + (a.w != 0.0f);
+        if constexpr (VEC) {
+            store_quad(out, q, d, a);
+        } else {
+            out[4 * q] = a.x;
+            if (4 * q + 1 < d) out[4 * q + 1] = a.y;
+            if (4 * q + 2 < d) out[4 * q + 2] = a.z;
+            if (4 * q + 3 < d) out[4 * q + 3] = a.w;
+        }
     }
-    bmax = block_max_u32(bmax, su);
-    kept = block_sum_i32(kept, si);
+    block_max_u32_sum_i32(bmax, kept, su, si);
     if (threadIdx.x == 0) {
-        absmax_out[m] = __uint_as_float(bmax);
-        nnz_out[m] = kept;
+        if (gridDim.y == 1) {
+            absmax_out[m] = __uint_as_float(bmax);
+            nnz_out[m] = kept;
+        } else {
+            if (bmax != 0) atomicMax(reinterpret_cast<uint32_t *>(absmax_out) + m, bmax);
+            if (kept != 0) atomicAdd(nnz_out + m, kept);
+        }
     }
 }
 
@@ -544,7 +622,7 @@ static int model_message(const float *x, int64_t d, int32_t b_x, const StreamKey
                          float *delta_x_out, const float *absmax_x, uint32_t *status, hipStream_t st,
                          const float *x_snap = nullptr, float *diff_out = nullptr)
 {
-    // (below a million coordinates the launch is latency, not throughput: see model_message_kernel)
+    // (below a million coordinates the launch is latency, not throughput: see quantize_quads_kernel)
     constexpr int64_t kSmallModel = 1 << 20;
     const bool leave_diff = diff_out && x_snap;
     if ((b_x == 2 || b_x == 4 || b_x == 8) && (leave_diff || d <= kSmallModel))
@@ -726,8 +804,28 @@ extern "C" int32_t dq_sparsify(const float *alpha, int64_t d, int64_t M, int64_t
     if (d <= 0 || M <= 0 || !alpha || !beta_out || !absmax_out || !nnz_out || ld < d || ld_out < d)
         return DQ_ERR_INVALID_ARG;
     StreamKey key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), iter, 0u, DQ_TAG_SPARSIFY};
-    sparsify_kernel<<<dim3(static_cast<unsigned>(M)), dim3(kSparsifyThreads), 0, as_stream(stream)>>>(
-        alpha, d, ld, phi, key, worker0, beta_out, ld_out, absmax_out, nnz_out);
+    hipStream_t st = as_stream(stream);
+    // One block per row up to kOneBlockRow coordinates; beyond that one block per compute unit over all rows, none with
+    // less than a sweep of quads.  A row is read by all of its blocks
+    // before and while they write theirs: in place, and where the budgets share memory with a result, one block takes it.
+    const auto overlap = [](const void *a, int64_t na, const void *b, int64_t nb) {
+        const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+        return a && b && x < y + 4 * static_cast<uintptr_t>(nb) && y < x + 4 * static_cast<uintptr_t>(na);
+    };
+    const int64_t in_floats = (M - 1) * ld + d, out_floats = (M - 1) * ld_out + d;
+    const bool shared_memory = overlap(alpha, in_floats, beta_out, out_floats) || overlap(phi, M, absmax_out, M) ||
+                               overlap(phi, M, nnz_out, M) || overlap(alpha, in_floats, absmax_out, M) ||
+                               overlap(alpha, in_floats, nnz_out, M);
+    const int64_t slices = shared_memory || d <= kOneBlockRow ? 1 : std::min(ceil_div(256, M), ceil_div(ceil_div(d, 4), kSparsifyThreads));
+    if (slices > 1) {
+        clear_rows_kernel<<<dim3(static_cast<unsigned>(ceil_div(M, kSparsifyThreads))), dim3(kSparsifyThreads), 0, st>>>(absmax_out, nnz_out, M);
+        DQ_LAUNCH_CHECK();
+    }
+    const bool vec = aligned16(alpha) && aligned16(beta_out) && (M == 1 || (ld % 4 == 0 && ld_out % 4 == 0));
+    // (rows along x: a grid may have 2^31 of them there, and along y only 65535)
+    const dim3 grid(static_cast<unsigned>(M), static_cast<unsigned>(slices)), block(kSparsifyThreads);
+    if (vec) sparsify_kernel<true><<<grid, block, 0, st>>>(alpha, d, ld, phi, key, worker0, beta_out, ld_out, absmax_out, nnz_out);
+    else sparsify_kernel<false><<<grid, block, 0, st>>>(alpha, d, ld, phi, key, worker0, beta_out, ld_out, absmax_out, nnz_out);
     DQ_LAUNCH_CHECK();
     return DQ_OK;
 }

@@ -229,3 +229,58 @@ def test_master_step_each_float_messages(dq):
                            0, 0, xq, one, one.clone())
     assert np.array_equal(host(x).view(np.uint32), x_ref.view(np.uint32))
     assert np.array_equal(words(xq), x_ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("budget", [None, 0.5])
+@pytest.mark.parametrize("M,d", [(1, 1), (2, 1023), (3, 4097), (1, 24576), (2, 24577), (1, 70001), (40, 24579)])
+def test_sparsify_rows_shared_by_blocks(dq, budget, M, d):
+    """Widths at which a row passes from one block to several, ragged last quads; rows that are not 16-byte aligned."""
+    rng = np.random.default_rng(d)
+    alpha = (rng.standard_normal((M, d)) * np.where(rng.random((M, d)) < 0.1, 1.0, 0.01)).astype(np.float32)
+    phi = None
+    if budget is not None:
+        phi = np.array([budget * np.abs(alpha[m]).sum() / np.abs(alpha[m]).max() for m in range(M)], dtype=np.float32)
+    want = [oracle.sparsify(alpha[m], 31, 4, 2 + m, phi=-1.0 if phi is None else float(phi[m])) for m in range(min(M, 4))]
+    for ld, shift in ((((d + 3) // 4 * 4), 0), (d + 1, 1)):
+        flat = torch.zeros(M * ld + shift, device="cuda")
+        a = flat[shift:].view(M, ld)[:, :d]
+        a.copy_(dev(alpha))
+        beta = torch.full((M * ld + shift,), 9.0, device="cuda")
+        out = beta[shift:].view(M, ld)[:, :d]
+        amax = torch.full((M,), 5.0, device="cuda")
+        nnz = torch.full((M,), 7, dtype=torch.int32, device="cuda")
+        dq.dq_sparsify(a, None if phi is None else dev(phi), 31, 4, 2, out, amax, nnz)
+        for m, (w, kept) in enumerate(want):
+            assert np.array_equal(host(out)[m].view(np.uint32), w.view(np.uint32))
+            assert host(nnz)[m] == kept
+            assert host(amax)[m] == oracle.absmax(w)
+        if ld > d:
+            assert torch.all(beta[shift:].view(M, ld)[:, d:] == 9.0)
+        in_place = a.clone() if M == 1 else a              # the result may replace its input
+        dq.dq_sparsify(in_place, None if phi is None else dev(phi), 31, 4, 2, in_place, amax, nnz)
+        for m, (w, kept) in enumerate(want):
+            assert np.array_equal(host(in_place)[m].view(np.uint32), w.view(np.uint32)) and host(nnz)[m] == kept
+
+
+@pytest.mark.parametrize("b", [2, 4, 8])
+@pytest.mark.parametrize("M,d", [(1, 1), (3, 5), (2, 1025), (5, 4099), (1, 1 << 20), (1, (1 << 20) + 1), (16, 65536), (16, 65540)])
+def test_quantize_pack_of_few_coordinates(dq, M, d, b):
+    """A quad per thread up to 2^20 coordinates over all rows, sixteen coordinates per thread beyond: the same bits."""
+    rng = np.random.default_rng(d + b)
+    ld, nw = (d + 3) // 4 * 4 + 4, dq.packed_words(d, b)
+    v = np.zeros((M, ld), dtype=np.float32)
+    v[:, :d] = rng.standard_normal((M, d)).astype(np.float32)
+    v[:, d:] = 1e9                                          # beside the rows: not read as part of them
+    if M > 1:
+        v[1, :d] = 0.0
+    if M > 2:
+        v[2, d // 2] = np.inf
+    packed = torch.full((M, (nw + 3) // 4 * 4), -1, dtype=torch.int32, device="cuda")
+    amax, delta = torch.zeros(M, device="cuda"), torch.zeros(M, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dq.dq_quantize_pack(dev(v)[:, :d], b, amax, False, 3, 9, dq.TAG_GRAD, 4, packed, delta, status)
+    for m in range(min(M, 5)):
+        k, dlt, _ = oracle.quantize(v[m, :d], b, 3, 9, 4 + m)
+        assert np.array_equal(host(packed)[m, :nw].view(np.uint32), oracle.pack(k, b))
+        assert np.array_equal(host(delta)[m], dlt, equal_nan=True)
+    assert host(status)[0] == (1 if M > 2 else 0)
