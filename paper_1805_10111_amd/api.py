@@ -123,7 +123,10 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor"):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream's handle without a Stream object around it: 0.2 us a call against 2.8 us for
+    # torch.cuda.current_stream().cuda_stream, half of what a call of this module took beside its launches
+    # (every call has been given a GPU tensor by now, so the runtime is initialised)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(fn: str, rc: int):
