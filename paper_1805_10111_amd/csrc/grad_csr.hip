@@ -22,6 +22,7 @@
 // previous round's launch (see kPrepInts).
 // The full gradient uses the same block procedure over many blocks, each leaving a partial
 // d-vector that a second kernel adds up in a fixed order.
+#include <algorithm>
 #include <mutex>
 
 #include <hip/hip_ext.h>
@@ -493,6 +494,9 @@ struct CsrWorkerArgs {
     // sparsifier split over the identical blocks of a worker (beta_ws != null): each block sparsifies its slice into
     // row m of beta_ws and leaves the slice's largest magnitude and kept count; the quantization is a second launch
     float *beta_ws; float *part_max; int32_t *part_kept;
+    // SLICED (slice_ws != null): a block leaves its columns of the gradient in row m of slice_ws and their largest
+    // magnitude in slice_max[m * slice_max_stride + slice]
+    float *slice_ws; float *slice_max; int64_t slice_max_stride;
     const float *model_diff;       // nullable: (decoded model) - snapshot for every column, see WorkerArgs::model_diff
     // a mini-batch prepared ahead (see kPrepInts): prep_in (nullable) holds this round's, one block of prep_stride words
     // per worker; with prep_out the grid has one more block per worker (the last blockIdx.y), which prepares the round
@@ -503,11 +507,21 @@ struct CsrWorkerArgs {
     uint32_t next_iter;
 };
 
-// DIFF: the model comes as a.model_diff (one float per column) instead of the message and the snapshot.
-// COMMON: the gradient fits in LDS as one window, the mini-batch in one pass of rows (B <= kCsrMaxRows), and the
-// margins at the snapshot are cached (z_snap given) -- the kernel is then straight-line code with one set of the
+// DIFF: the model comes as a.model_diff (one float per column) instead of the message and the snapshot.  (A third form was
+// built and measured on the sliced step: the kernel quantizing the model itself, per gathered entry and per column of its
+// slice, which saves the launch of the model message.  Three gathers per entry -- model, snapshot, random word -- for one
+// take as long as that launch at 20,958 columns and longer at 47,236, with or without the Philox rounds done by the
+// master before: 14.1 / 35.4 us a round against 14.3 / 33.2.)
+// COMMON: the gradient fits in LDS as one window (SLICED: always), the mini-batch in one pass of rows (B <= kCsrMaxRows),
+// and the margins at the snapshot are cached (z_snap given) -- the kernel is then straight-line code with one set of the
 // row-processing routines, which leaves the compiler far fewer values to keep alive across its phases.
-template <bool DIFF, bool COMMON>
+// SLICED: the blocks of a worker share its columns.  Every block stages the whole mini-batch and forms all margins, but
+// scatters into, finishes and stores only the columns of its own slice, `win` of them: an eighth of the passes over
+// the vector, which are what a block of the other form spends half of its time on (clearing, float window, maximum,
+// quantization), and no limit on the width from LDS.  What needs the whole gradient -- scale, sparsifier,
+// quantization -- is a later launch's, which finds the gradient in memory and its slices' maxima beside it.
+// Measured: see csr_worker.
+template <bool DIFF, bool COMMON, bool SLICED>
 __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorkerArgs a)
 {
     touch_kernel_arguments<sizeof(CsrWorkerArgs)>();
@@ -527,10 +541,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
 
     const int m = blockIdx.x;
     const ModelMsg msg{a.xq, a.b_x == 32 ? 1.0f : a.delta_x[0], a.b_x};
-    // identical copies of the worker; they share only the tail (a last one more prepares the next round instead)
+    // identical copies of the worker that share the tail, or slices (a last one more prepares the next round instead)
     const int slice = blockIdx.y, nslices = static_cast<int>(gridDim.y) - (a.prep_out ? 1 : 0);
     if (a.zero_word && blockIdx.x == 0 && slice == 0 && threadIdx.x == 0) *a.zero_word = 0u;
-    float *alpha_row = (!COMMON && a.alpha_ws) ? a.alpha_ws + static_cast<int64_t>(m) * a.ld_ws : nullptr;   // only with several windows
+    float *alpha_row = (!SLICED && !COMMON && a.alpha_ws) ? a.alpha_ws + static_cast<int64_t>(m) * a.ld_ws : nullptr;   // only with several windows
 
     const float inv_B = 1.0f / static_cast<float>(a.B);      // the mean over the mini-batch, as one multiplication per row
     const bool have_z = COMMON || a.z_snap != nullptr;
@@ -633,7 +647,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         }
         return;
     }
-    for (int64_t c0 = 0; c0 < d; c0 += win) {
+    for (int64_t c0 = SLICED ? static_cast<int64_t>(slice) * win : 0; c0 < d; c0 += win) {
         const int64_t c1 = min(d, c0 + win);
         const int64_t c1p = min((d + 3) / 4 * 4, c0 + win);     // the window, up to a whole quad past the end of the vector
         FixedAcc fx{0.0f, 0};
@@ -704,7 +718,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                 const int4 sum = *reinterpret_cast<const int4 *>(acc + (j - c0));
                 v.x += static_cast<float>(sum.x) * unit; v.y += static_cast<float>(sum.y) * unit;
                 v.z += static_cast<float>(sum.z) * unit; v.w += static_cast<float>(sum.w) * unit;
-                *reinterpret_cast<float4 *>(alpha + (j - c0)) = v;
+                if constexpr (SLICED) *reinterpret_cast<float4 *>(a.slice_ws + static_cast<int64_t>(m) * a.ld_ws + j) = v;
+                else *reinterpret_cast<float4 *>(alpha + (j - c0)) = v;
+                if (SLICED && a.alpha_out) store_quad(a.alpha_out + static_cast<int64_t>(m) * a.ld, j >> 2, d, v);
                 seen_max = max(max(seen_max, abs_bits(v.x)), max(max(abs_bits(v.y), abs_bits(v.z)), abs_bits(v.w)));
             };
             const auto slow_quad = [&](int64_t j) {
@@ -764,7 +780,12 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             for (int64_t j = c0 + threadIdx.x; j < c1p; j += kCsrThreads) alpha_row[j] = alpha[j - c0];
             __syncthreads();
         }
-        if constexpr (COMMON) break;                           // (one window)
+        if constexpr (COMMON || SLICED) break;                 // (one window)
+    }
+    if constexpr (SLICED) {
+        seen_max = block_max_u32(seen_max, su);
+        if (threadIdx.x == 0) a.slice_max[static_cast<int64_t>(m) * a.slice_max_stride + slice] = __uint_as_float(seen_max);
+        return;
     }
     // the whole gradient, padded with zeros to a whole quad: in LDS when it fits in one window, else in this worker's
     // workspace row (the block's own writes, visible to all its threads after the barrier above)
@@ -803,6 +824,52 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     case 4: worker_tail_from_lds<4, true>(av, d, a.sparsify != 0, a.b, key, out, su, si, slice, nslices, &seen_max); break;
     case 32: worker_tail_from_lds<32, true>(av, d, a.sparsify != 0, a.b, key, out, su, si, slice, nslices, &seen_max); break;
     default: worker_tail_from_lds<8, true>(av, d, a.sparsify != 0, a.b, key, out, su, si, slice, nslices, &seen_max); break;
+    }
+}
+
+// Alg. 2, worker (ii) on gradients that a SLICED launch left in memory: grid (M, slices).  Each block takes ||alpha||_inf
+// from the maxima that launch left per slice (alpha_parts of them, at alpha_max + m * alpha_max_stride), sparsifies a slice
+// of the quads of row m in place and leaves the slice's largest magnitude and kept count.  Rows are padded with
+// zeros to whole quads.  Everything is requested, and the first quad's random bits drawn, before anything is waited for.
+__global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
+    float *__restrict__ rows, int64_t ld, int64_t d, const float *__restrict__ alpha_max, int64_t alpha_max_stride,
+    int alpha_parts, StreamKey key, uint32_t worker0, float *__restrict__ part_max, int32_t *__restrict__ part_kept)
+{
+    touch_kernel_arguments<88>();
+    __shared__ uint32_t su[kCsrWaves];
+    __shared__ int si[kCsrWaves];
+    const int m = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y;
+    const int64_t quads = (d + 3) / 4, per = (quads + nslices - 1) / nslices;
+    const int64_t q_lo = min(quads, per * slice), q_hi = min(quads, q_lo + per), q_first = q_lo + threadIdx.x;
+    float4 *row = reinterpret_cast<float4 *>(rows + static_cast<int64_t>(m) * ld);
+    const PartsRaw maxima = parts_request(alpha_max + static_cast<int64_t>(m) * alpha_max_stride, alpha_parts);
+    float4 v = row[min(q_first, quads - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    key.worker = worker0 + static_cast<uint32_t>(m);
+    key.tag = DQ_TAG_SPARSIFY;
+    uint4 w = stream_block(key, static_cast<uint32_t>(q_first));
+    asm volatile("" ::"v"(w.x), "v"(w.y), "v"(w.z), "v"(w.w));
+    __builtin_amdgcn_sched_barrier(0);
+    const SparsifyRule rule{parts_absmax_of(maxima), 0.0f, false};
+    uint32_t bmax = 0;
+    int kept = 0;
+    for (int64_t q = q_first; q < q_hi; q += kCsrThreads) {
+        if (q != q_first) {
+            v = row[q];
+            w = stream_block(key, static_cast<uint32_t>(q));
+        }
+        v.x = sparsify_one(v.x, rule, w.x);
+        v.y = sparsify_one(v.y, rule, w.y);
+        v.z = sparsify_one(v.z, rule, w.z);
+        v.w = sparsify_one(v.w, rule, w.w);
+        bmax = max(max(bmax, abs_bits(v.x)), max(max(abs_bits(v.y), abs_bits(v.z)), abs_bits(v.w)));
+        kept += (v.x != 0.0f) + (v.y != 0.0f) + (v.z != 0.0f) + (v.w != 0.0f);
+        row[q] = v;
+    }
+    block_max_u32_sum_i32(bmax, kept, su, si);
+    if (threadIdx.x == 0) {
+        part_max[static_cast<int64_t>(m) * nslices + slice] = __uint_as_float(bmax);
+        part_kept[static_cast<int64_t>(m) * nslices + slice] = kept;
     }
 }
 
@@ -1011,12 +1078,49 @@ int csr_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z
     return launch_full_finish(partial, P, ldp, n, d, x, prob->l2, prob->l1, loss_partial, g_out, obj_out, st);
 }
 
+// Slices of a step split over the columns (0: the step is not split): eight per worker, fewer where that would be more
+// blocks than compute units (one block more per worker prepares the next round); a slice holds whole groups of 64
+// quads, so no word of a message belongs to two slices, and must fit in LDS beside `cap` staged entries.
+struct CsrSlices {
+    int count, win;
+};
+
+static CsrSlices csr_slices(int64_t d, int64_t M, const CsrPlan &plan, bool second)
+{
+    int64_t S = std::min<int64_t>(kMaxSlices, 256 / M - 1);
+    if (d < 4096 || (S < 3 && plan.nwin == 1)) return CsrSlices{0, 0};
+    S = std::max<int64_t>(S, 2);
+    const int64_t budget = kLdsBudget - kCsrFixedLds, each = second ? 16 : 12;
+    for (; S <= kMaxSlices; ++S) {
+        const int64_t win = ceil_div(ceil_div(d, S), 256) * 256;
+        if (win * 4 + plan.cap * each <= budget) return CsrSlices{static_cast<int>(ceil_div(d, win)), static_cast<int>(win)};
+    }
+    return CsrSlices{0, 0};
+}
+
+// Whether (and how) a step is split over the columns.  Vectors of several LDS windows always are, if their outputs allow
+// it (8 workers, 32 rows, 47,236 columns: one block per worker and two windows 48.4 us; split, with the sparsifier and the
+// quantization as launches of their own, 8.9 + 4.4 + 4.0 us).  Of the others those that can leave their quantization to
+// the master (see `deferred`): at 20,958 columns worker step and master 10.4 + 3.1 us -> 7.9 + 3.9 us.  Not those with a
+// sparsifier, which would need a launch for it between the two: 12.0 us as one launch, 8.8 + 3.9 as two.
+static CsrSlices csr_step_slices(const dq_problem *prob, const WorkerArgs &a, const CsrPlan &plan)
+{
+    const CsrSlices none{0, 0};
+    const bool count_ok = !a.nnz_out || (a.sparsify && a.b >= 4);      // after the sparsifier: count = kept coordinates
+    if (!a.packed || a.b == 32 || !count_ok || !a.ws) return none;
+    if (a.ws_bytes < csr_workspace_bytes(DQ_OP_WORKER_STEP, prob, a.M, a.B)) return none;
+    if (plan.nwin == 1 && (a.sparsify || !a.deferred)) return none;
+    return csr_slices(prob->d, a.M, plan, a.z_snap == nullptr);
+}
+
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
 {
     const int64_t d = prob->d;
     CsrPlan plan;
     if (!csr_plan(d, a.z_snap == nullptr, plan)) return DQ_ERR_UNSUPPORTED;
     const int64_t row_words = a.packed ? (a.b == 32 ? d : packed_words(d, a.b)) : 0;
+    if (a.deferred) *a.deferred = GradientParts{nullptr, 0, nullptr, nullptr, 0};
+    if (a.prepared_next) *a.prepared_next = false;
     if (a.model_is_snapshot) return launch_worker_zero(a, d, row_words, st);
     if (plan.nwin > 1 && (!a.ws || a.ws_bytes < a.M * pad4(d) * 4)) return DQ_ERR_WORKSPACE;
     CsrWorkerArgs k{};
@@ -1032,39 +1136,59 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     k.delta_out = a.delta_out; k.nnz_out = a.nnz_out; k.status = a.status; k.zero_word = a.zero_word;
     k.cap = plan.cap; k.win = plan.win;
     k.alpha_ws = plan.nwin > 1 ? static_cast<float *>(a.ws) : nullptr; k.ld_ws = pad4(d);
-    const size_t lds = plan.lds;
     k.model_diff = a.b_x == 32 ? nullptr : a.model_diff;
-    // (see csr_worker_kernel for the two switches)
-    const bool diff = k.model_diff != nullptr;
-    const bool common = plan.nwin == 1 && a.B <= kCsrMaxRows && a.z_snap != nullptr;
-    static std::once_flag attr_once[4];
-    static hipError_t attr_rc[4] = {hipSuccess, hipSuccess, hipSuccess, hipSuccess};
-    void (*const kernels[4])(const CsrWorkerArgs) = {csr_worker_kernel<false, false>, csr_worker_kernel<false, true>,
-                                                     csr_worker_kernel<true, false>, csr_worker_kernel<true, true>};
-    const int which = (diff ? 2 : 0) + (common ? 1 : 0);
-    const auto kernel = kernels[which];
-    int rc = allow_big_lds(kernel, attr_once[which], attr_rc[which]);
-    if (rc != DQ_OK) return rc;
+    const CsrSlices sl = csr_step_slices(prob, a, plan);
+    const bool sliced = sl.count > 0;
+    const bool count_ok = !a.nnz_out || (a.sparsify && a.b >= 4);
     // Few workers leave most compute units idle while each block spends a third of its time on the Philox rounds of
     // the final quantization: then several identical blocks per worker share that part (not when the nonzero count is
     // wanted and would need a sum across blocks, nor when the gradient lives in the per-worker workspace row).
-    const bool count_ok = !a.nnz_out || (a.sparsify && a.b >= 4);      // after the sparsifier: count = kept coordinates
     unsigned slices = 1;
     if (a.packed && count_ok && plan.nwin == 1 && a.b != 32 && d >= 4096 && a.M * 4 <= 128) slices = a.M * 8 <= 128 ? 8 : 4;
+    if (sliced) slices = static_cast<unsigned>(sl.count);
     // After the sparsifier the scale is ||beta||_inf, which needs every coordinate's random decision: sharing only the
     // quantization would leave each identical block a whole Philox-and-two-divisions pass over the vector (9 of the
     // 33 us of the step at d = 20958).  With workspace for a row per worker each block sparsifies its own slice into
     // memory instead and the quantization becomes a second launch that takes the scale from the slices' maxima.
-    const bool split_sparsifier = slices > 1 && a.sparsify && a.ws &&
+    const bool split_sparsifier = !sliced && slices > 1 && a.sparsify && a.ws &&
                                   a.ws_bytes >= csr_workspace_bytes(DQ_OP_WORKER_STEP, prob, a.M, a.B);
-    if (split_sparsifier) {
-        k.beta_ws = static_cast<float *>(a.ws);
-        k.part_max = k.beta_ws + a.M * k.ld_ws;
-        k.part_kept = reinterpret_cast<int32_t *>(k.part_max + a.M * kMaxSlices);
+    size_t lds = plan.lds;
+    GradientParts parts{nullptr, 0, nullptr, nullptr, 0};
+    float *alpha_max = nullptr;                          // the slices' maxima of the gradient itself
+    int64_t alpha_max_stride = 0;
+    if (sliced || split_sparsifier) {
+        float *part_max = static_cast<float *>(a.ws) + a.M * k.ld_ws;
+        int32_t *part_kept = reinterpret_cast<int32_t *>(part_max + a.M * kMaxSlices);
+        parts = GradientParts{static_cast<float *>(a.ws), k.ld_ws, part_max, a.sparsify ? part_kept : nullptr, static_cast<int>(slices)};
+        if (split_sparsifier) {
+            k.beta_ws = static_cast<float *>(a.ws);
+            k.part_max = part_max;
+            k.part_kept = part_kept;
+        }
     }
+    if (sliced) {
+        k.win = sl.win;
+        lds = static_cast<size_t>(sl.win) * 4 + static_cast<size_t>(plan.cap) * (a.z_snap ? 12 : 16);
+        k.slice_ws = static_cast<float *>(a.ws);
+        // (before the sparsifier the maxima wait at the head of the message rows, which are written only after it)
+        alpha_max = a.sparsify ? reinterpret_cast<float *>(a.packed) : const_cast<float *>(parts.part_max);
+        alpha_max_stride = a.sparsify ? a.ld_words : static_cast<int64_t>(slices);
+        k.slice_max = alpha_max; k.slice_max_stride = alpha_max_stride;
+    }
+    const bool common = (sliced || plan.nwin == 1) && a.B <= kCsrMaxRows && a.z_snap != nullptr;
+    static std::once_flag attr_once[8];
+    static hipError_t attr_rc[8];
+    void (*const kernels[8])(const CsrWorkerArgs) = {
+        csr_worker_kernel<false, false, false>, csr_worker_kernel<false, true, false>, csr_worker_kernel<true, false, false>,
+        csr_worker_kernel<true, true, false>,   csr_worker_kernel<false, false, true>, csr_worker_kernel<false, true, true>,
+        csr_worker_kernel<true, false, true>,   csr_worker_kernel<true, true, true>};
+    const int which = (sliced ? 4 : 0) + (k.model_diff ? 2 : 0) + (common ? 1 : 0);
+    const auto kernel = kernels[which];
+    int rc = allow_big_lds(kernel, attr_once[which], attr_rc[which]);
+    if (rc != DQ_OK) return rc;
     // a round of dq_run_rounds that has a successor in its call prepares that round's mini-batches in one more block
     // per worker (on compute units the launch leaves idle), and reads its own if the round before left them
-    const bool can_prepare = !a.idx && a.B <= kCsrMaxRows && plan.nwin == 1 && a.M * (slices + 1) <= 256;
+    const bool can_prepare = !a.idx && a.B <= kCsrMaxRows && (sliced || plan.nwin == 1) && a.M * (slices + 1) <= 256;
     if (can_prepare) {
         k.prep_in = a.prep_in;
         k.prep_out = a.prep_out;
@@ -1078,16 +1202,20 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     else
         kernel<<<grid, block, lds, st>>>(k);
     DQ_LAUNCH_CHECK();
-    if (a.deferred) *a.deferred = SparsifiedParts{nullptr, 0, nullptr, nullptr, 0};
-    if (split_sparsifier && a.deferred) {             // the master quantizes while it aggregates
-        *a.deferred = SparsifiedParts{k.beta_ws, k.ld_ws, k.part_max, k.part_kept, static_cast<int>(slices)};
+    if (parts.parts == 0) return DQ_OK;
+    if (sliced && a.sparsify) {
+        sparsify_parts_kernel<<<dim3(static_cast<unsigned>(a.M), slices), block, 0, st>>>(
+            k.slice_ws, k.ld_ws, d, alpha_max, alpha_max_stride, static_cast<int>(slices), k.key, a.worker0,
+            const_cast<float *>(parts.part_max), const_cast<int32_t *>(parts.part_kept));
+        DQ_LAUNCH_CHECK();
+    }
+    if (a.deferred) {                                    // the master quantizes while it aggregates
+        *a.deferred = parts;
         return DQ_OK;
     }
-    if (split_sparsifier)
-        return launch_quantize_pack_parts(k.beta_ws, d, a.M, k.ld_ws, a.b, a.b, k.part_max, static_cast<int>(slices),
-                                          a.nnz_out ? k.part_kept : nullptr, a.nnz_out, k.key, a.worker0, a.packed,
-                                          a.ld_words, a.delta_out, a.status, st);
-    return DQ_OK;
+    return launch_quantize_pack_parts(parts.rows, d, a.M, parts.ld, a.b, a.b, parts.part_max, parts.parts,
+                                      a.nnz_out ? parts.part_kept : nullptr, a.nnz_out, k.key, a.worker0, a.packed,
+                                      a.ld_words, a.delta_out, a.status, st);
 }
 
 }  // namespace dq

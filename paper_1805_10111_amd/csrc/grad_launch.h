@@ -5,10 +5,10 @@
 
 namespace dq {
 
-// M sparsified gradients as the split sparsifier leaves them in the workspace: rows of ld floats, and per worker
-// `parts` slice maxima (the scale is ||beta||_inf, their largest) and kept counts.
-struct SparsifiedParts {
-    const float *beta; int64_t ld;
+// M gradients (sparsified or not) as a worker step that is split over the columns leaves them in the workspace: rows of ld
+// floats, and per worker `parts` slice maxima (the scale is the largest of them) and, after the sparsifier, kept counts.
+struct GradientParts {
+    const float *rows; int64_t ld;
     const float *part_max; const int32_t *part_kept; int parts;
 };
 
@@ -43,15 +43,12 @@ struct WorkerArgs {
     // kernel that streams the rows quantizes the model x_model[d] with scale ||x||_inf = *absmax_model and the master's
     // stream (seed, iter, DQ_MASTER_ID, DQ_TAG_MODEL) -- every block for its own use, one block also storing the
     // message to `xq` and its scale to `delta_x`, which are then outputs of the call.  Needs dense_model_fusable().
-    // (The same for CSR features was built and measured on the real-sim-shaped configurations: every block
-    // quantizing the 20958-coordinate model for itself, and again per gathered entry, made the worker kernel 4.5 us
-    // longer, more than the 4.2 us launch it saves -- not kept.)
     const float *x_model, *absmax_model;
-    // Alg. 2 with the sparsifier split over several blocks per worker (CSR features): when `deferred` is given and the
-    // step takes that route, it stops after the sparsifier -- no message is quantized, `packed`, `delta_out` and
-    // `nnz_out` stay untouched -- and describes what it left in *deferred for master_step_from_parts_impl, which
-    // quantizes while it aggregates.  deferred->parts == 0 on return: the step was a complete one.
-    SparsifiedParts *deferred;
+    // CSR features, step split over the columns or sparsifier split over several blocks per worker: when `deferred` is given and the step takes that route, it stops before the
+    // quantization -- `delta_out` and `nnz_out` stay untouched, `packed` holds nothing of use -- and describes what it left in
+    // *deferred for master_step_from_parts_impl, which quantizes while it aggregates.  deferred->parts == 0 on return:
+    // the step was a complete one.
+    GradientParts *deferred;
     // CSR features (nullable): model_diff[c] = (model as decoded from `xq`) - x_snap[c] for every column, formed by
     // the master of the previous round (master_leaves_model_diff) in exactly the worker's arithmetic; the worker then
     // reads one float per column instead of decoding the message and subtracting the snapshot.
@@ -90,16 +87,17 @@ int32_t master_step_impl(const uint32_t *packed, int64_t ld_words, const float *
 // model in a launch of its own with a message width of 2, 4 or 8 bits, which this function tells beforehand.
 bool master_leaves_model_diff(int64_t d, int32_t b_x, bool from_parts);
 
-// The master step of a round of Alg. 2 whose workers deferred their quantization (WorkerArgs::deferred): one kernel
-// quantizes the M sparsified gradients with the workers' streams (seed, worker_iter, worker0 + m, DQ_TAG_GRAD), stores the
-// messages, scales and nonzero counts exactly as the worker step would have, and applies the master update; the model
-// quantization follows as in master_step_impl.  nnz_out nullable.
-int32_t master_step_from_parts_impl(const SparsifiedParts &parts, uint32_t worker0, uint32_t worker_iter, uint32_t *packed, int64_t ld_words,
+// The master step of a round whose workers deferred their quantization (WorkerArgs::deferred): one kernel quantizes the M
+// gradients with the workers' streams (seed, worker_iter, worker0 + m, DQ_TAG_GRAD), stores the messages, scales and
+// (after the sparsifier; nnz_out nullable) nonzero counts exactly as the worker step would have, and applies the master
+// update; the model quantization follows as in master_step_impl.
+int32_t master_step_from_parts_impl(const GradientParts &parts, uint32_t worker0, uint32_t worker_iter, uint32_t *packed, int64_t ld_words,
                                     float *delta_out, int32_t *nnz_out, int64_t M, int32_t b, float scale, int each,
-                                    const float *g_snap, float *x, float eta, float l1, int64_t d, int32_t b_x,
+                                    const float *g_snap, float *x, float *y, const float *x_snap, float *xsum, float eta,
+                                    float theta, float l1, int64_t d, int32_t b_x,
                                     uint64_t seed, uint32_t iter, uint32_t *xq_packed_out, float *delta_x_out,
                                     float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
-                                    const float *x_snap = nullptr, float *model_diff_out = nullptr);
+                                    float *model_diff_out);
 
 int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t B);
 int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,

@@ -172,10 +172,10 @@ static int launch_master_update(bool acc, dim3 grid, hipStream_t st, const Maste
     return DQ_OK;
 }
 
-// ------------------------------------------------------------------ Alg. 2: quantization inside the master update
-// The workers of a round left their sparsified gradients beta_m unquantized (SparsifiedParts).  A block of 16 x 64
-// threads takes 64 quads of the model: thread (worker lane, quad lane) quantizes its worker's quad -- scale
-// ||beta_m||_inf from the slice maxima, the worker's own Philox stream -- stores the message bits and leaves the four
+// ------------------------------------------------------------------ quantization of the gradients inside the master update
+// The workers of a round left their gradients (of Alg. 2: sparsified) unquantized (GradientParts).  A block of 16 x 64
+// threads takes 64 quads of the model: thread (worker lane, quad lane) quantizes its worker's quad -- the scale
+// from the slice maxima, the worker's own Philox stream -- stores the message bits and leaves the four
 // codes in LDS; after the barrier the threads of worker lane 0 (one wavefront) aggregate delta_m * code_m in worker
 // order and update the model exactly as master_quad does.  More than 16 workers take several passes over two LDS
 // buffers.  (64 quads per block: a block then writes whole 128-byte lines of every message row, and 82 blocks cover
@@ -185,13 +185,13 @@ static int launch_master_update(bool acc, dim3 grid, hipStream_t st, const Maste
 constexpr int kPartsWorkers = 16, kPartsQuads = 64;
 
 struct PartsArgs {
-    SparsifiedParts in;
+    GradientParts in;
     int b; StreamKey key; uint32_t worker0;
     uint32_t *packed;                                    // rows of MasterArgs::ld_words words
     float *delta_out; int32_t *nnz_out; uint32_t *status;
 };
 
-template <int FIELD, bool EACH>
+template <int FIELD, bool ACC, bool EACH>
 __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts_kernel(const MasterArgs a, const PartsArgs p,
                                                                                        uint32_t *__restrict__ absmax_bits)
 {
@@ -214,23 +214,29 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
     const int64_t q = static_cast<int64_t>(blockIdx.x) * kPartsQuads + ql;
     const bool inside = q < quads;
     constexpr int kB = CodeBias<FIELD>::value;
+    const bool have_sum = ACC && a.xsum != nullptr;
     float gs[4] = {0.0f, 0.0f, 0.0f, 0.0f}, xn[4] = {0.0f, 0.0f, 0.0f, 0.0f}, acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    float unused_y[4] = {0.0f, 0.0f, 0.0f, 0.0f}, unused_s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    const float unused_xs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float yn[4] = {0.0f, 0.0f, 0.0f, 0.0f}, xs[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sm[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (wl == 0 && inside) {
         // requested here, looked at only after the first barrier: whole quads, or single elements at clamped
         // positions where the vector ends inside the quad (what was read past d is discarded there)
         const int64_t i = 4 * q, last = d - 1;
-        if ((d & 3) == 0) {
-            const float4 g4 = reinterpret_cast<const float4 *>(a.g_snap)[q], x4 = reinterpret_cast<const float4 *>(a.x)[q];
-            gs[0] = g4.x; gs[1] = g4.y; gs[2] = g4.z; gs[3] = g4.w;
-            xn[0] = x4.x; xn[1] = x4.y; xn[2] = x4.z; xn[3] = x4.w;
-        } else {
+        const auto request = [&](const float *v, float (&to)[4]) {
+            if ((d & 3) == 0) {
+                const float4 t = reinterpret_cast<const float4 *>(v)[q];
+                to[0] = t.x; to[1] = t.y; to[2] = t.z; to[3] = t.w;
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                gs[e] = a.g_snap[min(i + e, last)];
-                xn[e] = a.x[min(i + e, last)];
+                for (int e = 0; e < 4; ++e) to[e] = v[min(i + e, last)];
             }
+        };
+        request(a.g_snap, gs);
+        if constexpr (ACC) {
+            request(a.y, yn);
+            request(a.x_snap, xs);
+            if (have_sum) request(a.xsum, sm);
+        } else {
+            request(a.x, xn);
         }
     }
     for (int m0 = 0; m0 < a.M; m0 += kPartsWorkers) {
@@ -244,7 +250,7 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
             // not depend on either
             const PartsRaw maxima = parts_request(p.in.part_max + static_cast<int64_t>(m) * p.in.parts, p.in.parts);
             // (rows are padded to whole quads; what lies past d is not part of the vector)
-            float4 v = reinterpret_cast<const float4 *>(p.in.beta + static_cast<int64_t>(m) * p.in.ld)[inside ? q : 0];
+            float4 v = reinterpret_cast<const float4 *>(p.in.rows + static_cast<int64_t>(m) * p.in.ld)[inside ? q : 0];
             __builtin_amdgcn_sched_barrier(0);           // (the requests go out, then the Philox rounds, then the waits)
             StreamKey key = p.key;
             key.worker = p.worker0 + static_cast<uint32_t>(m);
@@ -272,14 +278,14 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
         if (wl == 0 && inside) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (4 * q + e >= d) gs[e] = xn[e] = 0.0f;
+                if (4 * q + e >= d) gs[e] = xn[e] = yn[e] = xs[e] = 0.0f;
             const auto apply = [&](int u) {
                 const float4 v = codes[buf][u][ql];
                 const float dm = deltas[buf][u];
                 const float vv[4] = {v.x, v.y, v.z, v.w};
                 if (EACH) {
                     const float dir[4] = {dm * vv[0] + gs[0], dm * vv[1] + gs[1], dm * vv[2] + gs[2], dm * vv[3] + gs[3]};
-                    master_apply_quad<false>(dir, xn, unused_y, unused_xs, unused_s, false, a.eta, a.theta, a.kappa);
+                    master_apply_quad<ACC>(dir, xn, yn, xs, sm, have_sum, a.eta, a.theta, a.kappa);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[e] = fmaf(dm, vv[e], acc[e]);
@@ -299,13 +305,17 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
         if (!EACH) {
             const float dir[4] = {a.scale * acc[0] + gs[0], a.scale * acc[1] + gs[1], a.scale * acc[2] + gs[2],
                                   a.scale * acc[3] + gs[3]};
-            master_apply_quad<false>(dir, xn, unused_y, unused_xs, unused_s, false, a.eta, a.theta, a.kappa);
+            master_apply_quad<ACC>(dir, xn, yn, xs, sm, have_sum, a.eta, a.theta, a.kappa);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (4 * q + e >= d) xn[e] = 0.0f;
         const float4 x4 = make_float4(xn[0], xn[1], xn[2], xn[3]);
         store_quad(a.x, q, d, x4);
+        if constexpr (ACC) {
+            store_quad(a.y, q, d, make_float4(yn[0], yn[1], yn[2], yn[3]));
+            if (have_sum) store_quad(a.xsum, q, d, make_float4(sm[0], sm[1], sm[2], sm[3]));
+        }
         amax = quad_abs_bits(x4);
     }
     if (threadIdx.x < kWave) {                           // (worker lane 0 lies in the first wavefront)
@@ -712,32 +722,35 @@ bool dq::master_leaves_model_diff(int64_t d, int32_t b_x, bool from_parts)
     return (b_x == 2 || b_x == 4 || b_x == 8) && (from_parts || d > kFusedMaxD);
 }
 
-int32_t dq::master_step_from_parts_impl(const SparsifiedParts &parts, uint32_t worker0, uint32_t worker_iter, uint32_t *packed, int64_t ld_words,
+int32_t dq::master_step_from_parts_impl(const GradientParts &parts, uint32_t worker0, uint32_t worker_iter, uint32_t *packed, int64_t ld_words,
                                         float *delta_out, int32_t *nnz_out, int64_t M, int32_t b, float scale, int each,
-                                        const float *g_snap, float *x, float eta, float l1, int64_t d, int32_t b_x,
+                                        const float *g_snap, float *x, float *y, const float *x_snap, float *xsum, float eta,
+                                        float theta, float l1, int64_t d, int32_t b_x,
                                         uint64_t seed, uint32_t iter, uint32_t *xq_packed_out, float *delta_x_out,
                                         float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
-                                        const float *x_snap, float *model_diff_out)
+                                        float *model_diff_out)
 {
-    int32_t rc0 = check_master_args(packed, ld_words, delta_out, M, b, g_snap, x, nullptr, nullptr, nullptr, d);
+    int32_t rc0 = check_master_args(packed, ld_words, delta_out, M, b, g_snap, x, y, x_snap, xsum, d);
     if (rc0 != DQ_OK) return rc0;
-    if (b == 32 || !parts.beta || !parts.part_max || !parts.part_kept || parts.parts <= 0 || parts.parts > kMaxParts || parts.ld < (d + 3) / 4 * 4 ||
-        parts.ld % 4 != 0 || !aligned16(parts.beta))
+    if (b == 32 || !parts.rows || !parts.part_max || (nnz_out && !parts.part_kept) || parts.parts <= 0 || parts.parts > kMaxParts ||
+        parts.ld < (d + 3) / 4 * 4 || parts.ld % 4 != 0 || !aligned16(parts.rows))
         return DQ_ERR_INVALID_ARG;
     if (!xq_packed_out || !delta_x_out || !absmax_x_out || !aligned16(xq_packed_out)) return DQ_ERR_INVALID_ARG;
     if (b_x < 2 || (b_x > 16 && b_x != 32)) return DQ_ERR_INVALID_ARG;
     hipStream_t st = as_stream(stream);
     const MasterArgs a{packed, ld_words, packed_words(d, b), delta_out, static_cast<int>(M), scale, each, g_snap,
-                       x, nullptr, nullptr, nullptr, eta, 0.0f, eta * l1, d};
+                       x, y, x_snap, xsum, eta, theta, eta * l1, d};
     const StreamKey wkey{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), worker_iter, 0u, DQ_TAG_GRAD};
     const PartsArgs p{parts, b, wkey, worker0, packed, delta_out, nnz_out, status};
     uint32_t *absmax_bits = reinterpret_cast<uint32_t *>(absmax_x_out);
     int rc = absmax_zeroed ? DQ_OK : fill_u32(absmax_bits, 1, 0u, st);
     if (rc != DQ_OK) return rc;
     const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kPartsQuads)) + 1u), block(kPartsWorkers * kPartsQuads);
-#define DQ_PARTS(FIELD)                                                                        \
-    if (each) master_from_parts_kernel<FIELD, true><<<grid, block, 0, st>>>(a, p, absmax_bits); \
-    else master_from_parts_kernel<FIELD, false><<<grid, block, 0, st>>>(a, p, absmax_bits)
+#define DQ_PARTS(FIELD)                                                                                       \
+    if (y && each) master_from_parts_kernel<FIELD, true, true><<<grid, block, 0, st>>>(a, p, absmax_bits);     \
+    else if (y) master_from_parts_kernel<FIELD, true, false><<<grid, block, 0, st>>>(a, p, absmax_bits);       \
+    else if (each) master_from_parts_kernel<FIELD, false, true><<<grid, block, 0, st>>>(a, p, absmax_bits);    \
+    else master_from_parts_kernel<FIELD, false, false><<<grid, block, 0, st>>>(a, p, absmax_bits)
     switch (b) {
     case 8: DQ_PARTS(8); break;
     case 4: DQ_PARTS(4); break;

@@ -48,9 +48,9 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // The two slots of absmax_x alternate: the kernel that reads one clears the other for the master of its round.
     const bool fusable = cfg->tau == 0 && cfg->b_x != 32 &&
                          dq::dense_model_fusable(prob, cfg->M, cfg->B, cfg->b_x, st->z_snap != nullptr);
-    // Alg. 2, one group of workers, messages not crossing as (position, value) streams: a worker step whose sparsifier
-    // is split over several blocks leaves the quantization of its messages to the master kernel (one launch less)
-    const bool defer_ok = cfg->algo == DQ_ALGO_SPARSE && cfg->b != 32 && cfg->tau == 0 && !st->wire;
+    // CSR features, one group of workers, messages not crossing as (position, value) streams: a worker step that is split
+    // over the columns leaves the quantization of its messages to the master kernel (one launch less)
+    const bool defer_ok = prob->layout == 1 && cfg->b != 32 && cfg->tau == 0 && !st->wire;
     // CSR features, one group of workers: the master that quantizes the model in a launch of its own also leaves
     // (decoded model) - snapshot in the workspace for the workers of the next round of this call
     const bool csr = prob->layout == 1;
@@ -88,7 +88,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
             }
         }
         // worker side: group g of the workers is g rounds behind (g = 0 only when tau = 0)
-        dq::SparsifiedParts parts{nullptr, 0, nullptr, nullptr, 0};
+        dq::GradientParts parts{nullptr, 0, nullptr, nullptr, 0};
         for (int64_t g = 0; g < slots; ++g) {
             const int64_t w_lo = dq::ceil_div(g * cfg->M, slots), w_hi = dq::ceil_div((g + 1) * cfg->M, slots);
             if (w_hi <= w_lo) continue;
@@ -143,10 +143,11 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         diff_ready = diff_out != nullptr;
         if (parts.parts > 0)
             rc = dq::master_step_from_parts_impl(parts, 0u, it, st->packed, st->ld_words, st->delta,
-                                                 st->nnz ? st->nnz + t * cfg->M : nullptr, cfg->M, cfg->b, scale, cfg->each,
-                                                 st->g_snap, st->x, eta, prob->l1, prob->d, cfg->b_x, cfg->seed, it + 1u,
-                                                 xq_next, dx_next, st->absmax_x + (t & 1), st->status,
-                                                 /*absmax_zeroed=*/true, stream, st->x_snap, diff_out);
+                                                 st->nnz && cfg->algo == DQ_ALGO_SPARSE ? st->nnz + t * cfg->M : nullptr,
+                                                 cfg->M, cfg->b, scale, cfg->each, st->g_snap, st->x, acc ? st->y : nullptr,
+                                                 st->x_snap, acc ? st->xsum : nullptr, eta, theta, prob->l1, prob->d, cfg->b_x,
+                                                 cfg->seed, it + 1u, xq_next, dx_next, st->absmax_x + (t & 1), st->status,
+                                                 /*absmax_zeroed=*/true, stream, diff_out);
         else if (model_pending)
             rc = dq::master_update_impl(st->packed, st->ld_words, st->delta, cfg->M, cfg->b, scale, cfg->each, st->g_snap,
                                         st->x, acc ? st->y : nullptr, st->x_snap, acc ? st->xsum : nullptr, eta, theta,

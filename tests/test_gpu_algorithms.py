@@ -468,3 +468,45 @@ def test_rounds_replayed_from_a_captured_graph(dq, name):
         assert torch.equal(eager.x, graph.x) and torch.equal(eager.packed, graph.packed), rep
         assert torch.equal(eager.delta, graph.delta) and torch.equal(eager.xq, graph.xq), rep
     assert np.isfinite(host(graph.x)).all()
+
+
+@pytest.mark.parametrize("algo,b,M,each,b_x", [("asylpg", 8, 8, False, 8), ("asylpg", 2, 17, True, 6), ("acc", 8, 8, False, 8),
+                                               ("acc", 4, 33, True, 4), ("sparse", 4, 5, False, 8), ("sparse", 8, 40, True, 8)])
+@pytest.mark.parametrize("d,B", [(4099, 24), (20958, 32), (36001, 24), (47236, 260)])
+def test_worker_steps_split_over_the_columns_equal_the_separate_calls(dq, algo, b, M, each, b_x, d, B):
+    """CSR features: inside dq_run_rounds the blocks of a worker share the columns of the gradient and the master quantizes
+    it, and wide models are split the same way in any call.  Messages, scales and iterates must be those of dq_vr_grad,
+    dq_sparsify, dq_quantize_pack and the master step, one after the other, bit for bit.  (Ragged last quads, several
+    LDS windows, more rows than one pass takes, 17, 33 and 40 workers: fewer slices each.)"""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    p = synth.sparse_text_logistic(600, d, mean_nnz=30.0, seed=3)
+    P = dq.DeviceProblem.from_host(p)
+    m, seed = 4, 9
+    one = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each)
+    two = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each)
+    one.epoch_prologue(); two.epoch_prologue()
+    one.rounds(0, 3)
+    ld = (d + 3) // 4 * 4
+    idx = torch.empty(M * B, dtype=torch.int32, device="cuda")
+    alpha, beta = torch.zeros((M, ld), device="cuda")[:, :d], torch.zeros((M, ld), device="cuda")[:, :d]
+    amax, kept = torch.zeros(M, device="cuda"), torch.zeros(M, dtype=torch.int32, device="cuda")
+    acc = algo == "acc"
+    for t in range(3):
+        if t == 0:
+            two.rounds(0, 1)                               # (the model is the snapshot: all-zero messages)
+            continue
+        dq.dq_sample_indices(P.n, M, B, seed, t, 0, idx)
+        dq.dq_vr_grad(P, idx, M, B, two.xq, two.delta_x, b_x, False, two.x_snap, two.z_snap, alpha, amax, None, two.ws)
+        if algo == "sparse":
+            dq.dq_sparsify(alpha, None, seed, t, 0, beta, amax, kept)
+            assert torch.equal(kept, one.nnz[t])
+        dq.dq_quantize_pack(beta if algo == "sparse" else alpha, b, amax, True, seed, t, dq.TAG_GRAD, 0, two.packed, two.delta,
+                            two.status)
+        step = dq.dq_master_step_each if each else dq.dq_master_step
+        args = (two.packed, two.delta, M, b) + (() if each else (float(np.float32(1) / np.float32(M)),))
+        step(*args, two.g_snap, two.x, two.y if acc else None, two.x_snap, two.xsum if acc else None, two.eta, two.theta, P.l1,
+             b_x, seed, t + 1, two.xq, two.delta_x, two.absmax_x[t & 1:], two.status)
+    torch.cuda.synchronize()
+    for name in ("packed", "delta", "x", "xq", "delta_x", "status") + (("y", "xsum") if acc else ()):
+        assert torch.equal(getattr(one, name), getattr(two, name)), name
+    assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
