@@ -20,8 +20,8 @@
 // Between the rounds of one dq_run_rounds call, everything of step 1 that does not depend on the model (which rows,
 // their extents and labels, the flat run itself) is laid out one round ahead by an extra block per worker of the
 // previous round's launch (see kPrepInts).
-// The full gradient uses the same block procedure over many blocks, each leaving a partial
-// d-vector that a second kernel adds up in a fixed order.
+// The full gradient takes its rows straight from memory in many blocks, each leaving a partial d-vector of fixed-point
+// sums that a second kernel adds up in a fixed order.
 #include <algorithm>
 #include <mutex>
 
@@ -40,7 +40,6 @@ constexpr int kColBits = 20;                     // staged entries carry column 
 constexpr int kColMask = (1 << kColBits) - 1;
 constexpr int kFlight = 4;                       // rows a wavefront reduces at the same time
 constexpr int kStageFlight = 4;                  // entries a thread stages at the same time (worker step)
-constexpr int kFullFlight = 8;                   // ... in the full gradient, whose groups of rows fill the staging buffer
 constexpr int kFlushRows = 1024;                 // rows between two flushes of the fixed-point sums (full gradient)
 constexpr int kCsrMaxRows = 256;                 // rows a block handles per pass (LDS metadata)
 constexpr int kMaxStage = 8192;                  // most entries the staging buffer is given
@@ -63,7 +62,7 @@ struct RowMeta {
     int len[kCsrMaxRows];
     int pre[kCsrMaxRows + 1];    // exclusive prefix sum of len
     float coef[kCsrMaxRows];
-    float z[kCsrMaxRows];        // cached margin at the snapshot (worker step); the label (full gradient)
+    float z[kCsrMaxRows];        // cached margin at the snapshot
     int chunk_row[kChunkSlots];  // the row that holds entry 64 c of the rows' concatenation, for the entries below 64 * kChunkSlots
 };
 
@@ -323,8 +322,7 @@ __device__ __forceinline__ void csr_reduce_group(RowMeta &meta, int g0, int g1, 
 // A row longer than `cap` is handled alone, straight from memory.
 // Only the columns of the window [c0, c1) are accumulated: a vector too long for LDS is built one window at a
 // time (the caller repeats the call per window; margins are recomputed).
-// FLIGHT: entries a thread stages at the same time.
-template <bool SECOND, int FLIGHT, typename VecReq, typename VecVal, typename CoefFn>
+template <bool SECOND, typename VecReq, typename VecVal, typename CoefFn>
 __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta, int nrows, int *acc, int c0, int c1,
                                                  const CsrStage &sg, FixedAcc &fx, uint32_t *su, int *poison,
                                                  VecReq vec_req, VecVal vec_val, CoefFn coef_of)
@@ -355,23 +353,23 @@ __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta
             const int total = meta.pre[g1] - base;
             uint32_t vmax = 0;
             // (the loop bound is the same for a whole wavefront: its lanes find their rows together)
-            for (int p0 = threadIdx.x; p0 - lane < total; p0 += FLIGHT * kCsrThreads) {
-                int64_t src[FLIGHT];
-                int tag[FLIGHT], col[FLIGHT];
-                float val[FLIGHT];
+            for (int p0 = threadIdx.x; p0 - lane < total; p0 += kStageFlight * kCsrThreads) {
+                int64_t src[kStageFlight];
+                int tag[kStageFlight], col[kStageFlight];
+                float val[kStageFlight];
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u)     // (a position past the end repeats an entry and is not stored)
+                for (int u = 0; u < kStageFlight; ++u)     // (a position past the end repeats an entry and is not stored)
                     src[u] = csr_stage_source(meta, g0, g1, base, total, p0 - lane + u * kCsrThreads, lane, u ? src[0] : 0, tag[u]);
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u) {
+                for (int u = 0; u < kStageFlight; ++u) {
                     col[u] = A.indices[src[u]];
                     val[u] = A.values[src[u]];
                 }
-                decltype(vec_req(0)) raw[FLIGHT];
+                decltype(vec_req(0)) raw[kStageFlight];
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u) raw[u] = vec_req(col[u]);
+                for (int u = 0; u < kStageFlight; ++u) raw[u] = vec_req(col[u]);
 #pragma unroll
-                for (int u = 0; u < FLIGHT; ++u) {
+                for (int u = 0; u < kStageFlight; ++u) {
                     const int p = p0 + u * kCsrThreads;
                     const float2 f = vec_val(raw[u], col[u]);
                     vmax = max(vmax, abs_bits(val[u]));
@@ -702,10 +700,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             }
             csr_prefix_lengths(meta, nrows);
             if (have_z)
-                csr_process_rows<false, kStageFlight>(a.A, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1), sg, fx, su,
+                csr_process_rows<false>(a.A, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1), sg, fx, su,
                                         &sh_poison, vec_req, vec_val, coef_of);
             else
-                csr_process_rows<true, kStageFlight>(a.A, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1), sg, fx, su,
+                csr_process_rows<true>(a.A, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1), sg, fx, su,
                                        &sh_poison, vec_req, vec_val, coef_of);
             if constexpr (COMMON) break;                       // (one pass)
         }
@@ -874,79 +872,183 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
 }
 
 // ------------------------------------------------------------------ epoch prologue
-// grid (P): block p owns rows [p*per, (p+1)*per), processed kCsrMaxRows at a time.
+// Grid (P): block p owns rows [p*per, (p+1)*per), in chunks of kFlushRows.  What bounds it is latency: a block has one
+// compute unit to itself (the sums of up to 35 k columns in LDS) and some fifteen thousand entries to fetch, each with a
+// gather behind it.  So there is no staging and no barrier between the rows: a wavefront takes kFullRows rows at
+// a time straight from memory -- 64 entries of each requested together, then their 64 gathers --, adds up their
+// margins across its lanes and keeps the coefficients in LDS.  Once all rows of the chunk have theirs, one barrier
+// gives the bound that fixes the unit of the fixed-point sums (FixedAcc), and every wavefront adds its rows' entries
+// (from L2 now) to the columns.  72,000 rows of 52 entries, 20,958 columns: 50.4 us with rows staged in LDS in groups of a
+// hundred, five barrier-separated phases each; now TEXT_US us.
+constexpr int kFullRows = 8;                              // rows a wavefront has in flight
+constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; about 17 KB of static arrays beside them
+
 __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
     const CsrView A, const float *__restrict__ x, float *__restrict__ z_out, float *__restrict__ partial, int64_t ldp,
-    double *__restrict__ loss_partial, int cap, int win)
+    double *__restrict__ loss_partial, int win)
 {
     extern __shared__ __align__(16) float lds[];
-    __shared__ RowMeta meta;
+    __shared__ int64_t sh_start[kFlushRows];
+    __shared__ int sh_len[kFlushRows];
+    __shared__ float sh_coef[kFlushRows];                // (the row's label until its coefficient is known)
     __shared__ double sh_loss[kCsrWaves];
     __shared__ uint32_t su[kCsrWaves];
-    __shared__ int sh_poison;
+    __shared__ float sf[kCsrWaves];
     int *acc = reinterpret_cast<int *>(lds);             // the window [c0, c1) of this block's partial sum, fixed point
-    const CsrStage sg = csr_stage_in(lds + win, cap, false);
-    if (threadIdx.x == 0) sh_poison = 0;                 // (published by the barriers of the first row pass)
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t per = (A.n + gridDim.x - 1) / gridDim.x;
     const int64_t i0 = blockIdx.x * per, i1 = min(A.n, i0 + per);
     const float inv_n = 1.0f / static_cast<float>(A.n);
     double loss = 0.0;                                   // the lanes that evaluate row scalars add to theirs
     float *mine = partial + static_cast<int64_t>(blockIdx.x) * ldp;
-    for (int64_t c0 = 0; c0 < ldp; c0 += win) {          // one window when the vector fits in LDS
-        const int64_t c1 = min(ldp, c0 + win);
-        for (int64_t j = threadIdx.x; j < c1 - c0; j += kCsrThreads) acc[j] = 0;
-        FixedAcc fx{0.0f, 0};
-        const bool first = c0 == 0;                      // margins and losses are recorded once
-        // The fixed-point sums go to this block's float32 partial vector at the end, and in between whenever
-        // kFlushRows rows have been added: a term is rounded relative to the bound of everything in the accumulator,
-        // which grows with the number of rows, so that number is kept small.
-        int since_flush = 0;
-        bool wrote = false;
-        for (int64_t ib = i0; ib < i1; ib += kCsrMaxRows) {
-            const int nrows = static_cast<int>(min<int64_t>(kCsrMaxRows, i1 - ib));
-            if (static_cast<int>(threadIdx.x) < nrows) {
-                const int64_t i = ib + threadIdx.x;
-                const int64_t s = A.indptr[i];
-                meta.row[threadIdx.x] = static_cast<int>(i);
-                meta.start[threadIdx.x] = s;
-                meta.len[threadIdx.x] = static_cast<int>(A.indptr[i + 1] - s);
-                meta.z[threadIdx.x] = A.y[i];            // (here: the row's label, so that no lane fetches it later)
-            }
-            csr_prefix_lengths(meta, nrows);
-            const int64_t ib_now = ib;
-            auto vec_req = [&](int c) { return x[c]; };
-            auto vec_val = [&](float xc, int) { return make_float2(xc, 0.0f); };
-            auto coef_of = [&](int r, float z, float) {
-                const int64_t i = ib_now + r;
-                const float y = meta.z[r];
-                if (first) {
-                    if (z_out) z_out[i] = z;
-                    loss += static_cast<double>(logistic_loss_fast(y * z));
-                }
-                // (a few lanes evaluate this while every other lane of the block waits: hardware exp, log and
-                // reciprocal, as in the dense kernel)
-                return logistic_slope_fast(y, z) * inv_n;
-            };
-            csr_process_rows<false, kFullFlight>(A, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(min(A.d, c1)), sg, fx, su,
-                                    &sh_poison, vec_req, vec_val, coef_of);
-            since_flush += nrows;
-            if (since_flush >= kFlushRows || ib + kCsrMaxRows >= i1) {         // (ends with a barrier: all adds are in)
-                const float unit = sh_poison ? __uint_as_float(0x7FC00000u) : ldexpf(1.0f, -fx.k);
-                for (int64_t j = c0 + threadIdx.x; j < c1; j += kCsrThreads) {
-                    const float v = static_cast<float>(acc[j - c0]) * unit;
-                    mine[j] = wrote ? mine[j] + v : v;
-                    acc[j - c0] = 0;
-                }
-                __syncthreads();
-                fx = FixedAcc{0.0f, 0};
-                since_flush = 0;
-                wrote = true;
-            }
+    for (int64_t j = 4ll * threadIdx.x; j < min<int64_t>(win, ldp); j += 4ll * kCsrThreads)
+        *reinterpret_cast<int4 *>(acc + j) = make_int4(0, 0, 0, 0);
+    if (i0 >= i1)                                        // a block without rows
+        for (int64_t j = 4ll * threadIdx.x; j < ldp; j += 4ll * kCsrThreads)
+            *reinterpret_cast<float4 *>(mine + j) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int64_t ib = i0; ib < i1; ib += kFlushRows) {
+        const int cn = static_cast<int>(min<int64_t>(kFlushRows, i1 - ib));
+        if (static_cast<int>(threadIdx.x) < cn) {        // (kFlushRows = kCsrThreads)
+            const int64_t i = ib + threadIdx.x, s = A.indptr[i];
+            sh_start[threadIdx.x] = s;
+            sh_len[threadIdx.x] = static_cast<int>(A.indptr[i + 1] - s);
+            sh_coef[threadIdx.x] = A.y[i];
         }
-        if (!wrote)                                      // a block without rows
-            for (int64_t j = c0 + threadIdx.x; j < c1; j += kCsrThreads) mine[j] = 0.0f;
         __syncthreads();
+        // One sweep over the wavefront's rows, kFullRows at a time: each_batch(first row, starts, lengths, longest, an entry
+        // that exists).  Row u of a batch is r + u * kCsrWaves; rows past the end have length 0.
+        const auto sweep = [&](auto each_batch) {
+            for (int r = wave; r < cn; r += kFullRows * kCsrWaves) {
+                int64_t st[kFullRows], some = 0;
+                int len[kFullRows], longest = 0;
+#pragma unroll
+                for (int u = 0; u < kFullRows; ++u) {
+                    const int ru = r + u * kCsrWaves;
+                    len[u] = __builtin_amdgcn_readfirstlane(ru < cn ? sh_len[min(ru, cn - 1)] : 0);
+                    const int64_t s = sh_start[min(ru, cn - 1)];
+                    st[u] = (static_cast<int64_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s >> 32))) << 32) |
+                            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s)));
+                    longest = max(longest, len[u]);
+                    some = len[u] > 0 ? st[u] : some;
+                }
+                each_batch(r, st, len, longest, some);
+            }
+        };
+        // 64 entries of each row of a batch, from position k of the row on (a lane past a row's end repeats its last one)
+        const auto fetch = [&](const int64_t (&st)[kFullRows], const int (&len)[kFullRows], int k, int64_t some,
+                               int (&col)[kFullRows], float (&val)[kFullRows]) {
+#pragma unroll
+            for (int u = 0; u < kFullRows; ++u) {
+                const int64_t base = len[u] > 0 ? st[u] : some;
+                const int at = min(k, max(len[u], 1) - 1);
+                col[u] = A.indices[base + at];
+                val[u] = A.values[base + at];
+            }
+        };
+        constexpr int kTogether = 4 * kWave;             // positions up to here are taken for all rows of a batch together
+        // ---- margins, losses and coefficients
+        uint32_t vmax = 0;
+        float csum = 0.0f;
+        sweep([&](int r, const int64_t (&st)[kFullRows], const int (&len)[kFullRows], int longest, int64_t some) {
+            float sum[kFullRows];
+#pragma unroll
+            for (int u = 0; u < kFullRows; ++u) sum[u] = 0.0f;
+            for (int k = lane; k - lane < min(longest, kTogether); k += kWave) {
+                int col[kFullRows];
+                float val[kFullRows], xv[kFullRows];
+                fetch(st, len, k, some, col, val);
+#pragma unroll
+                for (int u = 0; u < kFullRows; ++u) xv[u] = x[col[u]];
+#pragma unroll
+                for (int u = 0; u < kFullRows; ++u) {
+                    vmax = max(vmax, abs_bits(val[u]));
+                    sum[u] += k < len[u] ? val[u] * xv[u] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kFullRows; ++u)          // what long rows have left, kFullRows times 64 entries at a time
+                for (int k = kTogether + lane; k - lane < len[u]; k += kFullRows * kWave) {
+                    int col[kFullRows];
+                    float val[kFullRows], xv[kFullRows];
+#pragma unroll
+                    for (int v = 0; v < kFullRows; ++v) {
+                        const int64_t at = st[u] + min(k + v * kWave, len[u] - 1);
+                        col[v] = A.indices[at];
+                        val[v] = A.values[at];
+                    }
+#pragma unroll
+                    for (int v = 0; v < kFullRows; ++v) xv[v] = x[col[v]];
+#pragma unroll
+                    for (int v = 0; v < kFullRows; ++v) {
+                        vmax = max(vmax, abs_bits(val[v]));
+                        sum[u] += k + v * kWave < len[u] ? val[v] * xv[v] : 0.0f;
+                    }
+                }
+            float z = 0.0f;                              // lane u keeps and evaluates row u
+#pragma unroll
+            for (int u = 0; u < kFullRows; ++u) {
+                const float t = wave_sum_f32(sum[u]);
+                z = lane == u ? t : z;
+            }
+            const int rl = r + lane * kCsrWaves;
+            if (lane < kFullRows && rl < cn) {
+                const float y = sh_coef[rl];
+                // (hardware exp, log and reciprocal, as in the dense kernel)
+                const float coef = logistic_slope_fast(y, z) * inv_n;
+                if (z_out) z_out[ib + rl] = z;
+                loss += static_cast<double>(logistic_loss_fast(y * z));
+                sh_coef[rl] = coef;
+                csum += fabsf(coef);
+            }
+        });
+        csum = wave_sum_f32(csum);
+        if (lane == 0) sf[wave] = csum;
+        vmax = block_max_u32(vmax, su);                  // (its barriers also publish sf, the coefficients, the cleared sums)
+        const float bound = wave_sum_f32(lane < kCsrWaves ? sf[lane] : 0.0f) * __uint_as_float(vmax);
+        // The fixed-point sums go to this block's float32 partial vector after every chunk: a term is rounded relative to
+        // the bound of everything in the accumulator, which grows with the number of rows, so that number is kept small.
+        const bool finite = bound <= FLT_MAX;            // else Inf or NaN among the values or coefficients: all is NaN
+        const int k_unit = fixed_exponent(finite ? bound : 0.0f);
+        const float two_k = ldexpf(1.0f, k_unit), unit = finite ? ldexpf(1.0f, -k_unit) : __uint_as_float(0x7FC00000u);
+        // ---- scatter, a window of columns at a time (one when the vector fits in LDS)
+        for (int64_t c0 = 0; c0 < ldp; c0 += win) {
+            const int64_t c1 = min(ldp, c0 + win);
+            const int lo = static_cast<int>(c0), hi = static_cast<int>(c1);
+            if (finite)
+                sweep([&](int r, const int64_t (&st)[kFullRows], const int (&len)[kFullRows], int longest, int64_t some) {
+                    float coef[kFullRows];
+#pragma unroll
+                    for (int u = 0; u < kFullRows; ++u) coef[u] = sh_coef[min(r + u * kCsrWaves, cn - 1)];
+                    for (int k = lane; k - lane < min(longest, kTogether); k += kWave) {
+                        int col[kFullRows];
+                        float val[kFullRows];
+                        fetch(st, len, k, some, col, val);
+#pragma unroll
+                        for (int u = 0; u < kFullRows; ++u)
+                            if (k < len[u] && col[u] >= lo && col[u] < hi)
+                                atomicAdd(&acc[col[u] - lo], fixed_term(coef[u], val[u], two_k));
+                    }
+#pragma unroll
+                    for (int u = 0; u < kFullRows; ++u)
+                        for (int k = kTogether + lane; k < len[u]; k += kWave) {
+                            const int c = A.indices[st[u] + k];
+                            if (c >= lo && c < hi) atomicAdd(&acc[c - lo], fixed_term(coef[u], A.values[st[u] + k], two_k));
+                        }
+                });
+            __syncthreads();
+            for (int64_t j = c0 + 4ll * threadIdx.x; j < c1; j += 4ll * kCsrThreads) {
+                const int4 sum = *reinterpret_cast<const int4 *>(acc + (j - c0));
+                float4 v = make_float4(static_cast<float>(sum.x) * unit, static_cast<float>(sum.y) * unit,
+                                       static_cast<float>(sum.z) * unit, static_cast<float>(sum.w) * unit);
+                if (ib > i0) {
+                    const float4 before = *reinterpret_cast<const float4 *>(mine + j);
+                    v = make_float4(before.x + v.x, before.y + v.y, before.z + v.z, before.w + v.w);
+                }
+                *reinterpret_cast<float4 *>(mine + j) = v;
+                *reinterpret_cast<int4 *>(acc + (j - c0)) = make_int4(0, 0, 0, 0);
+            }
+            __syncthreads();
+        }
     }
     loss = wave_sum_f64(loss);
     if (lane == 0) sh_loss[wave] = loss;
@@ -1067,13 +1169,15 @@ int csr_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z
     const int P = static_cast<int>(csr_full_splits(n));
     float *partial = static_cast<float *>(ws);
     double *loss_partial = reinterpret_cast<double *>(partial + static_cast<int64_t>(P) * ldp);
-    const size_t lds = plan.lds;
+    // equal windows of columns, one when the vector fits
+    const int64_t win = pad4(ceil_div(ldp, ceil_div(ldp * 4, kFullLds)));
     static std::once_flag attr_once;
     static hipError_t attr_rc = hipSuccess;
     int rc = allow_big_lds(csr_full_partial_kernel, attr_once, attr_rc);
     if (rc != DQ_OK) return rc;
     const CsrView A{prob->indptr, prob->indices, prob->values, prob->y, n, d};
-    csr_full_partial_kernel<<<dim3(P), dim3(kCsrThreads), lds, st>>>(A, x, z_out, partial, ldp, loss_partial, plan.cap, plan.win);
+    csr_full_partial_kernel<<<dim3(P), dim3(kCsrThreads), static_cast<size_t>(win) * 4, st>>>(A, x, z_out, partial, ldp, loss_partial,
+                                                                                              static_cast<int>(win));
     DQ_LAUNCH_CHECK();
     return launch_full_finish(partial, P, ldp, n, d, x, prob->l2, prob->l1, loss_partial, g_out, obj_out, st);
 }

@@ -739,9 +739,10 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
 }
 
 // g = sum_p partial_p + l2*x.  Block (16 x 64): thread (tx, ty) adds partials ty, ty+64, ... of
-// float4 column blockIdx.x*16 + tx; the 64 sub-sums are then added in two fixed steps (8 threads add
-// 8 each, one adds those 8).  Narrow column tiles keep many compute units busy (d = 4096: 64 blocks).
-// Block 0 also writes P(x) = loss/n + (l2/2)||x||^2 + l1||x||_1.
+// float4 column blockIdx.x*16 + tx, four of them requested together; the 64 sub-sums are then added in two fixed steps
+// (8 threads add 8 each, one adds those 8).  Narrow column tiles keep many compute units busy (d = 4096: 64 blocks).
+// One block more, the first, writes P(x) = loss/n + (l2/2)||x||^2 + l1||x||_1: a pass over x that would otherwise come
+// after the sums of some block (20,958 columns 11.0 -> TEXT_FIN us, 47,236 columns 23.6 -> WIDE_FIN us).
 constexpr int kFinishX = 16, kFinishY = 64;
 __global__ __launch_bounds__(kFinishX *kFinishY) void full_finish_kernel(
     const float *__restrict__ partial, int P, int64_t ldp, int64_t n, int64_t d, const float *__restrict__ x, float l2,
@@ -751,11 +752,48 @@ __global__ __launch_bounds__(kFinishX *kFinishY) void full_finish_kernel(
     __shared__ float4 sh2[8][kFinishX];
     __shared__ double sdl[(kFinishX * kFinishY / kWave) * 3];
     const int tx = threadIdx.x, ty = threadIdx.y;
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * kFinishX + tx;      // float4 index
+    const int64_t k = static_cast<int64_t>(blockIdx.x - (obj_out ? 1 : 0)) * kFinishX + tx;      // float4 index
+    if (obj_out && blockIdx.x == 0) {
+        const int tid = ty * kFinishX + tx, nt = kFinishX * kFinishY;
+        double loss = 0.0, sq = 0.0, ab = 0.0;
+        for (int p = tid; p < P; p += nt) loss += loss_partial[p];
+        constexpr int kFlight = 8;
+        for (int64_t j0 = tid; j0 < d; j0 += kFlight * nt) {
+            float v[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) v[u] = x[min<int64_t>(j0 + u * nt, d - 1)];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                const double xj = j0 + u * nt < d ? static_cast<double>(v[u]) : 0.0;
+                sq += xj * xj;
+                ab += fabs(xj);
+            }
+        }
+        loss = wave_sum_f64(loss);
+        sq = wave_sum_f64(sq);
+        ab = wave_sum_f64(ab);
+        if ((tid & (kWave - 1)) == 0) { const int w = tid / kWave; sdl[w * 3] = loss; sdl[w * 3 + 1] = sq; sdl[w * 3 + 2] = ab; }
+        __syncthreads();
+        if (tid == 0) {
+            double L = 0.0, S = 0.0, A = 0.0;
+            for (int j = 0; j < nt / kWave; ++j) { L += sdl[j * 3]; S += sdl[j * 3 + 1]; A += sdl[j * 3 + 2]; }
+            obj_out[0] = L / static_cast<double>(n) + 0.5 * static_cast<double>(l2) * S + static_cast<double>(l1) * A;
+        }
+        return;
+    }
     const int64_t col = 4 * k;
     float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (col < ldp) {
-        for (int p = ty; p < P; p += kFinishY) {
+        constexpr int kFlight = 4;
+        int p = ty;
+        for (; p + (kFlight - 1) * kFinishY < P; p += kFlight * kFinishY) {
+            float4 t[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) t[u] = reinterpret_cast<const float4 *>(partial + static_cast<int64_t>(p + u * kFinishY) * ldp)[k];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
+        }
+        for (; p < P; p += kFinishY) {
             const float4 t = reinterpret_cast<const float4 *>(partial + static_cast<int64_t>(p) * ldp)[k];
             s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
         }
@@ -781,32 +819,12 @@ __global__ __launch_bounds__(kFinishX *kFinishY) void full_finish_kernel(
         for (int e = 0; e < 4; ++e)
             if (col + e < d) g_out[col + e] = v[e] + l2 * x[col + e];
     }
-    if (blockIdx.x == 0 && obj_out) {
-        const int tid = ty * kFinishX + tx, nt = kFinishX * kFinishY;
-        double loss = 0.0, sq = 0.0, ab = 0.0;
-        for (int p = tid; p < P; p += nt) loss += loss_partial[p];
-        for (int64_t j = tid; j < d; j += nt) {
-            const double xj = static_cast<double>(x[j]);
-            sq += xj * xj;
-            ab += fabs(xj);
-        }
-        loss = wave_sum_f64(loss);
-        sq = wave_sum_f64(sq);
-        ab = wave_sum_f64(ab);
-        if ((tid & (kWave - 1)) == 0) { const int w = tid / kWave; sdl[w * 3] = loss; sdl[w * 3 + 1] = sq; sdl[w * 3 + 2] = ab; }
-        __syncthreads();
-        if (tid == 0) {
-            double L = 0.0, S = 0.0, A = 0.0;
-            for (int j = 0; j < nt / kWave; ++j) { L += sdl[j * 3]; S += sdl[j * 3 + 1]; A += sdl[j * 3 + 2]; }
-            obj_out[0] = L / static_cast<double>(n) + 0.5 * static_cast<double>(l2) * S + static_cast<double>(l1) * A;
-        }
-    }
 }
 
 int launch_full_finish(const float *partial, int P, int64_t ldp, int64_t n, int64_t d, const float *x, float l2, float l1,
                        const double *loss_partial, float *g_out, double *obj_out, hipStream_t st)
 {
-    full_finish_kernel<<<dim3(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kFinishX))), dim3(kFinishX, kFinishY), 0, st>>>(
+    full_finish_kernel<<<dim3(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kFinishX) + (obj_out ? 1 : 0))), dim3(kFinishX, kFinishY), 0, st>>>(
         partial, P, ldp, n, d, x, l2, l1, loss_partial, g_out, obj_out);
     DQ_LAUNCH_CHECK();
     return DQ_OK;
