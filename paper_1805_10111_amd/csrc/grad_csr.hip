@@ -875,12 +875,13 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
 // Grid (P): block p owns rows [p*per, (p+1)*per), in chunks of kFlushRows.  What bounds it is latency: a block has one
 // compute unit to itself (the sums of up to 35 k columns in LDS) and some fifteen thousand entries to fetch, each with a
 // gather behind it.  So there is no staging and no barrier between the rows: a wavefront takes kFullRows rows at
-// a time straight from memory -- 64 entries of each requested together, then their 64 gathers --, adds up their
+// a time straight from memory -- 128 entries of each requested together, then their gathers --, adds up their
 // margins across its lanes and keeps the coefficients in LDS.  Once all rows of the chunk have theirs, one barrier
 // gives the bound that fixes the unit of the fixed-point sums (FixedAcc), and every wavefront adds its rows' entries
 // (from L2 now) to the columns.  72,000 rows of 52 entries, 20,958 columns: 50.4 us with rows staged in LDS in groups of a
 // hundred, five barrier-separated phases each; now TEXT_US us.
-constexpr int kFullRows = 8;                              // rows a wavefront has in flight
+constexpr int kFullRows = 9;                              // rows a wavefront has in flight,
+constexpr int kFullChunks = 2;                            // with so many pieces of 64 entries each
 constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; about 17 KB of static arrays beside them
 
 __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
@@ -888,7 +889,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
     double *__restrict__ loss_partial, int win)
 {
     extern __shared__ __align__(16) float lds[];
-    __shared__ int64_t sh_start[kFlushRows];
+    __shared__ uint32_t sh_start[kFlushRows];            // of the row's entries in the chunk's, in bytes of either array
     __shared__ int sh_len[kFlushRows];
     __shared__ float sh_coef[kFlushRows];                // (the row's label until its coefficient is known)
     __shared__ double sh_loss[kCsrWaves];
@@ -908,76 +909,93 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
             *reinterpret_cast<float4 *>(mine + j) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int64_t ib = i0; ib < i1; ib += kFlushRows) {
         const int cn = static_cast<int>(min<int64_t>(kFlushRows, i1 - ib));
+        // The chunk's entries: a scalar base and 32-bit byte offsets (1024 rows of fewer than 2^20 entries), so that a
+        // load takes two instructions of address arithmetic; with sixteen wavefronts on the compute unit the kernel is bound
+        // by instructions as much as by latency.
+        const int64_t e0 = A.indptr[ib];
+        const uint64_t e0u = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(e0 >> 32)))) << 32) |
+                             static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(e0)));
+        const char *ind = reinterpret_cast<const char *>(A.indices + e0u), *values = reinterpret_cast<const char *>(A.values + e0u);
+        const auto index_at = [&](uint32_t at) { return *reinterpret_cast<const uint32_t *>(ind + at); };
+        const auto value_at = [&](uint32_t at) { return *reinterpret_cast<const float *>(values + at); };
+        const auto x_at = [&](uint32_t col) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(x) + 4u * col); };
         if (static_cast<int>(threadIdx.x) < cn) {        // (kFlushRows = kCsrThreads)
             const int64_t i = ib + threadIdx.x, s = A.indptr[i];
-            sh_start[threadIdx.x] = s;
+            sh_start[threadIdx.x] = static_cast<uint32_t>(s - e0) * 4u;
             sh_len[threadIdx.x] = static_cast<int>(A.indptr[i + 1] - s);
             sh_coef[threadIdx.x] = A.y[i];
         }
         __syncthreads();
-        // One sweep over the wavefront's rows, kFullRows at a time: each_batch(first row, starts, lengths, longest, an entry
-        // that exists).  Row u of a batch is r + u * kCsrWaves; rows past the end have length 0.
+        // One sweep over the wavefront's rows, kFullRows at a time: each_batch(first row, starts, lengths, longest).  Row u
+        // of a batch is r + u * kCsrWaves; a row past the end has length 0, and a row of length 0 the start of one that
+        // has entries.
         const auto sweep = [&](auto each_batch) {
             for (int r = wave; r < cn; r += kFullRows * kCsrWaves) {
-                int64_t st[kFullRows], some = 0;
+                uint32_t st[kFullRows], some = 0;
                 int len[kFullRows], longest = 0;
 #pragma unroll
                 for (int u = 0; u < kFullRows; ++u) {
                     const int ru = r + u * kCsrWaves;
                     len[u] = __builtin_amdgcn_readfirstlane(ru < cn ? sh_len[min(ru, cn - 1)] : 0);
-                    const int64_t s = sh_start[min(ru, cn - 1)];
-                    st[u] = (static_cast<int64_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s >> 32))) << 32) |
-                            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s)));
+                    st[u] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh_start[min(ru, cn - 1)])));
                     longest = max(longest, len[u]);
                     some = len[u] > 0 ? st[u] : some;
                 }
-                each_batch(r, st, len, longest, some);
+#pragma unroll
+                for (int u = 0; u < kFullRows; ++u) st[u] = len[u] > 0 ? st[u] : some;
+                each_batch(r, st, len, longest);
             }
         };
-        // 64 entries of each row of a batch, from position k of the row on (a lane past a row's end repeats its last one)
-        const auto fetch = [&](const int64_t (&st)[kFullRows], const int (&len)[kFullRows], int k, int64_t some,
-                               int (&col)[kFullRows], float (&val)[kFullRows]) {
+        // kFullChunks pieces of 64 entries of each row of a batch, from position k of the row on (a lane past a row's end
+        // repeats its last one)
+        const auto fetch = [&](const uint32_t (&st)[kFullRows], const int (&len)[kFullRows], int k,
+                               uint32_t (&col)[kFullRows][kFullChunks], float (&val)[kFullRows][kFullChunks]) {
 #pragma unroll
-            for (int u = 0; u < kFullRows; ++u) {
-                const int64_t base = len[u] > 0 ? st[u] : some;
-                const int at = min(k, max(len[u], 1) - 1);
-                col[u] = A.indices[base + at];
-                val[u] = A.values[base + at];
-            }
+            for (int u = 0; u < kFullRows; ++u)
+#pragma unroll
+                for (int c = 0; c < kFullChunks; ++c) {
+                    const uint32_t at = st[u] + min(4u * static_cast<uint32_t>(k + c * kWave), 4u * (max(len[u], 1) - 1u));
+                    col[u][c] = index_at(at);
+                    val[u][c] = value_at(at);
+                }
         };
         constexpr int kTogether = 4 * kWave;             // positions up to here are taken for all rows of a batch together
         // ---- margins, losses and coefficients
         uint32_t vmax = 0;
         float csum = 0.0f;
-        sweep([&](int r, const int64_t (&st)[kFullRows], const int (&len)[kFullRows], int longest, int64_t some) {
+        sweep([&](int r, const uint32_t (&st)[kFullRows], const int (&len)[kFullRows], int longest) {
             float sum[kFullRows];
 #pragma unroll
             for (int u = 0; u < kFullRows; ++u) sum[u] = 0.0f;
-            for (int k = lane; k - lane < min(longest, kTogether); k += kWave) {
-                int col[kFullRows];
-                float val[kFullRows], xv[kFullRows];
-                fetch(st, len, k, some, col, val);
+            for (int k = lane; k - lane < min(longest, kTogether); k += kFullChunks * kWave) {
+                uint32_t col[kFullRows][kFullChunks];
+                float val[kFullRows][kFullChunks], xv[kFullRows][kFullChunks];
+                fetch(st, len, k, col, val);
 #pragma unroll
-                for (int u = 0; u < kFullRows; ++u) xv[u] = x[col[u]];
+                for (int u = 0; u < kFullRows; ++u)
 #pragma unroll
-                for (int u = 0; u < kFullRows; ++u) {
-                    vmax = max(vmax, abs_bits(val[u]));
-                    sum[u] += k < len[u] ? val[u] * xv[u] : 0.0f;
-                }
+                    for (int c = 0; c < kFullChunks; ++c) xv[u][c] = x_at(col[u][c]);
+#pragma unroll
+                for (int u = 0; u < kFullRows; ++u)
+#pragma unroll
+                    for (int c = 0; c < kFullChunks; ++c) {
+                        vmax = max(vmax, abs_bits(val[u][c]));
+                        sum[u] += k + c * kWave < len[u] ? val[u][c] * xv[u][c] : 0.0f;
+                    }
             }
 #pragma unroll
             for (int u = 0; u < kFullRows; ++u)          // what long rows have left, kFullRows times 64 entries at a time
                 for (int k = kTogether + lane; k - lane < len[u]; k += kFullRows * kWave) {
-                    int col[kFullRows];
+                    uint32_t col[kFullRows];
                     float val[kFullRows], xv[kFullRows];
 #pragma unroll
                     for (int v = 0; v < kFullRows; ++v) {
-                        const int64_t at = st[u] + min(k + v * kWave, len[u] - 1);
-                        col[v] = A.indices[at];
-                        val[v] = A.values[at];
+                        const uint32_t at = st[u] + 4u * min(k + v * kWave, len[u] - 1);
+                        col[v] = index_at(at);
+                        val[v] = value_at(at);
                     }
 #pragma unroll
-                    for (int v = 0; v < kFullRows; ++v) xv[v] = x[col[v]];
+                    for (int v = 0; v < kFullRows; ++v) xv[v] = x_at(col[v]);
 #pragma unroll
                     for (int v = 0; v < kFullRows; ++v) {
                         vmax = max(vmax, abs_bits(val[v]));
@@ -1013,26 +1031,28 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
         // ---- scatter, a window of columns at a time (one when the vector fits in LDS)
         for (int64_t c0 = 0; c0 < ldp; c0 += win) {
             const int64_t c1 = min(ldp, c0 + win);
-            const int lo = static_cast<int>(c0), hi = static_cast<int>(c1);
+            const uint32_t lo = static_cast<uint32_t>(c0), wide = static_cast<uint32_t>(c1 - c0);
             if (finite)
-                sweep([&](int r, const int64_t (&st)[kFullRows], const int (&len)[kFullRows], int longest, int64_t some) {
+                sweep([&](int r, const uint32_t (&st)[kFullRows], const int (&len)[kFullRows], int longest) {
                     float coef[kFullRows];
 #pragma unroll
                     for (int u = 0; u < kFullRows; ++u) coef[u] = sh_coef[min(r + u * kCsrWaves, cn - 1)];
-                    for (int k = lane; k - lane < min(longest, kTogether); k += kWave) {
-                        int col[kFullRows];
-                        float val[kFullRows];
-                        fetch(st, len, k, some, col, val);
+                    for (int k = lane; k - lane < min(longest, kTogether); k += kFullChunks * kWave) {
+                        uint32_t col[kFullRows][kFullChunks];
+                        float val[kFullRows][kFullChunks];
+                        fetch(st, len, k, col, val);
 #pragma unroll
                         for (int u = 0; u < kFullRows; ++u)
-                            if (k < len[u] && col[u] >= lo && col[u] < hi)
-                                atomicAdd(&acc[col[u] - lo], fixed_term(coef[u], val[u], two_k));
+#pragma unroll
+                            for (int c = 0; c < kFullChunks; ++c)
+                                if (k + c * kWave < len[u] && col[u][c] - lo < wide)
+                                    atomicAdd(&acc[col[u][c] - lo], fixed_term(coef[u], val[u][c], two_k));
                     }
 #pragma unroll
                     for (int u = 0; u < kFullRows; ++u)
                         for (int k = kTogether + lane; k < len[u]; k += kWave) {
-                            const int c = A.indices[st[u] + k];
-                            if (c >= lo && c < hi) atomicAdd(&acc[c - lo], fixed_term(coef[u], A.values[st[u] + k], two_k));
+                            const uint32_t c = index_at(st[u] + 4u * k);
+                            if (c - lo < wide) atomicAdd(&acc[c - lo], fixed_term(coef[u], value_at(st[u] + 4u * k), two_k));
                         }
                 });
             __syncthreads();
