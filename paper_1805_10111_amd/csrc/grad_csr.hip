@@ -872,26 +872,209 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
 }
 
 // ------------------------------------------------------------------ epoch prologue
-// Grid (P): block p owns rows [p*per, (p+1)*per), in chunks of kFlushRows.  What bounds it is latency: a block has one
-// compute unit to itself (the sums of up to 35 k columns in LDS) and some fifteen thousand entries to fetch, each with a
-// gather behind it.  So there is no staging and no barrier between the rows: a wavefront takes kFullRows rows at
-// a time straight from memory -- 128 entries of each requested together, then their gathers --, adds up their
-// margins across its lanes and keeps the coefficients in LDS.  Once all rows of the chunk have theirs, one barrier
-// gives the bound that fixes the unit of the fixed-point sums (FixedAcc), and every wavefront adds its rows' entries
-// (from L2 now) to the columns.  72,000 rows of 52 entries, 20,958 columns: 50.4 us with rows staged in LDS in groups of a
-// hundred, five barrier-separated phases each; now TEXT_US us.
-constexpr int kFullRows = 9;                              // rows a wavefront has in flight,
-constexpr int kFullChunks = 2;                            // with so many pieces of 64 entries each
+// Grid (P): block p owns rows [p*per, (p+1)*per), in chunks of kFlushRows.  What bounds it is latency and the instructions
+// of sixteen wavefronts on one compute unit: a block has one to itself (the sums of up to 35 k columns in LDS) and
+// some fifteen thousand entries to fetch, each with a gather behind it.  So there is no staging and no barrier between
+// the rows: L lanes of a wavefront take a row, ROWS such rows at a time straight from memory -- CHUNKS pieces of L
+// entries of each requested together, then their gathers --, add up its margin and keep its coefficient in LDS.  Once all
+// rows of the chunk have theirs, one barrier gives the bound that fixes the unit of the fixed-point sums (FixedAcc),
+// and the same lanes add the rows' entries (from L2 now) to the columns.  72,000 rows of 52 entries, 20,958
+// columns: 50.4 us with rows staged in LDS in groups of a hundred, five barrier-separated phases each; now 29.0 us;
+// 80,000 rows of 100 entries, 60,000 columns 236 -> 71 us; 40,000 rows of 20, 2000 columns 14.7 -> 13.4 us.
 constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; about 17 KB of static arrays beside them
+constexpr int kTogether = 256;                            // positions of a row up to here are its own lanes' work
+
+// The rows of a chunk in LDS, and where their entries lie: a scalar base and 32-bit byte offsets (1024 rows of fewer than
+// 2^20 entries each), so that a load takes two instructions of address arithmetic.
+struct FullChunk {
+    const char *indices, *values;
+    int rows;                                             // of the chunk
+    const uint32_t *start;                                // of a row's entries, in bytes of either array
+    const int *len;
+    float *coef;                                          // the row's label until its coefficient is known
+    __device__ __forceinline__ uint32_t index_at(uint32_t at) const { return *reinterpret_cast<const uint32_t *>(indices + at); }
+    __device__ __forceinline__ float value_at(uint32_t at) const { return *reinterpret_cast<const float *>(values + at); }
+};
+
+// The wavefront's rows, ROWS * (64 / L) at a time: each_batch(rows, starts, lengths, longest), all per lane but `longest`
+// (of the whole wavefront).  A row past the chunk's end has length 0, and a row of length 0 the start 0 of an entry that
+// exists wherever any row has one.
+template <int L, int ROWS, typename Batch>
+__device__ __forceinline__ void full_sweep(const FullChunk &ch, Batch each_batch)
+{
+    constexpr int G = kWave / L;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int r = wave * G; r < ch.rows; r += ROWS * G * kCsrWaves) {
+        int row[ROWS], len[ROWS], longest = 0;
+        uint32_t st[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            row[u] = r + u * G * kCsrWaves + (L == kWave ? 0 : lane / L);
+            const int rc = min(row[u], ch.rows - 1);
+            len[u] = row[u] < ch.rows ? ch.len[rc] : 0;
+            st[u] = len[u] > 0 ? ch.start[rc] : 0u;
+            if constexpr (L == kWave) {                   // (the same for all lanes: scalars)
+                len[u] = __builtin_amdgcn_readfirstlane(len[u]);
+                st[u] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(st[u])));
+            }
+            longest = max(longest, len[u]);
+        }
+        if constexpr (L != kWave) longest = static_cast<int>(wave_max_u32(static_cast<uint32_t>(longest)));
+        each_batch(row, st, len, longest);
+    }
+}
+
+template <int L, int ROWS, int CHUNKS>
+__device__ __forceinline__ void full_fetch(const FullChunk &ch, const uint32_t (&st)[ROWS], const int (&len)[ROWS], int k,
+                                           uint32_t (&col)[ROWS][CHUNKS], float (&val)[ROWS][CHUNKS])
+{
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {                // (a lane past a row's end repeats its last entry)
+            const uint32_t at = st[u] + min(4u * static_cast<uint32_t>(k + c * L), 4u * (max(len[u], 1) - 1u));
+            col[u][c] = ch.index_at(at);
+            val[u][c] = ch.value_at(at);
+        }
+}
+
+// Margins, losses and coefficients of the chunk's rows; the lanes' share of sum |coefficient| and the largest |value|.
+template <int L, int ROWS, int CHUNKS>
+__device__ __forceinline__ void full_margins(const FullChunk &ch, const float *__restrict__ x, float *__restrict__ z_out,
+                                             float inv_n, double &loss, float &csum, uint32_t &vmax)
+{
+    const int lane = threadIdx.x & (kWave - 1), in_row = lane % L;
+    const auto x_at = [&](uint32_t col) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(x) + 4u * col); };
+    full_sweep<L, ROWS>(ch, [&](const int (&row)[ROWS], const uint32_t (&st)[ROWS], const int (&len)[ROWS], int longest) {
+        float sum[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) sum[u] = 0.0f;
+        for (int k = in_row; k - in_row < min(longest, kTogether); k += CHUNKS * L) {
+            uint32_t col[ROWS][CHUNKS];
+            float val[ROWS][CHUNKS], xv[ROWS][CHUNKS];
+            full_fetch<L, ROWS, CHUNKS>(ch, st, len, k, col, val);
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+                for (int c = 0; c < CHUNKS; ++c) xv[u][c] = x_at(col[u][c]);
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+                for (int c = 0; c < CHUNKS; ++c) {
+                    vmax = max(vmax, abs_bits(val[u][c]));
+                    const int p = k + c * L;              // (positions past kTogether: below)
+                    sum[u] += p < min(len[u], kTogether) ? val[u][c] * xv[u][c] : 0.0f;
+                }
+        }
+        // what rows of more than kTogether entries have left: the whole wavefront's, eight pieces of 64 at a time
+        if (longest > kTogether) {
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u)
+                for (int g = 0; g < kWave / L; ++g) {
+                    const int n = __builtin_amdgcn_readlane(len[u], g * L);
+                    const uint32_t s = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(st[u]), g * L));
+                    if (n <= kTogether) continue;
+                    constexpr int kFlight = 8;
+                    float t = 0.0f;
+                    for (int k = kTogether + lane; k - lane < n; k += kFlight * kWave) {
+                        uint32_t col[kFlight];
+                        float val[kFlight], xv[kFlight];
+#pragma unroll
+                        for (int v = 0; v < kFlight; ++v) {
+                            const uint32_t at = s + 4u * min(k + v * kWave, n - 1);
+                            col[v] = ch.index_at(at);
+                            val[v] = ch.value_at(at);
+                        }
+#pragma unroll
+                        for (int v = 0; v < kFlight; ++v) xv[v] = x_at(col[v]);
+#pragma unroll
+                        for (int v = 0; v < kFlight; ++v) {
+                            vmax = max(vmax, abs_bits(val[v]));
+                            t += k + v * kWave < n ? val[v] * xv[v] : 0.0f;
+                        }
+                    }
+                    t = wave_sum_f32(t);
+                    sum[u] += lane == g * L ? t : 0.0f;
+                }
+        }
+        // the row's sum reaches its last lane (L = 16: two quad permutes and two row shifts); for L = 64 lane u takes row u
+        float z = 0.0f, y = 0.0f;
+        int at = -1;
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            float t = sum[u];
+            if constexpr (L == kWave) {
+                t = wave_sum_f32(t);
+                z = lane == u ? t : z;
+                at = lane == u ? row[u] : at;
+            } else {
+                static_assert(L == 16, "lanes per row");
+                t += __int_as_float(dpp_move_or_zero<0xb1, 0xf>(__float_as_int(t)));
+                t += __int_as_float(dpp_move_or_zero<0x4e, 0xf>(__float_as_int(t)));
+                t += __int_as_float(dpp_move_or_zero<0x114, 0xf>(__float_as_int(t)));
+                t += __int_as_float(dpp_move_or_zero<0x118, 0xf>(__float_as_int(t)));
+                // lane 15 of the row's lanes holds the sum; lane 15 - u is the one that evaluates row u
+                t = __shfl(t, lane | (L - 1), kWave);
+                z = in_row == L - 1 - u ? t : z;
+                at = in_row == L - 1 - u ? row[u] : at;
+            }
+        }
+        if (at >= 0 && at < ch.rows) {
+            y = ch.coef[at];
+            // (hardware exp, log and reciprocal, as in the dense kernel)
+            const float coef = logistic_slope_fast(y, z) * inv_n;
+            if (z_out) z_out[at] = z;
+            loss += static_cast<double>(logistic_loss_fast(y * z));
+            ch.coef[at] = coef;
+            csum += fabsf(coef);
+        }
+    });
+}
+
+// The entries of the chunk's rows in columns lo .. lo + wide - 1 are added to acc.
+template <int L, int ROWS, int CHUNKS>
+__device__ __forceinline__ void full_scatter(const FullChunk &ch, int *acc, uint32_t lo, uint32_t wide, float two_k)
+{
+    const int lane = threadIdx.x & (kWave - 1), in_row = lane % L;
+    full_sweep<L, ROWS>(ch, [&](const int (&row)[ROWS], const uint32_t (&st)[ROWS], const int (&len)[ROWS], int longest) {
+        float coef[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) coef[u] = ch.coef[min(row[u], ch.rows - 1)];
+        for (int k = in_row; k - in_row < min(longest, kTogether); k += CHUNKS * L) {
+            uint32_t col[ROWS][CHUNKS];
+            float val[ROWS][CHUNKS];
+            full_fetch<L, ROWS, CHUNKS>(ch, st, len, k, col, val);
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+                for (int c = 0; c < CHUNKS; ++c)
+                    if (k + c * L < min(len[u], kTogether) && col[u][c] - lo < wide)
+                        atomicAdd(&acc[col[u][c] - lo], fixed_term(coef[u], val[u][c], two_k));
+        }
+        if (longest > kTogether) {
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u)
+                for (int g = 0; g < kWave / L; ++g) {
+                    const int n = __builtin_amdgcn_readlane(len[u], g * L);
+                    const uint32_t s = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(st[u]), g * L));
+                    const float cf = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(coef[u]), g * L));
+                    for (int k = kTogether + lane; k < n; k += kWave) {
+                        const uint32_t c = ch.index_at(s + 4u * k);
+                        if (c - lo < wide) atomicAdd(&acc[c - lo], fixed_term(cf, ch.value_at(s + 4u * k), two_k));
+                    }
+                }
+        }
+    });
+}
 
 __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
     const CsrView A, const float *__restrict__ x, float *__restrict__ z_out, float *__restrict__ partial, int64_t ldp,
     double *__restrict__ loss_partial, int win)
 {
     extern __shared__ __align__(16) float lds[];
-    __shared__ uint32_t sh_start[kFlushRows];            // of the row's entries in the chunk's, in bytes of either array
+    __shared__ uint32_t sh_start[kFlushRows];
     __shared__ int sh_len[kFlushRows];
-    __shared__ float sh_coef[kFlushRows];                // (the row's label until its coefficient is known)
+    __shared__ float sh_coef[kFlushRows];
     __shared__ double sh_loss[kCsrWaves];
     __shared__ uint32_t su[kCsrWaves];
     __shared__ float sf[kCsrWaves];
@@ -909,116 +1092,32 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
             *reinterpret_cast<float4 *>(mine + j) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int64_t ib = i0; ib < i1; ib += kFlushRows) {
         const int cn = static_cast<int>(min<int64_t>(kFlushRows, i1 - ib));
-        // The chunk's entries: a scalar base and 32-bit byte offsets (1024 rows of fewer than 2^20 entries), so that a
-        // load takes two instructions of address arithmetic; with sixteen wavefronts on the compute unit the kernel is bound
-        // by instructions as much as by latency.
-        const int64_t e0 = A.indptr[ib];
-        const uint64_t e0u = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(e0 >> 32)))) << 32) |
-                             static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(e0)));
-        const char *ind = reinterpret_cast<const char *>(A.indices + e0u), *values = reinterpret_cast<const char *>(A.values + e0u);
-        const auto index_at = [&](uint32_t at) { return *reinterpret_cast<const uint32_t *>(ind + at); };
-        const auto value_at = [&](uint32_t at) { return *reinterpret_cast<const float *>(values + at); };
-        const auto x_at = [&](uint32_t col) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(x) + 4u * col); };
-        if (static_cast<int>(threadIdx.x) < cn) {        // (kFlushRows = kCsrThreads)
-            const int64_t i = ib + threadIdx.x, s = A.indptr[i];
-            sh_start[threadIdx.x] = static_cast<uint32_t>(s - e0) * 4u;
-            sh_len[threadIdx.x] = static_cast<int>(A.indptr[i + 1] - s);
-            sh_coef[threadIdx.x] = A.y[i];
+        const auto scalar64 = [](int64_t v) {
+            return (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)))) << 32) |
+                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+        };
+        // (requested side by side, for rows that exist: one trip to memory; kFlushRows = kCsrThreads)
+        const int64_t i = ib + min(static_cast<int>(threadIdx.x), cn - 1);
+        const int64_t first = A.indptr[ib], last = A.indptr[ib + cn], row_first = A.indptr[i], row_last = A.indptr[i + 1];
+        const float label = A.y[i];
+        const uint64_t e0 = scalar64(first), e1 = scalar64(last);
+        if (static_cast<int>(threadIdx.x) < cn) {
+            sh_start[threadIdx.x] = static_cast<uint32_t>(static_cast<uint64_t>(row_first) - e0) * 4u;
+            sh_len[threadIdx.x] = static_cast<int>(row_last - row_first);
+            sh_coef[threadIdx.x] = label;
         }
         __syncthreads();
-        // One sweep over the wavefront's rows, kFullRows at a time: each_batch(first row, starts, lengths, longest).  Row u
-        // of a batch is r + u * kCsrWaves; a row past the end has length 0, and a row of length 0 the start of one that
-        // has entries.
-        const auto sweep = [&](auto each_batch) {
-            for (int r = wave; r < cn; r += kFullRows * kCsrWaves) {
-                uint32_t st[kFullRows], some = 0;
-                int len[kFullRows], longest = 0;
-#pragma unroll
-                for (int u = 0; u < kFullRows; ++u) {
-                    const int ru = r + u * kCsrWaves;
-                    len[u] = __builtin_amdgcn_readfirstlane(ru < cn ? sh_len[min(ru, cn - 1)] : 0);
-                    st[u] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh_start[min(ru, cn - 1)])));
-                    longest = max(longest, len[u]);
-                    some = len[u] > 0 ? st[u] : some;
-                }
-#pragma unroll
-                for (int u = 0; u < kFullRows; ++u) st[u] = len[u] > 0 ? st[u] : some;
-                each_batch(r, st, len, longest);
-            }
-        };
-        // kFullChunks pieces of 64 entries of each row of a batch, from position k of the row on (a lane past a row's end
-        // repeats its last one)
-        const auto fetch = [&](const uint32_t (&st)[kFullRows], const int (&len)[kFullRows], int k,
-                               uint32_t (&col)[kFullRows][kFullChunks], float (&val)[kFullRows][kFullChunks]) {
-#pragma unroll
-            for (int u = 0; u < kFullRows; ++u)
-#pragma unroll
-                for (int c = 0; c < kFullChunks; ++c) {
-                    const uint32_t at = st[u] + min(4u * static_cast<uint32_t>(k + c * kWave), 4u * (max(len[u], 1) - 1u));
-                    col[u][c] = index_at(at);
-                    val[u][c] = value_at(at);
-                }
-        };
-        constexpr int kTogether = 4 * kWave;             // positions up to here are taken for all rows of a batch together
-        // ---- margins, losses and coefficients
+        const FullChunk ch{reinterpret_cast<const char *>(A.indices + e0), reinterpret_cast<const char *>(A.values + e0), cn,
+                           sh_start, sh_len, sh_coef};
+        // A row on a whole wavefront, or four rows side by side where they average at most kShortRow entries (measured at
+        // 20 entries: 18.2 us with whole wavefronts, 14.2 with quarters; at 52: 29.0 and 29.4).
+        constexpr uint64_t kShortRow = 32;
+        const bool short_rows = e1 - e0 <= kShortRow * static_cast<uint64_t>(cn);
         uint32_t vmax = 0;
         float csum = 0.0f;
-        sweep([&](int r, const uint32_t (&st)[kFullRows], const int (&len)[kFullRows], int longest) {
-            float sum[kFullRows];
-#pragma unroll
-            for (int u = 0; u < kFullRows; ++u) sum[u] = 0.0f;
-            for (int k = lane; k - lane < min(longest, kTogether); k += kFullChunks * kWave) {
-                uint32_t col[kFullRows][kFullChunks];
-                float val[kFullRows][kFullChunks], xv[kFullRows][kFullChunks];
-                fetch(st, len, k, col, val);
-#pragma unroll
-                for (int u = 0; u < kFullRows; ++u)
-#pragma unroll
-                    for (int c = 0; c < kFullChunks; ++c) xv[u][c] = x_at(col[u][c]);
-#pragma unroll
-                for (int u = 0; u < kFullRows; ++u)
-#pragma unroll
-                    for (int c = 0; c < kFullChunks; ++c) {
-                        vmax = max(vmax, abs_bits(val[u][c]));
-                        sum[u] += k + c * kWave < len[u] ? val[u][c] * xv[u][c] : 0.0f;
-                    }
-            }
-#pragma unroll
-            for (int u = 0; u < kFullRows; ++u)          // what long rows have left, kFullRows times 64 entries at a time
-                for (int k = kTogether + lane; k - lane < len[u]; k += kFullRows * kWave) {
-                    uint32_t col[kFullRows];
-                    float val[kFullRows], xv[kFullRows];
-#pragma unroll
-                    for (int v = 0; v < kFullRows; ++v) {
-                        const uint32_t at = st[u] + 4u * min(k + v * kWave, len[u] - 1);
-                        col[v] = index_at(at);
-                        val[v] = value_at(at);
-                    }
-#pragma unroll
-                    for (int v = 0; v < kFullRows; ++v) xv[v] = x_at(col[v]);
-#pragma unroll
-                    for (int v = 0; v < kFullRows; ++v) {
-                        vmax = max(vmax, abs_bits(val[v]));
-                        sum[u] += k + v * kWave < len[u] ? val[v] * xv[v] : 0.0f;
-                    }
-                }
-            float z = 0.0f;                              // lane u keeps and evaluates row u
-#pragma unroll
-            for (int u = 0; u < kFullRows; ++u) {
-                const float t = wave_sum_f32(sum[u]);
-                z = lane == u ? t : z;
-            }
-            const int rl = r + lane * kCsrWaves;
-            if (lane < kFullRows && rl < cn) {
-                const float y = sh_coef[rl];
-                // (hardware exp, log and reciprocal, as in the dense kernel)
-                const float coef = logistic_slope_fast(y, z) * inv_n;
-                if (z_out) z_out[ib + rl] = z;
-                loss += static_cast<double>(logistic_loss_fast(y * z));
-                sh_coef[rl] = coef;
-                csum += fabsf(coef);
-            }
-        });
+        float *z_chunk = z_out ? z_out + ib : nullptr;
+        if (short_rows) full_margins<16, 5, 3>(ch, x, z_chunk, inv_n, loss, csum, vmax);
+        else full_margins<kWave, 6, 2>(ch, x, z_chunk, inv_n, loss, csum, vmax);
         csum = wave_sum_f32(csum);
         if (lane == 0) sf[wave] = csum;
         vmax = block_max_u32(vmax, su);                  // (its barriers also publish sf, the coefficients, the cleared sums)
@@ -1028,33 +1127,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
         const bool finite = bound <= FLT_MAX;            // else Inf or NaN among the values or coefficients: all is NaN
         const int k_unit = fixed_exponent(finite ? bound : 0.0f);
         const float two_k = ldexpf(1.0f, k_unit), unit = finite ? ldexpf(1.0f, -k_unit) : __uint_as_float(0x7FC00000u);
-        // ---- scatter, a window of columns at a time (one when the vector fits in LDS)
-        for (int64_t c0 = 0; c0 < ldp; c0 += win) {
+        for (int64_t c0 = 0; c0 < ldp; c0 += win) {      // a window of columns at a time (one when the vector fits in LDS)
             const int64_t c1 = min(ldp, c0 + win);
             const uint32_t lo = static_cast<uint32_t>(c0), wide = static_cast<uint32_t>(c1 - c0);
-            if (finite)
-                sweep([&](int r, const uint32_t (&st)[kFullRows], const int (&len)[kFullRows], int longest) {
-                    float coef[kFullRows];
-#pragma unroll
-                    for (int u = 0; u < kFullRows; ++u) coef[u] = sh_coef[min(r + u * kCsrWaves, cn - 1)];
-                    for (int k = lane; k - lane < min(longest, kTogether); k += kFullChunks * kWave) {
-                        uint32_t col[kFullRows][kFullChunks];
-                        float val[kFullRows][kFullChunks];
-                        fetch(st, len, k, col, val);
-#pragma unroll
-                        for (int u = 0; u < kFullRows; ++u)
-#pragma unroll
-                            for (int c = 0; c < kFullChunks; ++c)
-                                if (k + c * kWave < len[u] && col[u][c] - lo < wide)
-                                    atomicAdd(&acc[col[u][c] - lo], fixed_term(coef[u], val[u][c], two_k));
-                    }
-#pragma unroll
-                    for (int u = 0; u < kFullRows; ++u)
-                        for (int k = kTogether + lane; k < len[u]; k += kWave) {
-                            const uint32_t c = index_at(st[u] + 4u * k);
-                            if (c - lo < wide) atomicAdd(&acc[c - lo], fixed_term(coef[u], value_at(st[u] + 4u * k), two_k));
-                        }
-                });
+            if (finite && short_rows) full_scatter<16, 5, 3>(ch, acc, lo, wide, two_k);
+            else if (finite) full_scatter<kWave, 6, 2>(ch, acc, lo, wide, two_k);
             __syncthreads();
             for (int64_t j = c0 + 4ll * threadIdx.x; j < c1; j += 4ll * kCsrThreads) {
                 const int4 sum = *reinterpret_cast<const int4 *>(acc + (j - c0));

@@ -456,3 +456,35 @@ def test_worker_step_with_and_without_workspace(dq, problems, sparsify, b, want_
     if want_nnz:
         codes = np.stack([oracle.unpack(words(outs[0][0])[w, :nw], d, b) for w in range(M)])
         assert np.array_equal(host(outs[0][2]), np.count_nonzero(codes, axis=1))
+
+
+@pytest.mark.parametrize("kind", ["short", "long", "one_long_row", "empty_rows", "one_row", "wide"])
+def test_full_gradient_over_row_lengths(dq, kind):
+    """Rows on a quarter of a wavefront and on a whole one, rows that whole wavefronts finish, rows and blocks without
+    entries, more columns than one LDS window, several chunks of rows per block: against the oracle."""
+    rng = np.random.default_rng(7)
+    n, d, lens = {"short": (300000, 900, lambda n: rng.integers(0, 20, n)), "long": (900, 6000, lambda n: rng.integers(200, 320, n)),
+                  "one_long_row": (700, 30000, lambda n: np.where(np.arange(n) == 33, 20000, 6)),
+                  "empty_rows": (1000, 500, lambda n: np.where(np.arange(n) % 5 == 0, 40, 0)),
+                  "one_row": (1, 77, lambda n: np.full(n, 77)), "wide": (400, 80001, lambda n: rng.integers(0, 60, n))}[kind]
+    lens = lens(n)
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=indptr[1:])
+    if kind == "short":                                      # (distinct columns of a row: a stride through the matrix)
+        first = np.repeat(rng.integers(0, d - 800, n), lens)
+        within = np.arange(indptr[-1]) - np.repeat(indptr[:-1], lens)
+        indices = (first + 37 * within).astype(np.int32)
+    else:
+        indices = np.concatenate([np.sort(rng.choice(d, size=l, replace=False)) for l in lens]).astype(np.int32)
+    values = (rng.standard_normal(indptr[-1]) / np.sqrt(np.repeat(np.maximum(lens, 1), lens))).astype(np.float32)
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    p = synth.Problem(n=n, d=d, y=y, l2=1e-3, l1=1e-4, indptr=indptr, indices=indices, values=values)
+    P = dq.DeviceProblem.from_host(p)
+    x = (0.5 * rng.standard_normal(d)).astype(np.float32)
+    g, z, obj = torch.zeros(d, device="cuda"), torch.zeros(n, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+    dq.dq_full_grad(P, dev(x), g, z, obj, dq.new_workspace(dq.OP_FULL_GRAD, P))
+    ref = oracle.RefProblem(p)
+    want_g, want_z = oracle.full_grad(ref, x, want_margins=True)
+    _close(host(g), want_g)
+    _close(host(z), want_z)
+    assert abs(host(obj)[0] - oracle.objective(ref, x)) <= TOL * abs(oracle.objective(ref, x))
