@@ -380,6 +380,23 @@ __device__ __forceinline__ void store_quad_bits(uint32_t bits, int64_t q, int64_
     if (q < quads && sub == 0) out[q / kQuadsPerWord] = bits;
 }
 
+// Fields of any width 2 <= b <= 16, which may straddle words: the 4 b bits of quad q (relative to a quad at which a word
+// begins, a multiple of eight) are ORed into `words` in LDS, zero before; bits are disjoint, so the order is of no interest.
+__device__ __forceinline__ void or_quad_bits(uint32_t *words, int q, int b, const int (&k)[4])
+{
+    const uint32_t mask = (1u << b) - 1u;
+    uint64_t v = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v |= static_cast<uint64_t>(static_cast<uint32_t>(k[e]) & mask) << (e * b);
+    if (v == 0) return;
+    const int bit = 4 * b * q, w = bit >> 5, sh = bit & 31;
+    const uint64_t lo = v << sh;
+    const uint32_t hi = sh ? static_cast<uint32_t>(v >> (64 - sh)) : 0u;
+    atomicOr(words + w, static_cast<uint32_t>(lo));
+    if (lo >> 32) atomicOr(words + w + 1, static_cast<uint32_t>(lo >> 32));
+    if (hi) atomicOr(words + w + 2, hi);
+}
+
 // prox of eta*l1*|.| : soft-threshold at kappa = eta*l1.
 __device__ __forceinline__ float soft_threshold(float z, float kappa)
 {

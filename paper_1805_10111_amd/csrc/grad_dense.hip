@@ -29,7 +29,6 @@
 namespace dq {
 
 constexpr int kRowThreads = 256;
-constexpr int kRowWaves = kRowThreads / kWave;
 constexpr int kMaxRowsPerBlock = 64;             // mini-batch rows a block may own: lane j of a wavefront keeps row j
 
 // Thread's share of a row: float4 columns tid + T*c, c < NC (T threads per block); zero past d.
@@ -415,11 +414,14 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         }
         my_row = static_cast<uint64_t>(i) < static_cast<uint64_t>(a.n) ? static_cast<int>(i) : -1;   // out of range: ignored
     }
-    // whole batches of valid rows only (the usual case): the row loads then carry no condition, so a wait for one
-    // batch can leave the loads of the next one in flight.  (Every wavefront holds the same row numbers and takes
-    // the same decision.)
-    const bool plain = DB == 2 || (nrows > 0 && nrows % R == 0 && __all(lane >= nrows || my_row >= 0));
-    const auto row_number = [&](int j) { return __builtin_amdgcn_readlane(my_row, j); };      // j < 64, wave-uniform
+    // valid rows only (the usual case): the row loads then carry no condition, so a wait for one batch can leave the
+    // loads of the next one in flight.  A position past the last row repeats that row, with coefficient 0 (a block of
+    // 15 rows whose loads sat behind tests took longer than four of four rows).  (Every wavefront holds the same row
+    // numbers and takes the same decision.)
+    const bool plain = DB == 2 || (nrows > 0 && __all(lane >= nrows || my_row >= 0));
+    const auto row_number = [&](int j) {                                                      // wave-uniform
+        return __builtin_amdgcn_readlane(my_row, DB == 2 ? j : min(j, nrows - 1));
+    };
 
     float4 dx[NC], xs[HAVE_Z ? 1 : NC], acc[NC];
     const float inv_B = 1.0f / static_cast<float>(a.B);      // the mean over the mini-batch, as one multiplication per row
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
     zero_cols<NC>(acc);
 
     // ---- stream the rows, R at a time
-    if (DB == 2 || (DB == 1 && plain && nrows % (2 * R) == 0)) {
+    if (DB == 2 || (DB == 1 && plain)) {
         // two row buffers: while one batch is reduced the other one is in flight; no load sits behind a condition
         float4 row2[R][NC];
         load_rows(R, row2);
@@ -841,11 +843,14 @@ int64_t dense_vr_splits(int64_t M, int64_t B, int64_t d)
     // (two per compute unit) stream rows, each owning at least 4 of them.  Rows wider than 1024 floats
     // are streamed with two row buffers per block (see dense_worker): one block per compute unit
     // then, and a whole number of batch pairs per block.
+    // For rows of up to 1024 floats a block takes whole batches of 16 rows: all of a batch are in flight together, so a
+    // batch cut over several blocks takes as long and leaves more partial sums (M = 10, B = 100, d = 784: 13.0 us for both kernels with
+    // four rows per block, 12.6 with 15).
     const bool two_buffers = dense_nc(d) >= 2;
     const int64_t target = two_buffers ? 256 : 512;
     if (B <= 32) return 1;
     int64_t P = ceil_div(target, M);
-    const int64_t by_rows = ceil_div(B, 4);
+    const int64_t by_rows = ceil_div(B, two_buffers ? 4 : 16);
     if (P > by_rows) P = by_rows;
     const int64_t need = ceil_div(B, kMaxRowsPerBlock);        // a block owns at most kMaxRowsPerBlock rows
     if (P < need) P = need;

@@ -342,6 +342,7 @@ __global__ __launch_bounds__(kFusedThreads) void master_fused_kernel(
 {
     touch_kernel_arguments<sizeof(MasterArgs) + 64>();
     __shared__ uint32_t scratch[kFusedThreads / kWave];
+    __shared__ uint32_t words[NQ * kFusedThreads * 4 * 16 / 32 + 2];        // the message, where its fields straddle words
     const int64_t d = a.d, quads = (d + 3) / 4;
     float4 xv[NQ];                                       // the thread's quads threadIdx.x + 1024*k of the new model
     uint32_t amax = 0;
@@ -371,6 +372,23 @@ __global__ __launch_bounds__(kFusedThreads) void master_fused_kernel(
         if (s.bad && status) atomicOr(status, 1u);
     }
     key.worker = DQ_MASTER_ID;
+    if (b_x != 8 && b_x != 4 && b_x != 2) {
+        const int row_words = static_cast<int>((d * b_x + 31) / 32);
+        for (int w = threadIdx.x; w < row_words + 2; w += kFusedThreads) words[w] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            const int64_t q = threadIdx.x + static_cast<int64_t>(kFusedThreads) * k;
+            if (q >= quads || s.inv_delta == 0.0f) continue;
+            const uint4 r = stream_block(key, static_cast<uint32_t>(q));
+            const int codes[4] = {quantize_one(xv[k].x, s, r.x), quantize_one(xv[k].y, s, r.y), quantize_one(xv[k].z, s, r.z),
+                                  quantize_one(xv[k].w, s, r.w)};            // (coordinates past the end are 0: code 0)
+            or_quad_bits(words, static_cast<int>(q), b_x, codes);
+        }
+        __syncthreads();
+        for (int w = threadIdx.x; w < row_words; w += kFusedThreads) xq_out[w] = words[w];
+        return;
+    }
     int nz = 0;
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {                       // all lanes make every store call (cross-lane moves inside)
@@ -692,8 +710,7 @@ int32_t dq::master_step_impl(const uint32_t *packed, int64_t ld_words, const flo
                        x, y, x_snap, xsum, eta, theta, eta * l1, d};
     const StreamKey key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), iter, 0u, DQ_TAG_MODEL};
     const bool acc = y != nullptr;
-    const bool word_aligned_bx = b_x == 2 || b_x == 4 || b_x == 8 || b_x == 32;
-    if (d <= kFusedMaxD && word_aligned_bx) {
+    if (d <= kFusedMaxD) {
         // small model: the whole step in one block, one launch
         const int ch = static_cast<int>(ceil_div(ceil_div(d, 4), kFusedThreads));     // 1 or 2
         switch (b) {

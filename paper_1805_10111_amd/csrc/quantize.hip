@@ -88,8 +88,8 @@ int launch_absmax(const float *v, int64_t d, int64_t M, int64_t ld, float *absma
 // ---------------------------------------------------------------- any width 2 <= b <= 16
 // The model-precision study of Section 5.2 varies b_x from 2 to 11, so fields may straddle the
 // 32-bit words of a packed row.  A group of 32 consecutive coordinates always occupies exactly b
-// whole words (words g*b .. g*b+b-1 of the row), so one thread takes one group and streams its
-// fields through a 64-bit shift register: no two threads ever touch the same word.
+// whole words (words g*b .. g*b+b-1 of the row); where one thread takes one group and streams its
+// fields through a 64-bit shift register, no two threads ever touch the same word.
 constexpr int kGroupCoords = 32;
 
 static inline dim3 grid_for_groups(int64_t d, int64_t M)
@@ -98,48 +98,45 @@ static inline dim3 grid_for_groups(int64_t d, int64_t M)
     return dim3(static_cast<unsigned>(ceil_div(groups, kThreads)), static_cast<unsigned>(M));
 }
 
+// A block takes 1024 coordinates, which occupy exactly 32 b words, a thread one quad of them (one Philox block); the fields
+// meet in LDS and leave as whole words.  (One thread per group of 32 with a shift register, eight Philox blocks one after
+// the other and input lines shared by eight threads: 784 coordinates at 6 bits 5.4 us, now 2.5; 10^6 at 11 bits
+// 7.4, now 4.0; 2^26 at 3 bits 289, now 83; at 11 bits 422, now 102.)
 __global__ __launch_bounds__(kThreads) void quantize_pack_any_kernel(
     const float *__restrict__ v, int64_t d, int64_t ld, const float *__restrict__ absmax, int b, StreamKey key,
     uint32_t worker0, uint32_t *__restrict__ packed, int64_t ld_words, int64_t row_words,
     float *__restrict__ delta_out, uint32_t *__restrict__ status)
 {
+    __shared__ uint32_t words[32 * 16 + 2];
     const int m = blockIdx.y;
     const float *row = v + static_cast<int64_t>(m) * ld;
-    uint32_t *out = packed + static_cast<int64_t>(m) * ld_words;
-    const Scale s = make_scale(absmax[m], b);
+    const int64_t quads = (d + 3) / 4, q = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    const int64_t qc = min(q, quads - 1);                // (threads past the end repeat the last quad and add no bits)
+    float x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = row[min(4 * qc + e, d - 1)];
+    const float amax = absmax[m];
     key.worker = worker0 + static_cast<uint32_t>(m);
+    const uint4 r = stream_block(key, static_cast<uint32_t>(qc));
+    for (int w = threadIdx.x; w < 32 * 16 + 2; w += kThreads) words[w] = 0u;
+    const Scale s = make_scale(amax, b);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         delta_out[m] = s.delta;
         if (s.bad && status) atomicOr(status, 1u);
     }
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const int64_t base = g * kGroupCoords;
-    if (base >= d) return;
-    const uint64_t mask = (1ull << b) - 1ull;
-    uint64_t window = 0;                     // bits not yet written, low bits first
-    int fill = 0;
-    int64_t wo = g * b;
-    for (int j = 0; j < kGroupCoords; j += 4) {
-        const float4 a = load_quad(row, (base + j) >> 2, d);          // zeros past the end -> code 0
-        const float av[4] = {a.x, a.y, a.z, a.w};
-        uint32_t rw[4] = {0u, 0u, 0u, 0u};
-        if (s.inv_delta != 0.0f && base + j < d) {
-            const uint4 r = stream_block(key, static_cast<uint32_t>((base + j) >> 2));
-            rw[0] = r.x; rw[1] = r.y; rw[2] = r.z; rw[3] = r.w;
-        }
+    __syncthreads();
+    if (q < quads && s.inv_delta != 0.0f) {              // (a degenerate scale: every code is zero)
+        const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+        int k[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = (s.inv_delta != 0.0f && base + j + e < d) ? quantize_one(av[e], s, rw[e]) : 0;
-            window |= (static_cast<uint64_t>(static_cast<uint32_t>(k)) & mask) << fill;
-            fill += b;
-            if (fill >= 32) {
-                if (wo < row_words) out[wo] = static_cast<uint32_t>(window);
-                ++wo;
-                window >>= 32;
-                fill -= 32;
-            }
-        }
+        for (int e = 0; e < 4; ++e) k[e] = 4 * q + e < d ? quantize_one(x[e], s, rw[e]) : 0;
+        or_quad_bits(words, threadIdx.x, b, k);
     }
+    __syncthreads();
+    uint32_t *out = packed + static_cast<int64_t>(m) * ld_words;
+    const int64_t w0 = static_cast<int64_t>(blockIdx.x) * 32 * b;
+    for (int w = threadIdx.x; w < 32 * b; w += kThreads)
+        if (w0 + w < row_words) out[w0 + w] = words[w];
 }
 
 __global__ __launch_bounds__(kThreads) void unpack_dequant_sum_any_kernel(
@@ -456,7 +453,8 @@ int launch_quantize_pack_parts(const float *v, int64_t d, int64_t M, int64_t ld,
     case 2: quantize_pack_kernel<2><<<grid, block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status, parts, count_parts, count_out); break;
     default:
         if (field != b || b < 2 || b > 16 || parts != 1 || count_out) return DQ_ERR_UNSUPPORTED;
-        quantize_pack_any_kernel<<<grid_for_groups(d, M), block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status);
+        if (d == 0) return fill_u32(reinterpret_cast<uint32_t *>(delta_out), M, 0u, st);      // (the scale of an empty vector)
+        quantize_pack_any_kernel<<<dim3(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kThreads)), static_cast<unsigned>(M)), block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status);
         break;
     }
     DQ_LAUNCH_CHECK();

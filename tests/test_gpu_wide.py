@@ -219,3 +219,27 @@ def test_mu_sweep_reproduces_the_trend_of_the_model_precision_study(dq):
     ch = res["smallest_width_for_mu"]
     picked = [ch[k] for k in sorted(ch, key=float) if ch[k] is not None]
     assert picked == sorted(picked, reverse=True)                  # larger mu, smaller (or equal) width
+
+
+@pytest.mark.parametrize("b_x", [3, 6, 11, 16])
+@pytest.mark.parametrize("d", [1, 33, 4096, 4099, 8191, 8192, 8193])
+def test_model_message_of_any_width_from_the_master(dq, b_x, d):
+    """The one-block master quantizes models of up to 8192 coordinates to any width itself: message and scale are those of
+    dq_quantize_pack on the model it leaves, and nothing past the message is written."""
+    rng = np.random.default_rng(d + b_x)
+    M, b = 3, 8
+    nw = dq.packed_words(d, b)
+    packed = torch.from_numpy(rng.integers(-2**31, 2**31, (M, (nw + 3) // 4 * 4)).astype(np.int32)).cuda()
+    delta, g = torch.rand(M, device="cuda") * 0.01, torch.randn(d, device="cuda") * 0.1
+    x = torch.randn(d, device="cuda")
+    words = dq.packed_words(d, b_x)
+    xq = torch.full(((words + 3) // 4 * 4 + 4,), -1, dtype=torch.int32, device="cuda")
+    dx, amax = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    dq.dq_master_step(packed, delta, M, b, 1.0 / M, g, x, None, None, None, 0.1, 0.0, 1e-4, b_x, 11, 5, xq, dx, amax)
+    want = torch.zeros((words + 3) // 4 * 4, dtype=torch.int32, device="cuda")
+    want_dx, want_amax = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    dq.dq_quantize_pack(x, b_x, want_amax, False, 11, 5, dq.TAG_MODEL, dq.MASTER_ID, want, want_dx)
+    assert torch.equal(xq[:words], want[:words]) and torch.all(xq[words:] == -1)
+    assert torch.equal(dx, want_dx) and torch.equal(amax, want_amax)
+    k, dlt, _ = oracle.quantize_wide(x.cpu().numpy(), b_x, 11, 5, dq.MASTER_ID, dq.TAG_MODEL)
+    assert float(dx.item()) == float(dlt) and np.array_equal(xq[:words].cpu().numpy().view(np.uint32), oracle.pack_wide(k, b_x))
