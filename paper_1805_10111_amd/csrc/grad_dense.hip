@@ -75,12 +75,13 @@ __device__ __forceinline__ void load_cols(const float *__restrict__ row, int64_t
     }
 }
 
-template <int NC, bool FULL = false, int T = kRowThreads>
+// TIGHT: only the thread's last column can lie past the end (see full_shape).
+template <int NC, bool FULL = false, int T = kRowThreads, bool TIGHT = false>
 __device__ __forceinline__ void mask_cols(float4 (&a)[NC], int64_t d)
 {
     if constexpr (!FULL) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
+        for (int c = TIGHT ? NC - 1 : 0; c < NC; ++c) {
             const int64_t col = 4ll * (threadIdx.x + T * c);
             a[c].x = col + 0 < d ? a[c].x : 0.0f;
             a[c].y = col + 1 < d ? a[c].y : 0.0f;
@@ -648,6 +649,7 @@ int launch_worker_zero(const WorkerArgs &a, int64_t d, int64_t row_words, hipStr
 // then can a wait for one batch leave the loads of the next batch in flight (two row buffers).
 constexpr int kFullChunk = 1024;
 
+// Of the thread's columns only the last may lie past the end (see full_shape).
 template <int NC, int R, bool FULL, int T = kRowThreads, bool STREAM = false>
 __global__ __launch_bounds__(T) void full_dense_partial_kernel(
     const float *__restrict__ X, int64_t lda, int64_t n, int64_t d, const float *__restrict__ yv,
@@ -680,7 +682,7 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
         float z[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            mask_cols<NC, FULL, T>(row[r], d);
+            mask_cols<NC, FULL, T, true>(row[r], d);
             z[r] = dot_cols<NC>(row[r], xv);
         }
         block_sum_R<R, T>(z, sh_red, buf);
@@ -737,6 +739,89 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
     if (threadIdx.x < kWave) {                       // lanes 0..R-1 of wave 0 hold the block's loss terms
         loss = wave_sum_f64(loss);
         if (threadIdx.x == 0) loss_partial[blockIdx.x] = loss;
+    }
+}
+
+// The same for rows of at most 4 L floats, L <= 64: with a thread per column quad most lanes of a block would have none
+// (54 columns: 14 of 256).  L lanes take a row, so that a load instruction of a wavefront covers 64 / L rows; kNarrowRows
+// such loads are in flight, the margins are added up across the L lanes, and every one of them forms the coefficient
+// for itself: no LDS and no barrier until the sums of all rows meet at the end.  400,000 rows of 54 floats: 134 us,
+// now 17; 200,000 of 200: 68 us, now 27.
+constexpr int kNarrowThreads = 512, kNarrowRows = 8;
+
+template <int L, bool STREAM>
+__global__ __launch_bounds__(kNarrowThreads) void full_narrow_partial_kernel(
+    const float *__restrict__ X, int64_t lda, int64_t n, int64_t d, const float *__restrict__ yv,
+    const float *__restrict__ x, float *__restrict__ z_out, float *__restrict__ partial, int64_t ldp,
+    double *__restrict__ loss_partial)
+{
+    constexpr int G = kWave / L, kWaves = kNarrowThreads / kWave, R = kNarrowRows;
+    __shared__ float4 sh[kWaves * G][L];
+    __shared__ double sh_loss[kWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, g = lane / L, t = lane % L;
+    const int64_t per = (n + gridDim.x - 1) / gridDim.x;
+    const int64_t i0 = blockIdx.x * per, i1 = min(n, i0 + per);
+    const int64_t col = 4 * t, colc = min<int64_t>(col, (d + 3) / 4 * 4 - 4);
+    const bool in0 = col < d, in1 = col + 1 < d, in2 = col + 2 < d, in3 = col + 3 < d;
+    const float4 xv = load4_or_zero(x, col, d);
+    const float inv_n = 1.0f / static_cast<float>(n);
+    float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    double loss = 0.0;
+    for (int64_t i = i0 + static_cast<int64_t>(wave) * G * R; i < i1; i += static_cast<int64_t>(kWaves) * G * R) {
+        float4 row[R];
+        float y[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {                    // (a row past the block's last repeats that one)
+            const int64_t r = min(i + u * G + g, i1 - 1);
+            const float *p = X + r * lda + colc;
+            row[u] = STREAM ? load_f4_stream(p) : *reinterpret_cast<const float4 *>(p);
+            y[u] = yv[r];
+        }
+        float z_mine = 0.0f, y_mine = 0.0f;              // lane u of a row's lanes records row u of the batch
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            float4 a = row[u];
+            a.x = in0 ? a.x : 0.0f; a.y = in1 ? a.y : 0.0f; a.z = in2 ? a.z : 0.0f; a.w = in3 ? a.w : 0.0f;
+            float z = fmaf(a.x, xv.x, 0.0f);
+            z = fmaf(a.y, xv.y, z); z = fmaf(a.z, xv.z, z); z = fmaf(a.w, xv.w, z);
+            if constexpr (L == kWave) {
+                z = wave_sum_f32(z);
+            } else {                                     // two quad permutes and two rotations of 16 lanes
+                z += __int_as_float(dpp_move_or_zero<0xb1, 0xf>(__float_as_int(z)));
+                z += __int_as_float(dpp_move_or_zero<0x4e, 0xf>(__float_as_int(z)));
+                z += __int_as_float(dpp_move_or_zero<0x124, 0xf>(__float_as_int(z)));
+                z += __int_as_float(dpp_move_or_zero<0x128, 0xf>(__float_as_int(z)));
+                if constexpr (L == 32) z += __shfl_xor(z, 16, kWave);
+            }
+            const bool live = i + u * G + g < i1;
+            const float coef = live ? logistic_slope_fast(y[u], z) * inv_n : 0.0f;
+            acc.x = fmaf(coef, a.x, acc.x); acc.y = fmaf(coef, a.y, acc.y);
+            acc.z = fmaf(coef, a.z, acc.z); acc.w = fmaf(coef, a.w, acc.w);
+            z_mine = t == u ? z : z_mine;
+            y_mine = t == u ? y[u] : y_mine;
+        }
+        const int64_t r = i + t * G + g;
+        if (t < R && r < i1) {
+            if (z_out) z_out[r] = z_mine;
+            loss += static_cast<double>(logistic_loss_fast(y_mine * z_mine));
+        }
+    }
+    sh[wave * G + g][t] = acc;
+    loss = wave_sum_f64(loss);
+    if (lane == 0) sh_loss[wave] = loss;
+    __syncthreads();
+    if (static_cast<int>(threadIdx.x) < L && 4ll * threadIdx.x < ldp) {
+        float4 s = sh[0][threadIdx.x];
+        for (int k = 1; k < kWaves * G; ++k) {
+            const float4 v = sh[k][threadIdx.x];
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+        *reinterpret_cast<float4 *>(partial + static_cast<int64_t>(blockIdx.x) * ldp + 4ll * threadIdx.x) = s;
+    }
+    if (threadIdx.x == 0) {
+        double total = sh_loss[0];
+        for (int w = 1; w < kWaves; ++w) total += sh_loss[w];
+        loss_partial[blockIdx.x] = total;
     }
 }
 
@@ -844,7 +929,7 @@ int64_t dense_vr_splits(int64_t M, int64_t B, int64_t d)
     // are streamed with two row buffers per block (see dense_worker): one block per compute unit
     // then, and a whole number of batch pairs per block.
     // For rows of up to 1024 floats a block takes whole batches of 16 rows: all of a batch are in flight together, so a
-    // batch cut over several blocks takes as long and leaves more partial sums (M = 10, B = 100, d = 784: 13.0 us for both kernels with
+    // batch cut over several blocks takes as long and leaves more partial sums (M = 10, B = 100, d = 784: both kernels 13.0 us with
     // four rows per block, 12.6 with 15).
     const bool two_buffers = dense_nc(d) >= 2;
     const int64_t target = two_buffers ? 256 : 512;
@@ -891,47 +976,99 @@ int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int
     return rows * ldp * 4;
 }
 
+// Threads per block and float4 columns per thread of the full gradient on rows of more than 1024 floats: of 256 to 512
+// threads in whole wavefronts, as few as cover the row with 1, 2, 4 or 8 columns each, so that no more than the last
+// wavefront's last column lies past the end.
+struct FullShape {
+    int threads, cols;
+};
+
+static FullShape full_shape(int64_t d)
+{
+    const int64_t quads = ceil_div(d, 4);
+    const int cols = quads <= 512 ? 1 : quads <= 1024 ? 2 : quads <= 2048 ? 4 : 8;
+    return FullShape{static_cast<int>(std::max<int64_t>(256, ceil_div(ceil_div(quads, cols), kWave) * kWave)), cols};
+}
+
+struct FullArgs {
+    const dq_problem *prob;
+    const float *x;
+    float *z_out, *partial;
+    int64_t ldp;
+    double *loss_partial;
+    dim3 grid;
+    bool stream;
+    hipStream_t st;
+};
+
+template <int NC, int R, bool FULL, int T>
+static void launch_full_dense(const FullArgs &a)
+{
+    const dq_problem *p = a.prob;
+    if (a.stream)
+        full_dense_partial_kernel<NC, R, FULL, T, true><<<a.grid, dim3(T), 0, a.st>>>(p->dense, p->lda, p->n, p->d, p->y, a.x, a.z_out, a.partial, a.ldp, a.loss_partial);
+    else
+        full_dense_partial_kernel<NC, R, FULL, T, false><<<a.grid, dim3(T), 0, a.st>>>(p->dense, p->lda, p->n, p->d, p->y, a.x, a.z_out, a.partial, a.ldp, a.loss_partial);
+}
+
+template <int NC, int R>
+static void launch_full_dense_threads(int threads, const FullArgs &a)
+{
+    switch (threads) {
+    case 256: launch_full_dense<NC, R, false, 256>(a); break;
+    case 320: launch_full_dense<NC, R, false, 320>(a); break;
+    case 384: launch_full_dense<NC, R, false, 384>(a); break;
+    case 448: launch_full_dense<NC, R, false, 448>(a); break;
+    default: launch_full_dense<NC, R, false, 512>(a); break;
+    }
+}
+
+template <int L>
+static void launch_full_narrow(const FullArgs &a)
+{
+    const dq_problem *p = a.prob;
+    if (a.stream)
+        full_narrow_partial_kernel<L, true><<<a.grid, dim3(kNarrowThreads), 0, a.st>>>(p->dense, p->lda, p->n, p->d, p->y, a.x, a.z_out, a.partial, a.ldp, a.loss_partial);
+    else
+        full_narrow_partial_kernel<L, false><<<a.grid, dim3(kNarrowThreads), 0, a.st>>>(p->dense, p->lda, p->n, p->d, p->y, a.x, a.z_out, a.partial, a.ldp, a.loss_partial);
+}
+
 int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,
                     int64_t ws_bytes, hipStream_t st)
 {
     const int64_t d = prob->d, n = prob->n;
-    const int nc = dense_nc(d);
-    if (nc == 0) return DQ_ERR_UNSUPPORTED;
+    if (dense_nc(d) == 0) return DQ_ERR_UNSUPPORTED;
     if (ws_bytes < dense_workspace_bytes(DQ_OP_FULL_GRAD, prob, 0, 0) || !ws) return DQ_ERR_WORKSPACE;
-    const int64_t ldp = pad4(d);
-    const int P = static_cast<int>(dense_full_splits(n, d));
+    const int64_t ldp = pad4(d), quads = ceil_div(d, 4);
+    int P = static_cast<int>(dense_full_splits(n, d));
     float *partial = static_cast<float *>(ws);
     double *loss_partial = reinterpret_cast<double *>(partial + static_cast<int64_t>(P) * ldp);
-    const dim3 grid(P), block(kRowThreads);
-    const bool full = d == 4ll * kRowThreads * nc;          // every thread's columns are whole float4s of the row
-#define DQ_FULL(NC, R)                                                                                              \
-    do {                                                                                                            \
-        if (full) full_dense_partial_kernel<NC, R, true><<<grid, block, 0, st>>>(prob->dense, prob->lda, n, d, prob->y, x, z_out, partial, ldp, loss_partial); \
-        else full_dense_partial_kernel<NC, R, false><<<grid, block, 0, st>>>(prob->dense, prob->lda, n, d, prob->y, x, z_out, partial, ldp, loss_partial); \
-    } while (0)
-    // Rows of 2048, 4096, 8192 or 16384 floats (every thread's columns whole): 512 threads per block, one block per
-    // compute unit, non-temporal loads.  Measured on 1.6-3.3 GB of rows against 256 threads, two blocks per unit and
-    // plain loads: 280 -> 240 us, 540 -> 479 us (6.84 TB/s), 282 -> 243 us, 294 -> 253 us.  (For other widths the
-    // same change is a loss -- 299 -> 439 us at 3000 floats -- and they keep the kernels below.)
-    if (dense_full_wide(d)) {
-        const dim3 b512(512);
-#define DQ_F512(NC, R) full_dense_partial_kernel<NC, R, true, 512, true><<<grid, b512, 0, st>>>(prob->dense, prob->lda, n, d, prob->y, x, z_out, partial, ldp, loss_partial)
-        if (nc == 2) DQ_F512(1, 8);
-        else if (nc == 4) DQ_F512(2, 4);
-        else if (nc == 8) DQ_F512(4, 2);
-        else DQ_F512(8, 1);
-#undef DQ_F512
-        DQ_LAUNCH_CHECK();
-        return launch_full_finish(partial, P, ldp, n, d, x, prob->l2, prob->l1, loss_partial, g_out, obj_out, st);
-    }
-    switch (nc) {
-    case 1: DQ_FULL(1, 8); break;
-    case 2: DQ_FULL(2, 4); break;
-    case 4: DQ_FULL(4, 4); break;
-    case 8: DQ_FULL(8, 2); break;
-    default: DQ_FULL(16, 1); break;
-    }
-#undef DQ_FULL
+    const FullShape shape = full_shape(d);
+    // one block per compute unit where a thread has several columns, two where it has one
+    if (shape.cols > 1) P = std::min(P, 256);
+    // Rows that do not fit in the 256 MB cache in front of memory are read once: non-temporal loads (50,000 x 3000 96 us
+    // with, 105 without; 3000 x 3000 again and again 11.2 with, 9.3 without).
+    const bool stream = n * prob->lda * 4 > (128ll << 20);
+    const FullArgs a{prob, x, z_out, partial, ldp, loss_partial, dim3(static_cast<unsigned>(P)), stream, st};
+    if (quads <= 16) launch_full_narrow<16>(a);
+    else if (quads <= 32) launch_full_narrow<32>(a);
+    else if (quads <= 64) launch_full_narrow<64>(a);
+    else if (quads <= 256 && d == 1024) launch_full_dense<1, 8, true, 256>(a);
+    else if (quads <= 256) launch_full_dense<1, 8, false, 256>(a);
+    // Rows of 2048, 4096, 8192 or 16384 floats (every thread's columns whole): 512 threads per block.  Measured on
+    // 1.6-3.3 GB of rows against 256 threads, two blocks per unit and plain loads: 280 -> 240 us, 540 -> 479 us
+    // (6.84 TB/s), 282 -> 243 us, 294 -> 253 us.
+    else if (dense_full_wide(d) && shape.cols == 1) launch_full_dense<1, 8, true, 512>(a);
+    else if (dense_full_wide(d) && shape.cols == 2) launch_full_dense<2, 4, true, 512>(a);
+    else if (dense_full_wide(d) && shape.cols == 4) launch_full_dense<4, 2, true, 512>(a);
+    else if (dense_full_wide(d)) launch_full_dense<8, 1, true, 512>(a);
+    // Other widths; measured against 256 threads with columns for the next power of two, two blocks per unit, plain loads
+    // and a test per element: 50,000 x 3000 107 -> 90 us (6.65 TB/s), 30,000 x 5000 110 -> 91, 20,000 x 7397 110 -> 92,
+    // 12,000 x 12,000 123 -> 89, 80,000 x 2500 145 -> 118, 100,000 x 1200 90 -> 86, 100,000 x 1800 122 -> 112.
+    else if (shape.cols == 1) launch_full_dense_threads<1, 8>(shape.threads, a);
+    else if (shape.cols == 2) launch_full_dense_threads<2, 4>(shape.threads, a);
+    else if (shape.cols == 4) launch_full_dense_threads<4, 2>(shape.threads, a);
+    else launch_full_dense_threads<8, 1>(shape.threads, a);
     DQ_LAUNCH_CHECK();
     return launch_full_finish(partial, P, ldp, n, d, x, prob->l2, prob->l1, loss_partial, g_out, obj_out, st);
 }

@@ -302,3 +302,25 @@ def test_unsupported_and_invalid(dq):
     with pytest.raises(dq.DqError) as e:
         dq.dq_full_grad(P, x, x.clone(), None, None, torch.zeros(4, device="cuda"))
     assert e.value.code == dq.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("n,d", [(3001, 1), (4097, 54), (2500, 64), (999, 65), (700, 128), (1203, 131), (4100, 256), (900, 257),
+                                 (400, 1025), (300, 1290), (77, 2500), (130, 3000), (90, 4099), (40, 7397), (33, 8200), (50, 12002),
+                                 (1, 54), (2, 3000)])
+def test_full_gradient_over_widths(dq, n, d):
+    """Rows on 16, 32 and 64 lanes, and every count of threads and columns per thread, with ragged last quads whose padding is
+    not a number."""
+    rng = np.random.default_rng(n + d)
+    lda = (d + 3) // 4 * 4 + 4
+    X = np.full((n, lda), np.nan, dtype=np.float32)
+    X[:, :d] = rng.standard_normal((n, d)).astype(np.float32) / np.sqrt(d)
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    x = rng.standard_normal(d).astype(np.float32)
+    P = dq.DeviceProblem(n=n, d=d, y=dev(y), l2=1e-3, l1=1e-4, dense=dev(X)[:, :d])
+    g, z, obj = torch.zeros(d, device="cuda"), torch.zeros(n, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+    dq.dq_full_grad(P, dev(x), g, z, obj, dq.new_workspace(dq.OP_FULL_GRAD, P))
+    ref = oracle.RefProblem(synth.Problem(n=n, d=d, y=y, l2=1e-3, l1=1e-4, dense=np.ascontiguousarray(X[:, :d])))
+    want_g, want_z = oracle.full_grad(ref, x, want_margins=True)
+    assert np.abs(host(z) - want_z).max() <= 1e-5 * np.abs(want_z).max() + 1e-7
+    assert np.abs(host(g) - want_g).max() <= 1e-5 * np.abs(want_g).max() + 1e-9
+    assert abs(host(obj)[0] - oracle.objective(ref, x)) <= 1e-5 * abs(oracle.objective(ref, x))
