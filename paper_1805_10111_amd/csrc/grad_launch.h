@@ -99,6 +99,12 @@ int32_t master_step_from_parts_impl(const GradientParts &parts, uint32_t worker0
                                     float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
                                     float *model_diff_out);
 
+// All rounds of a dq_run_rounds call in one launch (small_rounds.hip), for problems that small_rounds_ok admits: the message
+// of the first round's model in st->xq unless flag_first (the flag-bit case).
+bool small_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st);
+int32_t small_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
+                     int64_t rounds, float eta, float theta, bool flag_first, hipStream_t stream);
+
 int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t B);
 int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,
                     int64_t ws_bytes, hipStream_t st);

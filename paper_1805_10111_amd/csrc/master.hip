@@ -32,23 +32,6 @@ struct MasterArgs {
     int64_t d;
 };
 
-// Alg. 1, master (ii) (Alg. 3 when ACC) for one direction u on a quad; the state is updated in registers.
-template <bool ACC>
-__device__ __forceinline__ void master_apply_quad(const float (&u)[4], float (&xn)[4], float (&yn)[4], const float (&xs)[4],
-                                                  float (&sm)[4], bool have_sum, float eta, float theta, float kappa)
-{
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if (ACC) {
-            yn[e] = soft_threshold(yn[e] - eta * u[e], kappa);      // y <- prox(y - eta u)
-            xn[e] = xs[e] + theta * (yn[e] - xs[e]);                // x <- snapshot + theta (y - snapshot)
-            if (have_sum) sm[e] = sm[e] + xn[e];
-        } else {
-            xn[e] = soft_threshold(xn[e] - eta * u[e], kappa);      // x <- prox(x - eta u)
-        }
-    }
-}
-
 // The master update on quad q (coordinates 4q..4q+3): decodes the M messages, updates x (and y, xsum) in
 // memory and returns the new x (zeros past the end of the vector).
 template <int FIELD, bool ACC, bool EACH>

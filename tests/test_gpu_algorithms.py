@@ -510,3 +510,47 @@ def test_worker_steps_split_over_the_columns_equal_the_separate_calls(dq, algo, 
     for name in ("packed", "delta", "x", "xq", "delta_x", "status") + (("y", "xsum") if acc else ()):
         assert torch.equal(getattr(one, name), getattr(two, name)), name
     assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
+
+
+@pytest.mark.parametrize("algo,b,M,B,b_x,each", [("asylpg", 8, 4, 16, 8, False), ("acc", 4, 3, 9, 6, False), ("asylpg", 2, 1, 1, 2, True),
+                                                 ("acc", 8, 4, 16, 11, True), ("asylpg", 4, 2, 15, 16, False)])
+@pytest.mark.parametrize("n,d", [(2000, 1000), (300, 54), (77, 1), (500, 1024), (400, 257), (600, 1021)])
+def test_small_dense_rounds_in_one_launch_equal_the_separate_calls(dq, algo, b, M, B, b_x, each, n, d):
+    """Up to four workers of sixteen rows and 1024 columns: dq_run_rounds runs all rounds of a call in one block.  Messages,
+    scales, model, message of the model and largest magnitudes are those of dq_worker_step and the master step, round by
+    round, bit for bit, however the rounds are cut into calls, in the first epoch and in a later one."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    p = synth.dense_logistic(n, d, seed=2, l2=1e-2, l1=1e-5)
+    lda = (d + 3) // 4 * 4 + 4
+    X = np.full((n, lda), np.nan, dtype=np.float32)         # (padding that is not a number)
+    X[:, :d] = p.dense
+    P = dq.DeviceProblem(n=n, d=d, y=dev(p.y), l2=float(p.l2), l1=float(p.l1), dense=dev(X)[:, :d])
+    m, seed = 6, 5
+    x0 = torch.randn(d, device="cuda") * 0.3
+    one = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each, x0=x0)
+    two = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each, x0=x0)
+    acc = algo == "acc"
+    idx = torch.empty(M * B, dtype=torch.int32, device="cuda")
+    for e in range(2):
+        one.epoch_prologue(); two.epoch_prologue()
+        one.rounds(0, 3); one.rounds(3, 1); one.rounds(4, 2)
+        for t in range(m):
+            it = e * m + t
+            if t == 0 and two.is_flag_round(0):
+                two.packed.zero_(); two.delta.zero_()
+            else:
+                if t == 0:
+                    dq.dq_quantize_pack(two.x, b_x, two.absmax_x, False, seed, it, dq.TAG_MODEL, dq.MASTER_ID, two.xq, two.delta_x,
+                                        two.status)
+                dq.dq_sample_indices(n, M, B, seed, it, 0, idx)
+                dq.dq_worker_step(P, idx, M, B, two.xq, two.delta_x, b_x, False, two.x_snap, two.z_snap, False, b, seed, it, 0,
+                                  two.packed, two.delta, None, None, two.status, two.ws)
+            step = dq.dq_master_step_each if each else dq.dq_master_step
+            args = (two.packed, two.delta, M, b) + (() if each else (float(np.float32(1) / np.float32(M)),))
+            step(*args, two.g_snap, two.x, two.y if acc else None, two.x_snap, two.xsum if acc else None, two.eta, two.theta,
+                 P.l1, b_x, seed, it + 1, two.xq, two.delta_x, two.absmax_x[t & 1:], two.status)
+        torch.cuda.synchronize()
+        for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if acc else ()):
+            assert torch.equal(getattr(one, name), getattr(two, name)), (e, name)
+        one.epoch_epilogue(); two.epoch_epilogue()
+    assert host(one.x).any() and host(one.status)[0] == 0
