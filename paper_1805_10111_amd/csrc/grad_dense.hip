@@ -143,10 +143,15 @@ __device__ __forceinline__ void block_sum_R(float (&v)[R], float *sh, int &buf)
     constexpr int kWaves = T / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     float *mine = sh + buf * (kWaves * R);
+    if constexpr (R == 16) {
+        const float s = wave_sums16(v);
+        if (lane < R) mine[wave * R + lane] = s;
+    } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const float s = wave_sum_f32(v[r]);
-        if (lane == 0) mine[wave * R + r] = s;
+        for (int r = 0; r < R; ++r) {
+            const float s = wave_sum_f32(v[r]);
+            if (lane == 0) mine[wave * R + r] = s;
+        }
     }
     __syncthreads();
 #pragma unroll
