@@ -406,10 +406,13 @@ static int launch_master_fused(bool acc, int ch, hipStream_t st, const MasterArg
     return DQ_OK;
 }
 
-__global__ __launch_bounds__(kThreads) void copy_f32_kernel(const float *__restrict__ a, float *__restrict__ b, int64_t n)
+// The message of a model that is not quantized: the model itself, scale 1.
+__global__ __launch_bounds__(kThreads) void float_message_kernel(const float *__restrict__ x, float *__restrict__ message, int64_t n,
+                                                                 float *__restrict__ delta_out)
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    if (i < n) b[i] = a[i];
+    if (i < n) message[i] = x[i];
+    if (i == 0) delta_out[0] = 1.0f;
 }
 
 // ------------------------------------------------------------------ Alg. 3 epoch boundary
@@ -640,11 +643,10 @@ static int model_message(const float *x, int64_t d, int32_t b_x, const StreamKey
         return launch_model_message(x, d, b_x, absmax_x, key, xq_packed_out, delta_x_out, status,
                                     leave_diff ? x_snap : nullptr, leave_diff ? diff_out : nullptr, st);
     if (b_x == 32) {
-        // full-precision model: "packed" output is x itself, delta is 1
-        copy_f32_kernel<<<dim3(static_cast<unsigned>(ceil_div(d, kThreads))), dim3(kThreads), 0, st>>>(
-            x, reinterpret_cast<float *>(xq_packed_out), d);
+        float_message_kernel<<<dim3(static_cast<unsigned>(ceil_div(d, kThreads))), dim3(kThreads), 0, st>>>(
+            x, reinterpret_cast<float *>(xq_packed_out), d, delta_x_out);
         DQ_LAUNCH_CHECK();
-        return fill_u32(reinterpret_cast<uint32_t *>(delta_x_out), 1, 0x3F800000u, st);
+        return DQ_OK;
     }
     return launch_quantize_pack(x, d, 1, d, b_x, b_x, absmax_x, key, DQ_MASTER_ID, xq_packed_out,
                                 packed_words(d, b_x), delta_x_out, status, st);

@@ -333,15 +333,17 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(
 // rounds, which depend on none of it, and waited for after them.
 // DIFF (one row): together with diff_out[i] = delta * code_i - x_snap[i], the model a worker decodes minus the snapshot,
 // which every worker of the next round would otherwise form again, per column it touches, from the message
-// (dq_run_rounds on CSR features).  Same bits as quantize_pack_kernel.  Against that kernel, per launch: 1 x 1000
+// (dq_run_rounds on CSR features).  PARTS: a row's scale comes from `parts` slice maxima, and its count from as many
+// slice counts (see quantize_pack_kernel).  Same bits as quantize_pack_kernel.  Against that kernel, per launch: 1 x 1000
 // coordinates 3.1 -> 1.7 us, 1 x 20,958 4.1 -> 2.7, 16 x 20,958 4.1 -> 3.0, 1 x 10^6 4.1 -> 3.7 us.
-template <int FIELD, bool DIFF>
+template <int FIELD, bool DIFF, bool PARTS = false>
 __global__ __launch_bounds__(kThreads) void quantize_quads_kernel(
     const float *__restrict__ v, int64_t d, int64_t ld, const float *__restrict__ absmax, int b, StreamKey key,
     uint32_t worker0, uint32_t *__restrict__ packed, int64_t ld_words, float *__restrict__ delta_out,
-    uint32_t *__restrict__ status, const float *__restrict__ x_snap, float *__restrict__ diff_out)
+    uint32_t *__restrict__ status, const float *__restrict__ x_snap, float *__restrict__ diff_out, int parts,
+    const int32_t *__restrict__ count_parts, int32_t *__restrict__ count_out)
 {
-    touch_kernel_arguments<112>();                       // (six pointers, three sizes, b, the key, worker0, two more pointers)
+    touch_kernel_arguments<PARTS ? 136 : 112>();         // (the last three are read with PARTS only)
     const int m = blockIdx.y;
     const float *__restrict__ x = v + static_cast<int64_t>(m) * ld;
     const int64_t quads = (d + 3) / 4;
@@ -352,7 +354,10 @@ __global__ __launch_bounds__(kThreads) void quantize_quads_kernel(
     // arguments that the Philox rounds need, and those would wait for it)
     int lane_zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-    const float amax = absmax[m + lane_zero];
+    PartsRaw maxima;
+    float amax = 0.0f;
+    if constexpr (PARTS) maxima = parts_request(absmax + static_cast<int64_t>(m) * parts + lane_zero, parts);
+    else amax = absmax[m + lane_zero];
     float xv[4], sv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -362,10 +367,12 @@ __global__ __launch_bounds__(kThreads) void quantize_quads_kernel(
     key.worker = worker0 + static_cast<uint32_t>(m);
     const uint4 r = stream_block(key, static_cast<uint32_t>(qc));
     asm volatile("" ::"v"(r.x), "v"(r.y), "v"(r.z), "v"(r.w));      // (the rounds stay ahead of the first wait)
+    if constexpr (PARTS) amax = parts_absmax_of(maxima);
     const Scale s = make_scale(amax, b);
     if (q == 0) {
         delta_out[m] = s.delta;
         if (s.bad && status) atomicOr(status, 1u);
+        if (PARTS && count_out) count_out[m] = parts_sum(count_parts + static_cast<int64_t>(m) * parts, parts);
     }
     constexpr int kB = CodeBias<FIELD>::value;
     int k[4] = {kB, kB, kB, kB};
@@ -413,8 +420,8 @@ int launch_model_message(const float *x, int64_t d, int b_x, const float *absmax
     if (d < 1 || (x_snap == nullptr) != (diff_out == nullptr)) return DQ_ERR_INVALID_ARG;
     const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kThreads))), block(kThreads);
 #define DQ_MESSAGE(F)                                                                                                       \
-    if (diff_out) quantize_quads_kernel<F, true><<<grid, block, 0, st>>>(x, d, d, absmax, b_x, key, DQ_MASTER_ID, packed, 0, delta_out, status, x_snap, diff_out); \
-    else quantize_quads_kernel<F, false><<<grid, block, 0, st>>>(x, d, d, absmax, b_x, key, DQ_MASTER_ID, packed, 0, delta_out, status, nullptr, nullptr)
+    if (diff_out) quantize_quads_kernel<F, true><<<grid, block, 0, st>>>(x, d, d, absmax, b_x, key, DQ_MASTER_ID, packed, 0, delta_out, status, x_snap, diff_out, 1, nullptr, nullptr); \
+    else quantize_quads_kernel<F, false><<<grid, block, 0, st>>>(x, d, d, absmax, b_x, key, DQ_MASTER_ID, packed, 0, delta_out, status, nullptr, nullptr, 1, nullptr, nullptr)
     switch (b_x) {
     case 8: DQ_MESSAGE(8); break;
     case 4: DQ_MESSAGE(4); break;
@@ -437,9 +444,13 @@ int launch_quantize_pack_parts(const float *v, int64_t d, int64_t M, int64_t ld,
     const int64_t row_words = packed_words(d, field);
     const dim3 grid = grid_for(d, M), block(kThreads);
     // few coordinates: a quad per thread (see quantize_quads_kernel)
-    if (d > 0 && M * d <= kFewCoords && parts == 1 && !count_out && (field == 8 || field == 4 || field == 2)) {
+    if (d > 0 && M * d <= kFewCoords && (field == 8 || field == 4 || field == 2)) {
         const dim3 qgrid(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kThreads)), static_cast<unsigned>(M));
-#define DQ_QUADS(F) quantize_quads_kernel<F, false><<<qgrid, block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, delta_out, status, nullptr, nullptr)
+#define DQ_QUADS(F)                                                                                                            \
+    do {                                                                                                                          \
+        if (parts > 1 || count_out) quantize_quads_kernel<F, false, true><<<qgrid, block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, delta_out, status, nullptr, nullptr, parts, count_parts, count_out); \
+        else quantize_quads_kernel<F, false><<<qgrid, block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, delta_out, status, nullptr, nullptr, 1, nullptr, nullptr); \
+    } while (0)
         if (field == 8) DQ_QUADS(8);
         else if (field == 4) DQ_QUADS(4);
         else DQ_QUADS(2);
