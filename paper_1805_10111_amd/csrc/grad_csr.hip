@@ -491,10 +491,10 @@ struct CsrWorkerArgs {
     float *alpha_ws; int64_t ld_ws; // with several windows: M rows of workspace for the whole gradient, else null
     // sparsifier split over the identical blocks of a worker (beta_ws != null): each block sparsifies its slice into
     // row m of beta_ws and leaves the slice's largest magnitude and kept count; the quantization is a second launch
+    // SLICED: a block leaves its columns of the gradient in row m of beta_ws and their largest magnitude in part_max, one
+    // value per slice; with a sparsifier to come, part_max is the message rows, at whose heads the values wait
+    // (no fields of their own: arguments that reach into one more 64-byte line cost every launch 0.2 us)
     float *beta_ws; float *part_max; int32_t *part_kept;
-    // SLICED (slice_ws != null): a block leaves its columns of the gradient in row m of slice_ws and their largest
-    // magnitude in slice_max[m * slice_max_stride + slice]
-    float *slice_ws; float *slice_max; int64_t slice_max_stride;
     const float *model_diff;       // nullable: (decoded model) - snapshot for every column, see WorkerArgs::model_diff
     // a mini-batch prepared ahead (see kPrepInts): prep_in (nullable) holds this round's, one block of prep_stride words
     // per worker; with prep_out the grid has one more block per worker (the last blockIdx.y), which prepares the round
@@ -716,7 +716,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                 const int4 sum = *reinterpret_cast<const int4 *>(acc + (j - c0));
                 v.x += static_cast<float>(sum.x) * unit; v.y += static_cast<float>(sum.y) * unit;
                 v.z += static_cast<float>(sum.z) * unit; v.w += static_cast<float>(sum.w) * unit;
-                if constexpr (SLICED) *reinterpret_cast<float4 *>(a.slice_ws + static_cast<int64_t>(m) * a.ld_ws + j) = v;
+                if constexpr (SLICED) *reinterpret_cast<float4 *>(a.beta_ws + static_cast<int64_t>(m) * a.ld_ws + j) = v;
                 else *reinterpret_cast<float4 *>(alpha + (j - c0)) = v;
                 if (SLICED && a.alpha_out) store_quad(a.alpha_out + static_cast<int64_t>(m) * a.ld, j >> 2, d, v);
                 seen_max = max(max(seen_max, abs_bits(v.x)), max(max(abs_bits(v.y), abs_bits(v.z)), abs_bits(v.w)));
@@ -782,7 +782,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     }
     if constexpr (SLICED) {
         seen_max = block_max_u32(seen_max, su);
-        if (threadIdx.x == 0) a.slice_max[static_cast<int64_t>(m) * a.slice_max_stride + slice] = __uint_as_float(seen_max);
+        const int64_t stride = a.sparsify ? a.ld_words : nslices;
+        if (threadIdx.x == 0) a.part_max[m * stride + slice] = __uint_as_float(seen_max);
         return;
     }
     // the whole gradient, padded with zeros to a whole quad: in LDS when it fits in one window, else in this worker's
@@ -1370,11 +1371,11 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     if (sliced) {
         k.win = sl.win;
         lds = static_cast<size_t>(sl.win) * 4 + static_cast<size_t>(plan.cap) * (a.z_snap ? 12 : 16);
-        k.slice_ws = static_cast<float *>(a.ws);
+        k.beta_ws = static_cast<float *>(a.ws);
         // (before the sparsifier the maxima wait at the head of the message rows, which are written only after it)
         alpha_max = a.sparsify ? reinterpret_cast<float *>(a.packed) : const_cast<float *>(parts.part_max);
         alpha_max_stride = a.sparsify ? a.ld_words : static_cast<int64_t>(slices);
-        k.slice_max = alpha_max; k.slice_max_stride = alpha_max_stride;
+        k.part_max = alpha_max;
     }
     const bool common = (sliced || plan.nwin == 1) && a.B <= kCsrMaxRows && a.z_snap != nullptr;
     static std::once_flag attr_once[8];
@@ -1406,7 +1407,7 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     if (parts.parts == 0) return DQ_OK;
     if (sliced && a.sparsify) {
         sparsify_parts_kernel<<<dim3(static_cast<unsigned>(a.M), slices), block, 0, st>>>(
-            k.slice_ws, k.ld_ws, d, alpha_max, alpha_max_stride, static_cast<int>(slices), k.key, a.worker0,
+            k.beta_ws, k.ld_ws, d, alpha_max, alpha_max_stride, static_cast<int>(slices), k.key, a.worker0,
             const_cast<float *>(parts.part_max), const_cast<int32_t *>(parts.part_kept));
         DQ_LAUNCH_CHECK();
     }

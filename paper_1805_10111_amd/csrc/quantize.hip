@@ -3,6 +3,8 @@
 // master (i)/(ii) and worker (ii)).  All kernels stream their operands once with
 // 128-bit accesses; each thread owns 16 consecutive coordinates so that it emits
 // whole 32-bit words for every supported field width.
+#include <algorithm>
+
 #include "dq_common.h"
 #include "elementwise.h"
 
@@ -112,9 +114,11 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_any_kernel(
     const float *row = v + static_cast<int64_t>(m) * ld;
     const int64_t quads = (d + 3) / 4, q = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     const int64_t qc = min(q, quads - 1);                // (threads past the end repeat the last quad and add no bits)
-    float x[4];
+    float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (d > 0) {                                         // (the same for every thread; an empty row still has a scale)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = row[min(4 * qc + e, d - 1)];
+        for (int e = 0; e < 4; ++e) x[e] = row[min(4 * qc + e, d - 1)];
+    }
     const float amax = absmax[m];
     key.worker = worker0 + static_cast<uint32_t>(m);
     const uint4 r = stream_block(key, static_cast<uint32_t>(qc));
@@ -464,8 +468,7 @@ int launch_quantize_pack_parts(const float *v, int64_t d, int64_t M, int64_t ld,
     case 2: quantize_pack_kernel<2><<<grid, block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status, parts, count_parts, count_out); break;
     default:
         if (field != b || b < 2 || b > 16 || parts != 1 || count_out) return DQ_ERR_UNSUPPORTED;
-        if (d == 0) return fill_u32(reinterpret_cast<uint32_t *>(delta_out), M, 0u, st);      // (the scale of an empty vector)
-        quantize_pack_any_kernel<<<dim3(static_cast<unsigned>(ceil_div(ceil_div(d, 4), kThreads)), static_cast<unsigned>(M)), block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status);
+        quantize_pack_any_kernel<<<dim3(static_cast<unsigned>(std::max<int64_t>(1, ceil_div(ceil_div(d, 4), kThreads))), static_cast<unsigned>(M)), block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status);
         break;
     }
     DQ_LAUNCH_CHECK();

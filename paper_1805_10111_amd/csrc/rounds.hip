@@ -43,7 +43,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // first epoch of Alg. 3: flag-bit case of Section 4.1
     const bool start_is_snapshot = !acc || epoch == 0;
     // Small dense problems: everything in one launch (not when the caller wants the worker kernels' own times).
-    if (rounds > 0 && rounds < 0x7FFFFFFF && !worker_events && dq::small_rounds_ok(prob, cfg, st)) {
+    if (rounds > 0 && !worker_events && dq::small_rounds_ok(prob, cfg, st)) {
         if (t0 == 0 && !start_is_snapshot) {             // as below
             const int32_t rc = dq_quantize_pack(st->x, prob->d, 1, prob->d, cfg->b_x, st->absmax_x, 0, cfg->seed,
                                                 static_cast<uint32_t>(epoch * cfg->m), DQ_TAG_MODEL, DQ_MASTER_ID, st->xq, xq_words,

@@ -25,10 +25,10 @@ constexpr int kSmallWorkers = 4, kSmallRows = 16, kSmallD = 4 * kGroup;
 struct SmallArgs {
     const float *X; int64_t lda;
     const float *y, *z_snap;
-    int n, d, M, B, b, b_x, each, acc;
+    int n, d, M, B, b, b_x;
     float l2, scale, eta, theta, kappa;
     uint32_t k0, k1, iter0;                              // seed halves; iter of the first round of the call
-    int t0, rounds, flag_first;                          // flag_first: the first round is the flag-bit case
+    int t0, rounds, flag_first;                          // parity of the first round; its flag-bit case
     float *x, *yv, *xsum; const float *x_snap, *g_snap;
     uint32_t *xq; float *delta_x, *absmax_x;
     uint32_t *packed; int64_t ld_words;
@@ -285,20 +285,25 @@ int32_t small_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_
     SmallArgs a{};
     a.X = prob->dense; a.lda = prob->lda; a.y = prob->y; a.z_snap = st->z_snap;
     a.n = static_cast<int>(prob->n); a.d = static_cast<int>(prob->d); a.M = static_cast<int>(cfg->M); a.B = static_cast<int>(cfg->B);
-    a.b = cfg->b; a.b_x = cfg->b_x; a.each = cfg->each; a.acc = acc;
+    a.b = cfg->b; a.b_x = cfg->b_x;
     a.l2 = prob->l2; a.scale = 1.0f / static_cast<float>(cfg->M); a.eta = eta; a.theta = theta; a.kappa = eta * prob->l1;
     a.k0 = static_cast<uint32_t>(cfg->seed); a.k1 = static_cast<uint32_t>(cfg->seed >> 32);
-    a.iter0 = static_cast<uint32_t>(epoch * cfg->m + t0);
-    a.t0 = static_cast<int>(t0 & 1); a.rounds = static_cast<int>(rounds); a.flag_first = flag_first;
     a.x = st->x; a.yv = st->y; a.xsum = st->xsum; a.x_snap = st->x_snap; a.g_snap = st->g_snap;
     a.xq = st->xq; a.delta_x = st->delta_x; a.absmax_x = st->absmax_x;
     a.packed = st->packed; a.ld_words = st->ld_words; a.delta = st->delta; a.status = st->status;
     const dim3 block(static_cast<unsigned>(kGroup * cfg->M));
-    if (acc && cfg->each) small_rounds_kernel<true, true><<<dim3(1), block, 0, stream>>>(a);
-    else if (acc) small_rounds_kernel<true, false><<<dim3(1), block, 0, stream>>>(a);
-    else if (cfg->each) small_rounds_kernel<false, true><<<dim3(1), block, 0, stream>>>(a);
-    else small_rounds_kernel<false, false><<<dim3(1), block, 0, stream>>>(a);
-    DQ_LAUNCH_CHECK();
+    // (a launch for every kMostRounds rounds: about 27 ms of one compute unit each)
+    constexpr int64_t kMostRounds = 4096;
+    for (int64_t done = 0; done < rounds; done += kMostRounds) {
+        a.iter0 = static_cast<uint32_t>(epoch * cfg->m + t0 + done);
+        a.t0 = static_cast<int>((t0 + done) & 1); a.rounds = static_cast<int>(std::min(kMostRounds, rounds - done));
+        a.flag_first = done == 0 && flag_first;
+        if (acc && cfg->each) small_rounds_kernel<true, true><<<dim3(1), block, 0, stream>>>(a);
+        else if (acc) small_rounds_kernel<true, false><<<dim3(1), block, 0, stream>>>(a);
+        else if (cfg->each) small_rounds_kernel<false, true><<<dim3(1), block, 0, stream>>>(a);
+        else small_rounds_kernel<false, false><<<dim3(1), block, 0, stream>>>(a);
+        DQ_LAUNCH_CHECK();
+    }
     return DQ_OK;
 }
 
