@@ -306,17 +306,35 @@ __device__ __forceinline__ void worker_tail_from_lds(float *alpha, int64_t d, bo
     }
 }
 
-// The same tail (without sparsifier, b in {2, 4, 8}) when the block's threads hold the whole gradient in registers, thread t
-// the quad t (coordinates past d are zero): no trip through LDS, one block reduction for the scale.
+// The same tail (b in {2, 4, 8}) when the block's threads hold the whole gradient in registers, thread t the quad t
+// (coordinates past d are zero): no trip through LDS, one block reduction for the scale, one more after the
+// sparsifier, whose random bits are drawn before the first.
 template <int FIELD>
-__device__ __forceinline__ void worker_tail_one_quad(float4 v, int64_t d, int b, StreamKey key, const WorkerOut &out,
-                                                     uint32_t *su, int *si, int slice, int nslices)
+__device__ __forceinline__ void worker_tail_one_quad(float4 v, int64_t d, bool sparsify, int b, StreamKey key,
+                                                     const WorkerOut &out, uint32_t *su, int *si, int slice, int nslices)
 {
     const int64_t quads = (d + 3) / 4;
     const int64_t per = ((quads + nslices - 1) / nslices + kWave - 1) / kWave * kWave;       // as in worker_tail_from_lds
     const int64_t q_lo = min(quads, per * slice), q_hi = min(quads, q_lo + per);
     const int64_t q = threadIdx.x;
-    const uint32_t vmax = block_max_u32(max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w))), su);
+    uint4 w = make_uint4(0u, 0u, 0u, 0u);
+    if (sparsify) {                                      // (the same for every thread)
+        StreamKey sk = key;
+        sk.tag = DQ_TAG_SPARSIFY;
+        w = stream_block(sk, static_cast<uint32_t>(q));
+    }
+    uint32_t vmax = block_max_u32(max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w))), su);
+    if (sparsify) {
+        const SparsifyRule rule{__uint_as_float(vmax), 0.0f, false};
+        v.x = sparsify_one(v.x, rule, w.x);
+        v.y = sparsify_one(v.y, rule, w.y);
+        v.z = sparsify_one(v.z, rule, w.z);
+        v.w = sparsify_one(v.w, rule, w.w);
+        vmax = max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w)));
+        int kept = (v.x != 0.0f) + (v.y != 0.0f) + (v.z != 0.0f) + (v.w != 0.0f);
+        block_max_u32_sum_i32(vmax, kept, su, si);
+        if (nslices > 1 && out.nnz_out && threadIdx.x == 0 && slice == 0) out.nnz_out[0] = kept;   // (see worker_tail_from_lds)
+    }
     const Scale s = make_scale(__uint_as_float(vmax), b);
     if (threadIdx.x == 0 && slice == 0) {
         out.delta_out[0] = s.delta;

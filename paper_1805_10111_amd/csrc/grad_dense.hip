@@ -310,8 +310,8 @@ __device__ __forceinline__ void worker_finish(const VrDenseArgs &a, int m, const
 {
     const int64_t d = a.d;
     if constexpr (NC == 1) {
-        // thread t holds quad t of the whole gradient (zeros past d): the plain quantization runs from the registers
-        if (a.packed && !a.sparsify && a.b != 32) {            // (the same for every thread)
+        // thread t holds quad t of the whole gradient (zeros past d): sparsifier and quantization run from the registers
+        if (a.packed && a.b != 32) {            // (the same for every thread)
             const float4 v = make_float4(acc[0].x + a.l2 * dx[0].x, acc[0].y + a.l2 * dx[0].y, acc[0].z + a.l2 * dx[0].z,
                                          acc[0].w + a.l2 * dx[0].w);
             if (a.alpha_out) store_quad(a.alpha_out + static_cast<int64_t>(m) * a.ld, threadIdx.x, d, v);
@@ -320,9 +320,9 @@ __device__ __forceinline__ void worker_finish(const VrDenseArgs &a, int m, const
             const WorkerOut out{a.packed + static_cast<int64_t>(m) * a.ld_words, a.row_words, a.delta_out + m,
                                 a.nnz_out ? a.nnz_out + m : nullptr, a.status};
             switch (a.b) {
-            case 2: worker_tail_one_quad<2>(v, d, a.b, key, out, su, si, 0, 1); break;
-            case 4: worker_tail_one_quad<4>(v, d, a.b, key, out, su, si, 0, 1); break;
-            default: worker_tail_one_quad<8>(v, d, a.b, key, out, su, si, 0, 1); break;
+            case 2: worker_tail_one_quad<2>(v, d, a.sparsify != 0, a.b, key, out, su, si, 0, 1); break;
+            case 4: worker_tail_one_quad<4>(v, d, a.sparsify != 0, a.b, key, out, su, si, 0, 1); break;
+            default: worker_tail_one_quad<8>(v, d, a.sparsify != 0, a.b, key, out, su, si, 0, 1); break;
             }
             return;
         }
@@ -552,9 +552,9 @@ __global__ __launch_bounds__(kFinishThreads) void vr_dense_finish_kernel(const V
     const int64_t d = a.d;
     const ModelMsg msg{a.xq, a.delta_x[opaque_zero()], a.b_x};     // (b_x = 32: a valid dummy address, value unused)
     const float *base = a.partial + static_cast<int64_t>(m) * a.P * a.ldp;
-    // one sweep covers the vector and the tail is the plain quantization: then thread t keeps quad t in registers and the
-    // tail runs from there (no trip through LDS)
-    const bool in_registers = a.ldp <= 4ll * kFinishThreads && a.packed && !a.sparsify && a.b != 32;
+    // one sweep covers the vector: then thread t keeps quad t in registers and the tail runs from there (no trip through
+    // LDS)
+    const bool in_registers = a.ldp <= 4ll * kFinishThreads && a.packed && a.b != 32;
     float4 mine = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int64_t col = 4ll * threadIdx.x; col < a.ldp; col += 4ll * kFinishThreads) {
         float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -607,9 +607,9 @@ __global__ __launch_bounds__(kFinishThreads) void vr_dense_finish_kernel(const V
         const WorkerOut out{a.packed + static_cast<int64_t>(m) * a.ld_words, a.row_words, a.delta_out + m,
                             a.nnz_out ? a.nnz_out + m : nullptr, a.status};
         switch (a.b) {
-        case 2: worker_tail_one_quad<2>(mine, d, a.b, key, out, su, si, blockIdx.y, gridDim.y); break;
-        case 4: worker_tail_one_quad<4>(mine, d, a.b, key, out, su, si, blockIdx.y, gridDim.y); break;
-        default: worker_tail_one_quad<8>(mine, d, a.b, key, out, su, si, blockIdx.y, gridDim.y); break;
+        case 2: worker_tail_one_quad<2>(mine, d, a.sparsify != 0, a.b, key, out, su, si, blockIdx.y, gridDim.y); break;
+        case 4: worker_tail_one_quad<4>(mine, d, a.sparsify != 0, a.b, key, out, su, si, blockIdx.y, gridDim.y); break;
+        default: worker_tail_one_quad<8>(mine, d, a.sparsify != 0, a.b, key, out, su, si, blockIdx.y, gridDim.y); break;
         }
         return;
     }
