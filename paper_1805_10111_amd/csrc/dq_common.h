@@ -6,6 +6,7 @@
 #include <float.h>
 
 #include "../../include/dq.h"
+#include "launch_sizes.h"
 
 namespace dq {
 
@@ -26,8 +27,6 @@ void set_last_error(hipError_t e);
 #define DQ_LAUNCH_CHECK() DQ_HIP_TRY(hipGetLastError())
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-inline int64_t packed_words(int64_t d, int b) { return (d * b + 31) / 32; }
 
 // ---- Philox4x32-10 (Salmon et al., SC'11), from its published definition -------
 // Stream addressing: key = (seed_lo, seed_hi); counter = (coord/4, iter, worker, tag).

@@ -36,16 +36,11 @@ namespace dq {
 
 constexpr int kCsrThreads = 1024;
 constexpr int kCsrWaves = kCsrThreads / kWave;
-constexpr int kColBits = 20;                     // staged entries carry column | row << kColBits
 constexpr int kColMask = (1 << kColBits) - 1;
 constexpr int kFlight = 4;                       // rows a wavefront reduces at the same time
 constexpr int kStageFlight = 4;                  // entries a thread stages at the same time (worker step)
 constexpr int kFlushRows = 1024;                 // rows between two flushes of the fixed-point sums (full gradient)
-constexpr int kCsrMaxRows = 256;                 // rows a block handles per pass (LDS metadata)
-constexpr int kMaxStage = 8192;                  // most entries the staging buffer is given
 constexpr int kChunkSlots = kMaxStage / kWave;   // see RowMeta::chunk_row
-constexpr int64_t kLdsBudget = 152 * 1024;       // of the 160 KB per compute unit
-constexpr int64_t kCsrFixedLds = 10 * 1024;      // static arrays below, rounded up
 
 struct CsrView {
     const int64_t *indptr;
@@ -418,14 +413,11 @@ __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta
 // reading their extents, labels and cached margins, the prefix sums, and the copy of the rows' entries into one flat run
 // -- does not depend on the model.  Between two rounds of one dq_run_rounds call an extra block per worker of the
 // worker launch does all of that for the NEXT round, on compute units the launch leaves idle, and leaves it in
-// memory as kPrepInts(cap) 32-bit words per worker:
-//   [0] 1 when the flat run is there (the batch fits the staging buffer), else 0   [1] number of entries
+// memory as csr_prep_stride 32-bit words per worker:
+//   [0] 1 when the flat run is there (the batch has at most csr_prep_cap entries), else 0   [1] number of entries
 //   row[kCsrMaxRows] len[kCsrMaxRows] pre[kCsrMaxRows + 4] y[kCsrMaxRows] z[kCsrMaxRows]      (RowMeta's fields)
-//   cap pairs (column | row << kColBits, value bits), the first [1] of them written
+//   pairs (column | row << kColBits, value bits), [1] of them
 // The next round's blocks then start from one round trip to memory instead of a chain of five.
-constexpr int kPrepRow = 4, kPrepLen = kPrepRow + kCsrMaxRows, kPrepPre = kPrepLen + kCsrMaxRows,
-              kPrepY = kPrepPre + kCsrMaxRows + 4, kPrepZ = kPrepY + kCsrMaxRows, kPrepEntries = kPrepZ + kCsrMaxRows;
-__host__ __device__ constexpr int64_t kPrepInts(int64_t cap) { return kPrepEntries + (2 * cap + 3) / 4 * 4; }
 
 // Stage, margins and scatter for a prepared mini-batch: `entry` is its flat run of `total` <= cap entries, `first`
 // what the caller has already loaded of it (positions threadIdx.x + u * kCsrThreads, clamped to the buffer), meta
@@ -486,6 +478,7 @@ struct CsrWorkerArgs {
     uint32_t *packed; int64_t ld_words, row_words;
     float *delta_out; int32_t *nnz_out; uint32_t *status;
     int cap;                       // staging capacity in entries
+    int prep_cap;                  // most entries of a mini-batch prepared ahead (csr_prep_cap; never more than cap)
     uint32_t *zero_word;           // nullable: set to 0 by one thread of the grid
     int win;                       // columns of the gradient held in LDS at a time (multiple of 4; >= d: all of it)
     float *alpha_ws; int64_t ld_ws; // with several windows: M rows of workspace for the whole gradient, else null
@@ -498,7 +491,8 @@ struct CsrWorkerArgs {
     const float *model_diff;       // nullable: (decoded model) - snapshot for every column, see WorkerArgs::model_diff
     // a mini-batch prepared ahead (see kPrepInts): prep_in (nullable) holds this round's, one block of prep_stride words
     // per worker; with prep_out the grid has one more block per worker (the last blockIdx.y), which prepares the round
-    // whose streams carry next_iter into prep_out.  Both need B <= kCsrMaxRows, drawn rows (idx == null) and win >= d.
+    // whose streams carry next_iter into prep_out.  Both need B <= kCsrMaxRows, drawn rows (idx == null) and one window of columns per block (the whole vector, or
+    // a slice).
     const int32_t *prep_in;
     int32_t *prep_out;
     int64_t prep_stride;
@@ -611,7 +605,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         csr_prefix_lengths(meta, nrows);
         int32_t *out = a.prep_out + static_cast<int64_t>(m) * a.prep_stride;
         const int total = meta.pre[nrows];
-        const bool fits = total <= a.cap;
+        const bool fits = total <= a.prep_cap;
         if (static_cast<int>(threadIdx.x) < nrows) {
             out[kPrepRow + threadIdx.x] = ri.row;
             out[kPrepLen + threadIdx.x] = ri.len;
@@ -652,7 +646,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         bool rows_done = false;
         if (a.prep_in) {
             // ---- this round's mini-batch was prepared: descriptors and the first entries are requested together
-            // (a.B <= kCsrMaxRows, one window)
+            // (a.B <= kCsrMaxRows, one window or slice)
             const int32_t *in = a.prep_in + static_cast<int64_t>(m) * a.prep_stride;
             const int2 *entry = reinterpret_cast<const int2 *>(in + kPrepEntries);
             const int nrows = a.B;
@@ -663,7 +657,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             const float p_y = __int_as_float(in[kPrepY + tr]), p_z = __int_as_float(in[kPrepZ + tr]);
             int2 first[kStageFlight];
 #pragma unroll
-            for (int u = 0; u < kStageFlight; ++u) first[u] = entry[min(static_cast<int>(threadIdx.x) + u * kCsrThreads, a.cap - 1)];
+            for (int u = 0; u < kStageFlight; ++u) first[u] = entry[min(static_cast<int>(threadIdx.x) + u * kCsrThreads, a.prep_cap - 1)];
             for (int64_t j = 4ll * threadIdx.x; j < c1p - c0; j += 4ll * kCsrThreads)
                 *reinterpret_cast<int4 *>(acc + j) = make_int4(0, 0, 0, 0);
             if (ready) {                                          // (the same for every thread)
@@ -1168,37 +1162,6 @@ int launch_quantize_pack_parts(const float *v, int64_t d, int64_t M, int64_t ld,
                                hipStream_t st);
 
 // ------------------------------------------------------------------ host side
-static int64_t pad4(int64_t d) { return (d + 3) / 4 * 4; }
-
-// LDS plan for a d-vector plus the staging buffer.  When both fit, the vector is one window; otherwise it is built
-// in several equal windows (multiples of 4 columns) that leave room for at least kMinStage staged entries.
-// Columns carry the row number in the bits above kColBits while staged, hence the limit on d.
-constexpr int64_t kMinStage = 4096;
-struct CsrPlan {
-    int win;        // columns per window
-    int cap;        // staged (column, value) entries
-    int nwin;
-    size_t lds;     // bytes of dynamic LDS: window + staging
-};
-
-// A staged entry takes 12 bytes of LDS, 16 when the caller needs two sums per row (see CsrStage).
-static bool csr_plan(int64_t d, bool second, CsrPlan &p)
-{
-    if (d >= (1ll << kColBits)) return false;      // a staged entry keeps its row number above kColBits column bits
-    const int64_t budget = kLdsBudget - kCsrFixedLds;                     // bytes for window + staging
-    const int64_t each = second ? 16 : 12;
-    int64_t nwin = 1;
-    if (pad4(d) * 4 + each * 512 > budget) nwin = ceil_div(pad4(d) * 4, budget - each * kMinStage);
-    const int64_t win = pad4(ceil_div(pad4(d), nwin));
-    int64_t cap = (budget - win * 4) / each;
-    if (cap > kMaxStage) cap = kMaxStage;
-    p.lds = static_cast<size_t>(win * 4 + cap * each);
-    p.win = static_cast<int>(win);
-    p.cap = static_cast<int>(cap);
-    p.nwin = static_cast<int>(ceil_div(pad4(d), win));
-    return true;
-}
-
 static int64_t csr_full_splits(int64_t n)
 {
     int64_t P = ceil_div(n, 64);
@@ -1223,20 +1186,12 @@ int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64
     if (op == DQ_OP_WORKER_STEP) return csr_model_diff_offset(prob, M);
     // then one more row, in which dq_run_rounds keeps (decoded model) - snapshot between two rounds of a call; then two
     // sets of prepared mini-batches (see kPrepInts), the one a round reads and the one it leaves for the next
-    return csr_prep_offset(prob, M) + 2 * M * csr_prep_stride(prob) * 4;
+    return csr_prep_offset(prob, M) + 2 * M * csr_prep_stride(prob->d) * 4;
 }
 
 int64_t csr_prep_offset(const dq_problem *prob, int64_t M)
 {
     return csr_model_diff_offset(prob, M) + pad4(prob->d) * 4;
-}
-
-// 32-bit words per worker of a prepared mini-batch, for the larger of the two staging capacities
-int64_t csr_prep_stride(const dq_problem *prob)
-{
-    CsrPlan plan;
-    if (!csr_plan(prob->d, false, plan)) return 0;
-    return kPrepInts(plan.cap);
 }
 
 int64_t csr_model_diff_offset(const dq_problem *prob, int64_t M)
@@ -1336,7 +1291,7 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     k.worker0 = a.worker0;
     k.packed = a.packed; k.ld_words = a.ld_words; k.row_words = row_words;
     k.delta_out = a.delta_out; k.nnz_out = a.nnz_out; k.status = a.status; k.zero_word = a.zero_word;
-    k.cap = plan.cap; k.win = plan.win;
+    k.cap = plan.cap; k.win = plan.win; k.prep_cap = csr_prep_cap(d, plan);
     k.alpha_ws = plan.nwin > 1 ? static_cast<float *>(a.ws) : nullptr; k.ld_ws = pad4(d);
     k.model_diff = a.b_x == 32 ? nullptr : a.model_diff;
     const CsrSlices sl = csr_step_slices(prob, a, plan);
@@ -1394,7 +1349,7 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     if (can_prepare) {
         k.prep_in = a.prep_in;
         k.prep_out = a.prep_out;
-        k.prep_stride = csr_prep_stride(prob);
+        k.prep_stride = csr_prep_stride(prob->d);
         k.next_iter = a.iter + 1u;
     }
     if (a.prepared_next) *a.prepared_next = k.prep_out != nullptr;

@@ -964,7 +964,6 @@ int64_t dense_full_splits(int64_t n, int64_t d)
     return P;
 }
 
-static int64_t pad4(int64_t d) { return (d + 3) / 4 * 4; }
 
 // Workspace of a worker step: partial sums, M*P*ldp floats (unused when P == 1).
 int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t B)

@@ -115,7 +115,6 @@ int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64
 int64_t csr_model_diff_offset(const dq_problem *prob, int64_t M);
 // where the two sets of prepared mini-batches lie there (WorkerArgs::prep_in / prep_out), and the words of one worker's
 int64_t csr_prep_offset(const dq_problem *prob, int64_t M);
-int64_t csr_prep_stride(const dq_problem *prob);
 int csr_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,
                   int64_t ws_bytes, hipStream_t st);
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st);

@@ -75,7 +75,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     int64_t prep_set_words = 0;
     if (csr && cfg->tau == 0 && st->ws) {
         const int64_t off = dq::csr_prep_offset(prob, cfg->M);
-        prep_set_words = cfg->M * dq::csr_prep_stride(prob);
+        prep_set_words = cfg->M * dq::csr_prep_stride(prob->d);
         if (prep_set_words > 0 && st->ws_bytes >= off + 2 * prep_set_words * 4)
             prep_sets = reinterpret_cast<int32_t *>(static_cast<char *>(st->ws) + off);
     }

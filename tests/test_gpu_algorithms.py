@@ -472,20 +472,27 @@ def test_rounds_replayed_from_a_captured_graph(dq, name):
 
 @pytest.mark.parametrize("algo,b,M,each,b_x", [("asylpg", 8, 8, False, 8), ("asylpg", 2, 17, True, 6), ("acc", 8, 8, False, 8),
                                                ("acc", 4, 33, True, 4), ("sparse", 4, 5, False, 8), ("sparse", 8, 40, True, 8)])
-@pytest.mark.parametrize("d,B", [(4099, 24), (20958, 32), (36001, 24), (47236, 260)])
-def test_worker_steps_split_over_the_columns_equal_the_separate_calls(dq, algo, b, M, each, b_x, d, B):
+@pytest.mark.parametrize("d,B,cache", [(4099, 24, True), (20958, 32, True), (36001, 24, True), (47236, 260, True),
+                                       (20958, 32, False), (34400, 8, False), (34400, 32, False), (47236, 155, False)])
+def test_worker_steps_split_over_the_columns_equal_the_separate_calls(dq, algo, b, M, each, b_x, d, B, cache):
     """CSR features: inside dq_run_rounds the blocks of a worker share the columns of the gradient and the master quantizes
     it, and wide models are split the same way in any call.  Messages, scales and iterates must be those of dq_vr_grad,
     dq_sparsify, dq_quantize_pack and the master step, one after the other, bit for bit.  (Ragged last quads, several
-    LDS windows, more rows than one pass takes, 17, 33 and 40 workers: fewer slices each.)"""
+    LDS windows, more rows than one pass takes, 17, 33 and 40 workers: fewer slices each.  Without cached margins: batches
+    on either side of what the workspace has room to prepare ahead, 650 entries at 34,400 columns and 4244 at 47,236, and
+    no more than the step itself can stage, 4788 and 5151.)  Nothing is written past the workspace."""
     from paper_1805_10111_amd.driver import DoubleQuantTrainer
     p = synth.sparse_text_logistic(600, d, mean_nnz=30.0, seed=3)
     P = dq.DeviceProblem.from_host(p)
     m, seed = 4, 9
-    one = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each)
-    two = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each)
+    one = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each, cache_margins=cache)
+    two = DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=seed, each=each, cache_margins=cache)
+    sentinel, size = 0x5A5A5A5A, one.ws.numel()
+    roomy = torch.full((size + 16384,), sentinel, dtype=torch.int32, device="cuda")
+    one.state.ws = roomy.data_ptr()                        # (of which the call is told the first `size` words)
     one.epoch_prologue(); two.epoch_prologue()
     one.rounds(0, 3)
+    assert bool((roomy[size:] == sentinel).all())
     ld = (d + 3) // 4 * 4
     idx = torch.empty(M * B, dtype=torch.int32, device="cuda")
     alpha, beta = torch.zeros((M, ld), device="cuda")[:, :d], torch.zeros((M, ld), device="cuda")[:, :d]

@@ -1,0 +1,36 @@
+"""The host's launch arithmetic (csrc/launch_sizes.h), compiled with the host compiler and swept over its whole range."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1805_10111_amd", "csrc")
+
+
+def _sweep(tmp_path, body):
+    """Runs `body` (statements of a main() that print what is wrong) and returns what it printed."""
+    src, exe = tmp_path / "sweep.cpp", tmp_path / "sweep"
+    src.write_text('#include <cstdio>\n#include "launch_sizes.h"\nusing namespace dq;\nint main() {\n' + body + "\nreturn 0;\n}\n")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+
+
+def test_a_prepared_mini_batch_fits_its_room_in_the_workspace(tmp_path):
+    """CSR features, every width the library takes, margins cached or not: the entries that a block may prepare ahead fit the
+    words the workspace holds per worker, and the staging buffer of the step that reads them; the plans fit in LDS."""
+    out = _sweep(tmp_path, """
+    long wider = 0;
+    for (int64_t d = 1; d < (1ll << kColBits); ++d)
+        for (int second = 0; second < 2; ++second) {
+            CsrPlan p;
+            if (!csr_plan(d, second, p)) { std::printf("no plan %ld\\n", (long)d); return 0; }
+            const int cap = csr_prep_cap(d, p);
+            if (cap < 1 || cap > p.cap || kPrepInts(cap) > csr_prep_stride(d)) std::printf("room %ld %d\\n", (long)d, second);
+            if ((int64_t)p.lds > kLdsBudget - kCsrFixedLds || p.win % 4 || (int64_t)p.win * p.nwin < d || p.cap > kMaxStage)
+                std::printf("lds %ld %d\\n", (long)d, second);
+            wider += kPrepInts(p.cap) > csr_prep_stride(d);
+        }
+    if (wider == 0) std::printf("no width whose plan stages more than the workspace has room for\\n");
+    CsrPlan p;
+    if (csr_plan(1ll << kColBits, false, p)) std::printf("too wide\\n");
+    """)
+    assert out == "", out[:2000]
