@@ -75,13 +75,13 @@ __device__ __forceinline__ void load_cols(const float *__restrict__ row, int64_t
     }
 }
 
-// TIGHT: only the thread's last column can lie past the end (see full_shape).
-template <int NC, bool FULL = false, int T = kRowThreads, bool TIGHT = false>
+// FROM: the thread's first column that can lie past the end.
+template <int NC, bool FULL = false, int T = kRowThreads, int FROM = 0>
 __device__ __forceinline__ void mask_cols(float4 (&a)[NC], int64_t d)
 {
     if constexpr (!FULL) {
 #pragma unroll
-        for (int c = TIGHT ? NC - 1 : 0; c < NC; ++c) {
+        for (int c = FROM; c < NC; ++c) {
             const int64_t col = 4ll * (threadIdx.x + T * c);
             a[c].x = col + 0 < d ? a[c].x : 0.0f;
             a[c].y = col + 1 < d ? a[c].y : 0.0f;
@@ -654,7 +654,7 @@ int launch_worker_zero(const WorkerArgs &a, int64_t d, int64_t row_words, hipStr
 // then can a wait for one batch leave the loads of the next batch in flight (two row buffers).
 constexpr int kFullChunk = 1024;
 
-// Of the thread's columns only the last may lie past the end (see full_shape).
+// Of the thread's columns only those from full_whole_cols(NC) on may lie past the end.
 template <int NC, int R, bool FULL, int T = kRowThreads, bool STREAM = false>
 __global__ __launch_bounds__(T) void full_dense_partial_kernel(
     const float *__restrict__ X, int64_t lda, int64_t n, int64_t d, const float *__restrict__ yv,
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
         float z[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            mask_cols<NC, FULL, T, true>(row[r], d);
+            mask_cols<NC, FULL, T, full_whole_cols(NC)>(row[r], d);
             z[r] = dot_cols<NC>(row[r], xv);
         }
         block_sum_R<R, T>(z, sh_red, buf);
@@ -978,20 +978,6 @@ int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int
     int64_t rows = 0;
     for (int64_t g = 1; g <= M; ++g) rows = std::max(rows, g * dense_vr_splits(g, B, prob->d));
     return rows * ldp * 4;
-}
-
-// Threads per block and float4 columns per thread of the full gradient on rows of more than 1024 floats: of 256 to 512
-// threads in whole wavefronts, as few as cover the row with 1, 2, 4 or 8 columns each, so that no more than the last
-// wavefront's last column lies past the end.
-struct FullShape {
-    int threads, cols;
-};
-
-static FullShape full_shape(int64_t d)
-{
-    const int64_t quads = ceil_div(d, 4);
-    const int cols = quads <= 512 ? 1 : quads <= 1024 ? 2 : quads <= 2048 ? 4 : 8;
-    return FullShape{static_cast<int>(std::max<int64_t>(256, ceil_div(ceil_div(quads, cols), kWave) * kWave)), cols};
 }
 
 struct FullArgs {

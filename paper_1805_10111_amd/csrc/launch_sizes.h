@@ -11,6 +11,27 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t packed_words(int64_t d, int b) { return (d * b + 31) / 32; }
 inline int64_t pad4(int64_t d) { return (d + 3) / 4 * 4; }
 
+// ------------------------------------------------------------------ full gradient on dense features (grad_dense.hip)
+// Threads per block and float4 columns per thread on rows of more than 1024 floats: of 256 to 512 threads in whole
+// wavefronts, as few as cover the row with 1, 2, 4 or 8 columns each.
+struct FullShape {
+    int threads, cols;
+};
+
+inline FullShape full_shape(int64_t d)
+{
+    const int64_t quads = ceil_div(d, 4);
+    const int cols = quads <= 512 ? 1 : quads <= 1024 ? 2 : quads <= 2048 ? 4 : 8;
+    const int64_t threads = ceil_div(ceil_div(quads, cols), 64) * 64;
+    return FullShape{static_cast<int>(threads < 256 ? 256 : threads), cols};
+}
+
+// Of a thread's `cols` columns the first so many lie inside the row for every thread and need no mask, in any shape that
+// full_shape gives: threads * full_whole_cols(cols) <= d / 4.  Rounding up to whole wavefronts adds up to 63 quads per
+// column; with eight columns those can pass the end by more than the last column (8197 floats: 320 threads, seven
+// columns of them 2240 quads of 2050).
+constexpr int full_whole_cols(int cols) { return cols >= 8 ? cols - 2 : cols - 1; }
+
 // ------------------------------------------------------------------ worker step on CSR features (grad_csr.hip)
 constexpr int kColBits = 20;                     // staged entries carry column | row << kColBits
 constexpr int kCsrMaxRows = 256;                 // rows a block handles per pass (LDS metadata)

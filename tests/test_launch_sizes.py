@@ -34,3 +34,16 @@ def test_a_prepared_mini_batch_fits_its_room_in_the_workspace(tmp_path):
     if (csr_plan(1ll << kColBits, false, p)) std::printf("too wide\\n");
     """)
     assert out == "", out[:2000]
+
+
+def test_the_full_gradient_masks_every_column_that_can_pass_the_end(tmp_path):
+    """Dense features, every width above 1024: the shape covers the row, and the columns that are not masked hold whole quads
+    of it for every thread."""
+    out = _sweep(tmp_path, """
+    for (int64_t d = 1025; d <= 16384; ++d) {
+        const FullShape s = full_shape(d);
+        if (s.threads < 256 || s.threads > 512 || s.threads % 64 || (int64_t)s.threads * s.cols < ceil_div(d, 4)) std::printf("shape %ld\\n", (long)d);
+        if ((int64_t)s.threads * full_whole_cols(s.cols) > d / 4) std::printf("mask %ld\\n", (long)d);
+    }
+    """)
+    assert out == "", out[:2000]
