@@ -421,7 +421,7 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         my_row = static_cast<uint64_t>(i) < static_cast<uint64_t>(a.n) ? static_cast<int>(i) : -1;   // out of range: ignored
     }
     // valid rows only (the usual case): the row loads then carry no condition, so a wait for one batch can leave the
-    // loads of the next one in flight.  A position past the last row repeats that row, with coefficient 0 (a block of
+    // loads of the next one in flight.  A position past the last row repeats that row and is not added (a block of
     // 15 rows whose loads sat behind tests took longer than four of four rows).  (Every wavefront holds the same row
     // numbers and takes the same decision.)
     const bool plain = DB == 2 || (nrows > 0 && __all(lane >= nrows || my_row >= 0));
@@ -478,10 +478,16 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         }
         float coef_l = 0.0f;
         if (lane < R && (DB == 2 || il >= 0)) coef_l = vr_slope_diff(yl, zs, dz) * inv_B;
+        const auto add_row = [&](int r) {
+            axpy_cols<NC>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(coef_l), r)), row[r], acc);
+        };
+        if (DB == 2 || rb + R <= nrows) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const float coef = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(coef_l), r));
-            axpy_cols<NC>(coef, row[r], acc);          // dead rows: coef = 0 and the row registers are 0
+            for (int r = 0; r < R; ++r) add_row(r);
+        } else {                                       // positions past the block's rows hold a repeated row, which may hold Inf
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (rb + r < nrows) add_row(r);
         }
     };
 
@@ -785,8 +791,10 @@ __global__ __launch_bounds__(kNarrowThreads) void full_narrow_partial_kernel(
         float z_mine = 0.0f, y_mine = 0.0f;              // lane u of a row's lanes records row u of the batch
 #pragma unroll
         for (int u = 0; u < R; ++u) {
+            const bool live = i + u * G + g < i1;        // (a repeated row is cleared: it may hold Inf)
             float4 a = row[u];
-            a.x = in0 ? a.x : 0.0f; a.y = in1 ? a.y : 0.0f; a.z = in2 ? a.z : 0.0f; a.w = in3 ? a.w : 0.0f;
+            a.x = in0 && live ? a.x : 0.0f; a.y = in1 && live ? a.y : 0.0f;
+            a.z = in2 && live ? a.z : 0.0f; a.w = in3 && live ? a.w : 0.0f;
             float z = fmaf(a.x, xv.x, 0.0f);
             z = fmaf(a.y, xv.y, z); z = fmaf(a.z, xv.z, z); z = fmaf(a.w, xv.w, z);
             if constexpr (L == kWave) {
@@ -798,7 +806,6 @@ __global__ __launch_bounds__(kNarrowThreads) void full_narrow_partial_kernel(
                 z += __int_as_float(dpp_move_or_zero<0x128, 0xf>(__float_as_int(z)));
                 if constexpr (L == 32) z += __shfl_xor(z, 16, kWave);
             }
-            const bool live = i + u * G + g < i1;
             const float coef = live ? logistic_slope_fast(y[u], z) * inv_n : 0.0f;
             acc.x = fmaf(coef, a.x, acc.x); acc.y = fmaf(coef, a.y, acc.y);
             acc.z = fmaf(coef, a.z, acc.z); acc.w = fmaf(coef, a.w, acc.w);

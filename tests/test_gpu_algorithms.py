@@ -561,3 +561,27 @@ def test_small_dense_rounds_in_one_launch_equal_the_separate_calls(dq, algo, b, 
             assert torch.equal(getattr(one, name), getattr(two, name)), (e, name)
         one.epoch_epilogue(); two.epoch_epilogue()
     assert host(one.x).any() and host(one.status)[0] == 0
+
+
+@pytest.mark.parametrize("B", [1, 5, 16])
+def test_small_dense_rounds_with_an_infinite_feature(dq, B):
+    """The scale of a gradient with an infinite coordinate is infinite, as in the separate worker step, not NaN: a row that is
+    requested twice to fill up a batch is not added a second time."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    d = 100
+    X = np.ones((1, d), dtype=np.float32)
+    X[0, 7] = np.inf
+    P = dq.DeviceProblem(n=1, d=d, y=-torch.ones(1, device="cuda"), l2=0.0, l1=0.0, dense=dev(X))
+    one = DoubleQuantTrainer(P, "asylpg", 2, B, 8, 8, 4, 0.5, x0=torch.ones(d, device="cuda"))
+    two = DoubleQuantTrainer(P, "asylpg", 2, B, 8, 8, 4, 0.5, x0=torch.ones(d, device="cuda"))
+    for tr in (one, two):
+        tr.z_snap.zero_()
+        tr.x_snap.copy_(torch.linspace(0.1, 1.0, d))
+        tr.delta_x.fill_(1.0 / 64)
+        tr.xq.copy_(torch.full_like(tr.xq, 0x20202020))    # (every coordinate of the model: 32/64)
+    one.rounds(1, 1)
+    idx = torch.zeros(2 * B, dtype=torch.int32, device="cuda")
+    dq.dq_worker_step(P, idx, 2, B, two.xq, two.delta_x, 8, False, two.x_snap, two.z_snap, False, 8, 0, 1, 0, two.packed, two.delta,
+                      None, None, two.status, two.ws)
+    assert host(two.delta).tolist() == [np.inf, np.inf] and host(one.delta).tolist() == [np.inf, np.inf]
+    assert torch.equal(one.packed, two.packed) and host(one.status)[0] == 1 and host(two.status)[0] == 1

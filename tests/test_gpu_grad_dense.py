@@ -325,3 +325,41 @@ def test_full_gradient_over_widths(dq, n, d):
     assert np.abs(host(z) - want_z).max() <= 1e-5 * np.abs(want_z).max() + 1e-7
     assert np.abs(host(g) - want_g).max() <= 1e-5 * np.abs(want_g).max() + 1e-9
     assert abs(host(obj)[0] - oracle.objective(ref, x)) <= 1e-5 * abs(oracle.objective(ref, x))
+
+
+@pytest.mark.parametrize("d,M,B", [(54, 3, 5), (1000, 2, 5), (1000, 3, 33), (1500, 2, 5), (2500, 2, 5), (5000, 2, 3), (12002, 2, 7),
+                                   (2500, 12, 90)])
+def test_an_infinite_feature_reaches_its_own_column_only(dq, d, M, B):
+    """A row with an infinite feature, the last of a block's: the gradient is infinite in that column and finite in all others.
+    (A row that is requested twice to fill up a batch must not be added a second time: 0 * Inf is not a number.)"""
+    n, j = 7, d // 2
+    rng = np.random.default_rng(d)
+    X = (rng.standard_normal((n, (d + 3) // 4 * 4)) / np.sqrt(d)).astype(np.float32)
+    X[n - 1, j] = np.inf
+    x_snap = np.zeros(d, dtype=np.float32)
+    q = rng.standard_normal(d).astype(np.float32)
+    q[j] = 1.0
+    y = -np.ones(n, dtype=np.float32)
+    P = dq.DeviceProblem(n=n, d=d, y=dev(y), l2=0.0, l1=0.0, dense=dev(X)[:, :d])
+    idx = np.full((M, B), n - 1, dtype=np.int32)
+    idx[:, :-1] = rng.integers(0, n - 1, (M, B - 1))
+    ld = (d + 3) // 4 * 4
+    alpha, amax = torch.zeros((M, ld), device="cuda")[:, :d], torch.zeros(M, device="cuda")
+    dq.dq_vr_grad(P, dev(idx).view(-1), M, B, dev(q).view(torch.int32), None, 32, False, dev(x_snap), torch.zeros(n, device="cuda"),
+                  alpha, amax, None, dq.new_workspace(dq.OP_VR_GRAD, P, M, B))
+    a = host(alpha)
+    assert np.isinf(host(amax)).all() and np.isinf(a[:, j]).all() and np.isfinite(np.delete(a, j, 1)).all()
+
+
+@pytest.mark.parametrize("d", [1, 54, 100, 200, 256])
+def test_an_infinite_feature_in_the_full_gradient_of_narrow_rows(dq, d):
+    n, j = 37, d // 2
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((n, (d + 3) // 4 * 4)).astype(np.float32)
+    X[n - 1, j] = np.inf
+    x = np.ones(d, dtype=np.float32)
+    y = -np.ones(n, dtype=np.float32)                      # (margin +Inf with label -1: slope 1)
+    P = dq.DeviceProblem(n=n, d=d, y=dev(y), l2=0.0, l1=0.0, dense=dev(X)[:, :d])
+    g = torch.zeros(d, device="cuda")
+    dq.dq_full_grad(P, dev(x), g, None, None, dq.new_workspace(dq.OP_FULL_GRAD, P))
+    assert host(g)[j] == np.inf and np.isfinite(np.delete(host(g), j)).all()
