@@ -100,7 +100,9 @@ static inline dim3 grid_for_groups(int64_t d, int64_t M)
     return dim3(static_cast<unsigned>(ceil_div(groups, kThreads)), static_cast<unsigned>(M));
 }
 
-// A block takes 1024 coordinates, which occupy exactly 32 b words, a thread one quad of them (one Philox block); the fields
+constexpr int64_t kAnyBlocksX = 1 << 23;         // (a launch may have fewer than 2^32 threads along x)
+
+// A block takes 1024 coordinates at a time, which occupy exactly 32 b words, a thread one quad of them (one Philox block); the fields
 // meet in LDS and leave as whole words.  (One thread per group of 32 with a shift register, eight Philox blocks one after
 // the other and input lines shared by eight threads: 784 coordinates at 6 bits 5.4 us, now 2.5; 10^6 at 11 bits
 // 7.4, now 4.0; 2^26 at 3 bits 289, now 83; at 11 bits 422, now 102.)
@@ -112,35 +114,42 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_any_kernel(
     __shared__ uint32_t words[32 * 16 + 2];
     const int m = blockIdx.y;
     const float *row = v + static_cast<int64_t>(m) * ld;
-    const int64_t quads = (d + 3) / 4, q = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const int64_t qc = min(q, quads - 1);                // (threads past the end repeat the last quad and add no bits)
-    float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (d > 0) {                                         // (the same for every thread; an empty row still has a scale)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = row[min(4 * qc + e, d - 1)];
-    }
-    const float amax = absmax[m];
-    key.worker = worker0 + static_cast<uint32_t>(m);
-    const uint4 r = stream_block(key, static_cast<uint32_t>(qc));
-    for (int w = threadIdx.x; w < 32 * 16 + 2; w += kThreads) words[w] = 0u;
-    const Scale s = make_scale(amax, b);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        delta_out[m] = s.delta;
-        if (s.bad && status) atomicOr(status, 1u);
-    }
-    __syncthreads();
-    if (q < quads && s.inv_delta != 0.0f) {              // (a degenerate scale: every code is zero)
-        const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
-        int k[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) k[e] = 4 * q + e < d ? quantize_one(x[e], s, rw[e]) : 0;
-        or_quad_bits(words, threadIdx.x, b, k);
-    }
-    __syncthreads();
     uint32_t *out = packed + static_cast<int64_t>(m) * ld_words;
-    const int64_t w0 = static_cast<int64_t>(blockIdx.x) * 32 * b;
-    for (int w = threadIdx.x; w < 32 * b; w += kThreads)
-        if (w0 + w < row_words) out[w0 + w] = words[w];
+    const int64_t quads = (d + 3) / 4;
+    key.worker = worker0 + static_cast<uint32_t>(m);
+    // (one turn up to kAnyBlocksX blocks a row, 2^33 coordinates; at least one, as an empty row still has a scale)
+    for (int64_t tile = blockIdx.x;;) {
+        const int64_t q = tile * kThreads + threadIdx.x;
+        const int64_t qc = min(q, quads - 1);            // (threads past the end repeat the last quad and add no bits)
+        float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (d > 0) {                                     // (the same for every thread)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = row[min(4 * qc + e, d - 1)];
+        }
+        const float amax = absmax[m];
+        const uint4 r = stream_block(key, static_cast<uint32_t>(qc));
+        for (int w = threadIdx.x; w < 32 * 16 + 2; w += kThreads) words[w] = 0u;
+        const Scale s = make_scale(amax, b);
+        if (tile == 0 && threadIdx.x == 0) {
+            delta_out[m] = s.delta;
+            if (s.bad && status) atomicOr(status, 1u);
+        }
+        __syncthreads();
+        if (q < quads && s.inv_delta != 0.0f) {          // (a degenerate scale: every code is zero)
+            const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+            int k[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k[e] = 4 * q + e < d ? quantize_one(x[e], s, rw[e]) : 0;
+            or_quad_bits(words, threadIdx.x, b, k);
+        }
+        __syncthreads();
+        const int64_t w0 = tile * 32 * b;
+        for (int w = threadIdx.x; w < 32 * b; w += kThreads)
+            if (w0 + w < row_words) out[w0 + w] = words[w];
+        tile += gridDim.x;
+        if (tile * kThreads >= quads) break;             // (the same for every thread)
+        __syncthreads();
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void unpack_dequant_sum_any_kernel(
@@ -468,7 +477,7 @@ int launch_quantize_pack_parts(const float *v, int64_t d, int64_t M, int64_t ld,
     case 2: quantize_pack_kernel<2><<<grid, block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status, parts, count_parts, count_out); break;
     default:
         if (field != b || b < 2 || b > 16 || parts != 1 || count_out) return DQ_ERR_UNSUPPORTED;
-        quantize_pack_any_kernel<<<dim3(static_cast<unsigned>(std::max<int64_t>(1, ceil_div(ceil_div(d, 4), kThreads))), static_cast<unsigned>(M)), block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status);
+        quantize_pack_any_kernel<<<dim3(static_cast<unsigned>(std::clamp<int64_t>(ceil_div(ceil_div(d, 4), kThreads), 1, kAnyBlocksX)), static_cast<unsigned>(M)), block, 0, st>>>(v, d, ld, absmax, b, key, worker0, packed, ld_words, row_words, delta_out, status);
         break;
     }
     DQ_LAUNCH_CHECK();

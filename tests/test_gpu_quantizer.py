@@ -298,3 +298,26 @@ def test_full_size_decode_and_sum_sampled(dq):
                 want, _, _ = oracle.quantize_given_uniforms(win, b, u)
                 assert np.array_equal(codes[w], want[:4096]), (b, s, w)
         del packed, res
+
+
+def test_any_width_takes_vectors_of_more_than_two_to_the_34_coordinates(dq):
+    """64 GiB of floats, zero but for the two ends: a launch has fewer than 2^32 threads, so the blocks take several turns.  The
+    random stream is addressed by the coordinate, modulo 2^34."""
+    d, b, ends = (1 << 34) + 3000, 3, 4096
+    rng = np.random.default_rng(1)
+    first, last = (rng.standard_normal(k).astype(np.float32) for k in (ends, ends + 3000))
+    last[-1] = 9.0                                         # the largest magnitude, at the very end
+    v = torch.zeros(d, device="cuda")
+    v[:ends], v[d - last.size:] = dev(first), dev(last)
+    packed = torch.full((dq.packed_words(d, b),), -1, dtype=torch.int32, device="cuda")
+    amax, delta = torch.full((1,), 9.0, device="cuda"), torch.zeros(1, device="cuda")
+    dq.dq_quantize_pack(v, b, amax, True, 11, 2, dq.TAG_GRAD, 5, packed, delta)
+    for x, at in ((first, 0), (last, d - last.size)):
+        u = oracle.uniform_range(11, 2, 5, dq.TAG_GRAD, at, x.size)
+        codes, want, _ = oracle.quantize_given_uniforms(np.append(x, np.float32(9.0)), b, np.append(u, np.float32(0.0)))
+        assert host(delta)[0] == want
+        words = oracle.pack_wide(codes[:-1], b)
+        got = host(packed[at * b // 32:][:words.size]).view(np.uint32)
+        assert np.array_equal(got, words)
+    mid = (1 << 33) * b // 32
+    assert not packed[mid - (1 << 20):mid + (1 << 20)].any()
