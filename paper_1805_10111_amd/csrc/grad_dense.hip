@@ -799,11 +799,14 @@ __global__ __launch_bounds__(kNarrowThreads) void full_narrow_partial_kernel(
             z = fmaf(a.y, xv.y, z); z = fmaf(a.z, xv.z, z); z = fmaf(a.w, xv.w, z);
             if constexpr (L == kWave) {
                 z = wave_sum_f32(z);
-            } else {                                     // two quad permutes and two rotations of 16 lanes
+            } else {
+                // Two quad permutes and two rotations of 16 lanes, by 8 before by 4: every lane then adds the quads' sums
+                // as (q0 + q2) + (q1 + q3), and all columns of the row get the same coefficient, that of the margin
+                // recorded.  (By 4 first, half of the lanes would add (q0 + q1) + (q2 + q3), half (q0 + q3) + (q2 + q1).)
                 z += __int_as_float(dpp_move_or_zero<0xb1, 0xf>(__float_as_int(z)));
                 z += __int_as_float(dpp_move_or_zero<0x4e, 0xf>(__float_as_int(z)));
-                z += __int_as_float(dpp_move_or_zero<0x124, 0xf>(__float_as_int(z)));
                 z += __int_as_float(dpp_move_or_zero<0x128, 0xf>(__float_as_int(z)));
+                z += __int_as_float(dpp_move_or_zero<0x124, 0xf>(__float_as_int(z)));
                 if constexpr (L == 32) z += __shfl_xor(z, 16, kWave);
             }
             const float coef = live ? logistic_slope_fast(y[u], z) * inv_n : 0.0f;

@@ -363,3 +363,18 @@ def test_an_infinite_feature_in_the_full_gradient_of_narrow_rows(dq, d):
     g = torch.zeros(d, device="cuda")
     dq.dq_full_grad(P, dev(x), g, None, None, dq.new_workspace(dq.OP_FULL_GRAD, P))
     assert host(g)[j] == np.inf and np.isfinite(np.delete(host(g), j)).all()
+
+
+@pytest.mark.parametrize("d", [16, 33, 64, 100, 128, 256, 1000])
+def test_all_columns_of_a_row_get_the_same_coefficient(dq, d):
+    """One row of powers of two: the gradient divided by the feature is exact, and is the row's coefficient in every column,
+    whatever the order in which the lanes added up the margin."""
+    rng = np.random.default_rng(d)
+    g = torch.zeros(d, device="cuda")
+    for _ in range(30):
+        X = np.ldexp(rng.choice([-1.0, 1.0], (1, (d + 3) // 4 * 4)), rng.integers(-3, 3, (1, (d + 3) // 4 * 4))).astype(np.float32)
+        x = (0.1 * rng.standard_normal(d)).astype(np.float32)
+        P = dq.DeviceProblem(n=1, d=d, y=torch.ones(1, device="cuda"), l2=0.0, l1=0.0, dense=dev(X)[:, :d])
+        dq.dq_full_grad(P, dev(x), g, None, None, dq.new_workspace(dq.OP_FULL_GRAD, P))
+        coef = host(g) / X[0, :d]
+        assert np.unique(coef).size == 1 and coef[0] < 0
