@@ -26,6 +26,12 @@ void set_last_error(hipError_t e);
 
 #define DQ_LAUNCH_CHECK() DQ_HIP_TRY(hipGetLastError())
 
+// whether na 32-bit words at a and nb at b share memory (either may be null)
+inline bool ranges_overlap(const void *a, int64_t na, const void *b, int64_t nb)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + 4 * static_cast<uintptr_t>(nb) && y < x + 4 * static_cast<uintptr_t>(na);
+}
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // ---- Philox4x32-10 (Salmon et al., SC'11), from its published definition -------

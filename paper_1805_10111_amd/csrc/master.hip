@@ -823,14 +823,10 @@ extern "C" int32_t dq_sparsify(const float *alpha, int64_t d, int64_t M, int64_t
     // One block per row up to kOneBlockRow coordinates; beyond that one block per compute unit over all rows, none with
     // less than a sweep of quads.  A row is read by all of its blocks
     // before and while they write theirs: in place, and where the budgets share memory with a result, one block takes it.
-    const auto overlap = [](const void *a, int64_t na, const void *b, int64_t nb) {
-        const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-        return a && b && x < y + 4 * static_cast<uintptr_t>(nb) && y < x + 4 * static_cast<uintptr_t>(na);
-    };
     const int64_t in_floats = (M - 1) * ld + d, out_floats = (M - 1) * ld_out + d;
-    const bool shared_memory = overlap(alpha, in_floats, beta_out, out_floats) || overlap(phi, M, absmax_out, M) ||
-                               overlap(phi, M, nnz_out, M) || overlap(alpha, in_floats, absmax_out, M) ||
-                               overlap(alpha, in_floats, nnz_out, M);
+    const bool shared_memory = ranges_overlap(alpha, in_floats, beta_out, out_floats) || ranges_overlap(phi, M, absmax_out, M) ||
+                               ranges_overlap(phi, M, nnz_out, M) || ranges_overlap(alpha, in_floats, absmax_out, M) ||
+                               ranges_overlap(alpha, in_floats, nnz_out, M);
     const int64_t slices = shared_memory || d <= kOneBlockRow ? 1 : std::min(ceil_div(256, M), ceil_div(ceil_div(d, 4), kSparsifyThreads));
     if (slices > 1) {
         clear_rows_kernel<<<dim3(static_cast<unsigned>(ceil_div(M, kSparsifyThreads))), dim3(kSparsifyThreads), 0, st>>>(absmax_out, nnz_out, M);

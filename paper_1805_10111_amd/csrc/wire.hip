@@ -59,6 +59,7 @@ __device__ __forceinline__ uint32_t nonzero_fields(uint32_t w)
 // would emit most (8.1 us against 6.8 in the first case below).  Measured at 47,236
 // columns, 4 bits, 8 rows: one block per row with a prefix sum of twenty barriers per 16,384 coordinates 16.0 us, now
 // 6.8 us; 20,958 columns, 16 rows: 10.6 us, now 5.5 us.
+// Where the streams take the place of the rows one block does all spans of a row, which it has in LDS by then.
 template <int FIELD>
 __global__ __launch_bounds__(kWireThreads) void sparse_encode_kernel(
     const uint32_t *__restrict__ packed, int64_t ld_words, int row_words, int d, int pos_bits, uint32_t *__restrict__ stream,
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(kWireThreads) void sparse_encode_kernel(
     __shared__ int sh_scan[kWireThreads / kWave];
     __shared__ int sh_first[kWireThreads];
     uint32_t *sh_stream = sh, *sh_row = sh + span;
-    const int m = blockIdx.x, w0 = blockIdx.y * span, nw = min(span, cap_words - w0);
+    const int m = blockIdx.x;
     const uint32_t *row = packed + static_cast<int64_t>(m) * ld_words;
     for (int w = threadIdx.x; w < per * kWireThreads; w += kWireThreads) {
         uint32_t v = row[min(w, row_words - 1)];
@@ -78,41 +79,48 @@ __global__ __launch_bounds__(kWireThreads) void sparse_encode_kernel(
         }
         sh_row[w] = v;
     }
-    for (int w = threadIdx.x; w < nw; w += kWireThreads) sh_stream[w] = 0u;
+    for (int w = threadIdx.x; w < span; w += kWireThreads) sh_stream[w] = 0u;
     __syncthreads();
     const int first = per * threadIdx.x;
     int count = 0, total;
     for (int j = 0; j < per; ++j) count += __popc(nonzero_fields<FIELD>(sh_row[first + j]));
     sh_first[threadIdx.x] = block_scan_exclusive(count, sh_scan, &total);        // (at most 2^17 entries of 25 bits)
     __syncthreads();
-    const int E = pos_bits + FIELD, lo = w0 * 32, hi = (w0 + nw) * 32;
-    for (int e = lo / E + threadIdx.x; e < total && e * E < hi; e += kWireThreads) {
-        int t = 0;                                                // the thread whose words hold entry e: the last with first <= e
+    const int E = pos_bits + FIELD;
+    for (int w0 = blockIdx.y * span;;) {
+        const int nw = min(span, cap_words - w0), lo = w0 * 32, hi = (w0 + nw) * 32;
+        for (int e = lo / E + threadIdx.x; e < total && e * E < hi; e += kWireThreads) {
+            int t = 0;                                            // the thread whose words hold entry e: the last with first <= e
 #pragma unroll
-        for (int step = kWireThreads / 2; step >= 1; step >>= 1) t += sh_first[t + step] <= e ? step : 0;
-        int rank = e - sh_first[t], at = per * t - 1;
-        uint32_t word = 0, mask = 0;
-        for (int left = rank; left >= 0; left -= __popc(mask)) {  // ... then its word, and the field in it
-            rank = left;
-            word = sh_row[++at];
-            mask = nonzero_fields<FIELD>(word);
+            for (int step = kWireThreads / 2; step >= 1; step >>= 1) t += sh_first[t + step] <= e ? step : 0;
+            int rank = e - sh_first[t], at = per * t - 1;
+            uint32_t word = 0, mask = 0;
+            for (int left = rank; left >= 0; left -= __popc(mask)) {      // ... then its word, and the field in it
+                rank = left;
+                word = sh_row[++at];
+                mask = nonzero_fields<FIELD>(word);
+            }
+            for (; rank > 0; --rank) mask &= mask - 1;
+            const int sh = __ffs(mask) - 1, bit = e * E, w = (bit >> 5) - w0;
+            const uint64_t entry = static_cast<uint64_t>(at * (32 / FIELD) + sh / FIELD) |
+                                   (static_cast<uint64_t>((word >> sh) & ((1u << FIELD) - 1u)) << pos_bits);
+            const uint64_t shifted = entry << (bit & 31);         // E + 31 < 64 bits: at most two words
+            if (w >= 0 && w < nw) atomicOr(sh_stream + w, static_cast<uint32_t>(shifted));
+            if (w + 1 < nw && (shifted >> 32)) atomicOr(sh_stream + w + 1, static_cast<uint32_t>(shifted >> 32));
         }
-        for (; rank > 0; --rank) mask &= mask - 1;
-        const int sh = __ffs(mask) - 1, bit = e * E, w = (bit >> 5) - w0;
-        const uint64_t entry = static_cast<uint64_t>(at * (32 / FIELD) + sh / FIELD) |
-                               (static_cast<uint64_t>((word >> sh) & ((1u << FIELD) - 1u)) << pos_bits);
-        const uint64_t shifted = entry << (bit & 31);             // E + 31 < 64 bits: at most two words
-        if (w >= 0 && w < nw) atomicOr(sh_stream + w, static_cast<uint32_t>(shifted));
-        if (w + 1 < nw && (shifted >> 32)) atomicOr(sh_stream + w + 1, static_cast<uint32_t>(shifted >> 32));
+        __syncthreads();
+        uint32_t *out = stream + static_cast<int64_t>(m) * ld_stream + w0;
+        for (int w = threadIdx.x; w < nw; w += kWireThreads) out[w] = sh_stream[w];
+        w0 += gridDim.y * span;
+        if (w0 >= cap_words) break;                               // (the same for every thread)
+        for (int w = threadIdx.x; w < span; w += kWireThreads) sh_stream[w] = 0u;      // (each thread the words it has stored)
+        __syncthreads();
     }
-    __syncthreads();
-    uint32_t *out = stream + static_cast<int64_t>(m) * ld_stream + w0;
-    for (int w = threadIdx.x; w < nw; w += kWireThreads) out[w] = sh_stream[w];
     if (threadIdx.x == 0 && blockIdx.y == 0) nnz_out[m] = total;
 }
 
-// A block owns `span` words of the dense row and takes from the stream, which it reads whole, the entries that fall
-// there.
+// A block owns `span` words of the dense row (all of them where the rows take the place of the streams) and takes from the
+// stream, which it reads whole, the entries that fall there.
 template <int FIELD>
 __global__ __launch_bounds__(kWireThreads) void sparse_decode_kernel(
     const uint32_t *__restrict__ stream, int64_t ld_stream, const int32_t *__restrict__ nnz, int64_t d, int pos_bits,
@@ -181,7 +189,8 @@ extern "C" int32_t dq_sparse_encode(const uint32_t *packed, int64_t ld_words, in
     const int span = static_cast<int>(ceil_div(cap, spans));
     const int per = static_cast<int>(ceil_div(row_words, kWireThreads)) | 1;
     const size_t lds = (static_cast<size_t>(span) + static_cast<size_t>(per) * kWireThreads) * 4;
-    const dim3 grid(static_cast<unsigned>(M), static_cast<unsigned>(ceil_div(cap, span))), block(kWireThreads);
+    const bool in_place = ranges_overlap(packed, (M - 1) * ld_words + row_words, stream_out, (M - 1) * ld_stream + cap);
+    const dim3 grid(static_cast<unsigned>(M), in_place ? 1u : static_cast<unsigned>(ceil_div(cap, span))), block(kWireThreads);
     hipStream_t st = as_stream(stream);
     int rc;
 #define DQ_ENCODE(F)                                                                                                     \
@@ -206,7 +215,8 @@ extern "C" int32_t dq_sparse_decode(const uint32_t *stream_in, int64_t ld_stream
     if (row_words > kWireLdsWords) return DQ_ERR_UNSUPPORTED;
     const int pb = position_bits(d);
     // (each block reads its row's whole stream: no more blocks than keep every thread busy with a word of its own)
-    const int span = static_cast<int>(ceil_div(row_words, std::min(ceil_div(256, M), ceil_div(row_words, kWireThreads))));
+    const bool in_place = ranges_overlap(packed_out, (M - 1) * ld_words + row_words, stream_in, (M - 1) * ld_stream + cap);
+    const int span = static_cast<int>(ceil_div(row_words, in_place ? 1 : std::min(ceil_div(256, M), ceil_div(row_words, kWireThreads))));
     const size_t lds = static_cast<size_t>(span) * 4;
     const dim3 grid(static_cast<unsigned>(M), static_cast<unsigned>(ceil_div(row_words, span))), block(kWireThreads);
     hipStream_t st = as_stream(stream);

@@ -162,3 +162,21 @@ def test_encode_decode_where_a_row_is_cut(dq, M, d, b):
     back = torch.full((M, ldw), -1, dtype=torch.int32, device="cuda")
     dq.dq_sparse_decode(stream, nnz, d, b, back)
     assert np.array_equal(words(back)[:, :nw], pw[:, :nw])
+
+
+@pytest.mark.parametrize("d,b,M", [(500, 4, 3), (20958, 4, 3), (47000, 4, 1), (40000, 8, 2), (30000, 2, 40)])
+def test_streams_and_rows_may_take_each_others_place(dq, d, b, M):
+    """Encoding into the rows' own memory and decoding back into it gives what separate buffers give."""
+    cap, words_ = dq.dq_sparse_stream_words(d, b), dq.packed_words(d, b)
+    ld = (max(cap, words_) + 3) // 4 * 4
+    v = torch.randn((M, (d + 3) // 4 * 4), device="cuda")[:, :d]
+    v[torch.rand(v.shape, device="cuda") < 0.7] = 0.0
+    rows, amax, delta = torch.zeros((M, ld), dtype=torch.int32, device="cuda"), torch.zeros(M, device="cuda"), torch.zeros(M, device="cuda")
+    dq.dq_quantize_pack(v, b, amax, False, 3, 1, dq.TAG_GRAD, 0, rows, delta)
+    stream, nnz = torch.zeros_like(rows), torch.zeros(M, dtype=torch.int32, device="cuda")
+    dq.dq_sparse_encode(rows, d, b, stream, nnz)
+    both, count = rows.clone(), torch.zeros_like(nnz)
+    dq.dq_sparse_encode(both, d, b, both, count)
+    assert torch.equal(count, nnz) and host(nnz).min() > 0 and torch.equal(both[:, :cap], stream[:, :cap])
+    dq.dq_sparse_decode(both, count, d, b, both)
+    assert torch.equal(both[:, :words_], rows[:, :words_])
