@@ -661,6 +661,10 @@ int launch_worker_zero(const WorkerArgs &a, int64_t d, int64_t row_words, hipStr
 constexpr int kFullChunk = 1024;
 
 // Of the thread's columns only those from full_whole_cols(NC) on may lie past the end.
+// Half as many blocks as the kernel of one column per thread has means float32 sums over twice as many rows: with several
+// columns (and not FULL, which never had more blocks) the two halves of the block's rows are added up separately and
+// then together, so that no sum is longer.  (With one sum the gradient was a tenth further from 64 bits, 1.55e-7 ->
+// 1.66e-7 on average over 1025-8192 columns; as two partial vectors in memory 50,000 x 3000 took 98.5 us instead of 92.9.)
 template <int NC, int R, bool FULL, int T = kRowThreads, bool STREAM = false>
 __global__ __launch_bounds__(T) void full_dense_partial_kernel(
     const float *__restrict__ X, int64_t lda, int64_t n, int64_t d, const float *__restrict__ yv,
@@ -672,11 +676,32 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
     const int64_t per = (n + gridDim.x - 1) / gridDim.x;
     const int64_t i0 = blockIdx.x * per, i1 = min(n, i0 + per);
     float4 xv[NC], acc[NC];
-    zero_cols<NC>(acc);
     load_vec_cols<NC, FULL, T>(x, d, xv);
     const float inv_n = 1.0f / static_cast<float>(n);
     double loss = 0.0;
     int buf = 0;
+    constexpr bool kHalves = NC > 1 && !FULL;
+    static_assert(kFullChunk % (2 * R) == 0, "chunks of whole pairs of batches");
+    // (the first half waits in registers, for eight columns in LDS: 12,000 x 12,000 with registers short took a fifth longer)
+    constexpr bool kInLds = kHalves && NC >= 8;
+    __shared__ float4 sh_half[kInLds ? NC * T : 1];
+    float4 first_half[kHalves && !kInLds ? NC : 1];
+    const int64_t half = i0 + (i1 - i0 + 4 * R - 1) / (4 * R) * (2 * R);     // (a pair of batches starts there)
+    const auto put_half = [&]() {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if constexpr (kInLds) sh_half[c * T + threadIdx.x] = acc[c];
+            else if constexpr (kHalves) first_half[c] = acc[c];
+        }
+        zero_cols<NC>(acc);
+    };
+    zero_cols<NC>(acc);
+    if constexpr (kHalves) put_half();
+    const auto change_half = [&](int64_t next_row) {
+        if constexpr (kHalves) {
+            if (next_row == half) put_half();             // (the same for every thread)
+        }
+    };
     auto load_rows = [&](int64_t ib, float4 (&row)[R][NC]) {          // rows ib .. ib+R-1 all exist
 #pragma unroll
         for (int r = 0; r < R; ++r) load_cols<NC, STREAM, FULL, T>(X + (ib + r) * lda, d, row[r]);
@@ -727,17 +752,20 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
         if (fast > 0) {
             load_rows(c0, rowA);
             for (; rel + 2 * R < fast; rel += 2 * R) {
+                change_half(c0 + rel);
                 load_rows(c0 + rel + R, rowB);
                 compute_batch(rel, cn, rowA);
                 load_rows(c0 + rel + 2 * R, rowA);
                 compute_batch(rel + R, cn, rowB);
             }
+            change_half(c0 + rel);
             load_rows(c0 + rel + R, rowB);
             compute_batch(rel, cn, rowA);
             compute_batch(rel + R, cn, rowB);
             rel += 2 * R;
         }
         for (; rel < cn; rel += R) {                          // the last rows of the block
+            change_half(c0 + rel);
             load_batch(c0 + rel, rowA);
             compute_batch(rel, cn, rowA);
         }
@@ -745,6 +773,13 @@ __global__ __launch_bounds__(T) void full_dense_partial_kernel(
         if (z_out)
             for (int t = threadIdx.x; t < cn; t += T) z_out[c0 + t] = sh_z[t];
         __syncthreads();
+    }
+    if constexpr (kHalves) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const float4 h = kInLds ? sh_half[c * T + threadIdx.x] : first_half[kInLds ? 0 : c];
+            acc[c].x += h.x; acc[c].y += h.y; acc[c].z += h.z; acc[c].w += h.w;
+        }
     }
     store_cols<NC, T>(partial + static_cast<int64_t>(blockIdx.x) * ldp, ldp, acc);
     if (threadIdx.x < kWave) {                       // lanes 0..R-1 of wave 0 hold the block's loss terms

@@ -378,3 +378,31 @@ def test_all_columns_of_a_row_get_the_same_coefficient(dq, d):
         dq.dq_full_grad(P, dev(x), g, None, None, dq.new_workspace(dq.OP_FULL_GRAD, P))
         coef = host(g) / X[0, :d]
         assert np.unique(coef).size == 1 and coef[0] < 0
+
+
+@pytest.mark.parametrize("n,d", [(40000, 2500), (30000, 5000), (12000, 10000)])
+def test_full_gradient_is_no_coarser_than_512_float32_sums(dq, n, d):
+    """With several columns per thread there are 256 blocks; the gradient is all the same as close to 64 bits as 512 float32
+    sums over n/512 rows each, one row after the other, leave it.  Beside those sums it has the roundings of the
+    coefficients and of the sum of the blocks' vectors, 2^-24 of their values each: two of them, in quadrature."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((n, (d + 3) // 4 * 4), device="cuda", generator=g)[:, :d] / d ** 0.5
+    X = torch.nn.functional.pad(X, (0, -d % 4))[:, :d]
+    x = 0.5 * torch.randn(d, device="cuda", generator=g)
+    y = torch.where(torch.rand(n, device="cuda", generator=g) < 0.5, 1.0, -1.0)
+    out = torch.zeros(d, device="cuda")
+    P = dq.DeviceProblem(n=n, d=d, y=y, l2=0.0, l1=0.0, dense=X)
+    dq.dq_full_grad(P, x, out, None, None, dq.new_workspace(dq.OP_FULL_GRAD, P))
+    exact, parts, per = torch.zeros(d, dtype=torch.float64, device="cuda"), torch.zeros((512, d), device="cuda"), -(-n // 512)
+    z = torch.cat([(X[r:r + 4096].double() * x.double()).sum(1) for r in range(0, n, 4096)])
+    coef = -y.double() / (1.0 + torch.exp(y.double() * z)) / n
+    for r in range(0, n, 4096):
+        exact += (X[r:r + 4096].double() * coef[r:r + 4096, None]).sum(0)
+    first = torch.arange(512, device="cuda") * per
+    for k in range(per):
+        rows = first + k
+        live = (rows < n).float()[:, None]
+        parts += coef.float()[rows.clamp(max=n - 1), None] * X[rows.clamp(max=n - 1)] * live
+    plain = (parts.double().sum(0).float().double() - exact).norm() / exact.norm()
+    mine = (out.double() - exact).norm() / exact.norm()
+    assert mine <= (plain ** 2 + (2 * 2.0 ** -24) ** 2) ** 0.5
