@@ -1079,17 +1079,24 @@ int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float 
     float *partial = static_cast<float *>(ws);
     double *loss_partial = reinterpret_cast<double *>(partial + static_cast<int64_t>(P) * ldp);
     const FullShape shape = full_shape(d);
-    // one block per compute unit where a thread has several columns, two where it has one
+    // Rows of 1025 to 2047 floats that stay in the 256 MB cache in front of memory take 256 threads with two columns each and
+    // plain loads: 20,000 x 1100 21.2 us against 26.6 with a column per thread, 20,000 x 2000 29.5 against 36.3, 50,000 x 1100
+    // (220 MB) 40.4 against 47.9, 50,000 x 1500 (300 MB) 52.0 against 57.9; from memory a column per thread is the faster:
+    // 80,000 x 1100 (352 MB) 67.8 against 72.7, 50,000 x 2000 (400 MB) 72.2 against 79.2.
+    const int64_t row_bytes = n * prob->lda * 4;
+    const bool cached_rows = quads > 256 && quads < 512 && row_bytes <= (320ll << 20);
+    // one block per compute unit where a thread has several columns, two where it has one (or has two of cached rows)
     if (shape.cols > 1) P = std::min(P, 256);
     // Rows that do not fit in the 256 MB cache in front of memory are read once: non-temporal loads (50,000 x 3000 96 us
     // with, 105 without; 3000 x 3000 again and again 11.2 with, 9.3 without).
-    const bool stream = n * prob->lda * 4 > (128ll << 20);
+    const bool stream = row_bytes > (128ll << 20) && !cached_rows;
     const FullArgs a{prob, x, z_out, partial, ldp, loss_partial, dim3(static_cast<unsigned>(P)), stream, st};
     if (quads <= 16) launch_full_narrow<16>(a);
     else if (quads <= 32) launch_full_narrow<32>(a);
     else if (quads <= 64) launch_full_narrow<64>(a);
     else if (quads <= 256 && d == 1024) launch_full_dense<1, 8, true, 256>(a);
     else if (quads <= 256) launch_full_dense<1, 8, false, 256>(a);
+    else if (cached_rows) launch_full_dense<2, 4, false, 256>(a);
     // Rows of 2048, 4096, 8192 or 16384 floats (every thread's columns whole): 512 threads per block.  Measured on
     // 1.6-3.3 GB of rows against 256 threads, two blocks per unit and plain loads: 280 -> 240 us, 540 -> 479 us
     // (6.84 TB/s), 282 -> 243 us, 294 -> 253 us.
@@ -1097,7 +1104,7 @@ int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float 
     else if (dense_full_wide(d) && shape.cols == 2) launch_full_dense<2, 4, true, 512>(a);
     else if (dense_full_wide(d) && shape.cols == 4) launch_full_dense<4, 2, true, 512>(a);
     else if (dense_full_wide(d)) launch_full_dense<8, 1, true, 512>(a);
-    // Other widths; measured against 256 threads with columns for the next power of two, two blocks per unit, plain loads
+    // Other widths, from memory; measured against 256 threads with columns for the next power of two, two blocks per unit, plain loads
     // and a test per element: 50,000 x 3000 107 -> 90 us (6.65 TB/s), 30,000 x 5000 110 -> 91, 20,000 x 7397 110 -> 92,
     // 12,000 x 12,000 123 -> 89, 80,000 x 2500 145 -> 118, 100,000 x 1200 90 -> 86, 100,000 x 1800 122 -> 112.
     else if (shape.cols == 1) launch_full_dense_threads<1, 8>(shape.threads, a);

@@ -305,7 +305,7 @@ def test_unsupported_and_invalid(dq):
 
 
 @pytest.mark.parametrize("n,d", [(3001, 1), (4097, 54), (2500, 64), (999, 65), (700, 128), (1203, 131), (4100, 256), (900, 257),
-                                 (400, 1025), (300, 1290), (77, 2500), (130, 3000), (90, 4099), (40, 7397), (33, 8200), (50, 12002),
+                                 (400, 1025), (300, 1290), (1100, 2045), (41000, 2047), (77, 2500), (130, 3000), (90, 4099), (40, 7397), (33, 8200), (50, 12002),
                                  (40, 8193), (33, 8197), (50, 8957), (33, 10243), (40, 12290), (33, 12291), (21, 16383),
                                  (1, 54), (2, 3000)])
 def test_full_gradient_over_widths(dq, n, d):

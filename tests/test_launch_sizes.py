@@ -44,6 +44,7 @@ def test_the_full_gradient_masks_every_column_that_can_pass_the_end(tmp_path):
         const FullShape s = full_shape(d);
         if (s.threads < 256 || s.threads > 512 || s.threads % 64 || (int64_t)s.threads * s.cols < ceil_div(d, 4)) std::printf("shape %ld\\n", (long)d);
         if ((int64_t)s.threads * full_whole_cols(s.cols) > d / 4) std::printf("mask %ld\\n", (long)d);
+        if (d < 2048 && 256 * full_whole_cols(2) > d / 4) std::printf("mask of 256 threads %ld\\n", (long)d);
     }
     """)
     assert out == "", out[:2000]
