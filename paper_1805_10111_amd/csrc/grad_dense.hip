@@ -420,11 +420,13 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         }
         my_row = static_cast<uint64_t>(i) < static_cast<uint64_t>(a.n) ? static_cast<int>(i) : -1;   // out of range: ignored
     }
-    // valid rows only (the usual case): the row loads then carry no condition, so a wait for one batch can leave the
+    constexpr int kFewRows = DB == 0 ? 0 : NC > 1 ? R : R / 2;
+    // valid rows only (the usual case), and more than would leave most of a batch, or of a pair of them, to repeated rows: the
+    // row loads then carry no condition, so a wait for one batch can leave the
     // loads of the next one in flight.  A position past the last row repeats that row and is not added (a block of
     // 15 rows whose loads sat behind tests took longer than four of four rows).  (Every wavefront holds the same row
     // numbers and takes the same decision.)
-    const bool plain = DB == 2 || (nrows > 0 && __all(lane >= nrows || my_row >= 0));
+    const bool plain = DB == 2 || (nrows > kFewRows && __all(lane >= nrows || my_row >= 0));
     const auto row_number = [&](int j) {                                                      // wave-uniform
         return __builtin_amdgcn_readlane(my_row, DB == 2 ? j : min(j, nrows - 1));
     };
@@ -502,7 +504,10 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
     zero_cols<NC>(acc);
 
     // ---- stream the rows, R at a time
-    if (DB == 2 || (DB == 1 && plain)) {
+    // (with one column per thread only for an even number of batches: the batch that fills up the last pair is worth its
+    // requests on wider rows alone.  Eight workers, 64 rows, 1500 columns: 12.3 us a round, with a pair for every batch 13.4;
+    // 17 rows, 5000 columns: 25 us, one by one 33.)
+    if (DB == 2 || (DB == 1 && plain && (NC > 1 || (nrows + R - 1) / R % 2 == 0))) {
         // two row buffers: while one batch is reduced the other one is in flight; no load sits behind a condition
         float4 row2[R][NC];
         load_rows(R, row2);
