@@ -420,13 +420,13 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         }
         my_row = static_cast<uint64_t>(i) < static_cast<uint64_t>(a.n) ? static_cast<int>(i) : -1;   // out of range: ignored
     }
-    constexpr int kFewRows = DB == 0 ? 0 : NC > 1 ? R : R / 2;
-    // valid rows only (the usual case), and more than would leave most of a batch, or of a pair of them, to repeated rows: the
-    // row loads then carry no condition, so a wait for one batch can leave the
-    // loads of the next one in flight.  A position past the last row repeats that row and is not added (a block of
-    // 15 rows whose loads sat behind tests took longer than four of four rows).  (Every wavefront holds the same row
-    // numbers and takes the same decision.)
-    const bool plain = DB == 2 || (nrows > kFewRows && __all(lane >= nrows || my_row >= 0));
+    // valid rows only (the usual case), and not so few that most of a batch, or of a pair of them, would be repeated rows (of a
+    // batch of sixteen: not a whole mini-batch of fifteen, not a block's share of ten): the row loads then carry no
+    // condition, so a wait for one batch can leave the loads of the next one in flight.  A position past the last row
+    // repeats that row and is not added (a block of 15 rows whose loads sat behind tests took longer than four of four
+    // rows).  (Every wavefront holds the same row numbers and takes the same decision.)
+    const int few = DB == 0 ? (a.P == 1 ? 15 : 10) : NC > 1 ? R : R / 2;
+    const bool plain = DB == 2 || (nrows > few && __all(lane >= nrows || my_row >= 0));
     const auto row_number = [&](int j) {                                                      // wave-uniform
         return __builtin_amdgcn_readlane(my_row, DB == 2 ? j : min(j, nrows - 1));
     };
@@ -983,14 +983,19 @@ int64_t dense_vr_splits(int64_t M, int64_t B, int64_t d)
     // (two per compute unit) stream rows, each owning at least 4 of them.  Rows wider than 1024 floats
     // are streamed with two row buffers per block (see dense_worker): one block per compute unit
     // then, and a whole number of batch pairs per block.
-    // For rows of up to 1024 floats a block takes whole batches of 16 rows: all of a batch are in flight together, so a
-    // batch cut over several blocks takes as long and leaves more partial sums (M = 10, B = 100, d = 784: both kernels 13.0 us with
-    // four rows per block, 12.6 with 15).
+    // For rows of up to 1024 floats a block takes whole batches of 16 rows: all of a batch are in flight together, so a batch
+    // cut over several blocks takes as long and leaves more partial sums (M = 10, B = 100, d = 784: both kernels 13.0 us with
+    // four rows per block, 12.6 with 15).  Not where blocks of four rows have a compute unit each and there are few of
+    // them, which are done sooner (rounds of 48 rows at 1000 columns: M = 8 12.6 against 13.6 us, M = 16 13.1 against
+    // 14.3), and not where sixteen rows make more blocks than compute units and the target divides evenly (M = 32, B =
+    // 160: 512 blocks of ten rows 16.7 us a round, 320 of sixteen 17.4).
     const bool two_buffers = dense_nc(d) >= 2;
     const int64_t target = two_buffers ? 256 : 512;
     if (B <= 32) return 1;
     int64_t P = ceil_div(target, M);
-    const int64_t by_rows = ceil_div(B, two_buffers ? 4 : 16);
+    const bool by_four = two_buffers || (B <= 80 && M * ceil_div(B, 4) <= (B <= 64 ? 256 : 160)) ||
+                         (M * ceil_div(B, 16) > 256 && target % M == 0);
+    const int64_t by_rows = ceil_div(B, by_four ? 4 : 16);
     if (P > by_rows) P = by_rows;
     const int64_t need = ceil_div(B, kMaxRowsPerBlock);        // a block owns at most kMaxRowsPerBlock rows
     if (P < need) P = need;
