@@ -1104,10 +1104,12 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
         __syncthreads();
         const FullChunk ch{reinterpret_cast<const char *>(A.indices + e0), reinterpret_cast<const char *>(A.values + e0), cn,
                            sh_start, sh_len, sh_coef};
-        // A row on a whole wavefront, or four rows side by side where they average at most kShortRow entries (measured at
-        // 20 entries: 18.2 us with whole wavefronts, 14.2 with quarters; at 52: 29.0 and 29.4).
-        constexpr uint64_t kShortRow = 32;
-        const bool short_rows = e1 - e0 <= kShortRow * static_cast<uint64_t>(cn);
+        // A row on a whole wavefront, or four rows side by side.  Whole wavefronts have 96 rows under way at a time, quarters
+        // 320, which is worth the more the more rows there are and the shorter they are (5000 columns): 80,000 rows of 28
+        // entries, 312 a block, 21.0 us on quarters and 25.6 on whole wavefronts; 30,000 of 20, 117 a block, 17.1 and
+        // 19.0, of 28 entries 19.0 and 19.3; up to 96 rows a block takes either in one go, whole wavefronts at once: 8000 of
+        // 24 entries 15.8 and 13.7.
+        const bool short_rows = cn > 96 && e1 - e0 <= static_cast<uint64_t>(cn > 192 ? 32 : 24) * static_cast<uint64_t>(cn);
         uint32_t vmax = 0;
         float csum = 0.0f;
         float *z_chunk = z_out ? z_out + ib : nullptr;

@@ -458,20 +458,23 @@ def test_worker_step_with_and_without_workspace(dq, problems, sparsify, b, want_
         assert np.array_equal(host(outs[0][2]), np.count_nonzero(codes, axis=1))
 
 
-@pytest.mark.parametrize("kind", ["short", "long", "one_long_row", "empty_rows", "one_row", "wide"])
+@pytest.mark.parametrize("kind", ["short", "long", "one_long_row", "empty_rows", "one_row", "wide", "short_and_long", "between"])
 def test_full_gradient_over_row_lengths(dq, kind):
     """Rows on a quarter of a wavefront and on a whole one, rows that whole wavefronts finish, rows and blocks without
-    entries, more columns than one LDS window, several chunks of rows per block: against the oracle."""
+    entries, more columns than one LDS window, several chunks of rows per block, blocks of either kind side by side and long
+    rows among short ones: against the oracle."""
     rng = np.random.default_rng(7)
     n, d, lens = {"short": (300000, 900, lambda n: rng.integers(0, 20, n)), "long": (900, 6000, lambda n: rng.integers(200, 320, n)),
                   "one_long_row": (700, 30000, lambda n: np.where(np.arange(n) == 33, 20000, 6)),
+                  "short_and_long": (60000, 30000, lambda n: np.where(np.arange(n) % 5000 == 17, 700, rng.integers(0, 20, n))),
+                  "between": (30000, 5000, lambda n: rng.integers(14, 36, n)),
                   "empty_rows": (1000, 500, lambda n: np.where(np.arange(n) % 5 == 0, 40, 0)),
                   "one_row": (1, 77, lambda n: np.full(n, 77)), "wide": (400, 80001, lambda n: rng.integers(0, 60, n))}[kind]
     lens = lens(n)
     indptr = np.zeros(n + 1, dtype=np.int64)
     np.cumsum(lens, out=indptr[1:])
-    if kind == "short":                                      # (distinct columns of a row: a stride through the matrix)
-        first = np.repeat(rng.integers(0, d - 800, n), lens)
+    if kind in ("short", "short_and_long", "between"):       # (distinct columns of a row: a stride through the matrix)
+        first = np.repeat(rng.integers(0, d - 37 * lens.max() if kind != "short" else d - 800, n), lens)
         within = np.arange(indptr[-1]) - np.repeat(indptr[:-1], lens)
         indices = (first + 37 * within).astype(np.int32)
     else:
