@@ -1246,19 +1246,35 @@ struct CsrSlices {
 
 static CsrSlices csr_slices(int64_t d, int64_t M, const CsrPlan &plan, bool second)
 {
-    int64_t S = std::min<int64_t>(kMaxSlices, 256 / M - 1);
-    if (d < 4096 || (S < 3 && plan.nwin == 1)) return CsrSlices{0, 0};
+    constexpr int64_t kUnits = 256;
+    int64_t S = std::min<int64_t>(kMaxSlices, kUnits / M - 1);
+    if (plan.nwin == 1) {
+        // At least three slices (or the passes over the vector are not shared out enough), 4096 columns (rounds of 32 rows,
+        // eight workers: 4096 columns 12.9 us split or not, 8192 13.2 against 15.0).  Above 8192 columns, where the unsplit step
+        // has a master spread over the chip too, that master takes up to 32 messages at once and the one over parts sixteen
+        // gradients after another, 1.9 us for every further sixteen: 14,000 columns, M = 32 10.4 + 3.6 us unsplit, 7.9 +
+        // 5.8 split (a round 2-4 % longer, and from 49 workers on 2-9 %; M = 24 3 % shorter, M = 40 and 48 even to 3 %).
+        // Unless so much of LDS is the vector's that fewer than 2048 entries can be staged beside it: 34,000 columns, M = 32 23.2
+        // against 21.5 us, M = 64 29.4 against 26.5.
+        if (d < 4096 || S < 3) return CsrSlices{0, 0};
+        if (d > 2 * 4096 && plan.cap >= 2048 && (M % 32 == 0 || M > 48)) return CsrSlices{0, 0};
+    }
     S = std::max<int64_t>(S, 2);
     const int64_t budget = kLdsBudget - kCsrFixedLds, each = second ? 16 : 12;
     for (; S <= kMaxSlices; ++S) {
         const int64_t win = ceil_div(ceil_div(d, S), 256) * 256;
-        if (win * 4 + plan.cap * each <= budget) return CsrSlices{static_cast<int>(ceil_div(d, win)), static_cast<int>(win)};
+        if (win * 4 + plan.cap * each > budget) continue;
+        // (several windows: a block of the unsplit step takes them one after the other, as the compute units would these
+        // slices if there were that many of them: 36,000 columns, M = 128 41 us a round either way, M = 256 49 against 59)
+        const int64_t count = ceil_div(d, win);
+        if (plan.nwin > 1 && ceil_div(M * count, kUnits) >= plan.nwin) break;
+        return CsrSlices{static_cast<int>(count), static_cast<int>(win)};
     }
     return CsrSlices{0, 0};
 }
 
 // Whether (and how) a step is split over the columns.  Vectors of several LDS windows always are, if their outputs allow
-// it (8 workers, 32 rows, 47,236 columns: one block per worker and two windows 48.4 us; split, with the sparsifier and the
+// it and the slices do not outnumber the compute units as often as there are windows (8 workers, 32 rows, 47,236 columns: one block per worker and two windows 48.4 us; split, with the sparsifier and the
 // quantization as launches of their own, 8.9 + 4.4 + 4.0 us).  Of the others those that can leave their quantization to
 // the master (see `deferred`): at 20,958 columns worker step and master 10.4 + 3.1 us -> 7.9 + 3.9 us.  Not those with a
 // sparsifier, which would need a launch for it between the two: 12.0 us as one launch, 8.8 + 3.9 as two.

@@ -471,7 +471,7 @@ def test_rounds_replayed_from_a_captured_graph(dq, name):
 
 
 @pytest.mark.parametrize("algo,b,M,each,b_x", [("asylpg", 8, 8, False, 8), ("asylpg", 2, 17, True, 6), ("acc", 8, 8, False, 8),
-                                               ("acc", 4, 33, True, 4), ("sparse", 4, 5, False, 8), ("sparse", 8, 40, True, 8)])
+                                               ("asylpg", 8, 64, False, 8), ("acc", 4, 33, True, 4), ("sparse", 4, 5, False, 8), ("sparse", 8, 40, True, 8)])
 @pytest.mark.parametrize("d,B,cache", [(4099, 24, True), (20958, 32, True), (36001, 24, True), (47236, 260, True),
                                        (20958, 32, False), (34400, 8, False), (34400, 32, False), (47236, 155, False)])
 def test_worker_steps_split_over_the_columns_equal_the_separate_calls(dq, algo, b, M, each, b_x, d, B, cache):
