@@ -143,9 +143,15 @@ __device__ __forceinline__ void block_sum_R(float (&v)[R], float *sh, int &buf)
     constexpr int kWaves = T / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     float *mine = sh + buf * (kWaves * R);
-    if constexpr (R == 16) {
-        const float s = wave_sums16(v);
-        if (lane < R) mine[wave * R + lane] = s;
+    if constexpr (R % 16 == 0) {
+#pragma unroll
+        for (int h = 0; h < R; h += 16) {
+            float part[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[r] = v[h + r];
+            const float s = wave_sums16(part);
+            if (lane < 16) mine[wave * R + h + lane] = s;
+        }
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -407,8 +413,8 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
     const int r0 = part * per;
     const int nrows = max(0, min(a.B, r0 + per) - r0);        // at most kMaxRowsPerBlock = 64 (the host sees to it)
     int my_row = -1;
-    if (lane < nrows) {
-        const int r = r0 + lane;
+    if (nrows > 0) {                                           // (a lane past the block's rows holds the last one)
+        const int r = r0 + min(lane, nrows - 1);
         int64_t i;
         if (DB != 2 && a.idx) {
             i = a.idx[static_cast<int64_t>(m) * a.B + r];
@@ -421,14 +427,14 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         my_row = static_cast<uint64_t>(i) < static_cast<uint64_t>(a.n) ? static_cast<int>(i) : -1;   // out of range: ignored
     }
     // valid rows only (the usual case), and not so few that most of a batch, or of a pair of them, would be repeated rows (of a
-    // batch of sixteen: not a whole mini-batch of fifteen, not a block's share of ten): the row loads then carry no
-    // condition, so a wait for one batch can leave the loads of the next one in flight.  A position past the last row
+    // batch of sixteen: not a whole mini-batch of fifteen, not a block's share of ten, unless two products are formed with
+    // them, as without cached margins, where 15 rows are 8 % the sooner done this way): the row loads then carry no condition, so a wait for one batch can leave the loads of the next one in flight.  A position past the last row
     // repeats that row and is not added (a block of 15 rows whose loads sat behind tests took longer than four of four
     // rows).  (Every wavefront holds the same row numbers and takes the same decision.)
-    const int few = DB == 0 ? (a.P == 1 ? 15 : 10) : NC > 1 ? R : R / 2;
+    const int few = DB == 0 ? (!HAVE_Z ? 0 : a.P == 1 ? 15 : 10) : NC > 1 ? R : R / 2;
     const bool plain = DB == 2 || (nrows > few && __all(lane >= nrows || my_row >= 0));
     const auto row_number = [&](int j) {                                                      // wave-uniform
-        return __builtin_amdgcn_readlane(my_row, DB == 2 ? j : min(j, nrows - 1));
+        return __builtin_amdgcn_readlane(my_row, DB == 1 ? min(j, nrows - 1) : j);
     };
 
     float4 dx[NC], xs[HAVE_Z ? 1 : NC], acc[NC];
@@ -976,7 +982,8 @@ int launch_full_finish(const float *partial, int P, int64_t ldp, int64_t n, int6
 // float4 columns per thread that cover a row: rows of up to 16384 floats are supported
 static int dense_nc(int64_t d) { return d <= 1024 ? 1 : d <= 2048 ? 2 : d <= 4096 ? 4 : d <= 8192 ? 8 : d <= 16384 ? 16 : 0; }
 
-int64_t dense_vr_splits(int64_t M, int64_t B, int64_t d)
+// (have_z: margins cached; without them never more blocks than with them)
+int64_t dense_vr_splits(int64_t M, int64_t B, int64_t d, bool have_z = true)
 {
     // blocks per worker.  A mini-batch of at most 32 rows stays in one block, which then runs the
     // whole worker step in a single launch; larger ones are split so that about 512 blocks
@@ -987,13 +994,13 @@ int64_t dense_vr_splits(int64_t M, int64_t B, int64_t d)
     // cut over several blocks takes as long and leaves more partial sums (M = 10, B = 100, d = 784: both kernels 13.0 us with
     // four rows per block, 12.6 with 15).  Not where blocks of four rows have a compute unit each and there are few of
     // them, which are done sooner (rounds of 48 rows at 1000 columns: M = 8 12.6 against 13.6 us, M = 16 13.1 against
-    // 14.3), and not where sixteen rows make more blocks than compute units and the target divides evenly (M = 32, B =
+    // 14.3; without cached margins 60 rows, M = 16 12.2 against 10.7), and not where sixteen rows make more blocks than compute units and the target divides evenly (M = 32, B =
     // 160: 512 blocks of ten rows 16.7 us a round, 320 of sixteen 17.4).
     const bool two_buffers = dense_nc(d) >= 2;
     const int64_t target = two_buffers ? 256 : 512;
     if (B <= 32) return 1;
     int64_t P = ceil_div(target, M);
-    const bool by_four = two_buffers || (B <= 80 && M * ceil_div(B, 4) <= (B <= 64 ? 256 : 160)) ||
+    const bool by_four = two_buffers || (have_z && B <= 80 && M * ceil_div(B, 4) <= (B <= 64 ? 256 : 160)) ||
                          (M * ceil_div(B, 16) > 256 && target % M == 0);
     const int64_t by_rows = ceil_div(B, by_four ? 4 : 16);
     if (P > by_rows) P = by_rows;
@@ -1199,7 +1206,7 @@ int dense_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     if (a.ws_bytes < dense_workspace_bytes(DQ_OP_VR_GRAD, prob, a.M, a.B) || !a.ws) return DQ_ERR_WORKSPACE;
     VrDenseArgs k{};
     k.X = prob->dense; k.lda = prob->lda; k.n = prob->n; k.d = d; k.y = prob->y;
-    k.idx = a.idx; k.B = static_cast<int>(a.B); k.P = static_cast<int>(dense_vr_splits(a.M, a.B, d));
+    k.idx = a.idx; k.B = static_cast<int>(a.B); k.P = static_cast<int>(dense_vr_splits(a.M, a.B, d, a.z_snap != nullptr));
     k.xq = a.xq; k.b_x = a.b_x; k.x_snap = a.x_snap; k.z_snap = a.z_snap; k.l2 = prob->l2;
     k.delta_x = a.b_x == 32 ? a.x_snap : a.delta_x;      // float32 model: no scale; the kernels read a valid dummy
     k.model_last_word = (a.b_x == 32 ? d : packed_words(d, a.b_x)) - 1;
