@@ -144,7 +144,7 @@ int32_t dq_unpack(const uint32_t *packed, int64_t ld_words, int64_t d, int64_t M
  * words: 32 + nnz*(ceil(log2 d) + b) bits in all.  dq_sparse_stream_words(d, b) is the row
  * capacity (every coordinate nonzero).  dq_sparse_encode turns M rows of dense packed codes
  * into M streams (stride ld_stream >= capacity, words past the used ones zero) and writes
- * nnz_out[M]; dq_sparse_decode is the inverse (packed_out rows fully rewritten).  b in {2,4,8};
+ * nnz_out[M]; dq_sparse_decode is the inverse (packed_out rows fully rewritten).  Either may work in place (equal strides).  b in {2,4,8};
  * streams of more than 36864 words (144 KB) are DQ_ERR_UNSUPPORTED. */
 int64_t dq_sparse_stream_words(int64_t d, int32_t b);
 int32_t dq_sparse_encode(const uint32_t *packed, int64_t ld_words, int64_t d, int64_t M, int32_t b,
@@ -220,8 +220,9 @@ int32_t dq_sparsify(const float *alpha, int64_t d, int64_t M, int64_t ld, const 
  * sparsify != 0: Alg. 2, worker (i)-(iii)):  dq_vr_grad -> [dq_sparsify] ->
  * dq_quantize_pack with tag DQ_TAG_GRAD, bit-identical to those calls, without
  * writing alpha to memory (dense features with B > 32: partial sums of alpha pass through
- * `ws`; CSR with a model too wide for the on-chip buffer: alpha is assembled in `ws`; CSR with
- * sparsify != 0 and few workers: the sparsified gradient passes through `ws` between two launches).
+ * `ws`; CSR with a model too wide for the on-chip buffer: alpha passes through `ws`, in one launch
+ * or between two or three; CSR with sparsify != 0 and few workers: the sparsified gradient passes
+ * through `ws` between two launches).
  * ws, ws_bytes: at least dq_workspace_bytes(DQ_OP_WORKER_STEP, prob, M, B) bytes (a DQ_OP_VR_GRAD workspace is never
  * smaller).  CSR features whose model fits the on-chip buffer also run without (NULL, 0), in a single launch.  packed_out: M rows of ld_words words; delta_out[M];
  * nnz_out (nullable) [M] = nonzero codes.  alpha_out (nullable): also store alpha.
@@ -384,8 +385,8 @@ typedef struct dq_run_state {
  * (null or misaligned state pointers, a workspace smaller than dq_workspace_bytes(DQ_OP_VR_GRAD, prob, M, B),
  * which covers every worker group of a delayed run).  worker_events (host array, nullable): 2*rounds hipEvent_t handles created by the caller; for
  * round k the pair [2k], [2k+1] receives the start and the end time of the kernel of the worker step
- * that streams the feature rows (its first kernel; for CSR its only one; with tau > 0 the one of the
- * first worker group): they are the start and stop events of that launch (hipExtLaunchKernel), so
+ * that reads the feature rows (its first kernel; for CSR sparsifier and quantization may be launches of their own
+ * after it; with tau > 0 the one of the first worker group): they are the start and stop events of that launch (hipExtLaunchKernel), so
  * hipEventElapsedTime over the pair is the kernel's own duration.  A flag-bit round leaves its pair
  * untouched; a pair of null handles makes that round's launch a plain one.  Pass null while `stream` is being
  * captured into a graph. */

@@ -876,7 +876,7 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
 // and the same lanes add the rows' entries (from L2 now) to the columns.  72,000 rows of 52 entries, 20,958
 // columns: 50.4 us with rows staged in LDS in groups of a hundred, five barrier-separated phases each; now 29.0 us;
 // 80,000 rows of 100 entries, 60,000 columns 236 -> 71 us; 40,000 rows of 20, 2000 columns 14.7 -> 13.4 us.
-constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; about 17 KB of static arrays beside them
+constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; 12.5 KB of static arrays beside them
 constexpr int kTogether = 256;                            // positions of a row up to here are its own lanes' work
 
 // The rows of a chunk in LDS, and where their entries lie: a scalar base and 32-bit byte offsets (1024 rows of fewer than

@@ -32,8 +32,8 @@ constexpr int kRowThreads = 256;
 constexpr int kMaxRowsPerBlock = 64;             // mini-batch rows a block may own: lane j of a wavefront keeps row j
 
 // Thread's share of a row: float4 columns tid + T*c, c < NC (T threads per block); zero past d.
-// STREAM: the row is read once and not again soon (the gathered rows of a mini-batch), so the load is
-// marked non-temporal; the contiguous sweep of the full gradient is faster without the mark (measured).
+// STREAM: the row is read once and not again soon (the gathered rows of a mini-batch; the sweep of the full gradient where
+// its rows do not stay in the cache, see dense_full_grad), so the load is marked non-temporal.
 // FULL: d equals 4 * T * NC, every column of every thread is a whole float4 inside the row and the loads
 // carry no condition at all.
 // The thread's columns of a vector of exactly d floats (zeros past its end).

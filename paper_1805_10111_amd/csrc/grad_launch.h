@@ -44,8 +44,8 @@ struct WorkerArgs {
     // stream (seed, iter, DQ_MASTER_ID, DQ_TAG_MODEL) -- every block for its own use, one block also storing the
     // message to `xq` and its scale to `delta_x`, which are then outputs of the call.  Needs dense_model_fusable().
     const float *x_model, *absmax_model;
-    // CSR features, step split over the columns or sparsifier split over several blocks per worker: when `deferred` is given and the step takes that route, it stops before the
-    // quantization -- `delta_out` and `nnz_out` stay untouched, `packed` holds nothing of use -- and describes what it left in
+    // CSR features, step split over the columns or sparsifier split over several blocks per worker: when `deferred` is given
+    // and the step takes that route, it stops before the quantization -- `delta_out` and `nnz_out` stay untouched, `packed` holds nothing of use -- and describes what it left in
     // *deferred for master_step_from_parts_impl, which quantizes while it aggregates.  deferred->parts == 0 on return:
     // the step was a complete one.
     GradientParts *deferred;

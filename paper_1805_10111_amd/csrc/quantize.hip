@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(
 
 // The same for few coordinates: the model message of Alg. 1, master (i), for vectors of up to a million coordinates or
 // so, and rows of gradients that are no more together.  Such a launch is all latency, so a thread takes one quad (one
-// Philox block; 1/16 of what a thread of the kernel above takes) and everything it reads -- the scale's input, the vector, the snapshot -- is requested before the Philox
+// Philox block; a quarter of what a thread of the kernel above takes) and everything it reads -- the scale's input, the vector, the snapshot -- is requested before the Philox
 // rounds, which depend on none of it, and waited for after them.
 // DIFF (one row): together with diff_out[i] = delta * code_i - x_snap[i], the model a worker decodes minus the snapshot,
 // which every worker of the next round would otherwise form again, per column it touches, from the message

@@ -19,6 +19,9 @@
 
 namespace dq {
 
+// The limits: a block has 1024 threads, and a thread the registers for one quad of sixteen rows (64 of 128) beside what it
+// works with.  A worker has 256 threads whatever the width, so that its sums across wavefronts are those of a block of
+// vr_dense_kernel, bit for bit: narrower rows do not make room for more workers.
 constexpr int kGroup = 256;                              // threads per worker, a quad of columns each
 constexpr int kSmallWorkers = 4, kSmallRows = 16, kSmallD = 4 * kGroup;
 
