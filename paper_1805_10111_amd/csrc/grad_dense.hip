@@ -29,6 +29,12 @@
 namespace dq {
 
 constexpr int kRowThreads = 256;
+// What a position of a batch past a block's rows loads where a thread holds one quad of columns: zeros.  (The block's last
+// row again, with coefficient 0, would turn an infinite feature of it into 0 * Inf.  Leaving such a position out of the sum
+// by a test costs 3 to 4 % of a round there: 100 rows of 784 floats, ten workers, 1.34 times the speed of rounds without
+// these batches against 1.38 with zeros.  With more quads per thread it is the other way round: 17 rows of 5000 floats
+// 1.19 with the test and 1.02 with zeros, 90 rows 1.00 and 0.93; those repeat the last row and do not add it.)
+static __device__ __align__(16) const float kNoRow[16384] = {};
 constexpr int kMaxRowsPerBlock = 64;             // mini-batch rows a block may own: lane j of a wavefront keeps row j
 
 // Thread's share of a row: float4 columns tid + T*c, c < NC (T threads per block); zero past d.
@@ -426,15 +432,15 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         }
         my_row = static_cast<uint64_t>(i) < static_cast<uint64_t>(a.n) ? static_cast<int>(i) : -1;   // out of range: ignored
     }
-    // valid rows only (the usual case), and not so few that most of a batch, or of a pair of them, would be repeated rows (of a
+    // valid rows only (the usual case), and not so few that most of a batch, or of a pair of them, would be empty (of a
     // batch of sixteen: not a whole mini-batch of fifteen, not a block's share of ten, unless two products are formed with
     // them, as without cached margins, where 15 rows are 8 % the sooner done this way): the row loads then carry no condition, so a wait for one batch can leave the loads of the next one in flight.  A position past the last row
-    // repeats that row and is not added (a block of 15 rows whose loads sat behind tests took longer than four of four
+    // loads kNoRow, or repeats that row and is not added (a block of 15 rows whose loads sat behind tests took longer than four of four
     // rows).  (Every wavefront holds the same row numbers and takes the same decision.)
     const int few = DB == 0 ? (!HAVE_Z ? 0 : a.P == 1 ? 15 : 10) : NC > 1 ? R : R / 2;
     const bool plain = DB == 2 || (nrows > few && __all(lane >= nrows || my_row >= 0));
     const auto row_number = [&](int j) {                                                      // wave-uniform
-        return __builtin_amdgcn_readlane(my_row, DB == 1 ? min(j, nrows - 1) : j);
+        return __builtin_amdgcn_readlane(my_row, DB == 1 ? min(j, kWave - 1) : j);
     };
 
     float4 dx[NC], xs[HAVE_Z ? 1 : NC], acc[NC];
@@ -451,8 +457,10 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
     };
     auto load_rows = [&](int rb, float4 (&row)[R][NC]) {          // `plain` blocks only
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            load_cols<NC, true, FULL, T>(a.X + static_cast<int64_t>(row_number(rb + r)) * a.lda, d, row[r]);
+        for (int r = 0; r < R; ++r) {
+            const float *from = a.X + static_cast<int64_t>(row_number(rb + r)) * a.lda;
+            load_cols<NC, true, FULL, T>(DB == 2 || NC > 1 || rb + r < nrows ? from : kNoRow, d, row[r]);
+        }
     };
     auto compute_batch = [&](int rb, float4 (&row)[R][NC]) {
         float dots[HAVE_Z ? R : 2 * R];
@@ -486,10 +494,10 @@ __global__ __launch_bounds__(T) void vr_dense_kernel(const VrDenseArgs a)
         }
         float coef_l = 0.0f;
         if (lane < R && (DB == 2 || il >= 0)) coef_l = vr_slope_diff(yl, zs, dz) * inv_B;
-        const auto add_row = [&](int r) {
+        const auto add_row = [&](int r) {              // (dead rows: coef = 0 and the row registers are 0)
             axpy_cols<NC>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(coef_l), r)), row[r], acc);
         };
-        if (DB == 2 || rb + R <= nrows) {
+        if (DB == 2 || NC == 1 || rb + R <= nrows) {
 #pragma unroll
             for (int r = 0; r < R; ++r) add_row(r);
         } else {                                       // positions past the block's rows hold a repeated row, which may hold Inf

@@ -25,6 +25,8 @@ namespace dq {
 constexpr int kGroup = 256;                              // threads per worker, a quad of columns each
 constexpr int kSmallWorkers = 4, kSmallRows = 16, kSmallD = 4 * kGroup;
 
+static __device__ __align__(16) const float kNoSmallRow[kSmallD] = {};      // (see kNoRow in grad_dense.hip)
+
 struct SmallArgs {
     const float *X; int64_t lda;
     const float *y, *z_snap;
@@ -74,8 +76,8 @@ __global__ __launch_bounds__(kGroup *kSmallWorkers) void small_rounds_kernel(con
             margins[w][lane] = a.z_snap[i];
         }
     };
-    // ... and requested by all of it (a position past the last row repeats that row, which is not added again; a lane past
-    // the last column its last quad, masked when it is used)
+    // ... and requested by all of it (a position past the last row loads zeros; a lane past the last column the row's last
+    // quad, masked when it is used)
     float4 row[R];
     const uint32_t lane_offset = 4u * static_cast<uint32_t>(min(col, last_col));
     const auto request = [&]() {
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(kGroup *kSmallWorkers) void small_rounds_kernel(con
 #pragma unroll
         for (int r = 0; r < R; ++r) {                    // (a scalar base per row and one 32-bit lane offset)
             const int64_t i = __builtin_amdgcn_readlane(mine, r);            // (lanes past the rows hold the last one)
-            const char *base = reinterpret_cast<const char *>(a.X + i * a.lda);
+            const char *base = reinterpret_cast<const char *>(r < nrows ? a.X + i * a.lda : kNoSmallRow);
             row[r] = *reinterpret_cast<const float4 *>(base + lane_offset);
         }
     };
@@ -155,20 +157,13 @@ __global__ __launch_bounds__(kGroup *kSmallWorkers) void small_rounds_kernel(con
             const int row_of = min(lr, nrows - 1);
             const float coef_l = lane < nrows ? vr_slope_diff(labels[w][row_of], margins[w][row_of], dz) * inv_B : 0.0f;
             float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            const auto add_row = [&](int r) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
                 const float coef = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(coef_l), r));
                 acc.x = fmaf(coef, row[r].x, acc.x);
                 acc.y = fmaf(coef, row[r].y, acc.y);
                 acc.z = fmaf(coef, row[r].z, acc.z);
                 acc.w = fmaf(coef, row[r].w, acc.w);
-            };
-            if (nrows == R) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) add_row(r);
-            } else {                                     // (a repeated row may hold Inf: it is left out, not added with 0)
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (r < nrows) add_row(r);
             }
             v = make_float4(acc.x + a.l2 * dx.x, acc.y + a.l2 * dx.y, acc.z + a.l2 * dx.z, acc.w + a.l2 * dx.w);
             const uint32_t m = wave_max_u32(max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w))));
