@@ -415,6 +415,7 @@ __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta
 // worker launch does all of that for the NEXT round, on compute units the launch leaves idle, and leaves it in
 // memory as csr_prep_stride 32-bit words per worker:
 //   [0] 1 when the flat run is there (the batch has at most csr_prep_cap entries), else 0   [1] number of entries
+//   [2] the largest |value| among them, as bits (with the flat run only)
 //   row[kCsrMaxRows] len[kCsrMaxRows] pre[kCsrMaxRows + 4] y[kCsrMaxRows] z[kCsrMaxRows]      (RowMeta's fields)
 //   pairs (column | row << kColBits, value bits), [1] of them
 // The next round's blocks then start from one round trip to memory instead of a chain of five.
@@ -462,7 +463,87 @@ __device__ __forceinline__ void csr_process_prepared(const int2 *entry, const in
     __syncthreads();
 }
 
+// The same for a batch of at most kCsrInFlight entries, which stay in the registers they were loaded into: `e` is all of
+// the flat run, `vmax` its largest |value|, and lane l of wavefront w holds row w + 16 l of the batch (its length, its
+// first entry's position, and whatever coef_of(zdiff) needs besides its margin).  What a block waits for here is latency,
+// one phase after another, so there are as few phases as the sums allow: products to LDS, barrier, margins and
+// coefficients, barrier, scatter.  The sums are those of csr_reduce_group, bit for bit.
+// Eight workers of 32 rows, 20,958 columns, from the block's start: products complete after 2.2 us, margins 2.8, scattered
+// 3.6, where the general form took 2.7 (with the maximum), 3.7 and 4.5.
+constexpr int kCsrInFlight = kStageFlight * kCsrThreads;
+
+template <int FLIGHT, typename CoefFn>
+__device__ __forceinline__ void csr_lane_margins(const float *prod, int total, int nrows, int my_len, int my_pre, CoefFn coef_of,
+                                                 float *coef)
+{
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    float margin = 0.0f;
+    for (int i = 0; wave + i * kCsrWaves < nrows; i += FLIGHT) {      // rows i .. i + FLIGHT - 1 of the wavefront
+        int len[FLIGHT], off[FLIGHT], maxlen = 0;
+        float sum[FLIGHT];
+#pragma unroll
+        for (int u = 0; u < FLIGHT; ++u) {                            // (lanes past the last row hold length 0)
+            len[u] = __builtin_amdgcn_readlane(my_len, i + u);
+            off[u] = __builtin_amdgcn_readlane(my_pre, i + u);
+            maxlen = max(maxlen, len[u]);
+            sum[u] = 0.0f;
+        }
+        for (int k = lane; k - lane < maxlen; k += kWave) {
+            float v[FLIGHT];
+#pragma unroll
+            for (int u = 0; u < FLIGHT; ++u) v[u] = prod[min(off[u] + k, total - 1)];
+#pragma unroll
+            for (int u = 0; u < FLIGHT; ++u) sum[u] += k < len[u] ? v[u] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < FLIGHT; ++u) {
+            const float t = wave_sum_f32(sum[u]);
+            margin = lane == i + u ? t : margin;
+        }
+    }
+    const int r = wave + lane * kCsrWaves;
+    if (r < nrows) coef[r] = coef_of(margin);
+}
+
+template <typename VecReq, typename VecVal, typename CoefFn>
+__device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlight], int total, float vmax, int nrows, int my_len,
+                                                      int my_pre, float *coef, int *acc, int c0, int c1, float *prod,
+                                                      FixedAcc &fx, int *poison, VecReq vec_req, VecVal vec_val, CoefFn coef_of)
+{
+    int col[kStageFlight];
+    decltype(vec_req(0)) raw[kStageFlight];
+#pragma unroll
+    for (int u = 0; u < kStageFlight; ++u) {
+        // (past the end `e` holds whatever the buffer held: column 0 is gathered instead)
+        col[u] = static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? e[u].x & kColMask : 0;
+        raw[u] = vec_req(col[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kStageFlight; ++u) {
+        const int p = threadIdx.x + u * kCsrThreads;
+        if (p < total) prod[p] = __int_as_float(e[u].y) * vec_val(raw[u], col[u]).x;
+    }
+    __syncthreads();
+    // (a wavefront has one or two rows of the common batches of up to 32)
+    if (nrows <= 2 * kCsrWaves) csr_lane_margins<2>(prod, total, nrows, my_len, my_pre, coef_of, coef);
+    else csr_lane_margins<kFlight>(prod, total, nrows, my_len, my_pre, coef_of, coef);
+    __syncthreads();                                     // (also behind the clearing of acc)
+    fixed_admit(fx, coef_abs_sum(coef, 0, nrows) * vmax, acc, c1 - c0, poison);
+    const float two_k = ldexpf(1.0f, fx.k);
+    float cf[kStageFlight];
+#pragma unroll
+    for (int u = 0; u < kStageFlight; ++u) cf[u] = coef[(e[u].x >> kColBits) & (kCsrMaxRows - 1)];
+#pragma unroll
+    for (int u = 0; u < kStageFlight; ++u)
+        if (static_cast<int>(threadIdx.x) + u * kCsrThreads < total && col[u] >= c0 && col[u] < c1)
+            atomicAdd(&acc[col[u] - c0], fixed_term(cf[u], __int_as_float(e[u].y), two_k));
+    __syncthreads();
+}
+
 // ------------------------------------------------------------------ worker step
+// how the model comes: as its message and the snapshot, as their difference, or as the model itself, not yet quantized
+enum { kModelMessage, kModelDiff, kModelPending };
+
 struct CsrWorkerArgs {
     CsrView A;
     const int32_t *idx;
@@ -499,11 +580,14 @@ struct CsrWorkerArgs {
     uint32_t next_iter;
 };
 
-// DIFF: the model comes as a.model_diff (one float per column) instead of the message and the snapshot.  (A third form was
-// built and measured on the sliced step: the kernel quantizing the model itself, per gathered entry and per column of its
-// slice, which saves the launch of the model message.  Three gathers per entry -- model, snapshot, random word -- for one
-// take as long as that launch at 20,958 columns and longer at 47,236, with or without the Philox rounds done by the
-// master before: 14.1 / 35.4 us a round against 14.3 / 33.2.)
+// MODEL == kModelDiff: the model comes as a.model_diff (one float per column) instead of the message and the snapshot.
+// MODEL == kModelPending: it comes as x itself, and every block quantizes what it needs of it: the columns of its entries,
+// and its slice's for the dense part (the blocks of worker 0 store those as the message).  That saves the launch of the
+// message, 2.9 us, and costs two gathers per entry for one and a Philox block for each entry and quad: 20,958 columns, eight
+// workers of 32 rows 13.1 -> 11.7 us a round.  At 47,236 columns (two quads of a slice per thread, 75 entries a row) it
+// costs more than the launch, 29.0 -> 30.6 us: see csr_model_fusable.  (Measured and dropped: x and its random word as
+// a pair per column, left by the master, so that an entry takes one 8-byte gather more and no Philox block: 13.0 us; the
+// snapshot values beside the prepared entries: 12.3 us.)
 // COMMON: the gradient fits in LDS as one window (SLICED: always), the mini-batch in one pass of rows (B <= kCsrMaxRows),
 // and the margins at the snapshot are cached (z_snap given) -- the kernel is then straight-line code with one set of the
 // row-processing routines, which leaves the compiler far fewer values to keep alive across its phases.
@@ -513,9 +597,10 @@ struct CsrWorkerArgs {
 // quantization), and no limit on the width from LDS.  What needs the whole gradient -- scale, sparsifier,
 // quantization -- is a later launch's, which finds the gradient in memory and its slices' maxima beside it.
 // Measured: see csr_worker.
-template <bool DIFF, bool COMMON, bool SLICED>
+template <int MODEL, bool COMMON, bool SLICED>
 __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorkerArgs a)
 {
+    constexpr bool DIFF = MODEL == kModelDiff, PENDING = MODEL == kModelPending;
     touch_kernel_arguments<sizeof(CsrWorkerArgs)>();
     extern __shared__ __align__(16) float lds[];
     __shared__ RowMeta meta;
@@ -524,18 +609,26 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     __shared__ int si[kCsrWaves];
     __shared__ double sd[kCsrWaves];
     __shared__ int sh_poison;
+    __shared__ uint32_t sh_max;
     const int64_t d = a.A.d;
     const int win = a.win;                                     // columns per window, a multiple of 4
     float *alpha = lds;                                        // the window of the gradient being built: fixed-point sums
     int *acc = reinterpret_cast<int *>(lds);                   // while the rows are added, float32 afterwards
-    if (threadIdx.x == 0) sh_poison = 0;                       // (published by the barriers of the first row pass)
+    if (threadIdx.x == 0) {                                    // (published by the barriers of the first row pass)
+        sh_poison = 0;
+        sh_max = 0u;
+    }
     const CsrStage sg = csr_stage_in(lds + win, a.cap, !COMMON && a.z_snap == nullptr);
 
     const int m = blockIdx.x;
-    const ModelMsg msg{a.xq, a.b_x == 32 ? 1.0f : a.delta_x[0], a.b_x};
+    const ModelMsg msg{a.xq, PENDING || a.b_x == 32 ? 1.0f : a.delta_x[0], a.b_x};
+    // (PENDING: the fields of dq_vr_grad's outputs and of the difference carry the model and its largest magnitude)
+    const Scale model_scale = PENDING ? make_scale(a.absmax_out[0], a.b_x) : Scale{};
+    StreamKey model_key = a.key;
+    model_key.worker = DQ_MASTER_ID;
+    model_key.tag = DQ_TAG_MODEL;
     // identical copies of the worker that share the tail, or slices (a last one more prepares the next round instead)
     const int slice = blockIdx.y, nslices = static_cast<int>(gridDim.y) - (a.prep_out ? 1 : 0);
-    if (a.zero_word && blockIdx.x == 0 && slice == 0 && threadIdx.x == 0) *a.zero_word = 0u;
     float *alpha_row = (!SLICED && !COMMON && a.alpha_ws) ? a.alpha_ws + static_cast<int64_t>(m) * a.ld_ws : nullptr;   // only with several windows
 
     const float inv_B = 1.0f / static_cast<float>(a.B);      // the mean over the mini-batch, as one multiplication per row
@@ -546,8 +639,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     struct Gather { uint32_t w0, w1; float xs, diff; };
     const bool straddles = (32 % a.b_x) != 0;                 // (the same for every thread) else a field lies in one word
     auto vec_req = [&](int c) {
-        if constexpr (DIFF) {
-            return Gather{0u, 0u, a.x_snap[c], a.model_diff[c]};     // (the snapshot value is only used without cached margins)
+        if constexpr (DIFF || PENDING) {
+            return Gather{0u, 0u, a.x_snap[c], a.model_diff[c]};     // (DIFF: the snapshot value is only used without cached margins)
         } else {
             const int w = (c * a.b_x) >> 5, last = static_cast<int>(a.model_last_word);   // (fewer than 2^20 words)
             return Gather{a.xq[w], straddles ? a.xq[w + 1 < last ? w + 1 : last] : 0u, a.x_snap[c], 0.0f};
@@ -555,6 +648,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     };
     auto vec_val = [&](const Gather &g, int c) {
         if constexpr (DIFF) return make_float2(g.diff, g.xs);
+        if constexpr (PENDING) {                               // (the random bits need no more than the column)
+            const uint32_t word = stream_word(model_key, static_cast<uint64_t>(c));
+            const int k = model_scale.inv_delta != 0.0f ? quantize_one(g.diff, model_scale, word) : 0;
+            return make_float2(model_scale.delta * static_cast<float>(k) - g.xs, g.xs);
+        }
         const uint32_t bits = __funnelshift_r(g.w0, g.w1, static_cast<unsigned>(c * a.b_x) & 31u);
         const float q = a.b_x == 32 ? __uint_as_float(bits)
                                     : msg.delta_x * static_cast<float>(sext_field(bits, 0, static_cast<unsigned>(a.b_x)));
@@ -621,6 +719,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         if (!fits) return;
         int2 *entry = reinterpret_cast<int2 *>(out + kPrepEntries);
         const int lane = threadIdx.x & (kWave - 1);
+        uint32_t vmax = 0;
         for (int p0 = threadIdx.x; p0 - lane < total; p0 += kStageFlight * kCsrThreads) {
             int64_t src[kStageFlight];
             int tag[kStageFlight], col[kStageFlight];
@@ -636,31 +735,129 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
 #pragma unroll
             for (int u = 0; u < kStageFlight; ++u)
                 if (p0 + u * kCsrThreads < total) entry[p0 + u * kCsrThreads] = make_int2(col[u] | tag[u], __float_as_int(val[u]));
+            // (a position past the end repeats an entry of the batch)
+#pragma unroll
+            for (int u = 0; u < kStageFlight; ++u) vmax = max(vmax, abs_bits(val[u]));
         }
+        vmax = block_max_u32(vmax, su);
+        if (threadIdx.x == 0) out[2] = static_cast<int>(vmax);
         return;
+    }
+    // PENDING: quad q of the model becomes its difference to the snapshot; the blocks of worker 0 also store the message,
+    // each its own slice of it (all lanes of a wavefront make the call; x, xs: the quad's values, r its random words)
+    const auto quantize_model_quad = [&](int64_t q, float4 x, float4 xs, const uint4 &r) {
+        const int64_t quads = (d + 3) / 4;
+        if (4 * q + 3 >= d && q < quads) {                     // the vector ends inside the quad
+            const int64_t i = 4 * q;
+            x.x = a.model_diff[i];
+            x.y = i + 1 < d ? a.model_diff[i + 1] : 0.0f;
+            x.z = i + 2 < d ? a.model_diff[i + 2] : 0.0f;
+            x.w = 0.0f;
+            xs.x = a.x_snap[i];
+            xs.y = i + 1 < d ? a.x_snap[i + 1] : 0.0f;
+            xs.z = i + 2 < d ? a.x_snap[i + 2] : 0.0f;
+            xs.w = 0.0f;
+        }
+        int k0 = 0, k1 = 0, k2 = 0, k3 = 0;
+        if (model_scale.inv_delta != 0.0f) {                   // (a degenerate scale: every code is zero)
+            k0 = quantize_one(x.x, model_scale, r.x);
+            k1 = quantize_one(x.y, model_scale, r.y);
+            k2 = quantize_one(x.z, model_scale, r.z);
+            k3 = quantize_one(x.w, model_scale, r.w);
+        }
+        if (m == 0) {                                          // (the same for the whole block)
+            uint32_t *message = const_cast<uint32_t *>(a.xq);
+            const int64_t at = q < quads ? q : quads;
+            if (a.b_x == 8) store_quad_bits<8>(pack4<8, true, false>(k0, k1, k2, k3), at, quads, message);
+            else if (a.b_x == 4) store_quad_bits<4>(q < quads ? pack4<4, true, false>(k0, k1, k2, k3) : 0u, at, quads, message);
+            else store_quad_bits<2>(q < quads ? pack4<2, true, false>(k0, k1, k2, k3) : 0u, at, quads, message);
+        }
+        const float delta = model_scale.delta;
+        return make_float4(delta * static_cast<float>(k0) - xs.x, delta * static_cast<float>(k1) - xs.y,
+                           delta * static_cast<float>(k2) - xs.z, delta * static_cast<float>(k3) - xs.w);
+    };
+    if (a.zero_word && m == 0 && slice == 0 && threadIdx.x == 0) *a.zero_word = 0u;
+    if (PENDING && m == 0 && slice == 0 && threadIdx.x == 0) {
+        const_cast<float *>(a.delta_x)[0] = model_scale.delta;
+        if (model_scale.bad && a.status) atomicOr(a.status, 1u);
     }
     for (int64_t c0 = SLICED ? static_cast<int64_t>(slice) * win : 0; c0 < d; c0 += win) {
         const int64_t c1 = min(d, c0 + win);
         const int64_t c1p = min((d + 3) / 4 * 4, c0 + win);     // the window, up to a whole quad past the end of the vector
         FixedAcc fx{0.0f, 0};
         bool rows_done = false;
+        // SLICED: the differences that the finished columns need, requested ahead of the rows (after the scatter they would be
+        // one more trip to memory, 0.8 us; in a block that finishes all columns the registers they take cost as much)
+        constexpr int kAhead = PENDING ? 1 : 2;
+        float4 ahead[kAhead];
+        bool have_ahead = false;
         if (a.prep_in) {
             // ---- this round's mini-batch was prepared: descriptors and the first entries are requested together
             // (a.B <= kCsrMaxRows, one window or slice)
             const int32_t *in = a.prep_in + static_cast<int64_t>(m) * a.prep_stride;
             const int2 *entry = reinterpret_cast<const int2 *>(in + kPrepEntries);
             const int nrows = a.B;
-            const int tr = min(static_cast<int>(threadIdx.x), kCsrMaxRows - 1);
             const int ready = in[0], total = in[1];
-            const int p_row = in[kPrepRow + tr], p_len = in[kPrepLen + tr], p_pre = in[kPrepPre + tr];
-            const int p_last = in[kPrepPre + nrows];
-            const float p_y = __int_as_float(in[kPrepY + tr]), p_z = __int_as_float(in[kPrepZ + tr]);
             int2 first[kStageFlight];
+            const auto request_first = [&] {
 #pragma unroll
-            for (int u = 0; u < kStageFlight; ++u) first[u] = entry[min(static_cast<int>(threadIdx.x) + u * kCsrThreads, a.prep_cap - 1)];
-            for (int64_t j = 4ll * threadIdx.x; j < c1p - c0; j += 4ll * kCsrThreads)
-                *reinterpret_cast<int4 *>(acc + j) = make_int4(0, 0, 0, 0);
-            if (ready) {                                          // (the same for every thread)
+                for (int u = 0; u < kStageFlight; ++u)
+                    first[u] = entry[min(static_cast<int>(threadIdx.x) + u * kCsrThreads, a.prep_cap - 1)];
+            };
+            const auto clear_window = [&] {
+                for (int64_t j = 4ll * threadIdx.x; j < c1p - c0; j += 4ll * kCsrThreads)
+                    *reinterpret_cast<int4 *>(acc + j) = make_int4(0, 0, 0, 0);
+            };
+            if constexpr (COMMON) {
+                const float vmax = __int_as_float(in[2]);
+                const int lr = static_cast<int>(threadIdx.x) / kWave + (static_cast<int>(threadIdx.x) & (kWave - 1)) * kCsrWaves;
+                const int tr = min(lr, nrows - 1);
+                const int p_row = in[kPrepRow + tr], p_len = in[kPrepLen + tr], p_pre = in[kPrepPre + tr];
+                const float p_y = __int_as_float(in[kPrepY + tr]), p_z = __int_as_float(in[kPrepZ + tr]);
+                request_first();
+                // (threads past the window read its last whole quad, all of them the same 16 bytes)
+                const int first_col = static_cast<int>(c0) + 4 * static_cast<int>(threadIdx.x);
+                const int last_quad = max(0, static_cast<int>(min<int64_t>(c1p, d / 4 * 4)) - 4);
+                if constexpr (PENDING) {
+                    float4 xv[kAhead], sv[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int at = min(first_col + 4 * kCsrThreads * u, last_quad);
+                        xv[u] = *reinterpret_cast<const float4 *>(a.model_diff + at);
+                        sv[u] = *reinterpret_cast<const float4 *>(a.x_snap + at);
+                    }
+                    clear_window();
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int64_t j = c0 + 4ll * threadIdx.x + 4ll * kCsrThreads * u;
+                        if (j - 4 * (static_cast<int>(threadIdx.x) & (kWave - 1)) >= c1p) continue;      // (a whole wavefront)
+                        const uint4 r = stream_block(model_key, static_cast<uint32_t>(j >> 2));
+                        ahead[u] = quantize_model_quad(j >> 2, xv[u], sv[u], r);
+                    }
+                    have_ahead = true;
+                }
+                if constexpr (DIFF && SLICED) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u)
+                        ahead[u] = *reinterpret_cast<const float4 *>(a.model_diff + min(first_col + 4 * kCsrThreads * u, last_quad));
+                    have_ahead = true;
+                }
+                if constexpr (!PENDING) clear_window();
+                if (ready && total <= kCsrInFlight) {             // (the same for every thread)
+                    csr_process_in_flight(first, total, vmax, nrows, lr < nrows ? p_len : 0, p_pre, meta.coef, acc,
+                                          static_cast<int>(c0), static_cast<int>(c1), sg.prod_a, fx, &sh_poison, vec_req, vec_val,
+                                          [&](float dz) { return p_row < 0 ? 0.0f : vr_slope_diff(p_y, p_z, dz) * inv_B; });
+                    rows_done = true;
+                }
+            } else {
+                request_first();
+                clear_window();
+            }
+            if (ready && !rows_done) {
+                const int tr = min(static_cast<int>(threadIdx.x), kCsrMaxRows - 1);
+                const int p_row = in[kPrepRow + tr], p_len = in[kPrepLen + tr], p_pre = in[kPrepPre + tr];
+                const int p_last = in[kPrepPre + nrows];
+                const float p_y = __int_as_float(in[kPrepY + tr]), p_z = __int_as_float(in[kPrepZ + tr]);
                 if (static_cast<int>(threadIdx.x) < nrows) {
                     meta.row[threadIdx.x] = p_row;
                     meta.len[threadIdx.x] = p_len;
@@ -724,9 +921,41 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                 finish_quad(j, make_float4(t[0], t[1], t[2], t[3]));
             };
             const int64_t whole = min(c1p, d / 4 * 4);            // whole quads of the vector end here
-            if constexpr (DIFF) {
+            if constexpr (PENDING) {
+                // (a slice is whole wavefronts of quads, so the lanes of one go through this together)
+                const auto finish_model_quad = [&](int64_t j, float4 df) {
+                    const int64_t past = d - j;                  // coordinates left; those past the end stay zero
+                    if (past > 0)
+                        finish_quad(j, make_float4(a.l2 * df.x, past > 1 ? a.l2 * df.y : 0.0f, past > 2 ? a.l2 * df.z : 0.0f,
+                                                   past > 3 ? a.l2 * df.w : 0.0f));
+                };
+                if (have_ahead) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int64_t j = c0 + 4ll * threadIdx.x + 4ll * kCsrThreads * u;
+                        if (j < c1p) finish_model_quad(j, ahead[u]);
+                    }
+                }
+                const int64_t lane4 = 4 * (static_cast<int>(threadIdx.x) & (kWave - 1));
+                for (int64_t j = c0 + 4ll * threadIdx.x + (have_ahead ? 4ll * kCsrThreads * kAhead : 0); j - lane4 < c1p;
+                     j += 4ll * kCsrThreads) {
+                    const int64_t at = min<int64_t>(j, d / 4 * 4 - 4);
+                    const float4 x = *reinterpret_cast<const float4 *>(a.model_diff + at);
+                    const float4 xs = *reinterpret_cast<const float4 *>(a.x_snap + at);
+                    const float4 df = quantize_model_quad(j >> 2, x, xs, stream_block(model_key, static_cast<uint32_t>(j >> 2)));
+                    if (j < c1p) finish_model_quad(j, df);
+                }
+            } else if constexpr (DIFF) {
                 constexpr int kInitFlight = 6;                   // (as below: requested together, at clamped positions)
-                for (int64_t j0 = c0 + 4ll * threadIdx.x; j0 < whole; j0 += 4ll * kCsrThreads * kInitFlight) {
+                if (have_ahead) {                                // (the same for every thread)
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int64_t j = c0 + 4ll * threadIdx.x + 4ll * kCsrThreads * u;
+                        if (j < whole)
+                            finish_quad(j, make_float4(a.l2 * ahead[u].x, a.l2 * ahead[u].y, a.l2 * ahead[u].z, a.l2 * ahead[u].w));
+                    }
+                }
+                for (int64_t j0 = c0 + 4ll * threadIdx.x + (have_ahead ? 4ll * kCsrThreads * kAhead : 0); j0 < whole; j0 += 4ll * kCsrThreads * kInitFlight) {
                     float4 df[kInitFlight];
 #pragma unroll
                     for (int u = 0; u < kInitFlight; ++u)
@@ -766,7 +995,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             } else {
                 for (int64_t j = c0 + 4ll * threadIdx.x; j < c1p; j += 4ll * kCsrThreads) slow_quad(j);
             }
-            __syncthreads();
+            if constexpr (!SLICED) __syncthreads();
         }
         if (alpha_row) {                                       // several windows: the finished one goes to memory
             for (int64_t j = c0 + threadIdx.x; j < c1p; j += kCsrThreads) alpha_row[j] = alpha[j - c0];
@@ -775,9 +1004,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         if constexpr (COMMON || SLICED) break;                 // (one window)
     }
     if constexpr (SLICED) {
-        seen_max = block_max_u32(seen_max, su);
         const int64_t stride = a.sparsify ? a.ld_words : nslices;
-        if (threadIdx.x == 0) a.part_max[m * stride + slice] = __uint_as_float(seen_max);
+        seen_max = wave_max_u32(seen_max);
+        if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&sh_max, seen_max);
+        __syncthreads();
+        if (threadIdx.x == 0) a.part_max[m * stride + slice] = __uint_as_float(sh_max);
         return;
     }
     // the whole gradient, padded with zeros to a whole quad: in LDS when it fits in one window, else in this worker's
@@ -1288,6 +1519,18 @@ static CsrSlices csr_step_slices(const dq_problem *prob, const WorkerArgs &a, co
     return csr_slices(prob->d, a.M, plan, a.z_snap == nullptr);
 }
 
+// Whether the step `a` can take the model as x itself (WorkerArgs::x_model): split over the columns, mini-batches prepared
+// ahead, margins cached, a message of whole words per 64 quads; and no more than one quad of a slice per thread, as far as
+// it is the faster (see csr_worker_kernel).
+bool csr_model_fusable(const dq_problem *prob, const WorkerArgs &a)
+{
+    CsrPlan plan;
+    if (!csr_plan(prob->d, a.z_snap == nullptr, plan)) return false;
+    if (a.b_x != 2 && a.b_x != 4 && a.b_x != 8) return false;
+    const CsrSlices sl = csr_step_slices(prob, a, plan);
+    return sl.count > 0 && sl.win <= 4 * kCsrThreads && a.z_snap && !a.idx && a.B <= kCsrMaxRows && a.M * (sl.count + 1) <= 256;
+}
+
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
 {
     const int64_t d = prob->d;
@@ -1312,6 +1555,10 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     k.cap = plan.cap; k.win = plan.win; k.prep_cap = csr_prep_cap(d, plan);
     k.alpha_ws = plan.nwin > 1 ? static_cast<float *>(a.ws) : nullptr; k.ld_ws = pad4(d);
     k.model_diff = a.b_x == 32 ? nullptr : a.model_diff;
+    if (a.x_model) {
+        k.model_diff = a.x_model;
+        k.absmax_out = const_cast<float *>(a.absmax_model);
+    }
     const CsrSlices sl = csr_step_slices(prob, a, plan);
     const bool sliced = sl.count > 0;
     const bool count_ok = !a.nnz_out || (a.sparsify && a.b >= 4);
@@ -1351,13 +1598,16 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
         k.part_max = alpha_max;
     }
     const bool common = (sliced || plan.nwin == 1) && a.B <= kCsrMaxRows && a.z_snap != nullptr;
-    static std::once_flag attr_once[8];
-    static hipError_t attr_rc[8];
-    void (*const kernels[8])(const CsrWorkerArgs) = {
-        csr_worker_kernel<false, false, false>, csr_worker_kernel<false, true, false>, csr_worker_kernel<true, false, false>,
-        csr_worker_kernel<true, true, false>,   csr_worker_kernel<false, false, true>, csr_worker_kernel<false, true, true>,
-        csr_worker_kernel<true, false, true>,   csr_worker_kernel<true, true, true>};
-    const int which = (sliced ? 4 : 0) + (k.model_diff ? 2 : 0) + (common ? 1 : 0);
+    if (a.x_model && !(sliced && common)) return DQ_ERR_INVALID_ARG;       // (see csr_model_fusable)
+    static std::once_flag attr_once[9];
+    static hipError_t attr_rc[9];
+    void (*const kernels[9])(const CsrWorkerArgs) = {
+        csr_worker_kernel<kModelMessage, false, false>, csr_worker_kernel<kModelMessage, true, false>,
+        csr_worker_kernel<kModelDiff, false, false>,    csr_worker_kernel<kModelDiff, true, false>,
+        csr_worker_kernel<kModelMessage, false, true>,  csr_worker_kernel<kModelMessage, true, true>,
+        csr_worker_kernel<kModelDiff, false, true>,     csr_worker_kernel<kModelDiff, true, true>,
+        csr_worker_kernel<kModelPending, true, true>};
+    const int which = a.x_model ? 8 : (sliced ? 4 : 0) + (k.model_diff ? 2 : 0) + (common ? 1 : 0);
     const auto kernel = kernels[which];
     int rc = allow_big_lds(kernel, attr_once[which], attr_rc[which]);
     if (rc != DQ_OK) return rc;

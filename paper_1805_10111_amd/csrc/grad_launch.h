@@ -39,10 +39,10 @@ struct WorkerArgs {
                                   // streams the feature rows (start/stop events of an extended launch)
     uint32_t *zero_word;          // nullable: one device word the worker kernel sets to 0 (dq_run_rounds uses it to
                                   // prepare the master's ||x||_inf accumulator without a launch of its own)
-    // Alg. 1, master (i) done by the worker kernel itself (dq_run_rounds, dense features): when x_model is given the
-    // kernel that streams the rows quantizes the model x_model[d] with scale ||x||_inf = *absmax_model and the master's
+    // Alg. 1, master (i) done by the worker kernel itself (dq_run_rounds): when x_model is given the
+    // kernel that reads the rows quantizes the model x_model[d] with scale ||x||_inf = *absmax_model and the master's
     // stream (seed, iter, DQ_MASTER_ID, DQ_TAG_MODEL) -- every block for its own use, one block also storing the
-    // message to `xq` and its scale to `delta_x`, which are then outputs of the call.  Needs dense_model_fusable().
+    // message to `xq` and its scale to `delta_x`, which are then outputs of the call.  Needs dense_model_fusable() or csr_model_fusable().
     const float *x_model, *absmax_model;
     // CSR features, step split over the columns or sparsifier split over several blocks per worker: when `deferred` is given
     // and the step takes that route, it stops before the quantization -- `delta_out` and `nnz_out` stay untouched, `packed` holds nothing of use -- and describes what it left in
@@ -90,14 +90,14 @@ bool master_leaves_model_diff(int64_t d, int32_t b_x, bool from_parts);
 // The master step of a round whose workers deferred their quantization (WorkerArgs::deferred): one kernel quantizes the M
 // gradients with the workers' streams (seed, worker_iter, worker0 + m, DQ_TAG_GRAD), stores the messages, scales and
 // (after the sparsifier; nnz_out nullable) nonzero counts exactly as the worker step would have, and applies the master
-// update; the model quantization follows as in master_step_impl.
+// update; the model quantization follows as in master_step_impl, unless update_only (the next worker step's work).
 int32_t master_step_from_parts_impl(const GradientParts &parts, uint32_t worker0, uint32_t worker_iter, uint32_t *packed, int64_t ld_words,
                                     float *delta_out, int32_t *nnz_out, int64_t M, int32_t b, float scale, int each,
                                     const float *g_snap, float *x, float *y, const float *x_snap, float *xsum, float eta,
                                     float theta, float l1, int64_t d, int32_t b_x,
                                     uint64_t seed, uint32_t iter, uint32_t *xq_packed_out, float *delta_x_out,
                                     float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
-                                    float *model_diff_out);
+                                    float *model_diff_out, bool update_only);
 
 // All rounds of a dq_run_rounds call in one launch (small_rounds.hip), for problems that small_rounds_ok admits: the message
 // of the first round's model in st->xq unless flag_first (the flag-bit case).
@@ -118,5 +118,7 @@ int64_t csr_prep_offset(const dq_problem *prob, int64_t M);
 int csr_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,
                   int64_t ws_bytes, hipStream_t st);
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st);
+// Whether the CSR worker step `a` can take the model from x_model (see WorkerArgs).
+bool csr_model_fusable(const dq_problem *prob, const WorkerArgs &a);
 
 }  // namespace dq

@@ -734,7 +734,7 @@ int32_t dq::master_step_from_parts_impl(const GradientParts &parts, uint32_t wor
                                         float theta, float l1, int64_t d, int32_t b_x,
                                         uint64_t seed, uint32_t iter, uint32_t *xq_packed_out, float *delta_x_out,
                                         float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
-                                        float *model_diff_out)
+                                        float *model_diff_out, bool update_only)
 {
     int32_t rc0 = check_master_args(packed, ld_words, delta_out, M, b, g_snap, x, y, x_snap, xsum, d);
     if (rc0 != DQ_OK) return rc0;
@@ -765,6 +765,7 @@ int32_t dq::master_step_from_parts_impl(const GradientParts &parts, uint32_t wor
 #undef DQ_PARTS
     DQ_LAUNCH_CHECK();
     const StreamKey key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), iter, 0u, DQ_TAG_MODEL};
+    if (update_only) return DQ_OK;                       // (the next worker step quantizes the model)
     return model_message(x, d, b_x, key, xq_packed_out, delta_x_out, absmax_x_out, status, st, x_snap, model_diff_out);
 }
 

@@ -56,8 +56,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // update and ||x||_inf (spread over the chip), and the next round's row-streaming kernel quantizes the model in
     // its prologue, while its first rows are on their way -- every block for itself, one of them storing the message.
     // The two slots of absmax_x alternate: the kernel that reads one clears the other for the master of its round.
-    const bool fusable = cfg->tau == 0 && cfg->b_x != 32 &&
-                         dq::dense_model_fusable(prob, cfg->M, cfg->B, cfg->b_x, st->z_snap != nullptr);
+    // (CSR features the same, where the worker step is split over the columns: csr_model_fusable.)
     // CSR features, one group of workers, messages not crossing as (position, value) streams: a worker step that is split
     // over the columns leaves the quantization of its messages to the master kernel (one launch less)
     const bool defer_ok = prob->layout == 1 && cfg->b != 32 && cfg->tau == 0 && !st->wire;
@@ -78,6 +77,21 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         prep_set_words = cfg->M * dq::csr_prep_stride(prob->d);
         if (prep_set_words > 0 && st->ws_bytes >= off + 2 * prep_set_words * 4)
             prep_sets = reinterpret_cast<int32_t *>(static_cast<char *>(st->ws) + off);
+    }
+    bool fusable = false;
+    if (cfg->tau == 0 && cfg->b_x != 32) {
+        if (csr) {
+            dq::GradientParts unused{};
+            dq::WorkerArgs w{};
+            w.M = cfg->M; w.B = cfg->B; w.b_x = cfg->b_x; w.z_snap = st->z_snap; w.b = cfg->b; w.packed = st->packed;
+            w.sparsify = cfg->algo == DQ_ALGO_SPARSE;
+            w.nnz_out = w.sparsify ? st->nnz : nullptr;
+            w.ws = st->ws; w.ws_bytes = st->ws_bytes;
+            if (defer_ok) w.deferred = &unused;
+            fusable = prep_sets && dq::csr_model_fusable(prob, w);
+        } else {
+            fusable = dq::dense_model_fusable(prob, cfg->M, cfg->B, cfg->b_x, st->z_snap != nullptr);
+        }
     }
     bool prep_ready = false;             // the set of this round's parity holds this round's mini-batches
     bool model_pending = false;          // the model of this round is still x itself (not yet a message)
@@ -148,7 +162,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         float *dx_next = st->delta_x + ((t + 1) % slots);
         model_pending = fusable && t + 1 < t0 + rounds;
         // (the difference is of use only to a next round of this call)
-        float *diff_out = (model_diff && t + 1 < t0 + rounds &&
+        float *diff_out = (model_diff && !model_pending && t + 1 < t0 + rounds &&
                            dq::master_leaves_model_diff(prob->d, cfg->b_x, parts.parts > 0)) ? model_diff : nullptr;
         diff_ready = diff_out != nullptr;
         if (parts.parts > 0)
@@ -157,7 +171,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
                                                  cfg->M, cfg->b, scale, cfg->each, st->g_snap, st->x, acc ? st->y : nullptr,
                                                  st->x_snap, acc ? st->xsum : nullptr, eta, theta, prob->l1, prob->d, cfg->b_x,
                                                  cfg->seed, it + 1u, xq_next, dx_next, st->absmax_x + (t & 1), st->status,
-                                                 /*absmax_zeroed=*/true, stream, diff_out);
+                                                 /*absmax_zeroed=*/true, stream, diff_out, model_pending);
         else if (model_pending)
             rc = dq::master_update_impl(st->packed, st->ld_words, st->delta, cfg->M, cfg->b, scale, cfg->each, st->g_snap,
                                         st->x, acc ? st->y : nullptr, st->x_snap, acc ? st->xsum : nullptr, eta, theta,

@@ -585,3 +585,23 @@ def test_small_dense_rounds_with_an_infinite_feature(dq, B):
                       None, None, two.status, two.ws)
     assert host(two.delta).tolist() == [np.inf, np.inf] and host(one.delta).tolist() == [np.inf, np.inf]
     assert torch.equal(one.packed, two.packed) and host(one.status)[0] == 1 and host(two.status)[0] == 1
+
+
+@pytest.mark.parametrize("d,b_x", [(4096, 8), (4097, 2), (8194, 4), (20959, 8), (32768, 2), (32771, 8)])
+@pytest.mark.parametrize("algo,b,B", [("asylpg", 8, 1), ("acc", 4, 33), ("asylpg", 2, 150)])
+def test_csr_rounds_of_one_call_equal_single_rounds(dq, d, b_x, algo, b, B):
+    """CSR features: between the rounds of a call the model is quantized by the next round's worker kernel, from
+    mini-batches prepared a round ahead (150 rows of 30 entries: more than a block keeps in its registers); in calls of a
+    single round by the master, from rows read in the round.  Everything must be identical, ragged last quads and slices
+    of up to 4096 columns included."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    P = dq.DeviceProblem.from_host(synth.sparse_text_logistic(500, d, mean_nnz=30.0, seed=4))
+    one, many = (DoubleQuantTrainer(P, algo, 6, B, b_x, b, 5, 0.5, seed=3) for _ in range(2))
+    one.epoch_prologue(); many.epoch_prologue()
+    one.rounds(0, 5)
+    for t in range(5):
+        many.rounds(t, 1)
+    torch.cuda.synchronize()
+    for name in ("packed", "delta", "x", "xq", "delta_x", "status") + (("y", "xsum") if algo == "acc" else ()):
+        assert torch.equal(getattr(one, name), getattr(many, name)), name
+    assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
