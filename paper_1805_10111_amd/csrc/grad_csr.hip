@@ -19,7 +19,7 @@
 //      step (sparsify, scale, quantize, pack) runs from LDS.
 // Between the rounds of one dq_run_rounds call, everything of step 1 that does not depend on the model (which rows,
 // their extents and labels, the flat run itself) is laid out one round ahead by an extra block per worker of the
-// previous round's launch (see kPrepInts).
+// previous round's launch (see PrepLayout).
 // The full gradient takes its rows straight from memory in many blocks, each leaving a partial d-vector of fixed-point
 // sums that a second kernel adds up in a fixed order.
 #include <algorithm>
@@ -413,11 +413,12 @@ __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta
 // reading their extents, labels and cached margins, the prefix sums, and the copy of the rows' entries into one flat run
 // -- does not depend on the model.  Between two rounds of one dq_run_rounds call an extra block per worker of the
 // worker launch does all of that for the NEXT round, on compute units the launch leaves idle, and leaves it in
-// memory as csr_prep_stride 32-bit words per worker:
-//   [0] 1 when the flat run is there (the batch has at most csr_prep_cap entries), else 0   [1] number of entries
-//   [2] the largest |value| among them, as bits (with the flat run only)
-//   row[kCsrMaxRows] len[kCsrMaxRows] pre[kCsrMaxRows + 4] y[kCsrMaxRows] z[kCsrMaxRows]      (RowMeta's fields)
-//   pairs (column | row << kColBits, value bits), [1] of them
+// memory as PrepRoom::stride 32-bit words per worker:
+//   [0] 1 when the flat run is there (the batch has at most PrepRoom::cap entries), else 0   [1] number of entries
+//   [2] the largest |value| among them, as bits (with the flat run only)   [3] 1 when the snapshot values are there
+//   row[B] len[B] pre[B + 4] y[B] z[B], each from a multiple of four words on      (RowMeta's fields)
+//   pairs (column | row << kColBits, value bits), [1] of them; room for PrepRoom::snap_cap pairs further on the snapshot
+//   at their columns, if there are no more of them than that
 // The next round's blocks then start from one round trip to memory instead of a chain of five.
 
 // Stage, margins and scatter for a prepared mini-batch: `entry` is its flat run of `total` <= cap entries, `first`
@@ -465,7 +466,7 @@ __device__ __forceinline__ void csr_process_prepared(const int2 *entry, const in
 
 // The same for a batch of at most kCsrInFlight entries, which stay in the registers they were loaded into: `e` is all of
 // the flat run, `vmax` its largest |value|, and lane l of wavefront w holds row w + 16 l of the batch (its length, its
-// first entry's position, and whatever coef_of(zdiff) needs besides its margin).  What a block waits for here is latency,
+// first entry's position, and whatever coef_of(zdiff) needs besides its margin); the first operands are left in `operand`.  What a block waits for here is latency,
 // one phase after another, so there are as few phases as the sums allow: products to LDS, barrier, margins and
 // coefficients, barrier, scatter.  The sums are those of csr_reduce_group, bit for bit.
 // Eight workers of 32 rows, 20,958 columns, from the block's start: products complete after 2.2 us, margins 2.8, scattered
@@ -508,20 +509,24 @@ __device__ __forceinline__ void csr_lane_margins(const float *prod, int total, i
 template <typename VecReq, typename VecVal, typename CoefFn>
 __device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlight], int total, float vmax, int nrows, int my_len,
                                                       int my_pre, float *coef, int *acc, int c0, int c1, float *prod,
-                                                      FixedAcc &fx, int *poison, VecReq vec_req, VecVal vec_val, CoefFn coef_of)
+                                                      FixedAcc &fx, int *poison, VecReq vec_req, VecVal vec_val, CoefFn coef_of,
+                                                      float (&operand)[kStageFlight])
 {
     int col[kStageFlight];
-    decltype(vec_req(0)) raw[kStageFlight];
+    decltype(vec_req(0, 0)) raw[kStageFlight];
 #pragma unroll
     for (int u = 0; u < kStageFlight; ++u) {
         // (past the end `e` holds whatever the buffer held: column 0 is gathered instead)
         col[u] = static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? e[u].x & kColMask : 0;
-        raw[u] = vec_req(col[u]);
+        raw[u] = vec_req(col[u], u);
     }
 #pragma unroll
     for (int u = 0; u < kStageFlight; ++u) {
         const int p = threadIdx.x + u * kCsrThreads;
-        if (p < total) prod[p] = __int_as_float(e[u].y) * vec_val(raw[u], col[u]).x;
+        if (p < total) {
+            operand[u] = vec_val(raw[u], col[u]).x;
+            prod[p] = __int_as_float(e[u].y) * operand[u];
+        }
     }
     __syncthreads();
     // (a wavefront has one or two rows of the common batches of up to 32)
@@ -559,9 +564,11 @@ struct CsrWorkerArgs {
     uint32_t *packed; int64_t ld_words, row_words;
     float *delta_out; int32_t *nnz_out; uint32_t *status;
     int cap;                       // staging capacity in entries
-    int prep_cap;                  // most entries of a mini-batch prepared ahead (csr_prep_cap; never more than cap)
+    int prep_cap;                  // most entries of a mini-batch prepared ahead (PrepRoom::cap; never more than cap)
     uint32_t *zero_word;           // nullable: set to 0 by one thread of the grid
     int win;                       // columns of the gradient held in LDS at a time (multiple of 4; >= d: all of it)
+    int snap_cap;                  // PrepRoom::snap_cap
+    int dev_max_at;               // word of prep_in where WorkerArgs::dev_max lies, 0: not given
     float *alpha_ws; int64_t ld_ws; // with several windows: M rows of workspace for the whole gradient, else null
     // sparsifier split over the identical blocks of a worker (beta_ws != null): each block sparsifies its slice into
     // row m of beta_ws and leaves the slice's largest magnitude and kept count; the quantization is a second launch
@@ -570,7 +577,7 @@ struct CsrWorkerArgs {
     // (no fields of their own: arguments that reach into one more 64-byte line cost every launch 0.2 us)
     float *beta_ws; float *part_max; int32_t *part_kept;
     const float *model_diff;       // nullable: (decoded model) - snapshot for every column, see WorkerArgs::model_diff
-    // a mini-batch prepared ahead (see kPrepInts): prep_in (nullable) holds this round's, one block of prep_stride words
+    // a mini-batch prepared ahead (see PrepLayout): prep_in (nullable) holds this round's, one block of prep_stride words
     // per worker; with prep_out the grid has one more block per worker (the last blockIdx.y), which prepares the round
     // whose streams carry next_iter into prep_out.  Both need B <= kCsrMaxRows, drawn rows (idx == null) and one window of columns per block (the whole vector, or
     // a slice).
@@ -690,7 +697,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         return ri;
     };
     if (a.prep_out && slice == nslices) {
-        // ---- the extra block: worker m's mini-batch of the next round, left in memory (see kPrepInts)
+        // ---- the extra block: worker m's mini-batch of the next round, left in memory (see PrepLayout)
         StreamKey next_key = a.key;
         next_key.iter = a.next_iter;
         const int nrows = a.B;
@@ -701,25 +708,29 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             meta.len[threadIdx.x] = ri.len;
         }
         csr_prefix_lengths(meta, nrows);
+        const PrepLayout at(nrows);
         int32_t *out = a.prep_out + static_cast<int64_t>(m) * a.prep_stride;
         const int total = meta.pre[nrows];
         const bool fits = total <= a.prep_cap;
         if (static_cast<int>(threadIdx.x) < nrows) {
-            out[kPrepRow + threadIdx.x] = ri.row;
-            out[kPrepLen + threadIdx.x] = ri.len;
-            out[kPrepPre + threadIdx.x] = meta.pre[threadIdx.x];
-            out[kPrepY + threadIdx.x] = __float_as_int(ri.y);
-            out[kPrepZ + threadIdx.x] = __float_as_int(ri.z);
+            out[at.row + threadIdx.x] = ri.row;
+            out[at.len + threadIdx.x] = ri.len;
+            out[at.pre + threadIdx.x] = meta.pre[threadIdx.x];
+            out[at.y + threadIdx.x] = __float_as_int(ri.y);
+            out[at.z + threadIdx.x] = __float_as_int(ri.z);
         }
         if (threadIdx.x == 0) {
             out[0] = fits ? 1 : 0;
             out[1] = total;
-            out[kPrepPre + nrows] = total;
+            out[at.pre + nrows] = total;
         }
+        if (m == 0 && threadIdx.x == 0) out[at.dev_max] = 0;
         if (!fits) return;
-        int2 *entry = reinterpret_cast<int2 *>(out + kPrepEntries);
+        int2 *entry = reinterpret_cast<int2 *>(out + at.entries);
         const int lane = threadIdx.x & (kWave - 1);
         uint32_t vmax = 0;
+        const bool snaps = total <= a.snap_cap;
+        float *entry_snap = reinterpret_cast<float *>(entry + a.snap_cap);
         for (int p0 = threadIdx.x; p0 - lane < total; p0 += kStageFlight * kCsrThreads) {
             int64_t src[kStageFlight];
             int tag[kStageFlight], col[kStageFlight];
@@ -735,12 +746,23 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
 #pragma unroll
             for (int u = 0; u < kStageFlight; ++u)
                 if (p0 + u * kCsrThreads < total) entry[p0 + u * kCsrThreads] = make_int2(col[u] | tag[u], __float_as_int(val[u]));
+            if (snaps) {                                       // (the same for every thread)
+                float xs[kStageFlight];
+#pragma unroll
+                for (int u = 0; u < kStageFlight; ++u) xs[u] = a.x_snap[col[u]];
+#pragma unroll
+                for (int u = 0; u < kStageFlight; ++u)
+                    if (p0 + u * kCsrThreads < total) entry_snap[p0 + u * kCsrThreads] = xs[u];
+            }
             // (a position past the end repeats an entry of the batch)
 #pragma unroll
             for (int u = 0; u < kStageFlight; ++u) vmax = max(vmax, abs_bits(val[u]));
         }
         vmax = block_max_u32(vmax, su);
-        if (threadIdx.x == 0) out[2] = static_cast<int>(vmax);
+        if (threadIdx.x == 0) {
+            out[2] = static_cast<int>(vmax);
+            out[3] = snaps ? 1 : 0;
+        }
         return;
     }
     // PENDING: quad q of the model becomes its difference to the snapshot; the blocks of worker 0 also store the message,
@@ -781,6 +803,60 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         const_cast<float *>(a.delta_x)[0] = model_scale.delta;
         if (model_scale.bad && a.status) atomicOr(a.status, 1u);
     }
+    // Alg. 2 once the rows are added (not SLICED: this block holds the sums of all columns), without the pass over the
+    // whole vector.  A column that no row touches holds l2 * model_diff, which is bounded (WorkerArgs::dev_max); where the
+    // largest of the touched ones, which every thread forms from the entries in its registers, is no less than the
+    // bound, it is ||alpha||_inf, and all that is left is the block's own slice.  The values are those of the pass,
+    // bit for bit.  Returns false (for every thread) where it is not.  72,000 x 20,958, 16 workers of 64 rows: the pass over
+    // 5240 quads and the tail behind it took half of the kernel, 12.3 us; now 10.3.
+    const int64_t tail_per = (((d + 3) / 4 + nslices - 1) / nslices + kWave - 1) / kWave * kWave, tail_first = tail_per * slice;
+    const auto sparsify_touched = [&](const int2 (&e)[kStageFlight], const float (&operand)[kStageFlight], int total,
+                                      const FixedAcc &fx, float dev_max, float4 own_diff, uint4 own_words) {
+        const float unit = ldexpf(1.0f, -fx.k);
+        uint32_t seen = 0;
+#pragma unroll
+        for (int u = 0; u < kStageFlight; ++u)
+            if (static_cast<int>(threadIdx.x) + u * kCsrThreads < total) {
+                float v = a.l2 * operand[u];
+                v += static_cast<float>(acc[e[u].x & kColMask]) * unit;
+                seen = max(seen, abs_bits(v));
+            }
+        seen = block_max_u32(seen, su);
+        // (|Q(x) - x| is at most the scale and a rounding of x; a degenerate scale is none)
+        const float rest = a.l2 * ((dev_max + msg.delta_x) * 1.001f);
+        if (sh_poison || !(rest <= FLT_MAX) || msg.delta_x == 0.0f || !(seen >= abs_bits(rest))) return false;
+        const SparsifyRule rule{__uint_as_float(seen), 0.0f, false};
+        StreamKey key = a.key;
+        key.worker = a.worker0 + static_cast<uint32_t>(m);
+        key.tag = DQ_TAG_SPARSIFY;
+        const int64_t quads = (d + 3) / 4, q_hi = min(quads, tail_first + tail_per);
+        uint32_t bmax = 0;
+        int kept = 0;
+        for (int64_t q = tail_first + threadIdx.x; q < q_hi; q += kCsrThreads) {
+            if (q != tail_first + threadIdx.x) {
+                own_diff = reinterpret_cast<const float4 *>(a.model_diff)[q];
+                own_words = stream_block(key, static_cast<uint32_t>(q));
+            }
+            const int4 sum = reinterpret_cast<const int4 *>(acc)[q];
+            float4 v = make_float4(a.l2 * own_diff.x, a.l2 * own_diff.y, a.l2 * own_diff.z, a.l2 * own_diff.w);
+            v.y = 4 * q + 1 < d ? v.y : 0.0f;                  // (past the end of the vector nothing was added)
+            v.z = 4 * q + 2 < d ? v.z : 0.0f;
+            v.w = 4 * q + 3 < d ? v.w : 0.0f;
+            v.x = sparsify_one(v.x + static_cast<float>(sum.x) * unit, rule, own_words.x);
+            v.y = sparsify_one(v.y + static_cast<float>(sum.y) * unit, rule, own_words.y);
+            v.z = sparsify_one(v.z + static_cast<float>(sum.z) * unit, rule, own_words.z);
+            v.w = sparsify_one(v.w + static_cast<float>(sum.w) * unit, rule, own_words.w);
+            bmax = max(max(bmax, abs_bits(v.x)), max(max(abs_bits(v.y), abs_bits(v.z)), abs_bits(v.w)));
+            kept += (v.x != 0.0f) + (v.y != 0.0f) + (v.z != 0.0f) + (v.w != 0.0f);
+            store_quad(a.beta_ws + static_cast<int64_t>(m) * a.ld_ws, q, d, v);
+        }
+        block_max_u32_sum_i32(bmax, kept, su, si);
+        if (threadIdx.x == 0) {
+            a.part_max[static_cast<int64_t>(m) * nslices + slice] = __uint_as_float(bmax);
+            a.part_kept[static_cast<int64_t>(m) * nslices + slice] = kept;
+        }
+        return true;
+    };
     for (int64_t c0 = SLICED ? static_cast<int64_t>(slice) * win : 0; c0 < d; c0 += win) {
         const int64_t c1 = min(d, c0 + win);
         const int64_t c1p = min((d + 3) / 4 * 4, c0 + win);     // the window, up to a whole quad past the end of the vector
@@ -794,11 +870,14 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         if (a.prep_in) {
             // ---- this round's mini-batch was prepared: descriptors and the first entries are requested together
             // (a.B <= kCsrMaxRows, one window or slice)
+            const PrepLayout at(a.B);
             const int32_t *in = a.prep_in + static_cast<int64_t>(m) * a.prep_stride;
-            const int2 *entry = reinterpret_cast<const int2 *>(in + kPrepEntries);
+            const int2 *entry = reinterpret_cast<const int2 *>(in + at.entries);
             const int nrows = a.B;
             const int ready = in[0], total = in[1];
             int2 first[kStageFlight];
+            float first_snap[kStageFlight];
+            const float *entry_snap = reinterpret_cast<const float *>(entry + a.snap_cap);
             const auto request_first = [&] {
 #pragma unroll
                 for (int u = 0; u < kStageFlight; ++u)
@@ -812,9 +891,15 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                 const float vmax = __int_as_float(in[2]);
                 const int lr = static_cast<int>(threadIdx.x) / kWave + (static_cast<int>(threadIdx.x) & (kWave - 1)) * kCsrWaves;
                 const int tr = min(lr, nrows - 1);
-                const int p_row = in[kPrepRow + tr], p_len = in[kPrepLen + tr], p_pre = in[kPrepPre + tr];
-                const float p_y = __int_as_float(in[kPrepY + tr]), p_z = __int_as_float(in[kPrepZ + tr]);
+                const int p_row = in[at.row + tr], p_len = in[at.len + tr], p_pre = in[at.pre + tr];
+                const float p_y = __int_as_float(in[at.y + tr]), p_z = __int_as_float(in[at.z + tr]);
                 request_first();
+                const int have_snaps = PENDING ? in[3] : 0;
+                const float dev_max = DIFF && !SLICED ? __int_as_float(a.prep_in[a.dev_max_at]) : 0.0f;
+                if constexpr (PENDING)
+#pragma unroll
+                    for (int u = 0; u < kStageFlight; ++u)
+                        first_snap[u] = entry_snap[min(static_cast<int>(threadIdx.x) + u * kCsrThreads, a.snap_cap - 1)];
                 // (threads past the window read its last whole quad, all of them the same 16 bytes)
                 const int first_col = static_cast<int>(c0) + 4 * static_cast<int>(threadIdx.x);
                 const int last_quad = max(0, static_cast<int>(min<int64_t>(c1p, d / 4 * 4)) - 4);
@@ -843,11 +928,35 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                     have_ahead = true;
                 }
                 if constexpr (!PENDING) clear_window();
+                float operand[kStageFlight];
+                // Alg. 2 with ||x - x_snap||_inf given: the slice's first quad and its random bits, ahead of the rows
+                float4 own_diff = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                uint4 own_words = make_uint4(0u, 0u, 0u, 0u);
+                const bool short_tail = DIFF && !SLICED && a.dev_max_at != 0 && a.beta_ws && !a.alpha_out;
+                if (short_tail) {
+                    const int64_t q = min(tail_first + threadIdx.x, (d + 3) / 4 - 1);      // (rows of model_diff are whole quads)
+                    own_diff = reinterpret_cast<const float4 *>(a.model_diff)[q];
+                    StreamKey key = a.key;
+                    key.worker = a.worker0 + static_cast<uint32_t>(m);
+                    key.tag = DQ_TAG_SPARSIFY;
+                    own_words = stream_block(key, static_cast<uint32_t>(q));
+                }
                 if (ready && total <= kCsrInFlight) {             // (the same for every thread)
+                    if (PENDING && !have_snaps)
+#pragma unroll
+                        for (int u = 0; u < kStageFlight; ++u)
+                            first_snap[u] = a.x_snap[static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? first[u].x & kColMask : 0];
                     csr_process_in_flight(first, total, vmax, nrows, lr < nrows ? p_len : 0, p_pre, meta.coef, acc,
-                                          static_cast<int>(c0), static_cast<int>(c1), sg.prod_a, fx, &sh_poison, vec_req, vec_val,
-                                          [&](float dz) { return p_row < 0 ? 0.0f : vr_slope_diff(p_y, p_z, dz) * inv_B; });
+                                          static_cast<int>(c0), static_cast<int>(c1), sg.prod_a, fx, &sh_poison,
+                                          [&](int c, int u) {
+                                              if constexpr (PENDING) return Gather{0u, 0u, first_snap[u], a.model_diff[c]};
+                                              else return vec_req(c);
+                                          }, vec_val,
+                                          [&](float dz) { return p_row < 0 ? 0.0f : vr_slope_diff(p_y, p_z, dz) * inv_B; }, operand);
                     rows_done = true;
+                    if constexpr (DIFF && !SLICED) {
+                        if (short_tail && sparsify_touched(first, operand, total, fx, dev_max, own_diff, own_words)) return;
+                    }
                 }
             } else {
                 request_first();
@@ -855,9 +964,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             }
             if (ready && !rows_done) {
                 const int tr = min(static_cast<int>(threadIdx.x), kCsrMaxRows - 1);
-                const int p_row = in[kPrepRow + tr], p_len = in[kPrepLen + tr], p_pre = in[kPrepPre + tr];
-                const int p_last = in[kPrepPre + nrows];
-                const float p_y = __int_as_float(in[kPrepY + tr]), p_z = __int_as_float(in[kPrepZ + tr]);
+                const int p_row = in[at.row + tr], p_len = in[at.len + tr], p_pre = in[at.pre + tr];
+                const int p_last = in[at.pre + nrows];
+                const float p_y = __int_as_float(in[at.y + tr]), p_z = __int_as_float(in[at.z + tr]);
                 if (static_cast<int>(threadIdx.x) < nrows) {
                     meta.row[threadIdx.x] = p_row;
                     meta.len[threadIdx.x] = p_len;
@@ -1405,6 +1514,12 @@ static int64_t csr_full_splits(int64_t n)
 
 constexpr int kMaxSlices = kMaxParts;       // identical blocks per worker that share the tail of a worker step
 
+// the M rows of a worker step's workspace and its slices' results: what comes behind them is dq_run_rounds' own
+static int64_t csr_run_offset(const dq_problem *prob, int64_t M)
+{
+    return M * pad4(prob->d) * 4 + M * kMaxSlices * 8;
+}
+
 int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t)
 {
     CsrPlan plan;
@@ -1416,20 +1531,10 @@ int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64
     // a row per worker: the whole gradient when it does not fit in LDS, else the sparsified gradient when the
     // sparsifier is split over several blocks per worker (see csr_worker); then 8 values + 8 counts per worker: all
     // that a single step uses
-    if (op == DQ_OP_WORKER_STEP) return csr_model_diff_offset(prob, M);
+    if (op == DQ_OP_WORKER_STEP) return csr_run_offset(prob, M);
     // then one more row, in which dq_run_rounds keeps (decoded model) - snapshot between two rounds of a call; then two
-    // sets of prepared mini-batches (see kPrepInts), the one a round reads and the one it leaves for the next
-    return csr_prep_offset(prob, M) + 2 * M * csr_prep_stride(prob->d) * 4;
-}
-
-int64_t csr_prep_offset(const dq_problem *prob, int64_t M)
-{
-    return csr_model_diff_offset(prob, M) + pad4(prob->d) * 4;
-}
-
-int64_t csr_model_diff_offset(const dq_problem *prob, int64_t M)
-{
-    return M * pad4(prob->d) * 4 + M * kMaxSlices * 8;
+    // sets of prepared mini-batches (see PrepLayout), the one a round reads and the one it leaves for the next
+    return csr_run_offset(prob, M) + pad4(prob->d) * 4 + 2 * M * csr_prep_stride(prob->d) * 4;
 }
 
 // Kernels that use more than 64 KB of dynamic LDS must be told so once (the limit is raised to the budget).
@@ -1519,16 +1624,24 @@ static CsrSlices csr_step_slices(const dq_problem *prob, const WorkerArgs &a, co
     return csr_slices(prob->d, a.M, plan, a.z_snap == nullptr);
 }
 
-// Whether the step `a` can take the model as x itself (WorkerArgs::x_model): split over the columns, mini-batches prepared
-// ahead, margins cached, a message of whole words per 64 quads; and no more than one quad of a slice per thread, as far as
+// The worker kernel quantizes the model where the step is split over the columns, its mini-batches are prepared ahead, its
+// margins cached, the model's message whole words per 64 quads, and no slice more than one quad per thread, as far as
 // it is the faster (see csr_worker_kernel).
-bool csr_model_fusable(const dq_problem *prob, const WorkerArgs &a)
+CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &a)
 {
+    CsrRunLayout out{};
     CsrPlan plan;
-    if (!csr_plan(prob->d, a.z_snap == nullptr, plan)) return false;
-    if (a.b_x != 2 && a.b_x != 4 && a.b_x != 8) return false;
+    if (!a.ws || !csr_plan(prob->d, a.z_snap == nullptr, plan) || a.ws_bytes < csr_workspace_bytes(DQ_OP_VR_GRAD, prob, a.M, a.B)) return out;
+    char *base = static_cast<char *>(a.ws) + csr_run_offset(prob, a.M);
     const CsrSlices sl = csr_step_slices(prob, a, plan);
-    return sl.count > 0 && sl.win <= 4 * kCsrThreads && a.z_snap && !a.idx && a.B <= kCsrMaxRows && a.M * (sl.count + 1) <= 256;
+    out.pending = (a.b_x == 2 || a.b_x == 4 || a.b_x == 8) && sl.count > 0 && a.z_snap && !a.idx && a.B <= kCsrMaxRows &&
+                  sl.win <= 4 * kCsrThreads && a.M * (sl.count + 1) <= 256;
+    out.prep = csr_prep_room(prob->d, a.M, a.B, plan, out.pending);
+    if (!out.pending) out.model_diff = reinterpret_cast<float *>(base);
+    out.prep_sets[0] = reinterpret_cast<int32_t *>(base + (out.pending ? 0 : pad4(prob->d) * 4));
+    out.prep_sets[1] = out.prep_sets[0] + a.M * out.prep.stride;
+    out.dev_max = a.B <= kCsrMaxRows ? PrepLayout(static_cast<int>(a.B)).dev_max : 0;
+    return out;
 }
 
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
@@ -1552,7 +1665,7 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     k.worker0 = a.worker0;
     k.packed = a.packed; k.ld_words = a.ld_words; k.row_words = row_words;
     k.delta_out = a.delta_out; k.nnz_out = a.nnz_out; k.status = a.status; k.zero_word = a.zero_word;
-    k.cap = plan.cap; k.win = plan.win; k.prep_cap = csr_prep_cap(d, plan);
+    k.cap = plan.cap; k.win = plan.win;
     k.alpha_ws = plan.nwin > 1 ? static_cast<float *>(a.ws) : nullptr; k.ld_ws = pad4(d);
     k.model_diff = a.b_x == 32 ? nullptr : a.model_diff;
     if (a.x_model) {
@@ -1598,7 +1711,7 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
         k.part_max = alpha_max;
     }
     const bool common = (sliced || plan.nwin == 1) && a.B <= kCsrMaxRows && a.z_snap != nullptr;
-    if (a.x_model && !(sliced && common)) return DQ_ERR_INVALID_ARG;       // (see csr_model_fusable)
+    if (a.x_model && !(sliced && common)) return DQ_ERR_INVALID_ARG;       // (see csr_run_layout)
     static std::once_flag attr_once[9];
     static hipError_t attr_rc[9];
     void (*const kernels[9])(const CsrWorkerArgs) = {
@@ -1617,7 +1730,8 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     if (can_prepare) {
         k.prep_in = a.prep_in;
         k.prep_out = a.prep_out;
-        k.prep_stride = csr_prep_stride(prob->d);
+        k.prep_stride = a.prep.stride; k.prep_cap = a.prep.cap; k.snap_cap = a.prep.snap_cap;
+        k.dev_max_at = a.prep_in && a.dev_max ? PrepLayout(k.B).dev_max : 0;
         k.next_iter = a.iter + 1u;
     }
     if (a.prepared_next) *a.prepared_next = k.prep_out != nullptr;

@@ -42,7 +42,7 @@ struct WorkerArgs {
     // Alg. 1, master (i) done by the worker kernel itself (dq_run_rounds): when x_model is given the
     // kernel that reads the rows quantizes the model x_model[d] with scale ||x||_inf = *absmax_model and the master's
     // stream (seed, iter, DQ_MASTER_ID, DQ_TAG_MODEL) -- every block for its own use, one block also storing the
-    // message to `xq` and its scale to `delta_x`, which are then outputs of the call.  Needs dense_model_fusable() or csr_model_fusable().
+    // message to `xq` and its scale to `delta_x`, which are then outputs of the call.  Needs dense_model_fusable() or CsrRunLayout::pending.
     const float *x_model, *absmax_model;
     // CSR features, step split over the columns or sparsifier split over several blocks per worker: when `deferred` is given
     // and the step takes that route, it stops before the quantization -- `delta_out` and `nnz_out` stay untouched, `packed` holds nothing of use -- and describes what it left in
@@ -61,7 +61,23 @@ struct WorkerArgs {
     const int32_t *prep_in;
     int32_t *prep_out;
     bool *prepared_next;
+    PrepRoom prep;                          // the room of either (CsrRunLayout)
+    // nullable (with model_diff and prep_in, in whose first worker's block it lies): ||x - x_snap||_inf, as bits, by the master
+    // of the previous round.  No column's |model_diff| exceeds it by more than the model's scale, so a step that sparsifies
+    // needs no pass over the columns for ||alpha||_inf where those that its rows touch reach beyond l2 times that sum.
+    const uint32_t *dev_max;
 };
+
+// How dq_run_rounds lays out what it keeps in a CSR workspace between two rounds of a call (see launch_sizes.h), for steps
+// like `step`; null pointers: no workspace for it.
+struct CsrRunLayout {
+    bool pending;                           // the worker kernel takes the model as x itself (WorkerArgs::x_model), or
+    float *model_diff;                      // d floats for WorkerArgs::model_diff
+    int32_t *prep_sets[2];                  // WorkerArgs::prep_in / prep_out
+    int dev_max;                           // word of either where WorkerArgs::dev_max lies
+    PrepRoom prep;
+};
+CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &step);
 
 // Whether the dense worker step can take the model from x_model (see WorkerArgs) for this shape.
 bool dense_model_fusable(const dq_problem *prob, int64_t M, int64_t B, int b_x, bool have_z);
@@ -91,13 +107,14 @@ bool master_leaves_model_diff(int64_t d, int32_t b_x, bool from_parts);
 // gradients with the workers' streams (seed, worker_iter, worker0 + m, DQ_TAG_GRAD), stores the messages, scales and
 // (after the sparsifier; nnz_out nullable) nonzero counts exactly as the worker step would have, and applies the master
 // update; the model quantization follows as in master_step_impl, unless update_only (the next worker step's work).
+// dev_max (nullable): receives the bits of ||x - x_snap||_inf, if larger than what it holds.
 int32_t master_step_from_parts_impl(const GradientParts &parts, uint32_t worker0, uint32_t worker_iter, uint32_t *packed, int64_t ld_words,
                                     float *delta_out, int32_t *nnz_out, int64_t M, int32_t b, float scale, int each,
                                     const float *g_snap, float *x, float *y, const float *x_snap, float *xsum, float eta,
                                     float theta, float l1, int64_t d, int32_t b_x,
                                     uint64_t seed, uint32_t iter, uint32_t *xq_packed_out, float *delta_x_out,
                                     float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
-                                    float *model_diff_out, bool update_only);
+                                    float *model_diff_out, uint32_t *dev_max, bool update_only);
 
 // All rounds of a dq_run_rounds call in one launch (small_rounds.hip), for problems that small_rounds_ok admits: the message
 // of the first round's model in st->xq unless flag_first (the flag-bit case).
@@ -111,14 +128,8 @@ int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float 
 int dense_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st);
 
 int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t B);
-// where in a DQ_OP_VR_GRAD workspace of a CSR problem dq_run_rounds keeps the d floats of WorkerArgs::model_diff
-int64_t csr_model_diff_offset(const dq_problem *prob, int64_t M);
-// where the two sets of prepared mini-batches lie there (WorkerArgs::prep_in / prep_out), and the words of one worker's
-int64_t csr_prep_offset(const dq_problem *prob, int64_t M);
 int csr_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,
                   int64_t ws_bytes, hipStream_t st);
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st);
-// Whether the CSR worker step `a` can take the model from x_model (see WorkerArgs).
-bool csr_model_fusable(const dq_problem *prob, const WorkerArgs &a);
 
 }  // namespace dq

@@ -68,9 +68,15 @@ inline bool csr_plan(int64_t d, bool second, CsrPlan &p)
     return true;
 }
 
-// A mini-batch prepared ahead of its round: layout in 32-bit words (see grad_csr.hip), for `cap` entries.
-constexpr int kPrepRow = 4, kPrepLen = kPrepRow + kCsrMaxRows, kPrepPre = kPrepLen + kCsrMaxRows,
-              kPrepY = kPrepPre + kCsrMaxRows + 4, kPrepZ = kPrepY + kCsrMaxRows, kPrepEntries = kPrepZ + kCsrMaxRows;
+// A mini-batch of B rows prepared ahead of its round: layout in 32-bit words (see grad_csr.hip), for `cap` entries.
+struct PrepLayout {
+    int row, len, pre, y, z, entries;
+    int dev_max;       // a word behind the row starts: see WorkerArgs::dev_max
+    constexpr explicit PrepLayout(int B)
+        : row(4), len(row + (B + 3) / 4 * 4), pre(len + (B + 3) / 4 * 4), y(pre + (B + 3) / 4 * 4 + 4), z(y + (B + 3) / 4 * 4),
+          entries(z + (B + 3) / 4 * 4), dev_max(y - 1) {}
+};
+constexpr int kPrepEntries = PrepLayout(kCsrMaxRows).entries;
 constexpr int64_t kPrepInts(int64_t cap) { return kPrepEntries + (2 * cap + 3) / 4 * 4; }
 
 // Words per worker that the workspace holds for one: room for what the plan for one sum per row stages.
@@ -88,6 +94,27 @@ inline int csr_prep_cap(int64_t d, const CsrPlan &plan)
     CsrPlan one_sum;
     if (!csr_plan(d, false, one_sum)) return 0;
     return plan.cap < one_sum.cap ? plan.cap : one_sum.cap;
+}
+
+// What a run's workspace holds behind its M rows and slice results: pad4(d) words and twice M times csr_prep_stride(d).
+// Either the difference of model and snapshot, a word per column, and the two sets of prepared mini-batches; or, where the
+// worker kernel quantizes the model and has no use for that row, two sets of mini-batches in all of it, whose entries
+// can have the snapshot at their column beside them.
+struct PrepRoom {
+    int64_t stride;     // words per worker
+    int cap;            // most entries of a mini-batch
+    int snap_cap;       // most entries that have the snapshot value beside them
+};
+
+inline PrepRoom csr_prep_room(int64_t d, int64_t M, int64_t B, const CsrPlan &plan, bool snaps)
+{
+    if (!snaps) return PrepRoom{csr_prep_stride(d), csr_prep_cap(d, plan), 0};
+    PrepRoom r{};
+    r.stride = (pad4(d) + 2 * M * csr_prep_stride(d)) / (2 * M) / 4 * 4;
+    const int64_t room = r.stride - PrepLayout(static_cast<int>(B)).entries;
+    r.cap = static_cast<int>(room / 2 < plan.cap ? room / 2 : plan.cap);
+    r.snap_cap = static_cast<int>(room / 3 < r.cap ? room / 3 : r.cap);
+    return r;
 }
 
 }  // namespace dq

@@ -172,6 +172,7 @@ struct PartsArgs {
     int b; StreamKey key; uint32_t worker0;
     uint32_t *packed;                                    // rows of MasterArgs::ld_words words
     float *delta_out; int32_t *nnz_out; uint32_t *status;
+    uint32_t *dev_max;                                   // nullable: WorkerArgs::dev_max of the next round
 };
 
 template <int FIELD, bool ACC, bool EACH>
@@ -220,6 +221,7 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
             if (have_sum) request(a.xsum, sm);
         } else {
             request(a.x, xn);
+            if (p.dev_max) request(a.x_snap, xs);
         }
     }
     for (int m0 = 0; m0 < a.M; m0 += kPartsWorkers) {
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
             }
         }
     }
-    uint32_t amax = 0;
+    uint32_t amax = 0, dev = 0;
     if (wl == 0 && inside) {
         if (!EACH) {
             const float dir[4] = {a.scale * acc[0] + gs[0], a.scale * acc[1] + gs[1], a.scale * acc[2] + gs[2],
@@ -300,10 +302,15 @@ __global__ __launch_bounds__(kPartsWorkers * kPartsQuads) void master_from_parts
             if (have_sum) store_quad(a.xsum, q, d, make_float4(sm[0], sm[1], sm[2], sm[3]));
         }
         amax = quad_abs_bits(x4);
+        dev = quad_abs_bits(make_float4(x4.x - xs[0], x4.y - xs[1], x4.z - xs[2], x4.w - xs[3]));
     }
     if (threadIdx.x < kWave) {                           // (worker lane 0 lies in the first wavefront)
         amax = wave_max_u32(amax);
         if (threadIdx.x == 0 && amax != 0) atomicMax(absmax_bits, amax);
+        if (p.dev_max) {
+            dev = wave_max_u32(dev);
+            if (threadIdx.x == 0) atomicMax(p.dev_max, dev);
+        }
     }
 }
 
@@ -734,7 +741,7 @@ int32_t dq::master_step_from_parts_impl(const GradientParts &parts, uint32_t wor
                                         float theta, float l1, int64_t d, int32_t b_x,
                                         uint64_t seed, uint32_t iter, uint32_t *xq_packed_out, float *delta_x_out,
                                         float *absmax_x_out, uint32_t *status, bool absmax_zeroed, void *stream,
-                                        float *model_diff_out, bool update_only)
+                                        float *model_diff_out, uint32_t *dev_max, bool update_only)
 {
     int32_t rc0 = check_master_args(packed, ld_words, delta_out, M, b, g_snap, x, y, x_snap, xsum, d);
     if (rc0 != DQ_OK) return rc0;
@@ -747,7 +754,7 @@ int32_t dq::master_step_from_parts_impl(const GradientParts &parts, uint32_t wor
     const MasterArgs a{packed, ld_words, packed_words(d, b), delta_out, static_cast<int>(M), scale, each, g_snap,
                        x, y, x_snap, xsum, eta, theta, eta * l1, d};
     const StreamKey wkey{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), worker_iter, 0u, DQ_TAG_GRAD};
-    const PartsArgs p{parts, b, wkey, worker0, packed, delta_out, nnz_out, status};
+    const PartsArgs p{parts, b, wkey, worker0, packed, delta_out, nnz_out, status, x_snap ? dev_max : nullptr};
     uint32_t *absmax_bits = reinterpret_cast<uint32_t *>(absmax_x_out);
     int rc = absmax_zeroed ? DQ_OK : fill_u32(absmax_bits, 1, 0u, st);
     if (rc != DQ_OK) return rc;

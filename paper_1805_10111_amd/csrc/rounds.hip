@@ -63,36 +63,24 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // CSR features, one group of workers: the master that quantizes the model in a launch of its own also leaves
     // (decoded model) - snapshot in the workspace for the workers of the next round of this call
     const bool csr = prob->layout == 1;
-    float *model_diff = nullptr;
-    if (csr && cfg->tau == 0 && st->ws) {
-        const int64_t off = dq::csr_model_diff_offset(prob, cfg->M);
-        if (st->ws_bytes >= off + (prob->d + 3) / 4 * 4 * 4) model_diff = reinterpret_cast<float *>(static_cast<char *>(st->ws) + off);
-    }
-    bool diff_ready = false;             // model_diff holds the difference for the model message of this round
     // ... and each worker launch prepares the mini-batches of the next round (two sets, alternating)
-    int32_t *prep_sets = nullptr;
-    int64_t prep_set_words = 0;
-    if (csr && cfg->tau == 0 && st->ws) {
-        const int64_t off = dq::csr_prep_offset(prob, cfg->M);
-        prep_set_words = cfg->M * dq::csr_prep_stride(prob->d);
-        if (prep_set_words > 0 && st->ws_bytes >= off + 2 * prep_set_words * 4)
-            prep_sets = reinterpret_cast<int32_t *>(static_cast<char *>(st->ws) + off);
-    }
+    dq::CsrRunLayout kept{};
     bool fusable = false;
-    if (cfg->tau == 0 && cfg->b_x != 32) {
-        if (csr) {
-            dq::GradientParts unused{};
-            dq::WorkerArgs w{};
-            w.M = cfg->M; w.B = cfg->B; w.b_x = cfg->b_x; w.z_snap = st->z_snap; w.b = cfg->b; w.packed = st->packed;
-            w.sparsify = cfg->algo == DQ_ALGO_SPARSE;
-            w.nnz_out = w.sparsify ? st->nnz : nullptr;
-            w.ws = st->ws; w.ws_bytes = st->ws_bytes;
-            if (defer_ok) w.deferred = &unused;
-            fusable = prep_sets && dq::csr_model_fusable(prob, w);
-        } else {
-            fusable = dq::dense_model_fusable(prob, cfg->M, cfg->B, cfg->b_x, st->z_snap != nullptr);
-        }
+    if (csr && cfg->tau == 0) {
+        dq::GradientParts unused{};
+        dq::WorkerArgs w{};
+        w.M = cfg->M; w.B = cfg->B; w.b_x = cfg->b_x; w.z_snap = st->z_snap; w.b = cfg->b; w.packed = st->packed;
+        w.sparsify = cfg->algo == DQ_ALGO_SPARSE;
+        w.nnz_out = w.sparsify ? st->nnz : nullptr;
+        w.ws = st->ws; w.ws_bytes = st->ws_bytes;
+        if (defer_ok) w.deferred = &unused;
+        kept = dq::csr_run_layout(prob, w);
+        fusable = kept.pending;
+    } else if (!csr) {
+        fusable = cfg->tau == 0 && cfg->b_x != 32 && dq::dense_model_fusable(prob, cfg->M, cfg->B, cfg->b_x, st->z_snap != nullptr);
     }
+    uint32_t *dev_max = nullptr;         // WorkerArgs::dev_max for it
+    bool diff_ready = false;             // kept.model_diff holds the difference for the model message of this round
     bool prep_ready = false;             // the set of this round's parity holds this round's mini-batches
     bool model_pending = false;          // the model of this round is still x itself (not yet a message)
     for (int64_t t = t0; t < t0 + rounds; ++t) {
@@ -135,11 +123,13 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
                 w.absmax_model = st->absmax_x + ((t - 1) & 1);
             }
             if (defer_ok) w.deferred = &parts;
-            if (diff_ready) w.model_diff = model_diff;
+            if (diff_ready) w.model_diff = kept.model_diff;
+            if (diff_ready && prep_ready) w.dev_max = dev_max;
             bool prepared_next = false;
-            if (prep_sets) {
-                if (prep_ready) w.prep_in = prep_sets + (t & 1) * prep_set_words;
-                if (t + 1 < t0 + rounds) w.prep_out = prep_sets + ((t + 1) & 1) * prep_set_words;
+            if (kept.prep_sets[0]) {
+                w.prep = kept.prep;
+                if (prep_ready) w.prep_in = kept.prep_sets[t & 1];
+                if (t + 1 < t0 + rounds) w.prep_out = kept.prep_sets[(t + 1) & 1];
                 w.prepared_next = &prepared_next;
             }
             if (worker_events && g == 0) {                       // (a null pair: this round's launch is a plain one)
@@ -162,16 +152,18 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         float *dx_next = st->delta_x + ((t + 1) % slots);
         model_pending = fusable && t + 1 < t0 + rounds;
         // (the difference is of use only to a next round of this call)
-        float *diff_out = (model_diff && !model_pending && t + 1 < t0 + rounds &&
-                           dq::master_leaves_model_diff(prob->d, cfg->b_x, parts.parts > 0)) ? model_diff : nullptr;
+        float *diff_out = (kept.model_diff && t + 1 < t0 + rounds &&
+                           dq::master_leaves_model_diff(prob->d, cfg->b_x, parts.parts > 0)) ? kept.model_diff : nullptr;
         diff_ready = diff_out != nullptr;
+        // (where this round's worker launch has prepared the next one, and cleared the word)
+        dev_max = diff_out && prep_ready && parts.parts > 0 && cfg->algo == DQ_ALGO_SPARSE ? reinterpret_cast<uint32_t *>(kept.prep_sets[(t + 1) & 1]) + kept.dev_max : nullptr;
         if (parts.parts > 0)
             rc = dq::master_step_from_parts_impl(parts, 0u, it, st->packed, st->ld_words, st->delta,
                                                  st->nnz && cfg->algo == DQ_ALGO_SPARSE ? st->nnz + t * cfg->M : nullptr,
                                                  cfg->M, cfg->b, scale, cfg->each, st->g_snap, st->x, acc ? st->y : nullptr,
                                                  st->x_snap, acc ? st->xsum : nullptr, eta, theta, prob->l1, prob->d, cfg->b_x,
                                                  cfg->seed, it + 1u, xq_next, dx_next, st->absmax_x + (t & 1), st->status,
-                                                 /*absmax_zeroed=*/true, stream, diff_out, model_pending);
+                                                 /*absmax_zeroed=*/true, stream, diff_out, dev_max, model_pending);
         else if (model_pending)
             rc = dq::master_update_impl(st->packed, st->ld_words, st->delta, cfg->M, cfg->b, scale, cfg->each, st->g_snap,
                                         st->x, acc ? st->y : nullptr, st->x_snap, acc ? st->xsum : nullptr, eta, theta,

@@ -605,3 +605,24 @@ def test_csr_rounds_of_one_call_equal_single_rounds(dq, d, b_x, algo, b, B):
     for name in ("packed", "delta", "x", "xq", "delta_x", "status") + (("y", "xsum") if algo == "acc" else ()):
         assert torch.equal(getattr(one, name), getattr(many, name)), name
     assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
+
+
+@pytest.mark.parametrize("d,M,B", [(4097, 5, 24), (20958, 16, 33), (30211, 3, 150)])
+@pytest.mark.parametrize("l2", [1e-4, 50.0])
+def test_csr_sparsified_rounds_of_one_call_equal_single_rounds(dq, d, M, B, l2):
+    """Alg. 2 on CSR features: between the rounds of a call a worker finds ||alpha||_inf among the columns that its rows touch
+    (l2 = 1e-4), unless the others may exceed them (l2 = 50: the whole vector is looked at); in calls of a single round
+    always from the whole vector.  Everything must be identical."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    p = synth.sparse_text_logistic(500, d, mean_nnz=30.0, seed=5)
+    P = dq.DeviceProblem.from_host(p)
+    P = dq.DeviceProblem(n=P.n, d=P.d, y=P.y, indptr=P.indptr, indices=P.indices, values=P.values, l2=l2, l1=1e-5)
+    one, many = (DoubleQuantTrainer(P, "sparse", M, B, 8, 4, 5, 0.01, seed=3) for _ in range(2))
+    one.epoch_prologue(); many.epoch_prologue()
+    one.rounds(0, 5)
+    for t in range(5):
+        many.rounds(t, 1)
+    torch.cuda.synchronize()
+    for name in ("packed", "delta", "nnz", "x", "xq", "delta_x", "status"):
+        assert torch.equal(getattr(one, name), getattr(many, name)), name
+    assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0

@@ -48,3 +48,26 @@ def test_the_full_gradient_masks_every_column_that_can_pass_the_end(tmp_path):
     }
     """)
     assert out == "", out[:2000]
+
+
+def test_both_sets_of_prepared_mini_batches_fit_the_workspace_of_a_run(tmp_path):
+    """CSR features, with and without the row of differences: two sets of M mini-batches fit what the workspace holds behind
+    its rows, a mini-batch's entries and their snapshot values fit its room, and no mini-batch is given less than before."""
+    out = _sweep(tmp_path, """
+    const int workers[] = {1, 2, 3, 8, 16, 63, 127}, rows[] = {1, 2, 31, 32, 255, 256};
+    for (int64_t d = 1; d < (1ll << kColBits); d += 1 + d / 97)
+        for (int second = 0; second < 2; ++second)
+            for (int M : workers)
+                for (int B : rows)
+                    for (int snaps = 0; snaps < 2; ++snaps) {
+                        CsrPlan p;
+                        csr_plan(d, second, p);
+                        const PrepRoom r = csr_prep_room(d, M, B, p, snaps);
+                        const int64_t words = pad4(d) + 2 * M * csr_prep_stride(d), at = PrepLayout(B).entries;
+                        bool ok = r.stride % 4 == 0 && (snaps ? 0 : pad4(d)) + 2 * M * r.stride <= words && r.cap <= p.cap;
+                        ok = ok && at + 2ll * r.cap <= r.stride && (!snaps || (at + 3ll * r.snap_cap <= r.stride && r.snap_cap >= 1));
+                        ok = ok && r.cap >= csr_prep_cap(d, p) && PrepLayout(B).dev_max < PrepLayout(B).y && PrepLayout(B).dev_max > PrepLayout(B).pre + B;
+                        if (!ok) std::printf("d %ld M %d B %d %d %d\\n", (long)d, M, B, second, snaps);
+                    }
+    """)
+    assert out == "", out[:2000]
