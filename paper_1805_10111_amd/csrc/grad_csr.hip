@@ -415,16 +415,16 @@ __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta
 // worker launch does all of that for the NEXT round, on compute units the launch leaves idle, and leaves it in
 // memory as PrepRoom::stride 32-bit words per worker:
 //   [0] 1 when the flat run is there (the batch has at most PrepRoom::cap entries), else 0   [1] number of entries
-//   [2] the largest |value| among them, as bits (with the flat run only)   [3] 1 when the snapshot values are there
+//   [2] the largest |value| among them, as bits, if they are more than kPrepNoMax   [3] 1 when the snapshot values are there
 //   row[B] len[B] pre[B + 4] y[B] z[B], each from a multiple of four words on      (RowMeta's fields)
 //   pairs (column | row << kColBits, value bits), [1] of them; room for PrepRoom::snap_cap pairs further on the snapshot
 //   at their columns, if there are no more of them than that
 // The next round's blocks then start from one round trip to memory instead of a chain of five.
 
-// Stage, margins and scatter for a prepared mini-batch: `entry` is its flat run of `total` <= cap entries, `first`
+// Stage, margins and scatter for a prepared mini-batch without cached margins: `entry` is its flat run of `total` <= cap entries, `first`
 // what the caller has already loaded of it (positions threadIdx.x + u * kCsrThreads, clamped to the buffer), meta
 // holds the rows.  The rest as csr_process_rows.
-template <bool SECOND, typename VecReq, typename VecVal, typename CoefFn>
+template <typename VecReq, typename VecVal, typename CoefFn>
 __device__ __forceinline__ void csr_process_prepared(const int2 *entry, const int2 (&first)[kStageFlight], int total,
                                                      RowMeta &meta, int nrows, int *acc, int c0, int c1, const CsrStage &sg,
                                                      FixedAcc &fx, uint32_t *su, int *poison, VecReq vec_req,
@@ -449,7 +449,7 @@ __device__ __forceinline__ void csr_process_prepared(const int2 *entry, const in
                 vmax = max(vmax, abs_bits(val));
                 sg.entry[p] = e[u];
                 sg.prod_a[p] = val * f.x;
-                if (SECOND) sg.prod_b[p] = val * f.y;
+                sg.prod_b[p] = val * f.y;
             }
         }
     };
@@ -460,12 +460,16 @@ __device__ __forceinline__ void csr_process_prepared(const int2 *entry, const in
         for (int u = 0; u < kStageFlight; ++u) e[u] = entry[min(p0 + u * kCsrThreads, total - 1)];
         stage_batch(p0, e);
     }
-    csr_reduce_group<SECOND>(meta, 0, nrows, 0, total, vmax, acc, c0, c1, sg, fx, su, poison, coef_of);
+    csr_reduce_group<true>(meta, 0, nrows, 0, total, vmax, acc, c0, c1, sg, fx, su, poison, coef_of);
     __syncthreads();
 }
 
-// The same for a batch of at most kCsrInFlight entries, which stay in the registers they were loaded into: `e` is all of
-// the flat run, `vmax` its largest |value|, and lane l of wavefront w holds row w + 16 l of the batch (its length, its
+// Up to here the preparing block, not the one that reads what it left, is what a launch waits for: then the reader forms
+// the largest |value| (4753 columns, 8 workers of 13 rows: 14.9 us a round where the preparing block did, now 14.1).
+constexpr int kPrepNoMax = kCsrThreads;
+
+// The same with cached margins; the first kCsrInFlight entries, nearly always all of them, stay in the registers they were
+// loaded into: `e` is the flat run's beginning, `entry` the run, `vmax` its largest |value|, and lane l of wavefront w holds row w + 16 l of the batch (its length, its
 // first entry's position, and whatever coef_of(zdiff) needs besides its margin); the first operands are left in `operand`.  What a block waits for here is latency,
 // one phase after another, so there are as few phases as the sums allow: products to LDS, barrier, margins and
 // coefficients, barrier, scatter.  The sums are those of csr_reduce_group, bit for bit.
@@ -507,18 +511,18 @@ __device__ __forceinline__ void csr_lane_margins(const float *prod, int total, i
 }
 
 template <typename VecReq, typename VecVal, typename CoefFn>
-__device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlight], int total, float vmax, int nrows, int my_len,
+__device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlight], const int2 *entry, int total, float vmax, int nrows, int my_len,
                                                       int my_pre, float *coef, int *acc, int c0, int c1, float *prod,
-                                                      FixedAcc &fx, int *poison, VecReq vec_req, VecVal vec_val, CoefFn coef_of,
+                                                      FixedAcc &fx, uint32_t *su, int *poison, VecReq vec_req, VecVal vec_val, CoefFn coef_of,
                                                       float (&operand)[kStageFlight])
 {
     int col[kStageFlight];
-    decltype(vec_req(0, 0)) raw[kStageFlight];
+    decltype(vec_req(0, 0, 0)) raw[kStageFlight];
 #pragma unroll
     for (int u = 0; u < kStageFlight; ++u) {
         // (past the end `e` holds whatever the buffer held: column 0 is gathered instead)
         col[u] = static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? e[u].x & kColMask : 0;
-        raw[u] = vec_req(col[u], u);
+        raw[u] = vec_req(col[u], u, u);
     }
 #pragma unroll
     for (int u = 0; u < kStageFlight; ++u) {
@@ -528,7 +532,18 @@ __device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlig
             prod[p] = __int_as_float(e[u].y) * operand[u];
         }
     }
+    for (int p = threadIdx.x + kCsrInFlight; p < total; p += kCsrThreads) {
+        const int2 more = entry[p];
+        const int c = more.x & kColMask;
+        prod[p] = __int_as_float(more.y) * vec_val(vec_req(c, -1, p), c).x;
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    if (total <= kPrepNoMax) {
+        const uint32_t top = wave_max_u32(static_cast<int>(threadIdx.x) < total ? abs_bits(__int_as_float(e[0].y)) : 0u);
+        if (lane == 0) su[threadIdx.x / kWave] = top;
+    }
     __syncthreads();
+    if (total <= kPrepNoMax) vmax = __uint_as_float(wave_max_u32(lane < kCsrWaves ? su[lane] : 0u));
     // (a wavefront has one or two rows of the common batches of up to 32)
     if (nrows <= 2 * kCsrWaves) csr_lane_margins<2>(prod, total, nrows, my_len, my_pre, coef_of, coef);
     else csr_lane_margins<kFlight>(prod, total, nrows, my_len, my_pre, coef_of, coef);
@@ -542,6 +557,12 @@ __device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlig
     for (int u = 0; u < kStageFlight; ++u)
         if (static_cast<int>(threadIdx.x) + u * kCsrThreads < total && col[u] >= c0 && col[u] < c1)
             atomicAdd(&acc[col[u] - c0], fixed_term(cf[u], __int_as_float(e[u].y), two_k));
+    for (int p = threadIdx.x + kCsrInFlight; p < total; p += kCsrThreads) {
+        const int2 more = entry[p];
+        const int c = more.x & kColMask;
+        if (c >= c0 && c < c1)
+            atomicAdd(&acc[c - c0], fixed_term(coef[(more.x >> kColBits) & (kCsrMaxRows - 1)], __int_as_float(more.y), two_k));
+    }
     __syncthreads();
 }
 
@@ -591,20 +612,22 @@ struct CsrWorkerArgs {
 // MODEL == kModelPending: it comes as x itself, and every block quantizes what it needs of it: the columns of its entries,
 // and its slice's for the dense part (the blocks of worker 0 store those as the message).  That saves the launch of the
 // message, 2.9 us, and costs two gathers per entry for one and a Philox block for each entry and quad: 20,958 columns, eight
-// workers of 32 rows 13.1 -> 11.7 us a round.  At 47,236 columns (two quads of a slice per thread, 75 entries a row) it
-// costs more than the launch, 29.0 -> 30.6 us: see csr_model_fusable.  (Measured and dropped: x and its random word as
-// a pair per column, left by the master, so that an entry takes one 8-byte gather more and no Philox block: 13.0 us; the
-// snapshot values beside the prepared entries: 12.3 us.)
+// workers of 32 rows 13.1 -> 11.7 us a round (11.5 with the snapshot beside the prepared entries).  At 47,236 columns (two
+// quads of a slice per thread, 75 entries a row) it costs more than the launch, 29.0 -> 30.6 us: see csr_run_layout.
+// (Measured and dropped: x and its random word as a pair per column, left by the master, so that an entry takes an
+// 8-byte gather and no Philox block: 13.0 us; the slice's own quads during the gathers instead of before them: 12.2 us.)
 // COMMON: the gradient fits in LDS as one window (SLICED: always), the mini-batch in one pass of rows (B <= kCsrMaxRows),
 // and the margins at the snapshot are cached (z_snap given) -- the kernel is then straight-line code with one set of the
 // row-processing routines, which leaves the compiler far fewer values to keep alive across its phases.
+// PREP: mini-batches may be prepared ahead (prep_in, prep_out); a single step has no use for that code, whose many values
+// it would pay for in scalar registers kept elsewhere.
 // SLICED: the blocks of a worker share its columns.  Every block stages the whole mini-batch and forms all margins, but
 // scatters into, finishes and stores only the columns of its own slice, `win` of them: an eighth of the passes over
 // the vector, which are what a block of the other form spends half of its time on (clearing, float window, maximum,
 // quantization), and no limit on the width from LDS.  What needs the whole gradient -- scale, sparsifier,
 // quantization -- is a later launch's, which finds the gradient in memory and its slices' maxima beside it.
 // Measured: see csr_worker.
-template <int MODEL, bool COMMON, bool SLICED>
+template <int MODEL, bool COMMON, bool SLICED, bool PREP>
 __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorkerArgs a)
 {
     constexpr bool DIFF = MODEL == kModelDiff, PENDING = MODEL == kModelPending;
@@ -635,7 +658,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     model_key.worker = DQ_MASTER_ID;
     model_key.tag = DQ_TAG_MODEL;
     // identical copies of the worker that share the tail, or slices (a last one more prepares the next round instead)
-    const int slice = blockIdx.y, nslices = static_cast<int>(gridDim.y) - (a.prep_out ? 1 : 0);
+    const int slice = blockIdx.y, nslices = static_cast<int>(gridDim.y) - (PREP && a.prep_out ? 1 : 0);
     float *alpha_row = (!SLICED && !COMMON && a.alpha_ws) ? a.alpha_ws + static_cast<int64_t>(m) * a.ld_ws : nullptr;   // only with several windows
 
     const float inv_B = 1.0f / static_cast<float>(a.B);      // the mean over the mini-batch, as one multiplication per row
@@ -696,7 +719,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         }
         return ri;
     };
-    if (a.prep_out && slice == nslices) {
+    if (PREP && a.prep_out && slice == nslices) {
         // ---- the extra block: worker m's mini-batch of the next round, left in memory (see PrepLayout)
         StreamKey next_key = a.key;
         next_key.iter = a.next_iter;
@@ -708,7 +731,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             meta.len[threadIdx.x] = ri.len;
         }
         csr_prefix_lengths(meta, nrows);
-        const PrepLayout at(nrows);
+        const PrepLayout at(COMMON ? nrows : kCsrMaxRows);
         int32_t *out = a.prep_out + static_cast<int64_t>(m) * a.prep_stride;
         const int total = meta.pre[nrows];
         const bool fits = total <= a.prep_cap;
@@ -729,7 +752,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         int2 *entry = reinterpret_cast<int2 *>(out + at.entries);
         const int lane = threadIdx.x & (kWave - 1);
         uint32_t vmax = 0;
-        const bool snaps = total <= a.snap_cap;
+        const bool snaps = COMMON && total <= a.snap_cap;      // (the same for every thread)
         float *entry_snap = reinterpret_cast<float *>(entry + a.snap_cap);
         for (int p0 = threadIdx.x; p0 - lane < total; p0 += kStageFlight * kCsrThreads) {
             int64_t src[kStageFlight];
@@ -746,7 +769,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
 #pragma unroll
             for (int u = 0; u < kStageFlight; ++u)
                 if (p0 + u * kCsrThreads < total) entry[p0 + u * kCsrThreads] = make_int2(col[u] | tag[u], __float_as_int(val[u]));
-            if (snaps) {                                       // (the same for every thread)
+            if (snaps) {
                 float xs[kStageFlight];
 #pragma unroll
                 for (int u = 0; u < kStageFlight; ++u) xs[u] = a.x_snap[col[u]];
@@ -756,12 +779,15 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             }
             // (a position past the end repeats an entry of the batch)
 #pragma unroll
-            for (int u = 0; u < kStageFlight; ++u) vmax = max(vmax, abs_bits(val[u]));
+            for (int u = 0; COMMON && u < kStageFlight; ++u) vmax = max(vmax, abs_bits(val[u]));
         }
-        vmax = block_max_u32(vmax, su);
-        if (threadIdx.x == 0) {
-            out[2] = static_cast<int>(vmax);
-            out[3] = snaps ? 1 : 0;
+        if constexpr (COMMON) {
+            if (threadIdx.x == 0) out[3] = snaps ? 1 : 0;
+            if (total <= kPrepNoMax) return;                   // (the same for every thread)
+            vmax = wave_max_u32(vmax);
+            if (lane == 0) atomicMax(&sh_max, vmax);           // (zero since before the barriers of the prefix sums)
+            __syncthreads();
+            if (threadIdx.x == 0) out[2] = static_cast<int>(sh_max);
         }
         return;
     }
@@ -810,7 +836,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     // bit for bit.  Returns false (for every thread) where it is not.  72,000 x 20,958, 16 workers of 64 rows: the pass over
     // 5240 quads and the tail behind it took half of the kernel, 12.3 us; now 10.3.
     const int64_t tail_per = (((d + 3) / 4 + nslices - 1) / nslices + kWave - 1) / kWave * kWave, tail_first = tail_per * slice;
-    const auto sparsify_touched = [&](const int2 (&e)[kStageFlight], const float (&operand)[kStageFlight], int total,
+    const auto sparsify_touched = [&](const int2 (&e)[kStageFlight], const float (&operand)[kStageFlight], const int2 *entry, int total,
                                       const FixedAcc &fx, float dev_max, float4 own_diff, uint4 own_words) {
         const float unit = ldexpf(1.0f, -fx.k);
         uint32_t seen = 0;
@@ -821,6 +847,12 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                 v += static_cast<float>(acc[e[u].x & kColMask]) * unit;
                 seen = max(seen, abs_bits(v));
             }
+        for (int p = threadIdx.x + kCsrInFlight; p < total; p += kCsrThreads) {
+            const int c = entry[p].x & kColMask;
+            float v = a.l2 * a.model_diff[c];
+            v += static_cast<float>(acc[c]) * unit;
+            seen = max(seen, abs_bits(v));
+        }
         seen = block_max_u32(seen, su);
         // (|Q(x) - x| is at most the scale and a rounding of x; a degenerate scale is none)
         const float rest = a.l2 * ((dev_max + msg.delta_x) * 1.001f);
@@ -867,10 +899,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         constexpr int kAhead = PENDING ? 1 : 2;
         float4 ahead[kAhead];
         bool have_ahead = false;
-        if (a.prep_in) {
+        if (PREP && a.prep_in) {
             // ---- this round's mini-batch was prepared: descriptors and the first entries are requested together
             // (a.B <= kCsrMaxRows, one window or slice)
-            const PrepLayout at(a.B);
+            const PrepLayout at(COMMON ? a.B : kCsrMaxRows);   // (of the launch that left it: constant where registers are short)
             const int32_t *in = a.prep_in + static_cast<int64_t>(m) * a.prep_stride;
             const int2 *entry = reinterpret_cast<const int2 *>(in + at.entries);
             const int nrows = a.B;
@@ -887,13 +919,15 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                 for (int64_t j = 4ll * threadIdx.x; j < c1p - c0; j += 4ll * kCsrThreads)
                     *reinterpret_cast<int4 *>(acc + j) = make_int4(0, 0, 0, 0);
             };
+            // (COMMON: lane l of wavefront w holds row w + 16 l, else thread r row r)
+            const int lr = !COMMON ? static_cast<int>(threadIdx.x)
+                                   : static_cast<int>(threadIdx.x) / kWave + (static_cast<int>(threadIdx.x) & (kWave - 1)) * kCsrWaves;
+            const int tr = min(lr, nrows - 1);
+            const int p_row = in[at.row + tr], p_len = in[at.len + tr], p_pre = in[at.pre + tr];
+            const float p_y = __int_as_float(in[at.y + tr]), p_z = __int_as_float(in[at.z + tr]);
+            request_first();
             if constexpr (COMMON) {
                 const float vmax = __int_as_float(in[2]);
-                const int lr = static_cast<int>(threadIdx.x) / kWave + (static_cast<int>(threadIdx.x) & (kWave - 1)) * kCsrWaves;
-                const int tr = min(lr, nrows - 1);
-                const int p_row = in[at.row + tr], p_len = in[at.len + tr], p_pre = in[at.pre + tr];
-                const float p_y = __int_as_float(in[at.y + tr]), p_z = __int_as_float(in[at.z + tr]);
-                request_first();
                 const int have_snaps = PENDING ? in[3] : 0;
                 const float dev_max = DIFF && !SLICED ? __int_as_float(a.prep_in[a.dev_max_at]) : 0.0f;
                 if constexpr (PENDING)
@@ -941,47 +975,39 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
                     key.tag = DQ_TAG_SPARSIFY;
                     own_words = stream_block(key, static_cast<uint32_t>(q));
                 }
-                if (ready && total <= kCsrInFlight) {             // (the same for every thread)
+                if (ready) {                                      // (the same for every thread)
                     if (PENDING && !have_snaps)
 #pragma unroll
                         for (int u = 0; u < kStageFlight; ++u)
                             first_snap[u] = a.x_snap[static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? first[u].x & kColMask : 0];
-                    csr_process_in_flight(first, total, vmax, nrows, lr < nrows ? p_len : 0, p_pre, meta.coef, acc,
-                                          static_cast<int>(c0), static_cast<int>(c1), sg.prod_a, fx, &sh_poison,
-                                          [&](int c, int u) {
-                                              if constexpr (PENDING) return Gather{0u, 0u, first_snap[u], a.model_diff[c]};
-                                              else return vec_req(c);
+                    csr_process_in_flight(first, entry, total, vmax, nrows, lr < nrows ? p_len : 0, p_pre, meta.coef, acc,
+                                          static_cast<int>(c0), static_cast<int>(c1), sg.prod_a, fx, su, &sh_poison,
+                                          [&](int c, int u, int p) {           // (entry p at column c; u >= 0: one of the first)
+                                              if constexpr (!PENDING) return vec_req(c);
+                                              else return Gather{0u, 0u, u >= 0 ? first_snap[u] : have_snaps ? entry_snap[p] : a.x_snap[c], a.model_diff[c]};
                                           }, vec_val,
                                           [&](float dz) { return p_row < 0 ? 0.0f : vr_slope_diff(p_y, p_z, dz) * inv_B; }, operand);
                     rows_done = true;
                     if constexpr (DIFF && !SLICED) {
-                        if (short_tail && sparsify_touched(first, operand, total, fx, dev_max, own_diff, own_words)) return;
+                        if (short_tail && sparsify_touched(first, operand, entry, total, fx, dev_max, own_diff, own_words)) return;
                     }
                 }
             } else {
-                request_first();
                 clear_window();
             }
-            if (ready && !rows_done) {
-                const int tr = min(static_cast<int>(threadIdx.x), kCsrMaxRows - 1);
-                const int p_row = in[at.row + tr], p_len = in[at.len + tr], p_pre = in[at.pre + tr];
-                const int p_last = in[at.pre + nrows];
-                const float p_y = __int_as_float(in[at.y + tr]), p_z = __int_as_float(in[at.z + tr]);
-                if (static_cast<int>(threadIdx.x) < nrows) {
-                    meta.row[threadIdx.x] = p_row;
-                    meta.len[threadIdx.x] = p_len;
-                    meta.pre[threadIdx.x] = p_pre;
-                    sh_y[threadIdx.x] = p_y;
-                    meta.z[threadIdx.x] = p_z;
+            if (!COMMON && ready) {
+                if (lr < nrows) {
+                    meta.row[lr] = p_row;
+                    meta.len[lr] = p_len;
+                    meta.pre[lr] = p_pre;
+                    sh_y[lr] = p_y;
+                    meta.z[lr] = p_z;
                 }
-                if (threadIdx.x == 0) meta.pre[nrows] = p_last;
+                if (threadIdx.x == 0) meta.pre[nrows] = total;
                 __syncthreads();
-                if (have_z)
-                    csr_process_prepared<false>(entry, first, total, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1),
-                                                sg, fx, su, &sh_poison, vec_req, vec_val, coef_of);
-                else
-                    csr_process_prepared<true>(entry, first, total, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1),
-                                               sg, fx, su, &sh_poison, vec_req, vec_val, coef_of);
+                // (one pass of rows in one window or slice, and not COMMON: no cached margins)
+                csr_process_prepared(entry, first, total, meta, nrows, acc, static_cast<int>(c0), static_cast<int>(c1), sg, fx, su,
+                                     &sh_poison, vec_req, vec_val, coef_of);
                 rows_done = true;
             }
         }
@@ -1712,18 +1738,6 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     }
     const bool common = (sliced || plan.nwin == 1) && a.B <= kCsrMaxRows && a.z_snap != nullptr;
     if (a.x_model && !(sliced && common)) return DQ_ERR_INVALID_ARG;       // (see csr_run_layout)
-    static std::once_flag attr_once[9];
-    static hipError_t attr_rc[9];
-    void (*const kernels[9])(const CsrWorkerArgs) = {
-        csr_worker_kernel<kModelMessage, false, false>, csr_worker_kernel<kModelMessage, true, false>,
-        csr_worker_kernel<kModelDiff, false, false>,    csr_worker_kernel<kModelDiff, true, false>,
-        csr_worker_kernel<kModelMessage, false, true>,  csr_worker_kernel<kModelMessage, true, true>,
-        csr_worker_kernel<kModelDiff, false, true>,     csr_worker_kernel<kModelDiff, true, true>,
-        csr_worker_kernel<kModelPending, true, true>};
-    const int which = a.x_model ? 8 : (sliced ? 4 : 0) + (k.model_diff ? 2 : 0) + (common ? 1 : 0);
-    const auto kernel = kernels[which];
-    int rc = allow_big_lds(kernel, attr_once[which], attr_rc[which]);
-    if (rc != DQ_OK) return rc;
     // a round of dq_run_rounds that has a successor in its call prepares that round's mini-batches in one more block
     // per worker (on compute units the launch leaves idle), and reads its own if the round before left them
     const bool can_prepare = !a.idx && a.B <= kCsrMaxRows && (sliced || plan.nwin == 1) && a.M * (slices + 1) <= 256;
@@ -1735,6 +1749,22 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
         k.next_iter = a.iter + 1u;
     }
     if (a.prepared_next) *a.prepared_next = k.prep_out != nullptr;
+    static std::once_flag attr_once[13];
+    static hipError_t attr_rc[13];
+    void (*const kernels[13])(const CsrWorkerArgs) = {
+        csr_worker_kernel<kModelMessage, false, false, true>,  csr_worker_kernel<kModelMessage, true, false, true>,
+        csr_worker_kernel<kModelDiff, false, false, true>,     csr_worker_kernel<kModelDiff, true, false, true>,
+        csr_worker_kernel<kModelMessage, false, true, true>,   csr_worker_kernel<kModelMessage, true, true, true>,
+        csr_worker_kernel<kModelDiff, false, true, true>,      csr_worker_kernel<kModelDiff, true, true, true>,
+        csr_worker_kernel<kModelPending, true, true, true>,    csr_worker_kernel<kModelMessage, false, false, false>,
+        csr_worker_kernel<kModelMessage, true, false, false>,  csr_worker_kernel<kModelMessage, false, true, false>,
+        csr_worker_kernel<kModelMessage, true, true, false>};
+    const int which = a.x_model ? 8
+                      : !k.model_diff && !k.prep_in && !k.prep_out && (sliced || plan.nwin == 1) ? 9 + (sliced ? 2 : 0) + (common ? 1 : 0)
+                      : (sliced ? 4 : 0) + (k.model_diff ? 2 : 0) + (common ? 1 : 0);
+    const auto kernel = kernels[which];
+    int rc = allow_big_lds(kernel, attr_once[which], attr_rc[which]);
+    if (rc != DQ_OK) return rc;
     const dim3 grid(static_cast<unsigned>(a.M), slices + (k.prep_out ? 1u : 0u)), block(kCsrThreads);
     if (a.ev_start && a.ev_stop)      // the kernel's own start and end times go to the two events
         hipExtLaunchKernelGGL(kernel, grid, block, static_cast<uint32_t>(lds), st, a.ev_start, a.ev_stop, 0u, k);
