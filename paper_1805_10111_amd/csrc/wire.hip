@@ -71,13 +71,21 @@ __global__ __launch_bounds__(kWireThreads) void sparse_encode_kernel(
     uint32_t *sh_stream = sh, *sh_row = sh + span;
     const int m = blockIdx.x;
     const uint32_t *row = packed + static_cast<int64_t>(m) * ld_words;
-    for (int w = threadIdx.x; w < per * kWireThreads; w += kWireThreads) {
-        uint32_t v = row[min(w, row_words - 1)];
-        if (w >= row_words - 1) {                                 // fields past the last coordinate are not part of the row
-            const int left = w >= row_words ? 0 : (d * FIELD - 1) % 32 + 1;
-            v = left == 32 ? v : v & ((1u << left) - 1u);
+    // (the words of a thread are requested together: one after the other they were `per` trips to memory, 7 at 47,236 columns)
+    constexpr int kFlight = 8;
+    for (int w0 = threadIdx.x; w0 < per * kWireThreads; w0 += kFlight * kWireThreads) {
+        uint32_t v[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) v[u] = row[min(w0 + u * kWireThreads, row_words - 1)];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            const int w = w0 + u * kWireThreads;
+            if (w >= row_words - 1) {                             // fields past the last coordinate are not part of the row
+                const int left = w >= row_words ? 0 : (d * FIELD - 1) % 32 + 1;
+                v[u] = left == 32 ? v[u] : v[u] & ((1u << left) - 1u);
+            }
+            if (w < per * kWireThreads) sh_row[w] = v[u];
         }
-        sh_row[w] = v;
     }
     for (int w = threadIdx.x; w < span; w += kWireThreads) sh_stream[w] = 0u;
     __syncthreads();
