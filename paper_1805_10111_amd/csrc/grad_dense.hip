@@ -17,7 +17,6 @@
 // chip's L2 slices; a per-block device-scope fence was measured to cost far more).
 // Either way the summation order is fixed, so results are run-to-run deterministic.
 #include <algorithm>
-#include <type_traits>
 #include <mutex>
 
 #include <hip/hip_ext.h>
@@ -606,22 +605,27 @@ __global__ __launch_bounds__(kFinishThreads) void vr_dense_finish_kernel(const V
 #pragma unroll
             for (int u = 0; u < 8; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
         }
-        // what is left of them in one group, its last requests at clamped positions and not added: two or three single ones
-        // were a trip to memory each (60,000 x 784, ten workers of 100 rows, P = 7: 5.1 us a launch, now 4.6)
-        const auto rest = [&](auto width) {
-            constexpr int G = decltype(width)::value;
-            float4 t[G];
+        if (p + 4 == a.P) {
+            float4 t[4];
 #pragma unroll
-            for (int u = 0; u < G; ++u) t[u] = *reinterpret_cast<const float4 *>(base + min(p + u, a.P - 1) * a.ldp + col);
+            for (int u = 0; u < 4; ++u) t[u] = *reinterpret_cast<const float4 *>(base + (p + u) * a.ldp + col);
 #pragma unroll
-            for (int u = 0; u < G; ++u)
+            for (int u = 0; u < 4; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
+        } else if (p + 1 < a.P) {
+            // any other rest in one group too, its last requests at clamped positions and not added: two or three single
+            // ones were a trip to memory each (60,000 x 784, ten workers of 100 rows, P = 7: 5.1 us a launch, now 4.6)
+            float4 t[7];
+#pragma unroll
+            for (int u = 0; u < 7; ++u) t[u] = *reinterpret_cast<const float4 *>(base + min(p + u, a.P - 1) * a.ldp + col);
+#pragma unroll
+            for (int u = 0; u < 7; ++u)
                 if (p + u < a.P) {                                  // (the same for every thread)
                     s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w;
                 }
-        };
-        if (p + 4 < a.P) rest(std::integral_constant<int, 8>{});
-        else if (p + 1 < a.P) rest(std::integral_constant<int, 4>{});
-        else if (p < a.P) rest(std::integral_constant<int, 1>{});
+        } else if (p < a.P) {
+            const float4 t = *reinterpret_cast<const float4 *>(base + p * a.ldp + col);
+            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+        }
         float q[4];
         model_quad_values<MODEL8>(msg, mq, col, d, q);
         const float4 v = make_float4(s.x + a.l2 * (q[0] - xs[0]), s.y + a.l2 * (q[1] - xs[1]), s.z + a.l2 * (q[2] - xs[2]),
