@@ -416,7 +416,8 @@ __device__ __forceinline__ void csr_process_rows(const CsrView &A, RowMeta &meta
 // memory as PrepRoom::stride 32-bit words per worker:
 //   [0] 1 when the flat run is there (the batch has at most PrepRoom::cap entries), else 0   [1] number of entries
 //   [2] the largest |value| among them, as bits, if they are more than kPrepNoMax   [3] 1 when the snapshot values are there
-//   row[B] len[B] pre[B + 4] y[B] z[B], each from a multiple of four words on      (RowMeta's fields)
+//   pre[kCsrMaxRows + 3], a word of the master's (WorkerArgs::dev_max; in the first worker's block), row[B] len[B] y[B]
+//   z[B], each from a multiple of four words on      (RowMeta's fields)
 //   pairs (column | row << kColBits, value bits), [1] of them; room for PrepRoom::snap_cap pairs further on the snapshot
 //   at their columns, if there are no more of them than that
 // The next round's blocks then start from one round trip to memory instead of a chain of five.

@@ -68,13 +68,16 @@ inline bool csr_plan(int64_t d, bool second, CsrPlan &p)
     return true;
 }
 
-// A mini-batch of B rows prepared ahead of its round: layout in 32-bit words (see grad_csr.hip), for `cap` entries.
+// A mini-batch prepared ahead of its round: layout in 32-bit words (see grad_csr.hip) of its tables for B rows, for `cap`
+// entries.  The kernels with cached margins lay it out for the rows of the batch, those without for kCsrMaxRows; the master,
+// which does not know which of them reads next, writes one word of it, so that word lies in the same place in every
+// layout: the row starts come first, as many as a block takes, and it is the last behind them.
 struct PrepLayout {
-    int row, len, pre, y, z, entries;
-    int dev_max;       // a word behind the row starts: see WorkerArgs::dev_max
+    int pre, dev_max;  // (see WorkerArgs::dev_max)
+    int row, len, y, z, entries;
     constexpr explicit PrepLayout(int B)
-        : row(4), len(row + (B + 3) / 4 * 4), pre(len + (B + 3) / 4 * 4), y(pre + (B + 3) / 4 * 4 + 4), z(y + (B + 3) / 4 * 4),
-          entries(z + (B + 3) / 4 * 4), dev_max(y - 1) {}
+        : pre(4), dev_max(pre + kCsrMaxRows + 3), row(dev_max + 1), len(row + (B + 3) / 4 * 4), y(len + (B + 3) / 4 * 4),
+          z(y + (B + 3) / 4 * 4), entries(z + (B + 3) / 4 * 4) {}
 };
 constexpr int kPrepEntries = PrepLayout(kCsrMaxRows).entries;
 constexpr int64_t kPrepInts(int64_t cap) { return kPrepEntries + (2 * cap + 3) / 4 * 4; }

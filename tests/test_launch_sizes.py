@@ -71,3 +71,24 @@ def test_both_sets_of_prepared_mini_batches_fit_the_workspace_of_a_run(tmp_path)
                     }
     """)
     assert out == "", out[:2000]
+
+
+def test_the_word_that_the_master_leaves_beside_a_prepared_mini_batch_is_in_none_of_its_tables(tmp_path):
+    """CSR features: the master of a round writes PrepLayout::dev_max of a mini-batch prepared for B rows; the launch that left
+    it and the one that reads it lay it out for B rows or for as many as a block takes.  In either layout the word is
+    in no table, the tables hold their rows and do not overlap, and none reaches into the header or the entries."""
+    out = _sweep(tmp_path, """
+    for (int B = 1; B <= kCsrMaxRows; ++B)
+        for (int rows = B; rows <= kCsrMaxRows; rows += rows < kCsrMaxRows ? kCsrMaxRows - rows : 1) {
+            const PrepLayout at(rows);
+            const int word = PrepLayout(B).dev_max;
+            const int first[] = {0, at.row, at.len, at.pre, at.y, at.z, at.entries}, size[] = {4, B, B, B + 1, B, B, 1 << 20};
+            for (int i = 0; i < 7; ++i) {
+                if (word >= first[i] && word < first[i] + size[i]) std::printf("B %d of %d: word %d in table %d\\n", B, rows, word, i);
+                if (first[i] % 4) std::printf("B %d of %d: table %d not on a quad\\n", B, rows, i);
+                for (int j = 0; j < i; ++j)
+                    if (first[i] < first[j] + size[j] && first[j] < first[i] + size[i]) std::printf("B %d of %d: tables %d %d\\n", B, rows, j, i);
+            }
+        }
+    """)
+    assert out == "", out[:2000]
