@@ -1651,31 +1651,66 @@ static CsrSlices csr_step_slices(const dq_problem *prob, const WorkerArgs &a, co
     return csr_slices(prob->d, a.M, plan, a.z_snap == nullptr);
 }
 
+// How a step runs, for csr_worker, which launches it, and for csr_run_layout, which must know it beforehand.
+struct CsrStep {
+    CsrPlan plan;
+    CsrSlices sl;
+    bool sliced;               // split over the columns
+    unsigned blocks;           // per worker: the slices, or identical blocks that share the tail
+    bool split_sparsifier;     // not split over the columns, every block sparsifies its share into the workspace
+    bool common;               // csr_worker_kernel's COMMON
+    bool can_prepare;          // mini-batches may be prepared a round ahead: one more block per worker
+};
+
+static bool csr_step(const dq_problem *prob, const WorkerArgs &a, CsrStep &s)
+{
+    const int64_t d = prob->d;
+    if (!csr_plan(d, a.z_snap == nullptr, s.plan)) return false;
+    s.sl = csr_step_slices(prob, a, s.plan);
+    s.sliced = s.sl.count > 0;
+    const bool one_window = s.sliced || s.plan.nwin == 1, count_ok = !a.nnz_out || (a.sparsify && a.b >= 4);
+    // Few workers leave most compute units idle while each block spends a third of its time on the Philox rounds of
+    // the final quantization: then several identical blocks per worker share that part (not when the nonzero count is
+    // wanted and would need a sum across blocks, nor when the gradient lives in the per-worker workspace row).
+    s.blocks = 1;
+    if (a.packed && count_ok && s.plan.nwin == 1 && a.b != 32 && d >= 4096 && a.M * 4 <= 128) s.blocks = a.M * 8 <= 128 ? 8 : 4;
+    if (s.sliced) s.blocks = static_cast<unsigned>(s.sl.count);
+    // After the sparsifier the scale is ||beta||_inf, which needs every coordinate's random decision: sharing only the
+    // quantization would leave each identical block a whole Philox-and-two-divisions pass over the vector (9 of the
+    // 33 us of the step at d = 20958).  With workspace for a row per worker each block sparsifies its own slice into
+    // memory instead and the quantization becomes a second launch that takes the scale from the slices' maxima.
+    s.split_sparsifier = !s.sliced && s.blocks > 1 && a.sparsify && a.ws &&
+                         a.ws_bytes >= csr_workspace_bytes(DQ_OP_WORKER_STEP, prob, a.M, a.B);
+    s.common = one_window && a.B <= kCsrMaxRows && a.z_snap != nullptr;
+    s.can_prepare = one_window && !a.idx && a.B <= kCsrMaxRows && a.M * (s.blocks + 1) <= 256;
+    return true;
+}
+
 // The worker kernel quantizes the model where the step is split over the columns, its mini-batches are prepared ahead, its
 // margins cached, the model's message whole words per 64 quads, and no slice more than one quad per thread, as far as
 // it is the faster (see csr_worker_kernel).
 CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &a)
 {
     CsrRunLayout out{};
-    CsrPlan plan;
-    if (!a.ws || !csr_plan(prob->d, a.z_snap == nullptr, plan) || a.ws_bytes < csr_workspace_bytes(DQ_OP_VR_GRAD, prob, a.M, a.B)) return out;
+    CsrStep s;
+    if (!a.ws || !csr_step(prob, a, s) || a.ws_bytes < csr_workspace_bytes(DQ_OP_VR_GRAD, prob, a.M, a.B)) return out;
     char *base = static_cast<char *>(a.ws) + csr_run_offset(prob, a.M);
-    const CsrSlices sl = csr_step_slices(prob, a, plan);
-    out.pending = (a.b_x == 2 || a.b_x == 4 || a.b_x == 8) && sl.count > 0 && a.z_snap && !a.idx && a.B <= kCsrMaxRows &&
-                  sl.win <= 4 * kCsrThreads && a.M * (sl.count + 1) <= 256;
-    out.prep = csr_prep_room(prob->d, a.M, a.B, plan, out.pending);
+    out.pending = s.sliced && s.common && s.can_prepare && (a.b_x == 2 || a.b_x == 4 || a.b_x == 8) && s.sl.win <= 4 * kCsrThreads;
+    out.prep = csr_prep_room(prob->d, a.M, a.B, s.plan, out.pending);
     if (!out.pending) out.model_diff = reinterpret_cast<float *>(base);
     out.prep_sets[0] = reinterpret_cast<int32_t *>(base + (out.pending ? 0 : pad4(prob->d) * 4));
     out.prep_sets[1] = out.prep_sets[0] + a.M * out.prep.stride;
-    out.dev_max = a.B <= kCsrMaxRows ? PrepLayout(static_cast<int>(a.B)).dev_max : 0;
+    // (the kernel's short_tail; anywhere else the master would read x_snap and the chip meet on one word for nothing)
+    if (s.split_sparsifier && s.common && s.can_prepare) out.dev_max = PrepLayout(static_cast<int>(a.B)).dev_max;
     return out;
 }
 
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
 {
     const int64_t d = prob->d;
-    CsrPlan plan;
-    if (!csr_plan(d, a.z_snap == nullptr, plan)) return DQ_ERR_UNSUPPORTED;
+    CsrStep step;
+    if (!csr_step(prob, a, step)) return DQ_ERR_UNSUPPORTED;
+    const CsrPlan &plan = step.plan;
     const int64_t row_words = a.packed ? (a.b == 32 ? d : packed_words(d, a.b)) : 0;
     if (a.deferred) *a.deferred = GradientParts{nullptr, 0, nullptr, nullptr, 0};
     if (a.prepared_next) *a.prepared_next = false;
@@ -1699,30 +1734,18 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
         k.model_diff = a.x_model;
         k.absmax_out = const_cast<float *>(a.absmax_model);
     }
-    const CsrSlices sl = csr_step_slices(prob, a, plan);
-    const bool sliced = sl.count > 0;
-    const bool count_ok = !a.nnz_out || (a.sparsify && a.b >= 4);
-    // Few workers leave most compute units idle while each block spends a third of its time on the Philox rounds of
-    // the final quantization: then several identical blocks per worker share that part (not when the nonzero count is
-    // wanted and would need a sum across blocks, nor when the gradient lives in the per-worker workspace row).
-    unsigned slices = 1;
-    if (a.packed && count_ok && plan.nwin == 1 && a.b != 32 && d >= 4096 && a.M * 4 <= 128) slices = a.M * 8 <= 128 ? 8 : 4;
-    if (sliced) slices = static_cast<unsigned>(sl.count);
-    // After the sparsifier the scale is ||beta||_inf, which needs every coordinate's random decision: sharing only the
-    // quantization would leave each identical block a whole Philox-and-two-divisions pass over the vector (9 of the
-    // 33 us of the step at d = 20958).  With workspace for a row per worker each block sparsifies its own slice into
-    // memory instead and the quantization becomes a second launch that takes the scale from the slices' maxima.
-    const bool split_sparsifier = !sliced && slices > 1 && a.sparsify && a.ws &&
-                                  a.ws_bytes >= csr_workspace_bytes(DQ_OP_WORKER_STEP, prob, a.M, a.B);
+    const CsrSlices sl = step.sl;
+    const bool sliced = step.sliced, common = step.common;
+    const unsigned slices = step.blocks;
     size_t lds = plan.lds;
     GradientParts parts{nullptr, 0, nullptr, nullptr, 0};
     float *alpha_max = nullptr;                          // the slices' maxima of the gradient itself
     int64_t alpha_max_stride = 0;
-    if (sliced || split_sparsifier) {
+    if (sliced || step.split_sparsifier) {
         float *part_max = static_cast<float *>(a.ws) + a.M * k.ld_ws;
         int32_t *part_kept = reinterpret_cast<int32_t *>(part_max + a.M * kMaxSlices);
         parts = GradientParts{static_cast<float *>(a.ws), k.ld_ws, part_max, a.sparsify ? part_kept : nullptr, static_cast<int>(slices)};
-        if (split_sparsifier) {
+        if (step.split_sparsifier) {
             k.beta_ws = static_cast<float *>(a.ws);
             k.part_max = part_max;
             k.part_kept = part_kept;
@@ -1737,12 +1760,10 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
         alpha_max_stride = a.sparsify ? a.ld_words : static_cast<int64_t>(slices);
         k.part_max = alpha_max;
     }
-    const bool common = (sliced || plan.nwin == 1) && a.B <= kCsrMaxRows && a.z_snap != nullptr;
     if (a.x_model && !(sliced && common)) return DQ_ERR_INVALID_ARG;       // (see csr_run_layout)
     // a round of dq_run_rounds that has a successor in its call prepares that round's mini-batches in one more block
     // per worker (on compute units the launch leaves idle), and reads its own if the round before left them
-    const bool can_prepare = !a.idx && a.B <= kCsrMaxRows && (sliced || plan.nwin == 1) && a.M * (slices + 1) <= 256;
-    if (can_prepare) {
+    if (step.can_prepare) {
         k.prep_in = a.prep_in;
         k.prep_out = a.prep_out;
         k.prep_stride = a.prep.stride; k.prep_cap = a.prep.cap; k.snap_cap = a.prep.snap_cap;

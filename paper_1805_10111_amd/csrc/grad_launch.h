@@ -74,7 +74,7 @@ struct CsrRunLayout {
     bool pending;                           // the worker kernel takes the model as x itself (WorkerArgs::x_model), or
     float *model_diff;                      // d floats for WorkerArgs::model_diff
     int32_t *prep_sets[2];                  // WorkerArgs::prep_in / prep_out
-    int dev_max;                           // word of either where WorkerArgs::dev_max lies
+    int dev_max;                            // word of either where WorkerArgs::dev_max lies, 0: the steps do not read it
     PrepRoom prep;
 };
 CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &step);

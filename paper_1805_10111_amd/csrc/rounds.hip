@@ -156,7 +156,8 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
                            dq::master_leaves_model_diff(prob->d, cfg->b_x, parts.parts > 0)) ? kept.model_diff : nullptr;
         diff_ready = diff_out != nullptr;
         // (where this round's worker launch has prepared the next one, and cleared the word)
-        dev_max = diff_out && prep_ready && parts.parts > 0 && cfg->algo == DQ_ALGO_SPARSE ? reinterpret_cast<uint32_t *>(kept.prep_sets[(t + 1) & 1]) + kept.dev_max : nullptr;
+        dev_max = kept.dev_max != 0 && diff_out && prep_ready && parts.parts > 0
+                      ? reinterpret_cast<uint32_t *>(kept.prep_sets[(t + 1) & 1]) + kept.dev_max : nullptr;
         if (parts.parts > 0)
             rc = dq::master_step_from_parts_impl(parts, 0u, it, st->packed, st->ld_words, st->delta,
                                                  st->nnz && cfg->algo == DQ_ALGO_SPARSE ? st->nnz + t * cfg->M : nullptr,
