@@ -64,7 +64,8 @@ extern "C" {
  * layout 0: dense row-major features, row i at dense + i*lda, lda % 4 == 0, lda >= d,
  *           dense 16-byte aligned and n*lda floats long (the padding of a row may be read, never used).
  * layout 1: CSR; indptr[n+1], indices sorted and unique within a row; indices and values must
- *           be non-null even when the matrix has no nonzeros (they are then never read).
+ *           be non-null even when the matrix has no nonzeros (they are then never read).  lda: the number of
+ *           nonzeros if the caller knows it, else 0; it only helps to choose between launches with the same results.
  * y[n] holds +1/-1.  l2 multiplies ||x||^2/2 inside every f_i (smooth part),
  * l1 multiplies ||x||_1 in h (handled by the prox). */
 typedef struct dq_problem {

@@ -1687,15 +1687,16 @@ static bool csr_step(const dq_problem *prob, const WorkerArgs &a, CsrStep &s)
 }
 
 // The worker kernel quantizes the model where the step is split over the columns, its mini-batches are prepared ahead, its
-// margins cached, the model's message whole words per 64 quads, and no slice more than one quad per thread, as far as
-// it is the faster (see csr_worker_kernel).
+// margins cached, the model's message whole words per 64 quads, no slice more than one quad per thread and the mini-batches
+// light, as far as it is the faster (see csr_worker_kernel, csr_light_batches).
 CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &a)
 {
     CsrRunLayout out{};
     CsrStep s;
     if (!a.ws || !csr_step(prob, a, s) || a.ws_bytes < csr_workspace_bytes(DQ_OP_VR_GRAD, prob, a.M, a.B)) return out;
     char *base = static_cast<char *>(a.ws) + csr_run_offset(prob, a.M);
-    out.pending = s.sliced && s.common && s.can_prepare && (a.b_x == 2 || a.b_x == 4 || a.b_x == 8) && s.sl.win <= 4 * kCsrThreads;
+    out.pending = s.sliced && s.common && s.can_prepare && (a.b_x == 2 || a.b_x == 4 || a.b_x == 8) && s.sl.win <= 4 * kCsrThreads &&
+                  csr_light_batches(a.B, prob->n, prob->lda, kCsrInFlight, s.plan.cap);
     out.prep = csr_prep_room(prob->d, a.M, a.B, s.plan, out.pending);
     if (!out.pending) out.model_diff = reinterpret_cast<float *>(base);
     out.prep_sets[0] = reinterpret_cast<int32_t *>(base + (out.pending ? 0 : pad4(prob->d) * 4));

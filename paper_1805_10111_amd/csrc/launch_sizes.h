@@ -120,4 +120,18 @@ inline PrepRoom csr_prep_room(int64_t d, int64_t M, int64_t B, const CsrPlan &pl
     return r;
 }
 
+// Whether mini-batches of B of the n rows are light enough for the worker kernel to quantize the model for them, entry by
+// entry in every block, instead of a launch of its own: on average little more entries than a block keeps in its registers
+// (`in_flight`), and no more than it can prepare ahead (`cap`, with an eighth to spare for batches above the average).
+// `entries` is what the caller says the matrix holds; unknown (0), rows of 100 are assumed.
+// Measured, Alg. 1, eight workers, us a round with a launch for the model and without: 4200 columns, 485 entries 11.7 and 9.7,
+// 4757 entries 13.3 and 13.0, 6627 entries 15.1 and 15.8, 9515 (not prepared) 24.5 and 27.2; 20,958 columns, 1656 entries 13.0 and
+// 11.5, 9518 (not prepared) 27.6 and 31.8; 32,000 columns, 1656 (not prepared) 19.9 and 21.0, 12,693 (not prepared) 60.2 and 74.0.
+// 25 workers: 4200 columns, 4757 entries 16.4 both; 14,000 columns, 4759 entries 17.9 and 18.1, 3838 entries 17.4 and 17.0.
+inline bool csr_light_batches(int64_t B, int64_t n, int64_t entries, int in_flight, int cap)
+{
+    const double mean = static_cast<double>(B) * (entries > 0 ? static_cast<double>(entries) / static_cast<double>(n) : 100.0);
+    return mean <= 1.2 * in_flight && mean * 1.125 <= cap;
+}
+
 }  // namespace dq

@@ -669,3 +669,26 @@ def test_the_distance_from_the_snapshot_is_formed_only_where_the_next_step_reads
     sets = words[rows + (d + 3) // 4 * 4:].reshape(2, M, -1)
     formed = sets[:, 0, 4 + 256 + 3].view(np.float32)
     assert (formed > 0).all() if read else not formed.any()
+
+
+@pytest.mark.parametrize("d,M,B,entries", [(4200, 8, 128, None), (20958, 8, 150, None), (32000, 6, 48, None), (20958, 8, 60, 0), (20958, 8, 16, 1 << 40)])
+def test_heavy_mini_batches_leave_the_model_to_a_launch_of_its_own(dq, d, M, B, entries):
+    """CSR features, step split over the columns: with heavy mini-batches (or such as may be) the model message is the master's, which
+    leaves (decoded model) - snapshot behind the rows and maxima in the workspace.  What the problem says of its entries changes no result."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    P = dq.DeviceProblem.from_host(synth.sparse_text_logistic(500, d, mean_nnz=60.0, seed=8))
+    if entries is not None:
+        P._s.lda = entries
+    one, two, light = (DoubleQuantTrainer(P, "asylpg", M, B, 8, 8, 4, 0.5, seed=3) for _ in range(3))
+    for tr in (one, two, light):
+        tr.epoch_prologue()
+    one.rounds(0, 2)
+    two.rounds(0, 3)
+    rows = M * ((d + 3) // 4 * 4) + 16 * M
+    q = one.xq.view(torch.int8)[:d].float() * one.delta_x[:1] - one.x_snap
+    assert torch.equal(two.ws[rows:rows + d], q) and bool(q.any())
+    two.rounds(3, 1)
+    P._s.lda = 500                                         # (rows of one entry: the worker kernel quantizes)
+    light.rounds(0, 4)
+    for name in ("packed", "delta", "x", "xq", "delta_x", "status"):
+        assert torch.equal(getattr(two, name), getattr(light, name)), name

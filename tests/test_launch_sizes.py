@@ -92,3 +92,21 @@ def test_the_word_that_the_master_leaves_beside_a_prepared_mini_batch_is_in_none
         }
     """)
     assert out == "", out[:2000]
+
+
+def test_the_model_is_quantized_by_the_worker_for_light_mini_batches_only(tmp_path):
+    """CSR features: little more entries on average than a block keeps in registers, no more than the width leaves room to prepare."""
+    out = _sweep(tmp_path, """
+    for (int64_t d = 4096; d <= 32768; d += 97)
+        for (int B = 1; B <= 256; ++B)
+            for (int per_row = 0; per_row <= 300; per_row += 1 + per_row / 8) {
+                CsrPlan p;
+                csr_plan(d, false, p);
+                const bool light = csr_light_batches(B, 1000, 1000ll * per_row, 4096, p.cap);
+                const int mean = B * (per_row ? per_row : 100);
+                if (light && (mean > 4096 * 5 / 4 || mean > p.cap)) std::printf("heavy: d %ld B %d, %d a row\\n", (long)d, B, per_row);
+                if (!light && mean <= 4096 && mean * 8 < p.cap * 7) std::printf("light: d %ld B %d, %d a row\\n", (long)d, B, per_row);
+            }
+    if (csr_light_batches(1, 1, 1ll << 60, 4096, 8192) || !csr_light_batches(1, 1ll << 40, 1, 4096, 8192)) std::printf("ends\\n");
+    """)
+    assert out == "", out[:2000]
