@@ -660,6 +660,12 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
     model_key.tag = DQ_TAG_MODEL;
     // identical copies of the worker that share the tail, or slices (a last one more prepares the next round instead)
     const int slice = blockIdx.y, nslices = static_cast<int>(gridDim.y) - (PREP && a.prep_out ? 1 : 0);
+    // (at once without cached margins, behind the preparing block's part with them: 1400 columns, eight workers of 32 rows,
+    // 13.1 us a round against 13.4 the other way; 3118 columns, eight workers of 39 rows, 13.9 against 14.1)
+    const auto clear_zero_word = [&] {
+        if (a.zero_word && m == 0 && slice == 0 && threadIdx.x == 0) *a.zero_word = 0u;
+    };
+    if (!COMMON) clear_zero_word();
     float *alpha_row = (!SLICED && !COMMON && a.alpha_ws) ? a.alpha_ws + static_cast<int64_t>(m) * a.ld_ws : nullptr;   // only with several windows
 
     const float inv_B = 1.0f / static_cast<float>(a.B);      // the mean over the mini-batch, as one multiplication per row
@@ -825,7 +831,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
         return make_float4(delta * static_cast<float>(k0) - xs.x, delta * static_cast<float>(k1) - xs.y,
                            delta * static_cast<float>(k2) - xs.z, delta * static_cast<float>(k3) - xs.w);
     };
-    if (a.zero_word && m == 0 && slice == 0 && threadIdx.x == 0) *a.zero_word = 0u;
+    if (COMMON) clear_zero_word();
     if (PENDING && m == 0 && slice == 0 && threadIdx.x == 0) {
         const_cast<float *>(a.delta_x)[0] = model_scale.delta;
         if (model_scale.bad && a.status) atomicOr(a.status, 1u);
