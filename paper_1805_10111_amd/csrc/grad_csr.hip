@@ -511,19 +511,24 @@ __device__ __forceinline__ void csr_lane_margins(const float *prod, int total, i
     if (r < nrows) coef[r] = coef_of(margin);
 }
 
-template <typename VecReq, typename VecVal, typename CoefFn>
+// GATED: a wavefront that has no entry among its 64 positions requests nothing for them, and up to 48 rows are added up two at
+// a time to a wavefront; the whole block issues less (1349 columns, four workers of 36 rows of 9 entries: 12.5 -> 12.2 us a round;
+// 3118 columns, eight workers of 39 rows of 10: 14.3 -> 13.9).  Not where the model is quantized here: 5000 columns, eight workers of
+// 64 rows of 52 entries 11.8 us without and 12.1 with it.
+template <bool GATED, typename VecReq, typename VecVal, typename CoefFn>
 __device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlight], const int2 *entry, int total, float vmax, int nrows, int my_len,
                                                       int my_pre, float *coef, int *acc, int c0, int c1, float *prod,
                                                       FixedAcc &fx, uint32_t *su, int *poison, VecReq vec_req, VecVal vec_val, CoefFn coef_of,
                                                       float (&operand)[kStageFlight])
 {
     int col[kStageFlight];
-    decltype(vec_req(0, 0, 0)) raw[kStageFlight];
+    decltype(vec_req(0, 0, 0)) raw[kStageFlight] = {};
+    const int wave_first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) & ~(kWave - 1));
 #pragma unroll
     for (int u = 0; u < kStageFlight; ++u) {
         // (past the end `e` holds whatever the buffer held: column 0 is gathered instead)
         col[u] = static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? e[u].x & kColMask : 0;
-        raw[u] = vec_req(col[u], u, u);
+        if (!GATED || wave_first + u * kCsrThreads < total) raw[u] = vec_req(col[u], u, u);
     }
 #pragma unroll
     for (int u = 0; u < kStageFlight; ++u) {
@@ -546,7 +551,7 @@ __device__ __forceinline__ void csr_process_in_flight(const int2 (&e)[kStageFlig
     __syncthreads();
     if (total <= kPrepNoMax) vmax = __uint_as_float(wave_max_u32(lane < kCsrWaves ? su[lane] : 0u));
     // (a wavefront has one or two rows of the common batches of up to 32)
-    if (nrows <= 2 * kCsrWaves) csr_lane_margins<2>(prod, total, nrows, my_len, my_pre, coef_of, coef);
+    if (nrows <= (GATED ? 3 : 2) * kCsrWaves) csr_lane_margins<2>(prod, total, nrows, my_len, my_pre, coef_of, coef);
     else csr_lane_margins<kFlight>(prod, total, nrows, my_len, my_pre, coef_of, coef);
     __syncthreads();                                     // (also behind the clearing of acc)
     fixed_admit(fx, coef_abs_sum(coef, 0, nrows) * vmax, acc, c1 - c0, poison);
@@ -987,7 +992,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
 #pragma unroll
                         for (int u = 0; u < kStageFlight; ++u)
                             first_snap[u] = a.x_snap[static_cast<int>(threadIdx.x) + u * kCsrThreads < total ? first[u].x & kColMask : 0];
-                    csr_process_in_flight(first, entry, total, vmax, nrows, lr < nrows ? p_len : 0, p_pre, meta.coef, acc,
+                    csr_process_in_flight<!PENDING>(first, entry, total, vmax, nrows, lr < nrows ? p_len : 0, p_pre, meta.coef, acc,
                                           static_cast<int>(c0), static_cast<int>(c1), sg.prod_a, fx, su, &sh_poison,
                                           [&](int c, int u, int p) {           // (entry p at column c; u >= 0: one of the first)
                                               if constexpr (!PENDING) return vec_req(c);
