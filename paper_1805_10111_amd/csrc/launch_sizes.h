@@ -120,8 +120,9 @@ inline PrepRoom csr_prep_room(int64_t d, int64_t M, int64_t B, const CsrPlan &pl
     return r;
 }
 
-// Whether mini-batches of B of the n rows are light enough for the worker kernel to quantize the model for them, entry by
-// entry in every block, instead of a launch of its own: on average little more entries than a block keeps in its registers
+// Whether mini-batches of B of the n rows are light enough for what the worker kernel does entry by entry instead of column by
+// column elsewhere: quantizing the model, in every block, instead of a launch of its own; and, in Alg. 2, finding ||alpha||_inf
+// (see csr_run_layout): on average little more entries than a block keeps in its registers
 // (`in_flight`), and no more than it can prepare ahead (`cap`, with an eighth to spare for batches above the average).
 // `entries` is what the caller says the matrix holds; unknown (0), rows of 100 are assumed.
 // Measured, Alg. 1, eight workers, us a round with a launch for the model and without: 4200 columns, 485 entries 11.7 and 9.7,

@@ -652,20 +652,22 @@ def test_csr_sparsified_rounds_from_prepared_batches_equal_single_rounds(dq, cac
     assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
 
 
-@pytest.mark.parametrize("cached,d,M,read", [(True, 8192, 8, True), (True, 20958, 16, True), (False, 8192, 8, False), (True, 47236, 8, False),
-                                             (True, 8192, 33, False), (True, 4000, 8, False)])
-def test_the_distance_from_the_snapshot_is_formed_only_where_the_next_step_reads_it(dq, cached, d, M, read):
+@pytest.mark.parametrize("cached,d,M,B,read", [(True, 8192, 8, 32, True), (True, 20958, 16, 32, True), (False, 8192, 8, 32, False),
+                                               (True, 47236, 8, 32, False), (True, 8192, 33, 32, False), (True, 4000, 8, 32, False),
+                                               (True, 8192, 8, 200, False)])
+def test_the_distance_from_the_snapshot_is_formed_only_where_the_next_step_reads_it(dq, cached, d, M, B, read):
     """Alg. 2 on CSR features: the master's ||x - x_snap||_inf beside the prepared mini-batches, a word of either set in the
     workspace (which ends with the two sets), is for steps with cached margins whose sparsifier is split over several blocks that
-    hold all columns.  A step split over the columns, one without cached margins or one of a single block per worker has no use for it."""
+    hold all columns, and light mini-batches.  A step split over the columns, one without cached margins or one of a single block
+    per worker has no use for it."""
     from paper_1805_10111_amd.driver import DoubleQuantTrainer
     P = dq.DeviceProblem.from_host(synth.sparse_text_logistic(500, d, mean_nnz=30.0, seed=7))
-    tr = DoubleQuantTrainer(P, "sparse", M, 32, 8, 4, 6, 0.05, seed=3, cache_margins=cached)
+    tr = DoubleQuantTrainer(P, "sparse", M, B, 8, 4, 6, 0.05, seed=3, cache_margins=cached)
     tr.epoch_prologue()
     tr.ws.zero_()
     tr.rounds(0, 6)
     words, rows = host(tr.ws).view(np.int32), M * ((d + 3) // 4 * 4) + 16 * M
-    words = words[:dq.dq_workspace_bytes(dq.OP_VR_GRAD, P, M, 32) // 4]
+    words = words[:dq.dq_workspace_bytes(dq.OP_VR_GRAD, P, M, B) // 4]
     sets = words[rows + (d + 3) // 4 * 4:].reshape(2, M, -1)
     formed = sets[:, 0, 4 + 256 + 3].view(np.float32)
     assert (formed > 0).all() if read else not formed.any()
