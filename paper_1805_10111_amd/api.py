@@ -175,7 +175,7 @@ class DeviceProblem:
             s.indptr = _ptr(self.indptr, torch.int64, "indptr")
             s.indices = _ptr(self.indices, torch.int32, "indices")
             s.values = _ptr(self.values, torch.float32, "values")
-            s.lda = self.indices.numel()
+            s.lda = 0 if self.indices is None else self.indices.numel()
         self._s = s
 
     @property

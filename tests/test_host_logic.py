@@ -203,3 +203,9 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=60)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_a_problem_with_csr_features_names_its_entries_only_where_it_has_them():
+    """The number of nonzeros is a hint: a problem without index array is made as ever (and refused by the calls that take it)."""
+    import paper_1805_10111_amd as dq
+    assert dq.DeviceProblem(n=3, d=2, y=None, l2=0.0, l1=0.0)._s.lda == 0
