@@ -612,11 +612,12 @@ __global__ __launch_bounds__(kFinishThreads) void vr_dense_finish_kernel(const V
 #pragma unroll
             for (int u = 0; u < 4; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
         } else if (p + 1 < a.P) {
-            // any other rest in one group too, its last requests at clamped positions and not added: two or three single
-            // ones were a trip to memory each (60,000 x 784, ten workers of 100 rows, P = 7: 5.1 us a launch, now 4.6)
-            float4 t[7];
+            // any other rest in one group too: two or three single ones were a trip to memory each (60,000 x 784, ten workers
+            // of 100 rows, P = 7: 5.1 us a launch, now 4.6)
+            float4 t[7] = {};
 #pragma unroll
-            for (int u = 0; u < 7; ++u) t[u] = *reinterpret_cast<const float4 *>(base + min(p + u, a.P - 1) * a.ldp + col);
+            for (int u = 0; u < 7; ++u)
+                if (p + u < a.P) t[u] = *reinterpret_cast<const float4 *>(base + (p + u) * a.ldp + col);
 #pragma unroll
             for (int u = 0; u < 7; ++u)
                 if (p + u < a.P) {                                  // (the same for every thread)
