@@ -628,12 +628,17 @@ def test_csr_sparsified_rounds_of_one_call_equal_single_rounds(dq, d, M, B, l2):
     assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
 
 
-@pytest.mark.parametrize("cached,d,M,B,nnz,least,most", [
-    (False, 8192, 8, 100, 30.0, 2049, 4096), (False, 8192, 8, 200, 30.0, 4097, 7040), (False, 20958, 8, 172, 18.0, 2049, 3848),
-    (False, 47236, 8, 100, 30.0, 2049, 4096), (False, 47236, 4, 200, 18.0, 2049, 4244)])
-def test_csr_sparsified_rounds_from_prepared_batches_equal_single_rounds(dq, cached, d, M, B, nnz, least, most):
-    """Alg. 2 on CSR features, mini-batches prepared a round ahead: of `least` to `most` entries each, which is no more than
-    a block stages at that width.  In calls of a single round nothing is prepared.  Everything must be identical."""
+@pytest.mark.parametrize("algo,cached,d,M,B,nnz,least,most", [
+    ("sparse", False, 8192, 8, 100, 30.0, 2049, 4096), ("sparse", False, 8192, 8, 200, 30.0, 4097, 7040),
+    ("sparse", False, 20958, 8, 172, 18.0, 2049, 3848), ("sparse", False, 47236, 8, 100, 30.0, 2049, 4096),
+    ("sparse", False, 47236, 4, 200, 18.0, 2049, 4244), ("sparse", True, 20958, 16, 80, 30.0, 1025, 4096),
+    ("sparse", True, 20958, 3, 147, 30.0, 4097, 5130), ("sparse", True, 4097, 5, 160, 30.0, 4097, 8192),
+    ("sparse", True, 4097, 5, 230, 30.0, 4097, 8192), ("asylpg", True, 2000, 6, 230, 30.0, 4097, 8192),
+    ("asylpg", True, 20958, 32, 40, 30.0, 1025, 4096), ("acc", True, 3001, 4, 40, 9.0, 1, 1024), ("acc", True, 777, 3, 5, 9.0, 1, 64)])
+def test_csr_rounds_from_prepared_batches_equal_single_rounds(dq, algo, cached, d, M, B, nnz, least, most):
+    """CSR features, mini-batches prepared a round ahead: of `least` to `most` entries each, which is no more than a block stages at
+    that width (up to 1024 entries the reading block forms their maximum, up to 4096 they stay in its registers).  In calls of a
+    single round nothing is prepared.  Everything must be identical."""
     from paper_1805_10111_amd.driver import DoubleQuantTrainer
     p = synth.sparse_text_logistic(500, d, mean_nnz=nnz, seed=6)
     lengths = np.diff(p.indptr)
@@ -641,13 +646,13 @@ def test_csr_sparsified_rounds_from_prepared_batches_equal_single_rounds(dq, cac
         for w in range(M):
             assert least <= lengths[oracle.sample_indices(500, B, 3, t, w)].sum() <= most
     P = dq.DeviceProblem.from_host(p)
-    one, many = (DoubleQuantTrainer(P, "sparse", M, B, 8, 4, 5, 0.05, seed=3, cache_margins=cached) for _ in range(2))
+    one, many = (DoubleQuantTrainer(P, algo, M, B, 8, 4, 5, 0.05, seed=3, cache_margins=cached) for _ in range(2))
     one.epoch_prologue(); many.epoch_prologue()
     one.rounds(0, 5)
     for t in range(5):
         many.rounds(t, 1)
     torch.cuda.synchronize()
-    for name in ("packed", "delta", "nnz", "x", "xq", "delta_x", "status"):
+    for name in ("packed", "delta", "x", "xq", "delta_x", "status") + (("nnz",) if algo == "sparse" else ()):
         assert torch.equal(getattr(one, name), getattr(many, name)), name
     assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
 

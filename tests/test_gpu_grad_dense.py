@@ -408,21 +408,27 @@ def test_full_gradient_is_no_coarser_than_512_float32_sums(dq, n, d):
     assert mine <= (plain ** 2 + (2 * 2.0 ** -24) ** 2) ** 0.5
 
 
-@pytest.mark.parametrize("B", [4, 8, 12, 16, 20, 24, 28, 33, 40, 44, 48, 60, 64, 72, 76, 150, 240])
+@pytest.mark.parametrize("M,B,P", [(2, 4, 1), (2, 8, 1), (2, 12, 1), (2, 16, 1), (2, 20, 1), (2, 24, 1), (2, 28, 1), (2, 33, 9), (2, 40, 10),
+                                   (2, 44, 11), (2, 48, 12), (2, 52, 13), (2, 56, 14), (2, 60, 15), (2, 64, 16), (2, 72, 18), (2, 76, 19),
+                                   (2, 150, 10), (2, 240, 15), (256, 40, 2), (32, 40, 3), (32, 56, 4), (16, 70, 5), (2, 90, 6), (2, 100, 7),
+                                   (2, 120, 8)])
 @pytest.mark.parametrize("b_x", [8, 32])
-def test_any_number_of_partial_sums(dq, B, b_x):
+def test_any_number_of_partial_sums(dq, M, B, P, b_x):
     """A worker's mini-batch on P blocks: the second kernel adds their partial sums eight at a time, then a rest of any size
-    (the workspace holds M P rows, so P is read from its size)."""
-    n, d, M = 300, 260, 2
+    (P = 1: no second kernel; else every rest of eight occurs, with eight sums before it and without; P is seen in the workspace,
+    of which the step writes M P rows)."""
+    n, d = 300, 260
     p = synth.dense_logistic(n, d, seed=d, l2=1e-3)
-    P, rp, rng = dq.DeviceProblem.from_host(p), oracle.RefProblem(p), np.random.default_rng(6)
+    prob, rp, rng = dq.DeviceProblem.from_host(p), oracle.RefProblem(p), np.random.default_rng(6)
     x_snap = (0.3 * rng.standard_normal(d)).astype(np.float32)
     xq, dx, q = _model(rng, d, b_x, x_snap)
     idx = np.stack([oracle.sample_indices(n, B, 11, 2, w) for w in range(M)])
     _, z_ref = oracle.full_grad(rp, x_snap, want_margins=True)
     alpha, amax = torch.full((M, d), 5.0, device="cuda"), torch.zeros(M, device="cuda")
-    assert dq.dq_workspace_bytes(dq.OP_VR_GRAD, P, M, B) % (M * d * 4) == 0
-    dq.dq_vr_grad(P, dev(idx), M, B, dev(xq.view(np.int32)), dev(np.array([dx], dtype=np.float32)), b_x, False,
-                  dev(x_snap), dev(z_ref), alpha, amax, None, _ws(dq, dq.OP_VR_GRAD, P, M, B))
+    ws = _ws(dq, dq.OP_VR_GRAD, prob, M, B).fill_(-77.0)
+    dq.dq_vr_grad(prob, dev(idx), M, B, dev(xq.view(np.int32)), dev(np.array([dx], dtype=np.float32)), b_x, False,
+                  dev(x_snap), dev(z_ref), alpha, amax, None, ws)
+    rows = ws[:ws.numel() // d * d].reshape(-1, d)
+    assert int((rows != -77.0).all(1).sum()) == (M * P if P > 1 else 0)
     for w in range(M):
         _close(host(alpha)[w], oracle.vr_grad(rp, idx[w], q, x_snap).astype(np.float64))
