@@ -24,6 +24,7 @@
 // sums that a second kernel adds up in a fixed order.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -1753,6 +1754,22 @@ CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &a)
     return out;
 }
 
+template <int MODEL, bool COMMON, bool SLICED, bool PREP>
+static int csr_launch(const CsrWorkerArgs &k, dim3 grid, size_t lds, const WorkerArgs &a, hipStream_t st)
+{
+    const auto kernel = csr_worker_kernel<MODEL, COMMON, SLICED, PREP>;
+    static std::once_flag attr_once;
+    static hipError_t attr_rc = hipSuccess;
+    const int rc = allow_big_lds(kernel, attr_once, attr_rc);
+    if (rc != DQ_OK) return rc;
+    if (a.ev_start && a.ev_stop)      // the kernel's own start and end times go to the two events
+        hipExtLaunchKernelGGL(kernel, grid, dim3(kCsrThreads), static_cast<uint32_t>(lds), st, a.ev_start, a.ev_stop, 0u, k);
+    else
+        kernel<<<grid, dim3(kCsrThreads), lds, st>>>(k);
+    DQ_LAUNCH_CHECK();
+    return DQ_OK;
+}
+
 int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
 {
     const int64_t d = prob->d;
@@ -1819,31 +1836,24 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
         k.next_iter = a.iter + 1u;
     }
     if (a.prepared_next) *a.prepared_next = k.prep_out != nullptr;
-    static std::once_flag attr_once[13];
-    static hipError_t attr_rc[13];
-    void (*const kernels[13])(const CsrWorkerArgs) = {
-        csr_worker_kernel<kModelMessage, false, false, true>,  csr_worker_kernel<kModelMessage, true, false, true>,
-        csr_worker_kernel<kModelDiff, false, false, true>,     csr_worker_kernel<kModelDiff, true, false, true>,
-        csr_worker_kernel<kModelMessage, false, true, true>,   csr_worker_kernel<kModelMessage, true, true, true>,
-        csr_worker_kernel<kModelDiff, false, true, true>,      csr_worker_kernel<kModelDiff, true, true, true>,
-        csr_worker_kernel<kModelPending, true, true, true>,    csr_worker_kernel<kModelMessage, false, false, false>,
-        csr_worker_kernel<kModelMessage, true, false, false>,  csr_worker_kernel<kModelMessage, false, true, false>,
-        csr_worker_kernel<kModelMessage, true, true, false>};
-    const int which = a.x_model ? 8
-                      : !k.model_diff && !k.prep_in && !k.prep_out && (sliced || plan.nwin == 1) ? 9 + (sliced ? 2 : 0) + (common ? 1 : 0)
-                      : (sliced ? 4 : 0) + (k.model_diff ? 2 : 0) + (common ? 1 : 0);
-    const auto kernel = kernels[which];
-    int rc = allow_big_lds(kernel, attr_once[which], attr_rc[which]);
+    const dim3 grid(static_cast<unsigned>(a.M), slices + (k.prep_out ? 1u : 0u));
+    const auto launch = [&](auto model, auto prep) {
+        constexpr int MODEL = decltype(model)::value;
+        constexpr bool PREP = decltype(prep)::value;
+        if (sliced) return common ? csr_launch<MODEL, true, true, PREP>(k, grid, lds, a, st) : csr_launch<MODEL, false, true, PREP>(k, grid, lds, a, st);
+        return common ? csr_launch<MODEL, true, false, PREP>(k, grid, lds, a, st) : csr_launch<MODEL, false, false, PREP>(k, grid, lds, a, st);
+    };
+    // (several windows one after the other: the kernel with the code of prepared mini-batches also where there are none)
+    const bool prep = k.prep_in || k.prep_out || !(sliced || plan.nwin == 1);
+    using Message = std::integral_constant<int, kModelMessage>;
+    const int rc = a.x_model      ? csr_launch<kModelPending, true, true, true>(k, grid, lds, a, st)
+                   : k.model_diff ? launch(std::integral_constant<int, kModelDiff>{}, std::true_type{})
+                   : prep         ? launch(Message{}, std::true_type{})
+                                  : launch(Message{}, std::false_type{});
     if (rc != DQ_OK) return rc;
-    const dim3 grid(static_cast<unsigned>(a.M), slices + (k.prep_out ? 1u : 0u)), block(kCsrThreads);
-    if (a.ev_start && a.ev_stop)      // the kernel's own start and end times go to the two events
-        hipExtLaunchKernelGGL(kernel, grid, block, static_cast<uint32_t>(lds), st, a.ev_start, a.ev_stop, 0u, k);
-    else
-        kernel<<<grid, block, lds, st>>>(k);
-    DQ_LAUNCH_CHECK();
     if (parts.parts == 0) return DQ_OK;
     if (sliced && a.sparsify) {
-        sparsify_parts_kernel<<<dim3(static_cast<unsigned>(a.M), slices), block, 0, st>>>(
+        sparsify_parts_kernel<<<dim3(static_cast<unsigned>(a.M), slices), dim3(kCsrThreads), 0, st>>>(
             k.beta_ws, k.ld_ws, d, alpha_max, alpha_max_stride, static_cast<int>(slices), k.key, a.worker0,
             const_cast<float *>(parts.part_max), const_cast<int32_t *>(parts.part_kept));
         DQ_LAUNCH_CHECK();
