@@ -55,9 +55,8 @@ struct WorkerArgs {
     const float *model_diff;
     // CSR features, between the rounds of one dq_run_rounds call (all nullable): what a worker step does before it
     // first needs the model (Alg. 1, worker step 2: drawing the rows; reading their extents and entries) is done one
-    // round ahead.  prep_out: this launch also prepares the mini-batches of round iter + 1 there (2 * M *
-    // csr_prep_stride words from csr_prep_offset in the workspace hold two such sets); *prepared_next tells whether it
-    // did.  prep_in: the set a previous launch prepared for this round, same M, B, worker0 and problem.
+    // round ahead.  prep_out: this launch also prepares the mini-batches of round iter + 1 there (M times PrepRoom::stride
+    // words; the workspace holds two such sets, CsrRunLayout::prep_sets); *prepared_next tells whether it did.  prep_in: the set a previous launch prepared for this round, same M, B, worker0 and problem.
     const int32_t *prep_in;
     int32_t *prep_out;
     bool *prepared_next;
@@ -65,6 +64,7 @@ struct WorkerArgs {
     // nullable (with model_diff and prep_in, in whose first worker's block it lies): ||x - x_snap||_inf, as bits, by the master
     // of the previous round.  No column's |model_diff| exceeds it by more than the model's scale, so a step that sparsifies
     // needs no pass over the columns for ||alpha||_inf where those that its rows touch reach beyond l2 times that sum.
+    // Formed only for steps that look at it: CsrRunLayout::dev_max.
     const uint32_t *dev_max;
 };
 

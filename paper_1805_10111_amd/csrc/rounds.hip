@@ -56,7 +56,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // update and ||x||_inf (spread over the chip), and the next round's row-streaming kernel quantizes the model in
     // its prologue, while its first rows are on their way -- every block for itself, one of them storing the message.
     // The two slots of absmax_x alternate: the kernel that reads one clears the other for the master of its round.
-    // (CSR features the same, where the worker step is split over the columns: csr_model_fusable.)
+    // (CSR features the same, where the worker step is split over the columns and the mini-batches are light: csr_run_layout.)
     // CSR features, one group of workers, messages not crossing as (position, value) streams: a worker step that is split
     // over the columns leaves the quantization of its messages to the master kernel (one launch less)
     const bool defer_ok = prob->layout == 1 && cfg->b != 32 && cfg->tau == 0 && !st->wire;
@@ -79,8 +79,8 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     } else if (!csr) {
         fusable = cfg->tau == 0 && cfg->b_x != 32 && dq::dense_model_fusable(prob, cfg->M, cfg->B, cfg->b_x, st->z_snap != nullptr);
     }
-    uint32_t *dev_max = nullptr;         // WorkerArgs::dev_max for it
-    bool diff_ready = false;             // kept.model_diff holds the difference for the model message of this round
+    bool diff_ready = false;             // kept.model_diff holds the difference for the model message of this round,
+    uint32_t *dev_max = nullptr;         // and this word (WorkerArgs::dev_max), if not null, ||x - x_snap||_inf
     bool prep_ready = false;             // the set of this round's parity holds this round's mini-batches
     bool model_pending = false;          // the model of this round is still x itself (not yet a message)
     for (int64_t t = t0; t < t0 + rounds; ++t) {
