@@ -901,9 +901,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
             seen = max(seen, abs_bits(v));
         }
         seen = block_max_u32(seen, su);
-        // (|Q(x) - x| is at most the scale and a rounding of x; a degenerate scale is none)
+        // (|Q(x) - x| is at most the scale and a rounding of x; a degenerate scale is none, and from one near the end of the range
+        // the largest codes come back as infinity)
         const float rest = a.l2 * ((dev_max + msg.delta_x) * 1.001f);
-        if (sh_poison || !(rest <= FLT_MAX) || msg.delta_x == 0.0f || !(seen >= abs_bits(rest))) return false;
+        if (sh_poison || !(rest <= FLT_MAX) || msg.delta_x == 0.0f || msg.delta_x > FLT_MAX / 256.0f || !(seen >= abs_bits(rest))) return false;
         const SparsifyRule rule{__uint_as_float(seen), 0.0f, false};
         StreamKey key = a.key;
         key.worker = a.worker0 + static_cast<uint32_t>(m);

@@ -699,3 +699,27 @@ def test_heavy_mini_batches_leave_the_model_to_a_launch_of_its_own(dq, d, M, B, 
     light.rounds(0, 4)
     for name in ("packed", "delta", "x", "xq", "delta_x", "status"):
         assert torch.equal(getattr(two, name), getattr(light, name)), name
+
+
+def test_csr_sparsified_rounds_with_a_model_whose_message_overflows(dq):
+    """Alg. 2 on CSR features: a coordinate at the largest float32 comes back from its 8-bit message as infinity (127 times the rounded
+    scale), although the model is as close to its snapshot as ever; it is in no row, so no touched column shows it.  The rounds of
+    one call still equal single ones."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    d, top = 8192, np.finfo(np.float32).max
+    p = synth.sparse_text_logistic(500, d - 1, mean_nnz=30.0, seed=9)
+    P = dq.DeviceProblem.from_host(p)
+    P = dq.DeviceProblem(n=P.n, d=d, y=P.y, indptr=P.indptr, indices=P.indices, values=P.values, l2=0.0, l1=0.0)
+    x0 = torch.linspace(-0.5, 0.5, d, device="cuda")       # (all but the last coordinate come back as zero)
+    x0[d - 1] = float(top)
+    one, many = (DoubleQuantTrainer(P, "sparse", 8, 32, 8, 4, 4, 0.01, seed=3, x0=x0.clone()) for _ in range(2))
+    one.epoch_prologue(); many.epoch_prologue()
+    one.rounds(0, 4)
+    for t in range(4):
+        many.rounds(t, 1)
+    torch.cuda.synchronize()
+    for name in ("packed", "nnz", "xq", "status"):
+        assert torch.equal(getattr(one, name), getattr(many, name)), name
+    assert host(one.xq.view(torch.int8))[d - 1] == 127 and host(one.x)[d - 1] == top
+    for name in ("delta", "x", "delta_x"):
+        assert np.array_equal(host(getattr(one, name)), host(getattr(many, name)), equal_nan=True), name
