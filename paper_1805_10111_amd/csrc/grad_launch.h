@@ -56,7 +56,8 @@ struct WorkerArgs {
     // CSR features, between the rounds of one dq_run_rounds call (all nullable): what a worker step does before it
     // first needs the model (Alg. 1, worker step 2: drawing the rows; reading their extents and entries) is done one
     // round ahead.  prep_out: this launch also prepares the mini-batches of round iter + 1 there (M times PrepRoom::stride
-    // words; the workspace holds two such sets, CsrRunLayout::prep_sets); *prepared_next tells whether it did.  prep_in: the set a previous launch prepared for this round, same M, B, worker0 and problem.
+    // words; the workspace holds two such sets, CsrRunLayout::prep_sets); *prepared_next tells whether it did.  prep_in: the
+    // set a previous launch prepared for this round, same M, B, worker0 and problem.
     const int32_t *prep_in;
     int32_t *prep_out;
     bool *prepared_next;
