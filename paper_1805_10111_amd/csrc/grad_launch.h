@@ -123,6 +123,11 @@ bool small_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_
 int32_t small_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
                      int64_t rounds, float eta, float theta, bool flag_first, hipStream_t stream);
 
+// The same for CSR features (csr_rounds.hip).
+bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds);
+int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
+                   int64_t rounds, float eta, float theta, bool flag_first, hipStream_t stream);
+
 int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t B);
 int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,
                     int64_t ws_bytes, hipStream_t st);

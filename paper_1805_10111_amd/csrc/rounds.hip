@@ -42,15 +42,18 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // the model equals the snapshot bit for bit at the first round of an epoch of Alg. 1/2 and of the
     // first epoch of Alg. 3: flag-bit case of Section 4.1
     const bool start_is_snapshot = !acc || epoch == 0;
-    // Small dense problems: everything in one launch (not when the caller wants the worker kernels' own times).
-    if (rounds > 0 && !worker_events && dq::small_rounds_ok(prob, cfg, st)) {
+    // Small dense problems, and CSR problems with mini-batches that a die has room for: everything in one launch (not when the
+    // caller wants the worker kernels' own times).
+    const bool small = rounds > 0 && !worker_events && dq::small_rounds_ok(prob, cfg, st);
+    if (small || (rounds > 0 && !worker_events && dq::csr_rounds_ok(prob, cfg, st, rounds))) {
         if (t0 == 0 && !start_is_snapshot) {             // as below
             const int32_t rc = dq_quantize_pack(st->x, prob->d, 1, prob->d, cfg->b_x, st->absmax_x, 0, cfg->seed,
                                                 static_cast<uint32_t>(epoch * cfg->m), DQ_TAG_MODEL, DQ_MASTER_ID, st->xq, xq_words,
                                                 st->delta_x, st->status, stream);
             if (rc != DQ_OK) return rc;
         }
-        return dq::small_rounds(prob, cfg, st, epoch, t0, rounds, eta, theta, t0 == 0 && start_is_snapshot, as_stream(stream));
+        return (small ? dq::small_rounds : dq::csr_rounds)(prob, cfg, st, epoch, t0, rounds, eta, theta, t0 == 0 && start_is_snapshot,
+                                                           as_stream(stream));
     }
     // Alg. 1, master (i) without a launch of its own: between two rounds of one call the master kernel stops at the
     // update and ||x||_inf (spread over the chip), and the next round's row-streaming kernel quantizes the model in

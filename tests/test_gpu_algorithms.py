@@ -607,6 +607,69 @@ def test_csr_rounds_of_one_call_equal_single_rounds(dq, d, b_x, algo, b, B):
     assert host(one.x).any() and host(one.packed).any() and host(one.status)[0] == 0
 
 
+def _many_rounds_and_few(dq, d, M, B, algo, b, b_x, each, nnz, entries, m=19):
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    P = dq.DeviceProblem.from_host(synth.sparse_text_logistic(500, d, mean_nnz=nnz, seed=4))
+    if entries:
+        P._s.lda = entries                                 # (what the problem says of its entries changes no result)
+    return tuple(DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=3, each=each) for _ in range(2))
+
+
+@pytest.mark.parametrize("d,M,B,algo,b,b_x,each,nnz,entries", [
+    (5, 1, 1, "asylpg", 8, 8, False, 2.0, 0), (257, 1, 9, "acc", 2, 2, True, 9.0, 0), (4097, 28, 24, "asylpg", 4, 3, True, 30.0, 0),
+    (7170, 14, 70, "acc", 8, 16, False, 30.0, 0), (20959, 8, 33, "acc", 4, 12, True, 30.0, 0), (20958, 8, 128, "asylpg", 8, 8, False, 30.0, 0),
+    (28415, 4, 25, "asylpg", 8, 4, False, 30.0, 0), (20958, 8, 64, "asylpg", 8, 8, False, 30.0, 500), (9001, 5, 128, "acc", 4, 8, False, 90.0, 500)])
+def test_csr_rounds_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x, each, nnz, entries):
+    """CSR features: a call of eight rounds or more does them in one launch on one die, a shorter one with launches for each.
+    Everything must be identical: one member and one slice a worker and several, ragged last quads and chunks, fields that straddle
+    words, and, where the problem says rows of one entry, batches that are more than the members hold or a step stages."""
+    many, few = _many_rounds_and_few(dq, d, M, B, algo, b, b_x, each, nnz, entries)
+    for epoch in range(2):
+        many.epoch_prologue(); few.epoch_prologue()
+        for t, n in ((0, 11), (11, 8)):
+            many.rounds(t, n)
+        for t, n in ((0, 5), (5, 5), (10, 1), (11, 5), (16, 3)):
+            few.rounds(t, n)
+        for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
+            assert torch.equal(getattr(many, name), getattr(few, name)), (epoch, name)
+        many.epoch_epilogue(); few.epoch_epilogue()
+    assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
+
+
+def test_csr_rounds_in_one_launch_on_several_streams_at_once(dq):
+    """Three threads, a stream each, call at the same time, beside products that want the whole part: each of their launches finds a
+    die, or waits for one, and the results are those of the separate rounds."""
+    import threading
+    pairs = [_many_rounds_and_few(dq, d, M, 32, "asylpg", 8, 8, False, 30.0, 0, m=40) for d, M in ((20958, 8), (7000, 14), (4097, 20))]
+    streams = [torch.cuda.Stream() for _ in range(len(pairs) + 1)]
+    for many, few in pairs:
+        many.epoch_prologue(); few.epoch_prologue()
+    a = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+
+    def call(tr, stream):
+        with torch.cuda.stream(stream):
+            for _ in range(5):
+                tr.rounds(0, 40)
+
+    threads = [threading.Thread(target=call, args=(many, s)) for (many, _), s in zip(pairs, streams)]
+    with torch.cuda.stream(streams[-1]):
+        for _ in range(10):
+            b = a @ a
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    for many, few in pairs:
+        for _ in range(5):
+            for t in range(0, 40, 5):
+                few.rounds(t, 5)
+        for name in ("packed", "delta", "x", "xq", "delta_x", "status"):
+            assert torch.equal(getattr(many, name), getattr(few, name)), name
+    assert bool(torch.isfinite(b).all())
+
+
 @pytest.mark.parametrize("d,M,B", [(4097, 5, 24), (20958, 16, 33), (30211, 3, 150)])
 @pytest.mark.parametrize("l2", [1e-4, 50.0])
 def test_csr_sparsified_rounds_of_one_call_equal_single_rounds(dq, d, M, B, l2):
