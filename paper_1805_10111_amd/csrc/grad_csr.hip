@@ -1089,8 +1089,9 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
 // the rows: L lanes of a wavefront take a row, ROWS such rows at a time straight from memory -- CHUNKS pieces of L
 // entries of each requested together, then their gathers --, add up its margin and keep its coefficient in LDS.  Once all
 // rows of the chunk have theirs, one barrier gives the bound that fixes the unit of the fixed-point sums (FixedAcc),
-// and the same lanes add the rows' entries (from L2 now) to the columns.  72,000 rows of 52 entries, 20,958
-// columns: 50.4 us with rows staged in LDS in groups of a hundred, five barrier-separated phases each; now 29.0 us;
+// and the same lanes add the rows' entries (from L2 now) to the columns.  A batch's first entries are requested before those
+// of the one before are used: a trip to memory less for each.  72,000 rows of 52 entries, 20,958
+// columns: 50.4 us with rows staged in LDS in groups of a hundred, five barrier-separated phases each; now 27.0 us;
 // 80,000 rows of 100 entries, 60,000 columns 236 -> 71 us; 40,000 rows of 20, 2000 columns 14.7 -> 13.4 us.
 constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; 12.5 KB of static arrays beside them
 constexpr int kTogether = 256;                            // positions of a row up to here are its own lanes' work
@@ -1107,32 +1108,40 @@ struct FullChunk {
     __device__ __forceinline__ float value_at(uint32_t at) const { return *reinterpret_cast<const float *>(values + at); }
 };
 
-// The wavefront's rows, ROWS * (64 / L) at a time: each_batch(rows, starts, lengths, longest), all per lane but `longest`
-// (of the whole wavefront).  A row past the chunk's end has length 0, and a row of length 0 the start 0 of an entry that
-// exists wherever any row has one.
-template <int L, int ROWS, typename Batch>
-__device__ __forceinline__ void full_sweep(const FullChunk &ch, Batch each_batch)
+// L lanes a row, ROWS * (64 / L) rows a batch, CHUNKS pieces of L entries at a time.
+template <int L, int ROWS, int CHUNKS>
+struct FullShapeOf {};
+
+// ROWS * (64 / L) of the wavefront's rows, all per lane but `longest` (of the whole wavefront).  A row past the chunk's end has
+// length 0, and a row of length 0 the start 0 of an entry that exists wherever any row has one.
+template <int ROWS>
+struct FullBatch {
+    int row[ROWS], len[ROWS], longest;
+    uint32_t st[ROWS];
+};
+
+template <int L, int ROWS>
+__device__ __forceinline__ FullBatch<ROWS> full_batch(const FullChunk &ch, int r)
 {
     constexpr int G = kWave / L;
-    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (int r = wave * G; r < ch.rows; r += ROWS * G * kCsrWaves) {
-        int row[ROWS], len[ROWS], longest = 0;
-        uint32_t st[ROWS];
+    const int lane = threadIdx.x & (kWave - 1);
+    FullBatch<ROWS> b;
+    b.longest = 0;
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            row[u] = r + u * G * kCsrWaves + (L == kWave ? 0 : lane / L);
-            const int rc = min(row[u], ch.rows - 1);
-            len[u] = row[u] < ch.rows ? ch.len[rc] : 0;
-            st[u] = len[u] > 0 ? ch.start[rc] : 0u;
-            if constexpr (L == kWave) {                   // (the same for all lanes: scalars)
-                len[u] = __builtin_amdgcn_readfirstlane(len[u]);
-                st[u] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(st[u])));
-            }
-            longest = max(longest, len[u]);
+    for (int u = 0; u < ROWS; ++u) {
+        b.row[u] = r + u * G * kCsrWaves + (L == kWave ? 0 : lane / L);
+        const int rc = min(b.row[u], ch.rows - 1), len = ch.len[rc];
+        const uint32_t st = ch.start[rc];
+        b.len[u] = b.row[u] < ch.rows ? len : 0;
+        b.st[u] = b.len[u] > 0 ? st : 0u;
+        if constexpr (L == kWave) {                       // (the same for all lanes: scalars)
+            b.len[u] = __builtin_amdgcn_readfirstlane(b.len[u]);
+            b.st[u] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b.st[u])));
         }
-        if constexpr (L != kWave) longest = static_cast<int>(wave_max_u32(static_cast<uint32_t>(longest)));
-        each_batch(row, st, len, longest);
+        b.longest = max(b.longest, b.len[u]);
     }
+    if constexpr (L != kWave) b.longest = static_cast<int>(wave_max_u32(static_cast<uint32_t>(b.longest)));
+    return b;
 }
 
 template <int L, int ROWS, int CHUNKS>
@@ -1149,34 +1158,79 @@ __device__ __forceinline__ void full_fetch(const FullChunk &ch, const uint32_t (
         }
 }
 
+// The wavefront's rows, a batch at a time: each_piece(batch, k, col, val, between) with the entries k, k + L, ... of its rows'
+// lanes, then each_batch(batch).  A batch's first entries are requested while those before are worked on: each_piece calls
+// `between` once it has requested what it needs itself.
+template <int L, int ROWS, int CHUNKS, typename Start, typename Piece, typename Finish>
+__device__ __forceinline__ void full_sweep(const FullChunk &ch, Start start, Piece each_piece, Finish each_batch)
+{
+    constexpr int G = kWave / L, kStep = ROWS * G * kCsrWaves;
+    const int lane = threadIdx.x & (kWave - 1), in_row = lane % L, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int r = wave * G;
+    if (r >= ch.rows) return;
+    uint32_t col[ROWS][CHUNKS], next_col[ROWS][CHUNKS];
+    float val[ROWS][CHUNKS], next_val[ROWS][CHUNKS];
+    FullBatch<ROWS> b = full_batch<L, ROWS>(ch, r), next = b;
+    if (b.longest > 0) full_fetch<L, ROWS, CHUNKS>(ch, b.st, b.len, in_row, col, val);
+    for (;;) {
+        const bool more = !(L == 16 && ROWS == 5) && r + kStep < ch.rows;      // (five rows are for all of a wavefront's at once)
+        const auto between = [&] {
+            if (!more) return;
+            next = full_batch<L, ROWS>(ch, r + kStep);
+            if (next.longest > 0) full_fetch<L, ROWS, CHUNKS>(ch, next.st, next.len, in_row, next_col, next_val);
+        };
+        start(b);
+        if (b.longest > 0) each_piece(b, in_row, col, val, between);
+        else between();
+        for (int k = in_row + CHUNKS * L; k - in_row < min(b.longest, kTogether); k += CHUNKS * L) {
+            full_fetch<L, ROWS, CHUNKS>(ch, b.st, b.len, k, col, val);
+            each_piece(b, k, col, val, [] {});
+        }
+        each_batch(b);
+        if (!more) break;
+        r += kStep;
+        b = next;
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+            for (int c = 0; c < CHUNKS; ++c) {
+                col[u][c] = next_col[u][c];
+                val[u][c] = next_val[u][c];
+            }
+    }
+}
+
 // Margins, losses and coefficients of the chunk's rows; the lanes' share of sum |coefficient| and the largest |value|.
 template <int L, int ROWS, int CHUNKS>
-__device__ __forceinline__ void full_margins(const FullChunk &ch, const float *__restrict__ x, float *__restrict__ z_out,
+__device__ __forceinline__ void full_margins(FullShapeOf<L, ROWS, CHUNKS>, const FullChunk &ch, const float *__restrict__ x, float *__restrict__ z_out,
                                              float inv_n, double &loss, float &csum, uint32_t &vmax)
 {
     const int lane = threadIdx.x & (kWave - 1), in_row = lane % L;
     const auto x_at = [&](uint32_t col) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(x) + 4u * col); };
-    full_sweep<L, ROWS>(ch, [&](const int (&row)[ROWS], const uint32_t (&st)[ROWS], const int (&len)[ROWS], int longest) {
-        float sum[ROWS];
+    float sum[ROWS];
+    full_sweep<L, ROWS, CHUNKS>(ch, [&](const FullBatch<ROWS> &) {
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) sum[u] = 0.0f;
-        for (int k = in_row; k - in_row < min(longest, kTogether); k += CHUNKS * L) {
-            uint32_t col[ROWS][CHUNKS];
-            float val[ROWS][CHUNKS], xv[ROWS][CHUNKS];
-            full_fetch<L, ROWS, CHUNKS>(ch, st, len, k, col, val);
+    }, [&](const FullBatch<ROWS> &b, int k, const uint32_t (&col)[ROWS][CHUNKS], const float (&val)[ROWS][CHUNKS], auto between) {
+        float xv[ROWS][CHUNKS];
 #pragma unroll
-            for (int u = 0; u < ROWS; ++u)
+        for (int u = 0; u < ROWS; ++u)
 #pragma unroll
-                for (int c = 0; c < CHUNKS; ++c) xv[u][c] = x_at(col[u][c]);
+            for (int c = 0; c < CHUNKS; ++c) xv[u][c] = x_at(col[u][c]);
+        between();
 #pragma unroll
-            for (int u = 0; u < ROWS; ++u)
+        for (int u = 0; u < ROWS; ++u)
 #pragma unroll
-                for (int c = 0; c < CHUNKS; ++c) {
-                    vmax = max(vmax, abs_bits(val[u][c]));
-                    const int p = k + c * L;              // (positions past kTogether: below)
-                    sum[u] += p < min(len[u], kTogether) ? val[u][c] * xv[u][c] : 0.0f;
-                }
-        }
+            for (int c = 0; c < CHUNKS; ++c) {
+                vmax = max(vmax, abs_bits(val[u][c]));
+                const int p = k + c * L;                  // (positions past kTogether: below)
+                sum[u] += p < min(b.len[u], kTogether) ? val[u][c] * xv[u][c] : 0.0f;
+            }
+    }, [&](const FullBatch<ROWS> &b) {
+        const auto &row = b.row;
+        const auto &len = b.len;
+        const auto &st = b.st;
+        const int longest = b.longest;
         // what rows of more than kTogether entries have left: the whole wavefront's, eight pieces of 64 at a time
         if (longest > kTogether) {
 #pragma unroll
@@ -1244,24 +1298,25 @@ __device__ __forceinline__ void full_margins(const FullChunk &ch, const float *_
 
 // The entries of the chunk's rows in columns lo .. lo + wide - 1 are added to acc.
 template <int L, int ROWS, int CHUNKS>
-__device__ __forceinline__ void full_scatter(const FullChunk &ch, int *acc, uint32_t lo, uint32_t wide, float two_k)
+__device__ __forceinline__ void full_scatter(FullShapeOf<L, ROWS, CHUNKS>, const FullChunk &ch, int *acc, uint32_t lo, uint32_t wide, float two_k)
 {
-    const int lane = threadIdx.x & (kWave - 1), in_row = lane % L;
-    full_sweep<L, ROWS>(ch, [&](const int (&row)[ROWS], const uint32_t (&st)[ROWS], const int (&len)[ROWS], int longest) {
-        float coef[ROWS];
+    const int lane = threadIdx.x & (kWave - 1);
+    float coef[ROWS];
+    full_sweep<L, ROWS, CHUNKS>(ch, [&](const FullBatch<ROWS> &b) {
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) coef[u] = ch.coef[min(row[u], ch.rows - 1)];
-        for (int k = in_row; k - in_row < min(longest, kTogether); k += CHUNKS * L) {
-            uint32_t col[ROWS][CHUNKS];
-            float val[ROWS][CHUNKS];
-            full_fetch<L, ROWS, CHUNKS>(ch, st, len, k, col, val);
+        for (int u = 0; u < ROWS; ++u) coef[u] = ch.coef[min(b.row[u], ch.rows - 1)];
+    }, [&](const FullBatch<ROWS> &b, int k, const uint32_t (&col)[ROWS][CHUNKS], const float (&val)[ROWS][CHUNKS], auto between) {
+        between();
 #pragma unroll
-            for (int u = 0; u < ROWS; ++u)
+        for (int u = 0; u < ROWS; ++u)
 #pragma unroll
-                for (int c = 0; c < CHUNKS; ++c)
-                    if (k + c * L < min(len[u], kTogether) && col[u][c] - lo < wide)
-                        atomicAdd(&acc[col[u][c] - lo], fixed_term(coef[u], val[u][c], two_k));
-        }
+            for (int c = 0; c < CHUNKS; ++c)
+                if (k + c * L < min(b.len[u], kTogether) && col[u][c] - lo < wide)
+                    atomicAdd(&acc[col[u][c] - lo], fixed_term(coef[u], val[u][c], two_k));
+    }, [&](const FullBatch<ROWS> &b) {
+        const auto &len = b.len;
+        const auto &st = b.st;
+        const int longest = b.longest;
         if (longest > kTogether) {
 #pragma unroll
             for (int u = 0; u < ROWS; ++u)
@@ -1320,17 +1375,34 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
         __syncthreads();
         const FullChunk ch{reinterpret_cast<const char *>(A.indices + e0), reinterpret_cast<const char *>(A.values + e0), cn,
                            sh_start, sh_len, sh_coef};
-        // A row on a whole wavefront, or four rows side by side.  Whole wavefronts have 96 rows under way at a time, quarters
-        // 320, which is worth the more the more rows there are and the shorter they are (5000 columns): 80,000 rows of 28
-        // entries, 312 a block, 21.0 us on quarters and 25.6 on whole wavefronts; 30,000 of 20, 117 a block, 17.1 and
-        // 19.0, of 28 entries 19.0 and 19.3; up to 96 rows a block takes either in one go, whole wavefronts at once: 8000 of
-        // 24 entries 15.8 and 13.7.
+        // A row on a whole wavefront, or four rows side by side, which is worth the more the more rows there are and the shorter
+        // they are (5000 columns): 80,000 rows of 28 entries, 312 a block, 21.0 us on quarters and 25.6 on whole wavefronts;
+        // 30,000 of 20, 117 a block, 17.1 and 19.0, of 28 entries 19.0 and 19.3; up to 96 rows a block whole wavefronts are at
+        // least as good: 8000 of 24 entries 15.8 and 13.7.
         const bool short_rows = cn > 96 && e1 - e0 <= static_cast<uint64_t>(cn > 192 ? 32 : 24) * static_cast<uint64_t>(cn);
+        // Rows of a batch: a place without a row costs what one with a row does, so of two sizes the one that leaves fewer.  Whole
+        // wavefronts, threes and fours: 72,000 rows of 52 entries, 18 a wavefront, 33.0 and 34.2 us; 20,242 of 75, five a
+        // wavefront, 36.8 and 38.6; 8000 of 24, four a wavefront, 14.1 and 12.7.  (Sixes with nothing requested ahead: 33.9, 37.6,
+        // 14.1.)  Quarters: 30,000 rows of 20, two turns, in pairs 14.6, in threes 15.8, all of five 17.6; 80,000 of 28, five turns, in
+        // threes 20.8, all at once 20.4.
+        const int turns = (cn + kCsrWaves - 1) / kCsrWaves, quarter_turns = (cn + 4 * kCsrWaves - 1) / (4 * kCsrWaves);
+        const bool threes = (turns + 2) / 3 * 3 < (turns + 3) / 4 * 4, pairs = quarter_turns <= 2, fives = quarter_turns == 4 || quarter_turns == 5;
+        const auto with_batches = [&](auto f) {
+            if (!short_rows) {
+                if (threes) f(FullShapeOf<kWave, 3, 2>{});
+                else f(FullShapeOf<kWave, 4, 2>{});
+            } else if (fives) {
+                f(FullShapeOf<16, 5, 3>{});
+            } else if (pairs) {
+                f(FullShapeOf<16, 2, 3>{});
+            } else {
+                f(FullShapeOf<16, 3, 3>{});
+            }
+        };
         uint32_t vmax = 0;
         float csum = 0.0f;
         float *z_chunk = z_out ? z_out + ib : nullptr;
-        if (short_rows) full_margins<16, 5, 3>(ch, x, z_chunk, inv_n, loss, csum, vmax);
-        else full_margins<kWave, 6, 2>(ch, x, z_chunk, inv_n, loss, csum, vmax);
+        with_batches([&](auto shape) { full_margins(shape, ch, x, z_chunk, inv_n, loss, csum, vmax); });
         csum = wave_sum_f32(csum);
         if (lane == 0) sf[wave] = csum;
         vmax = block_max_u32(vmax, su);                  // (its barriers also publish sf, the coefficients, the cleared sums)
@@ -1343,8 +1415,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_full_partial_kernel(
         for (int64_t c0 = 0; c0 < ldp; c0 += win) {      // a window of columns at a time (one when the vector fits in LDS)
             const int64_t c1 = min(ldp, c0 + win);
             const uint32_t lo = static_cast<uint32_t>(c0), wide = static_cast<uint32_t>(c1 - c0);
-            if (finite && short_rows) full_scatter<16, 5, 3>(ch, acc, lo, wide, two_k);
-            else if (finite) full_scatter<kWave, 6, 2>(ch, acc, lo, wide, two_k);
+            if (finite) with_batches([&](auto shape) { full_scatter(shape, ch, acc, lo, wide, two_k); });
             __syncthreads();
             for (int64_t j = c0 + 4ll * threadIdx.x; j < c1; j += 4ll * kCsrThreads) {
                 const int4 sum = *reinterpret_cast<const int4 *>(acc + (j - c0));

@@ -491,3 +491,30 @@ def test_full_gradient_over_row_lengths(dq, kind):
     _close(host(g), want_g)
     _close(host(z), want_z)
     assert abs(host(obj)[0] - oracle.objective(ref, x)) <= TOL * abs(oracle.objective(ref, x))
+
+
+@pytest.mark.parametrize("per,length", [(1, 9), (17, 9), (49, 40), (64, 70), (81, 9), (97, 9), (129, 9), (193, 30), (257, 9), (321, 9),
+                                        (330, 50), (1030, 9)])
+def test_full_gradient_over_rows_per_block(dq, per, length):
+    """Rows of a block on whole wavefronts in batches of three and of four, on quarters in pairs, threes and fives, one batch and several,
+    whole and with places left, more rows than one chunk: against the oracle."""
+    n, d = (per if per <= 64 else 256 * per - 3), 640
+    rng = np.random.default_rng(per)
+    lens = rng.integers(0, 2 * length, n)
+    lens[0] = length
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=indptr[1:])
+    within = np.arange(indptr[-1]) - np.repeat(indptr[:-1], lens)
+    indices = (np.repeat(rng.integers(0, d - 6 * 2 * length, n), lens) + 6 * within).astype(np.int32) if length < 50 else \
+        (np.repeat(rng.integers(0, d - 2 * 2 * length, n), lens) + 2 * within).astype(np.int32)
+    values = (rng.standard_normal(indptr[-1]) / np.sqrt(np.repeat(np.maximum(lens, 1), lens))).astype(np.float32)
+    p = synth.Problem(n=n, d=d, y=np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32), l2=1e-3, l1=1e-4, indptr=indptr,
+                      indices=indices, values=values)
+    x = (0.5 * rng.standard_normal(d)).astype(np.float32)
+    P, ref = dq.DeviceProblem.from_host(p), oracle.RefProblem(p)
+    g, z, obj = torch.zeros(d, device="cuda"), torch.zeros(n, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+    dq.dq_full_grad(P, dev(x), g, z, obj, dq.new_workspace(dq.OP_FULL_GRAD, P))
+    want_g, want_z = oracle.full_grad(ref, x, want_margins=True)
+    _close(host(g), want_g)
+    _close(host(z), want_z)
+    assert abs(host(obj)[0] - oracle.objective(ref, x)) <= TOL * abs(oracle.objective(ref, x))
