@@ -1040,16 +1040,18 @@ __global__ __launch_bounds__(kCsrThreads) void csr_worker_kernel(const CsrWorker
 // from the maxima that launch left per slice (alpha_parts of them, at alpha_max + m * alpha_max_stride), sparsifies a slice
 // of the quads of row m in place and leaves the slice's largest magnitude and kept count.  Rows are padded with
 // zeros to whole quads.  Everything is requested, and the first quad's random bits drawn, before anything is waited for.
+// wire (nullable): wire_words words of each of its rows are set to zero, for sparse_message_parts_kernel.
 __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
     float *__restrict__ rows, int64_t ld, int64_t d, const float *__restrict__ alpha_max, int64_t alpha_max_stride,
-    int alpha_parts, StreamKey key, uint32_t worker0, float *__restrict__ part_max, int32_t *__restrict__ part_kept)
+    int alpha_parts, StreamKey key, uint32_t worker0, float *__restrict__ part_max, int32_t *__restrict__ part_kept, int per,
+    uint32_t *__restrict__ wire, int64_t ld_wire, int wire_words)
 {
-    touch_kernel_arguments<88>();
+    touch_kernel_arguments<120>();
     __shared__ uint32_t su[kCsrWaves];
     __shared__ int si[kCsrWaves];
     const int m = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y;
-    const int64_t quads = (d + 3) / 4, per = (quads + nslices - 1) / nslices;
-    const int64_t q_lo = min(quads, per * slice), q_hi = min(quads, q_lo + per), q_first = q_lo + threadIdx.x;
+    const int64_t quads = (d + 3) / 4;
+    const int64_t q_lo = min<int64_t>(quads, static_cast<int64_t>(per) * slice), q_hi = min<int64_t>(quads, q_lo + per), q_first = q_lo + threadIdx.x;
     float4 *row = reinterpret_cast<float4 *>(rows + static_cast<int64_t>(m) * ld);
     const PartsRaw maxima = parts_request(alpha_max + static_cast<int64_t>(m) * alpha_max_stride, alpha_parts);
     float4 v = row[min(q_first, quads - 1)];
@@ -1059,6 +1061,10 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
     uint4 w = stream_block(key, static_cast<uint32_t>(q_first));
     asm volatile("" ::"v"(w.x), "v"(w.y), "v"(w.z), "v"(w.w));
     __builtin_amdgcn_sched_barrier(0);
+    if (wire) {
+        uint32_t *words = wire + static_cast<int64_t>(m) * ld_wire;
+        for (int w = slice * kCsrThreads + threadIdx.x; w < wire_words; w += nslices * kCsrThreads) words[w] = 0u;
+    }
     const SparsifyRule rule{parts_absmax_of(maxima), 0.0f, false};
     uint32_t bmax = 0;
     int kept = 0;
@@ -1727,10 +1733,18 @@ int csr_worker(const dq_problem *prob, const WorkerArgs &a, hipStream_t st)
     if (rc != DQ_OK) return rc;
     if (parts.parts == 0) return DQ_OK;
     if (sliced && a.sparsify) {
+        const bool encode = a.encoded && a.wire && sparse_message_parts_ok(d, a.M, a.b, a.packed, a.ld_words, a.wire, a.ld_wire);
         sparsify_parts_kernel<<<dim3(static_cast<unsigned>(a.M), slices), dim3(kCsrThreads), 0, st>>>(
             k.beta_ws, k.ld_ws, d, alpha_max, alpha_max_stride, static_cast<int>(slices), k.key, a.worker0,
-            const_cast<float *>(parts.part_max), const_cast<int32_t *>(parts.part_kept));
+            const_cast<float *>(parts.part_max), const_cast<int32_t *>(parts.part_kept),
+            static_cast<int>(sparse_parts_quads(d, static_cast<int>(slices))), encode ? a.wire : nullptr, a.ld_wire,
+            encode ? static_cast<int>(dq_sparse_stream_words(d, a.b)) : 0);
         DQ_LAUNCH_CHECK();
+        if (encode) {
+            *a.encoded = true;
+            return launch_sparse_message_parts(parts, d, a.M, a.b, k.key, a.worker0, a.packed, a.ld_words, a.wire, a.ld_wire, a.delta_out,
+                                               a.nnz_out, a.wire_nnz, a.status, st);
+        }
     }
     if (a.deferred) {                                    // the master quantizes while it aggregates
         *a.deferred = parts;

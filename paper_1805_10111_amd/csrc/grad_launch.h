@@ -62,6 +62,12 @@ struct WorkerArgs {
     int32_t *prep_out;
     bool *prepared_next;
     PrepRoom prep;                          // the room of either (CsrRunLayout)
+    // Alg. 2, messages that cross as (position, value) streams (nullable): a step that can (sparse_message_parts_ok, a sparsifier in a
+    // launch of its own) also encodes its message there (as dq_sparse_encode), and says so in *encoded.
+    uint32_t *wire;
+    int64_t ld_wire;
+    int32_t *wire_nnz;
+    bool *encoded;
     // nullable (with model_diff and prep_in, in whose first worker's block it lies): ||x - x_snap||_inf, as bits, by the master
     // of the previous round.  No column's |model_diff| exceeds it by more than the model's scale, so a step that sparsifies
     // needs no pass over the columns for ||alpha||_inf where those that its rows touch reach beyond l2 times that sum.
@@ -127,6 +133,14 @@ int32_t small_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_
 bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds);
 int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
                    int64_t rounds, float eta, float theta, bool flag_first, hipStream_t stream);
+
+// Quantizer and encoder of sparsified gradients in one launch (wire.hip), and the quads of a slice of them.
+int64_t sparse_parts_quads(int64_t d, int slices);
+bool sparse_message_parts_ok(int64_t d, int64_t M, int b, const uint32_t *packed, int64_t ld_words, const uint32_t *wire,
+                             int64_t ld_wire);
+int launch_sparse_message_parts(const GradientParts &parts, int64_t d, int64_t M, int b, const StreamKey &key, uint32_t worker0,
+                                uint32_t *packed, int64_t ld_words, uint32_t *wire, int64_t ld_wire, float *delta_out,
+                                int32_t *kept_out, int32_t *nnz_out, uint32_t *status, hipStream_t st);
 
 int64_t dense_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t B);
 int dense_full_grad(const dq_problem *prob, const float *x, float *g_out, float *z_out, double *obj_out, void *ws,

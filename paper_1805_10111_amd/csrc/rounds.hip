@@ -104,6 +104,7 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         }
         // worker side: group g of the workers is g rounds behind (g = 0 only when tau = 0)
         dq::GradientParts parts{nullptr, 0, nullptr, nullptr, 0};
+        bool encoded = false;
         for (int64_t g = 0; g < slots; ++g) {
             const int64_t w_lo = dq::ceil_div(g * cfg->M, slots), w_hi = dq::ceil_div((g + 1) * cfg->M, slots);
             if (w_hi <= w_lo) continue;
@@ -126,6 +127,9 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
                 w.absmax_model = st->absmax_x + ((t - 1) & 1);
             }
             if (defer_ok) w.deferred = &parts;
+            if (st->wire && cfg->tau == 0) {
+                w.wire = st->wire; w.ld_wire = st->ld_wire; w.wire_nnz = st->wire_nnz; w.encoded = &encoded;
+            }
             if (diff_ready) w.model_diff = kept.model_diff;
             if (diff_ready && prep_ready) w.dev_max = dev_max;
             bool prepared_next = false;
@@ -145,8 +149,10 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         }
         // Section 4.2 on request: the sparsified messages cross to the master as (position, value) streams
         if (st->wire && cfg->algo == DQ_ALGO_SPARSE && cfg->b != 32) {
-            rc = dq_sparse_encode(st->packed, st->ld_words, prob->d, cfg->M, cfg->b, st->wire, st->ld_wire, st->wire_nnz, stream);
-            if (rc != DQ_OK) return rc;
+            if (!encoded) {
+                rc = dq_sparse_encode(st->packed, st->ld_words, prob->d, cfg->M, cfg->b, st->wire, st->ld_wire, st->wire_nnz, stream);
+                if (rc != DQ_OK) return rc;
+            }
             rc = dq_sparse_decode(st->wire, st->ld_wire, st->wire_nnz, prob->d, cfg->M, cfg->b, st->packed, st->ld_words, stream);
             if (rc != DQ_OK) return rc;
         }

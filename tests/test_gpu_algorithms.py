@@ -440,6 +440,38 @@ def test_sparse_messages_through_the_wire_format(dq):
         assert not w[r, used[r]:].any() and (used[r] == 0 or w[r, :used[r]].any())
 
 
+@pytest.mark.parametrize("d,M,B,b,nnz,l2,infinite", [
+    (47236, 8, 32, 4, 60.0, 1e-4, False), (36003, 5, 24, 8, 30.0, 1e-4, False), (40001, 40, 9, 4, 30.0, 50.0, False),
+    (36001, 130, 3, 4, 30.0, 1e-4, False), (47233, 3, 16, 8, 30.0, 50.0, False), (47236, 4, 32, 4, 30.0, 1e-4, True),
+    (47236, 8, 32, 2, 60.0, 1e-4, False), (20958, 8, 32, 4, 30.0, 1e-4, False)])
+def test_messages_encoded_by_the_worker_step_equal_the_separate_encoder(dq, d, M, B, b, nnz, l2, infinite):
+    """Models wider than the on-chip buffer, Alg. 2: the launch that quantizes also encodes (4 and 8 bits).  Streams are those of
+    dq_sparse_encode on the messages, every word; messages and models those of a run without streams.  Eight slices a worker
+    down to one, few entries and rows of which most is kept, ragged ends; an infinite feature: no entries; 2 bits
+    and a model of one slice, which keep the separate encoder."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    p = synth.sparse_text_logistic(400, d, mean_nnz=nnz, seed=8)
+    if infinite:
+        p.values[p.indptr[37]] = np.inf
+    P = dq.DeviceProblem.from_host(p)
+    P = dq.DeviceProblem(n=P.n, d=P.d, y=P.y, indptr=P.indptr, indices=P.indices, values=P.values, l2=l2, l1=1e-5)
+    plain, wired = (DoubleQuantTrainer(P, "sparse", M, B, 8, b, 4, 0.01, seed=3, sparse_wire=w) for w in (False, True))
+    for tr in (plain, wired):
+        tr.epoch_prologue()
+    seen = 0
+    for t in range(4):
+        wired.wire.fill_(-1)
+        plain.rounds(t, 1); wired.rounds(t, 1)
+        for name in ("packed", "delta", "x", "xq", "delta_x", "nnz", "status"):
+            a, c = getattr(plain, name), getattr(wired, name)
+            assert torch.equal(a.view(torch.int32), c.view(torch.int32)), (t, name)
+        stream, count = torch.full_like(wired.wire, -1), torch.full_like(wired.wire_nnz, -1)
+        dq.dq_sparse_encode(wired.packed, d, b, stream, count)
+        assert torch.equal(stream, wired.wire) and torch.equal(count, wired.wire_nnz), t
+        seen += int(count.sum())
+    assert (seen == 0) == infinite
+
+
 @pytest.mark.parametrize("name", ["C1", "C4", "C3"])
 def test_rounds_replayed_from_a_captured_graph(dq, name):
     """dq_run_rounds only enqueues kernels (no allocation, no memset), so a caller may capture an epoch's rounds
