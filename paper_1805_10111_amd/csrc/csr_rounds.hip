@@ -789,8 +789,9 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
     a.x = st->x; a.yv = st->y; a.xsum = st->xsum; a.x_snap = st->x_snap; a.g_snap = st->g_snap;
     a.xq = st->xq; a.delta_x = st->delta_x; a.absmax_x = st->absmax_x;
     a.packed = st->packed; a.ld_words = st->ld_words; a.delta = st->delta; a.status = st->status;
-    // (a launch for every kMostRounds rounds: tens of milliseconds of a die each)
-    constexpr int64_t kMostRounds = 4096;
+    // A launch for every kMostRounds rounds, 5 ms or so: blocks of other streams' launches that are meant for the die wait that
+    // long (the part deals a launch's blocks to the dies in turn).
+    constexpr int64_t kMostRounds = 512;
     for (int64_t done = 0; done < rounds; done += kMostRounds) {
         a.iter0 = static_cast<uint32_t>(epoch * cfg->m + t0 + done);
         a.t0 = static_cast<int>((t0 + done) & 1); a.rounds = static_cast<int>(std::min(kMostRounds, rounds - done));

@@ -16,6 +16,7 @@
 //  - Within a die the vector L1 caches write through to the die's L2: a store that has been waited for (vmcnt) is in L2, and
 //    a load with the sc1 bit, which does not look into L1, reads it there.  Data that one block leaves for another are
 //    read with load_fresh*, never with an ordinary load.  (Device-scope stores would go on to memory: 1.0 to 1.5 us.)
+//  - While the members are at work their compute units may have no room for other blocks, so a launch is kept to some milliseconds.
 //  - Every wait is bounded all the same: after kPolls polls, seconds, the members give up and set bit 31 of the status word.
 #pragma once
 

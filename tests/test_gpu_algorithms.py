@@ -668,6 +668,18 @@ def test_csr_rounds_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x
     assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
 
 
+def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq):
+    """A call of more rounds than one launch does, the model kept between the launches as between calls."""
+    many, few = _many_rounds_and_few(dq, 700, 2, 6, "acc", 8, 8, False, 9.0, 0, m=1050)
+    many.epoch_prologue(); few.epoch_prologue()
+    many.rounds(0, 1050)
+    for t in range(0, 1050, 5):
+        few.rounds(t, 5)
+    for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status", "y", "xsum"):
+        assert torch.equal(getattr(many, name), getattr(few, name)), name
+    assert host(many.x).any() and host(many.status)[0] == 0
+
+
 def test_csr_rounds_in_one_launch_on_several_streams_at_once(dq):
     """Three threads, a stream each, call at the same time, beside products that want the whole part: each of their launches finds a
     die, or waits for one, and the results are those of the separate rounds."""
