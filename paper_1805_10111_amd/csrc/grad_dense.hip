@@ -909,7 +909,9 @@ __global__ __launch_bounds__(kNarrowThreads) void full_narrow_partial_kernel(
 // float4 column blockIdx.x*16 + tx, four of them requested together; the 64 sub-sums are then added in two fixed steps
 // (8 threads add 8 each, one adds those 8).  Narrow column tiles keep many compute units busy (d = 4096: 64 blocks).
 // One block more, the first, writes P(x) = loss/n + (l2/2)||x||^2 + l1||x||_1: a pass over x that would otherwise come
-// after the sums of some block (20,958 columns 11.0 -> 6.7 us, 47,236 columns 23.6 -> 12.6 us).
+// after the sums of some block (20,958 columns 11.0 -> 6.7 us, 47,236 columns 23.6 -> 12.6 us).  Beyond 8192
+// columns it reads quads: by single floats it was the last to end (objective and gradient, 2000 rows of 60,000 columns 23.1 -> 20.5
+// us, 72,000 of 20,958 33.0 -> 32.5); below, one turn of single floats is sooner (8000 of 5000 columns 12.8, quads 13.1).
 constexpr int kFinishX = 16, kFinishY = 64;
 __global__ __launch_bounds__(kFinishX *kFinishY) void full_finish_kernel(
     const float *__restrict__ partial, int P, int64_t ldp, int64_t n, int64_t d, const float *__restrict__ x, float l2,
@@ -924,17 +926,32 @@ __global__ __launch_bounds__(kFinishX *kFinishY) void full_finish_kernel(
         const int tid = ty * kFinishX + tx, nt = kFinishX * kFinishY;
         double loss = 0.0, sq = 0.0, ab = 0.0;
         for (int p = tid; p < P; p += nt) loss += loss_partial[p];
-        constexpr int kFlight = 8;
-        for (int64_t j0 = tid; j0 < d; j0 += kFlight * nt) {
+        const auto add = [&](float v) {
+            const double xj = static_cast<double>(v);
+            sq += xj * xj;
+            ab += fabs(xj);
+        };
+        constexpr int kFlight = 8;                       // requested together, at clamped positions
+        const int64_t whole = d > kFlight * nt ? d / 4 : 0;
+        for (int64_t q0 = tid; q0 < whole; q0 += kFlight * nt) {
+            float4 v[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) v[u] = reinterpret_cast<const float4 *>(x)[min<int64_t>(q0 + u * nt, whole - 1)];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) {
+                if (q0 + u * nt >= whole) continue;
+                add(v[u].x);
+                add(v[u].y);
+                add(v[u].z);
+                add(v[u].w);
+            }
+        }
+        for (int64_t j0 = 4 * whole + tid; j0 < d; j0 += kFlight * nt) {
             float v[kFlight];
 #pragma unroll
             for (int u = 0; u < kFlight; ++u) v[u] = x[min<int64_t>(j0 + u * nt, d - 1)];
 #pragma unroll
-            for (int u = 0; u < kFlight; ++u) {
-                const double xj = j0 + u * nt < d ? static_cast<double>(v[u]) : 0.0;
-                sq += xj * xj;
-                ab += fabs(xj);
-            }
+            for (int u = 0; u < kFlight; ++u) add(j0 + u * nt < d ? v[u] : 0.0f);
         }
         loss = wave_sum_f64(loss);
         sq = wave_sum_f64(sq);
