@@ -104,8 +104,7 @@ def time_round_loop(tr, torch, steps, warmup):
         per_repeat.append(ev)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
-    if int(tr.status.item()) != 0:
-        raise FloatingPointError("non-finite quantization scale during the benchmark")
+    tr.check_status()
     loop_s = sorted(sum(e0.elapsed_time(e1) for e0, e1, _ in ev) * 1e-3 for ev in per_repeat)
     prologues = sorted(p0.elapsed_time(p1) * 1e-3 for p0, p1 in prologue_events)
     while tr._t != 0:                   # finish the epoch that the last measurement ended in

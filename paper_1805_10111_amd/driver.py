@@ -134,6 +134,7 @@ class DoubleQuantTrainer:
         quantized vector, 32*d unquantized; Section 4.2: position + value per nonzero of a sparsified one)."""
         d, M, m = self.prob.d, self.M, self.m
         self.log.objectives.append(float(self.obj.item()))
+        self.check_status(scales=False)
         self.log.rounds += m
         for flag in flags:
             self.log.bits_down += dq.dq_message_bits(dq.MSG_FLAG if flag else dq.MSG_DENSE, d, self.b_x)
@@ -147,9 +148,18 @@ class DoubleQuantTrainer:
         for _ in range(S):
             self.run_epoch()
         self.log.objectives.append(self.objective(self.x_snap))
-        if int(self.status.item()) != 0:
-            raise FloatingPointError("a quantization scale was not finite (NaN/Inf in a gradient or the model)")
+        self.check_status()
         return self.log
+
+    def check_status(self, scales: bool = True) -> None:
+        """The status word's bits, each by its own name: bit 31 at the end of every epoch, since the epoch would go on from a
+        state that is not that of its rounds; bit 0 (`scales`) at the end of a run, whose numbers tell it anyway."""
+        bits = int(self.status.item()) & 0xFFFFFFFF
+        if bits & 0x80000000:
+            raise RuntimeError("dq_run_rounds: the blocks of a launch waited for each other for seconds and gave up; "
+                               "the state is not that of the rounds asked for")
+        if scales and bits != 0:
+            raise FloatingPointError("a quantization scale was not finite (NaN/Inf in a gradient or the model)")
 
     def objective(self, x: torch.Tensor) -> float:
         g = torch.empty_like(self.g_snap)

@@ -209,3 +209,25 @@ def test_a_problem_with_csr_features_names_its_entries_only_where_it_has_them():
     """The number of nonzeros is a hint: a problem without index array is made as ever (and refused by the calls that take it)."""
     import paper_1805_10111_amd as dq
     assert dq.DeviceProblem(n=3, d=2, y=None, l2=0.0, l1=0.0)._s.lda == 0
+
+
+def test_the_driver_names_what_the_status_word_says():
+    """Bit 31 (the blocks of a launch gave up waiting for each other: the state is of no use) is not reported as a scale that is not
+    finite, and at the end of an epoch already; bit 0 at the end of a run."""
+    import torch
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer, RunLog
+    tr = object.__new__(DoubleQuantTrainer)
+    tr.status = torch.zeros(1, dtype=torch.int32)
+    tr.check_status()
+    tr.status[0] = 1
+    tr.check_status(scales=False)
+    with pytest.raises(FloatingPointError):
+        tr.check_status()
+    for word in (-2 ** 31, -2 ** 31 + 1):
+        tr.status[0] = word
+        for scales in (False, True):
+            with pytest.raises(RuntimeError, match="gave up"):
+                tr.check_status(scales=scales)
+    tr.prob, tr.M, tr.m, tr.algo, tr.obj, tr.log = csr(), 2, 3, "asylpg", torch.zeros(1, dtype=torch.float64), RunLog()
+    with pytest.raises(RuntimeError, match="gave up"):
+        tr._account([False] * 3)
