@@ -26,16 +26,10 @@
 
 namespace dq {
 
-constexpr int kRoundsRows = 128;                          // rows of a mini-batch: two a lane of the wavefront that lays them out
-constexpr int kBusyWaves = kCsrWaves - 1, kBusy = kBusyWaves * kWave;     // all but the wavefront that waits at exchanges
 constexpr int kNoRow = 0x7FFFFFFF;                        // where the rows past the last one begin
-constexpr int kEntriesEach = 8;                           // entries a thread holds; with more of them the rows are read in the round
-constexpr int kChunk = 256;                               // columns of a chunk: a quad a lane
-constexpr int kMostChunks = 7, kColumns = 2;              // of a member, and columns a thread
-constexpr int kPasses = 2;                                // chunks of all workers that a wavefront takes in turn
-constexpr int kUnitWaves = kBusyWaves - 1;                // (not the one that lays out mini-batches)
 
-static_assert(kMostChunks * kChunk <= kColumns * kBusy, "every column has a thread");
+static_assert(kBusyWaves == kCsrWaves - 1 && kBusy == kBusyWaves * kWave, "one wavefront waits at exchanges");
+static_assert(sizeof(DieControl) <= kRoundsControl, "room in the workspace");
 
 struct CsrRoundsArgs {
     CsrView A;
@@ -67,6 +61,7 @@ struct CsrRoundsLds {
     int total, poison, dead, sh[2];
     uint32_t slice_max, value;
 };
+static_assert(sizeof(CsrRoundsLds) + 512 <= kRoundsFixedLds, "static LDS");
 
 // The arguments, read again wherever they are used: more of them than there are scalar registers to keep them in.
 typedef const CsrRoundsArgs __attribute__((address_space(4))) *CsrRoundsArgsPtr;
@@ -701,58 +696,19 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
 }
 
 // ------------------------------------------------------------------ host side
-constexpr int64_t kFewRounds = 8;                        // calls of fewer are not for one die
-constexpr int64_t kRoundsLds = 160 * 1024 - static_cast<int64_t>(sizeof(CsrRoundsLds)) - 512;     // for the dynamic part
-
 int fill_u32(uint32_t *p, int64_t n, uint32_t value, hipStream_t st);
 
-// Lays out members, LDS and workspace; false: these rounds are not for one die.  They are where measured faster than launches
-// (us a round, 30 rounds a call unless said; launches, then this):
-//  - the snapshot has room in LDS: d 26,323, M 12, read from L2 instead: 13.1, 18.2; d 38,834, M 8: 16.1, 19.1.
-//  - no wavefront has more than two chunks of gradients to quantize, which stay in registers: M 8, d 20,958 (24 chunks a
-//    member) 11.4, 9.9; M 4, d 28,409 12.6, 11.3; M 28, d 5000 12.7, 10.7; M 21, d 4340 12.2, 10.1; M 1, d 300 9.0, 7.7; M 8,
-//    d 20,000, b_x 12 16.4, 11.5; M 20, d 6385, batches of 128 17.2, 14.5.  With four: M 10, d 20,958 12.0, 12.7; M 16, d
-//    12,000 11.6, 12.7; M 32, d 6400 13.3, 14.0.
-//  - calls of eight rounds or more: the launches around it, and finding together, are 10 us a call.  M 8, d 20,958: two rounds
-//    12.5, 15.2; five 11.8, 12.0; eight 11.6, 11.2.
-//  - mini-batches that the busy threads hold in registers, as far as the caller's count of entries can tell.
-static bool csr_rounds_layout(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds,
-                              CsrRoundsArgs &a, size_t &lds)
+static bool csr_rounds_layout(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds, CsrRoundsShape &s)
 {
-    const int64_t d = prob->d, M = cfg->M, B = cfg->B;
-    CsrPlan plan;
-    if (prob->layout != 1 || cfg->tau != 0 || !st->z_snap || cfg->algo == DQ_ALGO_SPARSE || cfg->b == 32 || cfg->b_x < 2 || cfg->b_x > 16 ||
-        B > kRoundsRows || M > kDieUnits || rounds < kFewRounds || !csr_plan(d, false, plan))
-        return false;
-    const int64_t S = std::min<int64_t>(std::min<int64_t>(kDieUnits / M, 16), ceil_div(d, 256));
-    a.win = static_cast<int>(ceil_div(ceil_div(d, S), 256) * 256);
-    a.S = static_cast<int>(ceil_div(d, a.win));
-    a.want = static_cast<int>(std::max<int64_t>(M * a.S, std::min<int64_t>(kDieUnits, ceil_div(d, kChunk))));
-    a.chunks = static_cast<int>(ceil_div(ceil_div(d, kChunk), a.want));
-    if (a.chunks > kMostChunks || M * a.chunks > kPasses * kUnitWaves) return false;
-    const double mean = static_cast<double>(B) * (prob->lda > 0 ? static_cast<double>(prob->lda) / static_cast<double>(prob->n) : 100.0);
-    a.cap = plan.cap;
-    const int64_t most = std::min<int64_t>(plan.cap, kEntriesEach * kBusy);
-    if (mean * 1.25 > static_cast<double>(most)) return false;
-    a.room = static_cast<int>(std::max<int64_t>(M * a.chunks * (kChunk / 4), std::min<int64_t>(most, static_cast<int64_t>(1.5 * mean) + 256)));
-    a.room = (a.room + 63) / 64 * 64;
-    const int64_t message = pad4((d * cfg->b_x + 31) / 32 + 1);
-    const int64_t words = a.win + message + a.room + pad4(d);
-    if (words * 4 > kRoundsLds) return false;
-    // (what makes up more than half of a compute unit's LDS: no two blocks on one)
-    lds = static_cast<size_t>(std::max<int64_t>(words * 4, 72 * 1024));
-    // the M rows of a step, its slices' results, then what dq_run_rounds has for itself
-    a.ld = pad4(d);
-    a.rows = static_cast<float *>(st->ws);
-    a.ctl = reinterpret_cast<DieControl *>(reinterpret_cast<char *>(a.rows + M * a.ld) + M * 64);
-    return true;
+    return prob->layout == 1 && cfg->tau == 0 && st->z_snap && cfg->algo != DQ_ALGO_SPARSE && cfg->b != 32 &&
+           csr_rounds_shape(prob->d, prob->n, prob->lda, cfg->M, cfg->B, cfg->b_x, rounds, s) &&
+           st->ws_bytes >= csr_run_offset(prob->d, cfg->M) + kRoundsControl;
 }
 
 bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds)
 {
-    CsrRoundsArgs a{};
-    size_t lds;
-    return csr_rounds_layout(prob, cfg, st, rounds, a, lds);
+    CsrRoundsShape s;
+    return csr_rounds_layout(prob, cfg, st, rounds, s);
 }
 
 template <bool ACC, bool EACH, bool ALONE>
@@ -778,9 +734,15 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
     const void *quads[] = {st->x, st->x_snap, st->g_snap, acc ? st->y : nullptr, acc ? st->xsum : nullptr, st->ws};
     for (const void *p : quads)
         if (p && !aligned16(p)) return DQ_ERR_INVALID_ARG;
+    CsrRoundsShape s;
+    if (!csr_rounds_layout(prob, cfg, st, rounds, s)) return DQ_ERR_UNSUPPORTED;
     CsrRoundsArgs a{};
-    size_t lds;
-    if (!csr_rounds_layout(prob, cfg, st, rounds, a, lds)) return DQ_ERR_UNSUPPORTED;
+    a.S = s.S; a.win = s.win; a.want = s.want; a.chunks = s.chunks; a.cap = s.cap; a.room = s.room;
+    // the M rows of a step, its slices' results, then what dq_run_rounds has for itself
+    a.ld = pad4(prob->d);
+    a.rows = static_cast<float *>(st->ws);
+    a.ctl = reinterpret_cast<DieControl *>(static_cast<char *>(st->ws) + csr_run_offset(prob->d, cfg->M));
+    const size_t lds = static_cast<size_t>(s.lds);
     a.A = CsrView{prob->indptr, prob->indices, prob->values, prob->y, prob->n, prob->d};
     a.z_snap = st->z_snap;
     a.M = static_cast<int>(cfg->M); a.B = static_cast<int>(cfg->B); a.b = cfg->b; a.b_x = cfg->b_x;

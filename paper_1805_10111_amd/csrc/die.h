@@ -24,7 +24,6 @@
 
 namespace dq {
 
-constexpr int kDieUnits = 32;                    // compute units of a die
 constexpr int kDies = 16;                        // (numbers that a die may have)
 constexpr long long kPickTicks = 3000, kJoinTicks = 500000;          // of the 100 MHz clock: 30 us, 5 ms
 constexpr int kPolls = 1 << 23;

@@ -1465,13 +1465,7 @@ static int64_t csr_full_splits(int64_t n)
     return P;
 }
 
-constexpr int kMaxSlices = kMaxParts;       // identical blocks per worker that share the tail of a worker step
-
-// the M rows of a worker step's workspace and its slices' results: what comes behind them is dq_run_rounds' own
-static int64_t csr_run_offset(const dq_problem *prob, int64_t M)
-{
-    return M * pad4(prob->d) * 4 + M * kMaxSlices * 8;
-}
+static_assert(kMaxSlices == kMaxParts, "a row's blocks leave a value each");
 
 int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64_t)
 {
@@ -1484,10 +1478,10 @@ int64_t csr_workspace_bytes(int32_t op, const dq_problem *prob, int64_t M, int64
     // a row per worker: the whole gradient when it does not fit in LDS, else the sparsified gradient when the
     // sparsifier is split over several blocks per worker (see csr_worker); then 8 values + 8 counts per worker: all
     // that a single step uses
-    if (op == DQ_OP_WORKER_STEP) return csr_run_offset(prob, M);
+    if (op == DQ_OP_WORKER_STEP) return csr_run_offset(prob->d, M);
     // then one more row, in which dq_run_rounds keeps (decoded model) - snapshot between two rounds of a call; then two
     // sets of prepared mini-batches (see PrepLayout), the one a round reads and the one it leaves for the next
-    return csr_run_offset(prob, M) + pad4(prob->d) * 4 + 2 * M * csr_prep_stride(prob->d) * 4;
+    return csr_run_bytes(prob->d, M);
 }
 
 // Kernels that use more than 64 KB of dynamic LDS must be told so once (the limit is raised to the budget).
@@ -1620,7 +1614,7 @@ CsrRunLayout csr_run_layout(const dq_problem *prob, const WorkerArgs &a)
     CsrRunLayout out{};
     CsrStep s;
     if (!a.ws || !csr_step(prob, a, s) || a.ws_bytes < csr_workspace_bytes(DQ_OP_VR_GRAD, prob, a.M, a.B)) return out;
-    char *base = static_cast<char *>(a.ws) + csr_run_offset(prob, a.M);
+    char *base = static_cast<char *>(a.ws) + csr_run_offset(prob->d, a.M);
     const bool light = csr_light_batches(a.B, prob->n, prob->lda, kCsrInFlight, s.plan.cap);
     out.pending = s.sliced && s.common && s.can_prepare && (a.b_x == 2 || a.b_x == 4 || a.b_x == 8) && s.sl.win <= 4 * kCsrThreads && light;
     out.prep = csr_prep_room(prob->d, a.M, a.B, s.plan, out.pending);

@@ -99,7 +99,13 @@ inline int csr_prep_cap(int64_t d, const CsrPlan &plan)
     return plan.cap < one_sum.cap ? plan.cap : one_sum.cap;
 }
 
-// What a run's workspace holds behind its M rows and slice results: pad4(d) words and twice M times csr_prep_stride(d).
+// A step's workspace: M rows of the gradient, then kMaxSlices maxima and as many counts per worker.  A run's has its own behind
+// them: pad4(d) words and twice M times csr_prep_stride(d).
+constexpr int kMaxSlices = 8;                    // blocks that share a worker's step
+inline int64_t csr_run_offset(int64_t d, int64_t M) { return M * pad4(d) * 4 + M * kMaxSlices * 8; }
+inline int64_t csr_run_bytes(int64_t d, int64_t M) { return csr_run_offset(d, M) + pad4(d) * 4 + 2 * M * csr_prep_stride(d) * 4; }
+
+// What a run's workspace holds behind its M rows and slice results.
 // Either the difference of model and snapshot, a word per column, and the two sets of prepared mini-batches; or, where the
 // worker kernel quantizes the model and has no use for that row, two sets of mini-batches in all of it, whose entries
 // can have the snapshot at their column beside them.
@@ -133,6 +139,67 @@ inline bool csr_light_batches(int64_t B, int64_t n, int64_t entries, int in_flig
 {
     const double mean = static_cast<double>(B) * (entries > 0 ? static_cast<double>(entries) / static_cast<double>(n) : 100.0);
     return mean <= 1.2 * in_flight && mean * 1.125 <= cap;
+}
+
+// ------------------------------------------------------------------ rounds on one die, CSR features (csr_rounds.hip)
+constexpr int kDieUnits = 32;                    // compute units of a die
+constexpr int kRoundsRows = 128;                 // rows of a mini-batch: two a lane of the wavefront that lays them out
+constexpr int kBusyWaves = 15, kBusy = kBusyWaves * 64;       // all but the wavefront that waits at exchanges
+constexpr int kUnitWaves = kBusyWaves - 1;       // (not the one that lays out mini-batches)
+constexpr int kEntriesEach = 8;                  // entries a thread holds; with more of them the rows are read in the round
+constexpr int kChunk = 256;                      // columns of a chunk: a quad a lane
+constexpr int kMostChunks = 7, kColumns = 2;     // of a member, and columns a thread
+constexpr int kPasses = 2;                       // chunks of all workers that a wavefront takes in turn
+constexpr int64_t kFewRounds = 8;                // calls of fewer are not for one die
+constexpr int64_t kRoundsFixedLds = 13360;       // static arrays
+constexpr int64_t kRoundsLds = 160 * 1024 - kRoundsFixedLds;  // for the dynamic part
+constexpr int64_t kRoundsControl = 720;          // bytes of a run's workspace, from csr_run_offset on, for what the members share
+
+static_assert(kMostChunks * kChunk <= kColumns * kBusy, "every column has a thread");
+
+struct CsrRoundsShape {
+    int S, win;                                  // slices of a worker, columns of one
+    int want, chunks;                            // members, chunks of one
+    int cap;                                     // entries of a group of rows (CsrPlan::cap)
+    int room;                                    // entries that LDS has room for
+    int64_t lds;                                 // bytes of dynamic LDS
+};
+
+// false: these rounds are not for one die.  They are where measured faster than launches (us a round, 30 rounds a call unless
+// said; launches, then this):
+//  - the snapshot has room in LDS: d 26,323, M 12, read from L2 instead: 13.1, 18.2; d 38,834, M 8: 16.1, 19.1.
+//  - no wavefront has more than two chunks of gradients to quantize, which stay in registers: M 8, d 20,958 (24 chunks a
+//    member) 11.4, 9.9; M 4, d 28,409 12.6, 11.3; M 28, d 5000 12.7, 10.7; M 21, d 4340 12.2, 10.1; M 1, d 300 9.0, 7.7; M 8,
+//    d 20,000, b_x 12 16.4, 11.5; M 20, d 6385, batches of 128 17.2, 14.5.  With four: M 10, d 20,958 12.0, 12.7; M 16, d
+//    12,000 11.6, 12.7; M 32, d 6400 13.3, 14.0.
+//  - calls of eight rounds or more: the launches around it, and finding together, are 10 us a call.  M 8, d 20,958: two rounds
+//    12.5, 15.2; five 11.8, 12.0; eight 11.6, 11.2.
+//  - mini-batches that the busy threads hold in registers, as far as the caller's count of entries can tell.
+inline bool csr_rounds_shape(int64_t d, int64_t n, int64_t entries, int64_t M, int64_t B, int b_x, int64_t rounds, CsrRoundsShape &s)
+{
+    const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
+    const auto most = [](int64_t a, int64_t b) { return a > b ? a : b; };
+    CsrPlan plan;
+    if (b_x < 2 || b_x > 16 || B > kRoundsRows || M > kDieUnits || rounds < kFewRounds || !csr_plan(d, false, plan)) return false;
+    const int64_t S = least(least(kDieUnits / M, 16), ceil_div(d, 256));
+    s.win = static_cast<int>(ceil_div(ceil_div(d, S), 256) * 256);
+    s.S = static_cast<int>(ceil_div(d, s.win));
+    s.want = static_cast<int>(most(M * s.S, least(kDieUnits, ceil_div(d, kChunk))));
+    const int64_t chunks = ceil_div(ceil_div(d, kChunk), s.want);
+    if (chunks > kMostChunks || M * chunks > kPasses * kUnitWaves) return false;
+    s.chunks = static_cast<int>(chunks);
+    const double mean = static_cast<double>(B) * (entries > 0 ? static_cast<double>(entries) / static_cast<double>(n) : 100.0);
+    s.cap = plan.cap;
+    const int64_t held = least(plan.cap, kEntriesEach * kBusy);
+    if (mean * 1.25 > static_cast<double>(held)) return false;
+    const int64_t room = most(M * chunks * (kChunk / 4), least(held, static_cast<int64_t>(1.5 * mean) + 256));
+    s.room = static_cast<int>(ceil_div(room, 64) * 64);
+    const int64_t message = pad4((d * b_x + 31) / 32 + 1);
+    const int64_t bytes = (s.win + message + s.room + pad4(d)) * 4;
+    if (bytes > kRoundsLds) return false;
+    // (what makes up more than half of a compute unit's LDS: no two blocks on one)
+    s.lds = most(bytes, 72 * 1024);
+    return true;
 }
 
 }  // namespace dq

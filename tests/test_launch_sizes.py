@@ -110,3 +110,35 @@ def test_the_model_is_quantized_by_the_worker_for_light_mini_batches_only(tmp_pa
     if (csr_light_batches(1, 1, 1ll << 60, 4096, 8192) || !csr_light_batches(1, 1ll << 40, 1, 4096, 8192)) std::printf("ends\\n");
     """)
     assert out == "", out[:2000]
+
+
+def test_rounds_on_one_die_fit_the_workspace_and_the_chip(tmp_path):
+    """CSR rounds in one launch, every width and number of workers: what the members share lies behind the rows of a step and inside a run's
+    workspace; slices, chunks and threads cover every column; members, LDS and what a wavefront quantizes are within bounds."""
+    out = _sweep(tmp_path, """
+    const int rows[] = {1, 8, 32, 128}, widths[] = {2, 3, 8, 11, 16};
+    const int64_t per_row[] = {0, 1, 9, 52, 400};
+    long taken = 0;
+    for (int64_t d = 1; d < (1ll << kColBits); d += 1 + d / 997)
+        for (int M = 1; M <= 33; ++M) {
+            const int64_t at = csr_run_offset(d, M);
+            if (at % 16 || at < M * pad4(d) * 4 + M * 2 * kMaxSlices * 4 || at + kRoundsControl > csr_run_bytes(d, M)) std::printf("room d %ld M %d\\n", (long)d, M);
+            for (int B : rows)
+                for (int b_x : widths)
+                    for (int64_t each : per_row) {
+                        CsrRoundsShape s;
+                        if (!csr_rounds_shape(d, 1000, 1000 * each, M, B, b_x, 8, s)) continue;
+                        ++taken;
+                        bool ok = M <= kDieUnits && s.want >= 1 && s.want <= kDieUnits && M * s.S <= s.want && s.S <= 16 && s.win % 256 == 0;
+                        ok = ok && (int64_t)s.S * s.win >= d && (int64_t)(s.S - 1) * s.win < d && (int64_t)s.want * s.chunks * kChunk >= d;
+                        ok = ok && s.chunks <= kMostChunks && M * s.chunks <= kPasses * kUnitWaves && s.room % 64 == 0 && s.room >= M * s.chunks * 64;
+                        ok = ok && s.lds > 160 * 1024 / 2 - kRoundsFixedLds && s.lds + kRoundsFixedLds <= 160 * 1024;
+                        ok = ok && s.lds >= 4 * (s.win + (d * b_x + 31) / 32 + 1 + s.room + pad4(d)) && s.cap <= kMaxStage;
+                        if (!ok) std::printf("d %ld M %d B %d b_x %d %ld\\n", (long)d, M, B, b_x, (long)each);
+                    }
+        }
+    CsrRoundsShape s;
+    if (!taken || csr_rounds_shape(20958, 1000, 52000, 8, 32, 8, 7, s) || csr_rounds_shape(20958, 1000, 52000, 8, 32, 17, 8, s) ||
+        csr_rounds_shape(20958, 1000, 52000, 8, 129, 8, 8, s) || !csr_rounds_shape(20958, 1000, 52000, 8, 32, 8, 8, s)) std::printf("ends\\n");
+    """)
+    assert out == "", out[:2000]
