@@ -131,21 +131,12 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
             }
         }
     };
-    const auto scan = [&](int v) {                       // inclusive, over the wavefront
-        v += dpp_move_or_zero<0x111, 0xf>(v);            // row_shr:1, 2, 4, 8, then the rows' last lanes
-        v += dpp_move_or_zero<0x112, 0xf>(v);
-        v += dpp_move_or_zero<0x114, 0xf>(v);
-        v += dpp_move_or_zero<0x118, 0xf>(v);
-        v += dpp_move_or_zero<0x142, 0xa>(v);
-        v += dpp_move_or_zero<0x143, 0xc>(v);
-        return v;
-    };
     const auto leave_rows = [&]() {                      // ... and leaves them in LDS
         int base = 0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (u * kWave >= B) break;
-            const int len = static_cast<int>(row_end[u] - row_start[u]), r = lane + kWave * u, incl = scan(len);
+            const int len = static_cast<int>(row_end[u] - row_start[u]), r = lane + kWave * u, incl = wave_scan_i32(len);
             if (r < B) {
                 const int pre = base + incl - len, end = base + incl;
                 l.meta.start[r] = row_start[u];

@@ -186,6 +186,18 @@ __device__ __forceinline__ float wave_sum_f32(float v)
     return v;
 }
 
+// Inclusive prefix sum over the wavefront's lanes.
+__device__ __forceinline__ int wave_scan_i32(int v)
+{
+    v += dpp_move_or_zero<0x111, 0xf>(v);            // row_shr:1, 2, 4, 8, then the rows' last lanes
+    v += dpp_move_or_zero<0x112, 0xf>(v);
+    v += dpp_move_or_zero<0x114, 0xf>(v);
+    v += dpp_move_or_zero<0x118, 0xf>(v);
+    v += dpp_move_or_zero<0x142, 0xa>(v);
+    v += dpp_move_or_zero<0x143, 0xc>(v);
+    return v;
+}
+
 // wave_sum_f32 of sixteen values at once, bit for bit: lane l receives the sum of v[l % 16].  The same tree of additions
 // (neighbours, pairs of them, ... halves), but at each of the first four levels a lane keeps only the half of the values
 // that its number selects and hands the other half to its partner: 15 additions and as many exchanges instead of 96.

@@ -28,13 +28,7 @@ static inline int position_bits(int64_t d)
 __device__ __forceinline__ int block_scan_exclusive(int v, int *scratch, int *total)
 {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    int incl = v;
-    incl += dpp_move_or_zero<0x111, 0xf>(incl);          // row_shr:1, 2, 4, 8, then the rows' last lanes
-    incl += dpp_move_or_zero<0x112, 0xf>(incl);
-    incl += dpp_move_or_zero<0x114, 0xf>(incl);
-    incl += dpp_move_or_zero<0x118, 0xf>(incl);
-    incl += dpp_move_or_zero<0x142, 0xa>(incl);
-    incl += dpp_move_or_zero<0x143, 0xc>(incl);
+    const int incl = wave_scan_i32(v);
     if (lane == kWave - 1) scratch[wave] = incl;
     __syncthreads();
     const int mine = lane < kWireThreads / kWave ? scratch[lane] : 0;      // (every wavefront scans the sixteen sums)
