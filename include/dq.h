@@ -32,7 +32,8 @@
  *  - `status` (nullable) is a device uint32 that is OR-ed into, never cleared:
  *    bit 0 = a scale delta was not finite (NaN/Inf in the input vector);
  *    bit 31 = dq_run_rounds, where the blocks of one launch do many rounds: they waited for each other
- *    for seconds and gave up, the state is not that of the rounds asked for.
+ *    for seconds and gave up, the state is not that of the rounds asked for.  (Without a status word no launch does
+ *    many rounds that way.)
  *  - Random streams are addressed, not stateful: (seed, iter, worker, tag,
  *    coordinate) names one variate; the same address gives the same variate in
  *    any call, any launch shape.  Generator: Philox4x32-10; key = halves of

@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 } else if (planner && lane < M) {
                     const Scale sc = make_scale(l.amax[lane], b);
                     l.delta[lane] = sc.delta;
-                    if (die.me == 0 && sc.bad && a->status) atomicOr(a->status, 1u);
+                    if (die.me == 0 && sc.bad) atomicOr(a->status, 1u);
                     if (die.me == 0 && last) a->delta[lane] = sc.delta;
                 }
             } else {
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
             if (die.me == 0 && t == 0) {
                 a->absmax_x[(a->t0 + k) & 1] = __uint_as_float(l.value);
                 if (last) a->delta_x[0] = ms.delta;
-                if (ms.bad && a->status) atomicOr(a->status, 1u);
+                if (ms.bad) atomicOr(a->status, 1u);
             }
 #pragma unroll 1
             for (int member = die.me; member < die.me + members; ++member) {
@@ -683,15 +683,16 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 if (!planner || C > kBusy - kWave) draw_model_words(die.me, iter + 2u);
             }, [](uint32_t) {})) break;
     }
-    if (l.dead && t == 0 && a->status) atomicOr(a->status, kGaveUp);
+    if (l.dead && t == 0) atomicOr(a->status, kGaveUp);
 }
 
 // ------------------------------------------------------------------ host side
 int fill_u32(uint32_t *p, int64_t n, uint32_t value, hipStream_t st);
 
+// (without a status word nobody would learn that the members gave up: die.h)
 static bool csr_rounds_layout(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds, CsrRoundsShape &s)
 {
-    return prob->layout == 1 && cfg->tau == 0 && st->z_snap && cfg->algo != DQ_ALGO_SPARSE && cfg->b != 32 &&
+    return prob->layout == 1 && cfg->tau == 0 && st->z_snap && st->status && cfg->algo != DQ_ALGO_SPARSE && cfg->b != 32 &&
            csr_rounds_shape(prob->d, prob->n, prob->lda, cfg->M, cfg->B, cfg->b_x, rounds, s) &&
            st->ws_bytes >= csr_run_offset(prob->d, cfg->M) + kRoundsControl;
 }

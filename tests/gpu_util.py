@@ -18,3 +18,16 @@ def words(t):
 
 def gpu_available():
     return torch.cuda.is_available()
+
+
+def launches(call):
+    """How many kernels `call` enqueues: the nodes of a graph that captures it (nothing of it runs)."""
+    import ctypes
+    from paper_1805_10111_amd import api
+    g, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            call()
+    n = ctypes.c_size_t(0)
+    assert api._lib.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value

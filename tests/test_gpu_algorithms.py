@@ -13,7 +13,7 @@ import torch
 import oracle
 from oracle import algorithms as alg
 import synth
-from gpu_util import dev, host, words
+from gpu_util import dev, host, launches, words
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-5
@@ -666,6 +666,21 @@ def test_csr_rounds_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x
             assert torch.equal(getattr(many, name), getattr(few, name)), (epoch, name)
         many.epoch_epilogue(); few.epoch_epilogue()
     assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
+
+
+def test_csr_rounds_without_a_status_word_are_not_done_in_one_launch(dq):
+    """The status word is how a caller learns that the blocks of such a launch gave up waiting for each other.  Without one each round has
+    launches of its own, with the same results."""
+    many, few = _many_rounds_and_few(dq, 4097, 8, 24, "asylpg", 8, 8, False, 30.0, 0)
+    for tr in (many, few):
+        tr.epoch_prologue()
+        tr.rounds(0, 11)
+    assert launches(lambda: many.rounds(0, 11)) <= 3
+    few.state.status = None
+    assert launches(lambda: few.rounds(0, 11)) >= 22
+    many.rounds(11, 8); few.rounds(11, 8)
+    for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x"):
+        assert torch.equal(getattr(many, name), getattr(few, name)), name
 
 
 def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq):
