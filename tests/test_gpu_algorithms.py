@@ -440,15 +440,17 @@ def test_sparse_messages_through_the_wire_format(dq):
         assert not w[r, used[r]:].any() and (used[r] == 0 or w[r, :used[r]].any())
 
 
-@pytest.mark.parametrize("d,M,B,b,nnz,l2,infinite", [
-    (47236, 8, 32, 4, 60.0, 1e-4, False), (36003, 5, 24, 8, 30.0, 1e-4, False), (40001, 40, 9, 4, 30.0, 50.0, False),
-    (36001, 130, 3, 4, 30.0, 1e-4, False), (47233, 3, 16, 8, 30.0, 50.0, False), (47236, 4, 32, 4, 30.0, 1e-4, True),
-    (47236, 8, 32, 2, 60.0, 1e-4, False), (20958, 8, 32, 4, 30.0, 1e-4, False)])
-def test_messages_encoded_by_the_worker_step_equal_the_separate_encoder(dq, d, M, B, b, nnz, l2, infinite):
+@pytest.mark.parametrize("d,M,B,b,nnz,l2,infinite,kernels", [
+    (47236, 8, 32, 4, 60.0, 1e-4, False, 6), (36003, 5, 24, 8, 30.0, 1e-4, False, 6), (40001, 40, 9, 4, 30.0, 50.0, False, 6),
+    (36001, 85, 3, 4, 30.0, 1e-4, False, 6), (36001, 130, 3, 4, 30.0, 1e-4, False, 5), (47233, 3, 16, 8, 30.0, 50.0, False, 6),
+    (47236, 4, 32, 4, 30.0, 1e-4, True, 6), (47236, 8, 32, 2, 60.0, 1e-4, False, 5), (20958, 8, 32, 4, 30.0, 1e-4, False, 6)])
+def test_messages_encoded_by_the_worker_step_equal_the_separate_encoder(dq, d, M, B, b, nnz, l2, infinite, kernels):
     """Models wider than the on-chip buffer, Alg. 2: the launch that quantizes also encodes (4 and 8 bits).  Streams are those of
     dq_sparse_encode on the messages, every word; messages and models those of a run without streams.  Eight slices a worker
-    down to one, few entries and rows of which most is kept, ragged ends; an infinite feature: no entries; 2 bits
-    and a model of one slice, which keep the separate encoder."""
+    down to two, few entries and rows of which most is kept, ragged ends; an infinite feature: no entries; and what keeps the separate
+    encoder: more workers than are split, 2 bits, a model that a block holds.  `kernels` of a round: worker, sparsifier, quantizer
+    and encoder, decoder, update, the model's message; without the split the worker has the sparsifier and (130 workers, 2 bits)
+    the quantizer, and the encoder is one of its own."""
     from paper_1805_10111_amd.driver import DoubleQuantTrainer
     p = synth.sparse_text_logistic(400, d, mean_nnz=nnz, seed=8)
     if infinite:
@@ -458,7 +460,11 @@ def test_messages_encoded_by_the_worker_step_equal_the_separate_encoder(dq, d, M
     plain, wired = (DoubleQuantTrainer(P, "sparse", M, B, 8, b, 4, 0.01, seed=3, sparse_wire=w) for w in (False, True))
     for tr in (plain, wired):
         tr.epoch_prologue()
+        tr.rounds(0, 2)                                    # (one-time function attributes are set outside a capture)
+    assert launches(lambda: wired.rounds(1, 1)) == kernels
     seen = 0
+    for tr in (plain, wired):
+        tr.epoch_prologue()
     for t in range(4):
         wired.wire.fill_(-1)
         plain.rounds(t, 1); wired.rounds(t, 1)
@@ -472,7 +478,7 @@ def test_messages_encoded_by_the_worker_step_equal_the_separate_encoder(dq, d, M
     assert (seen == 0) == infinite
 
 
-@pytest.mark.parametrize("name", ["C1", "C4", "C3"])
+@pytest.mark.parametrize("name", ["C1", "C4", "C3", "C2"])
 def test_rounds_replayed_from_a_captured_graph(dq, name):
     """dq_run_rounds only enqueues kernels (no allocation, no memset), so a caller may capture an epoch's rounds
     into a graph.  Every replay -- with eager work of the program between replays -- must give what the same
@@ -485,6 +491,7 @@ def test_rounds_replayed_from_a_captured_graph(dq, name):
         tr.epoch_prologue()
         tr.rounds(0, m)                                  # warm-up: one-time function attributes are set outside the capture
     torch.cuda.synchronize()
+    assert (launches(lambda: graph.rounds(0, m)) <= 3) == (name in ("C1", "C2")), "all rounds in one launch"
     g = torch.cuda.CUDAGraph()
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
