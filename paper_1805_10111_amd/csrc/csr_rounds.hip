@@ -77,7 +77,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
     if constexpr (ALONE) {
         if (load_fresh(&a->ctl->members) == static_cast<uint32_t>(a->want)) return;
     } else {
-        die = die_join(a->ctl, static_cast<uint32_t>(a->want), l.sh);
+        constexpr long long kJoinTicks = 200000;         // (2 to 4 ms: kernels of other streams end meanwhile)
+        die = die_join(a->ctl, static_cast<uint32_t>(a->want), 0u, kJoinTicks, l.sh);
         if (die.me < 0 || die.count != a->want) return;
     }
     int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);

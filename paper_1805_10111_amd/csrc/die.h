@@ -10,28 +10,31 @@
 //  - Nobody waits without end for a block that may not have started.  A launch has `want` blocks for every die; each block
 //    adds itself to the count of the die that it finds itself on, the first die whose blocks are complete is the one, and all
 //    others end.  Two launches that begin together can each hold a part of every die: so after kPickTicks a launch picks the die
-//    where it has most blocks and gives up the others.  Where that one is not complete for kJoinTicks either, because other
+//    where it has most blocks and gives up the others.  Where that one is not complete for `patience` either, because other
 //    work holds its compute units, it is closed with the blocks it has by then.  The members are running when the rounds begin,
-//    so whatever they wait for does happen; with fewer than it wants a kernel ends, and one behind it does the work.
+//    so whatever they wait for does happen; with fewer than it wants a kernel ends, and one behind it does the work with those
+//    that it finds.
+//  - Launches that hold equal parts pick among the dies by lot (two that always took the first would wait for each other, and
+//    neither be complete), and those that picked the same one all the same lose patience at different times, by lot again.
 //  - Within a die the vector L1 caches write through to the die's L2: a store that has been waited for (vmcnt) is in L2, and
 //    a load with the sc1 bit, which does not look into L1, reads it there.  Data that one block leaves for another are
 //    read with load_fresh*, never with an ordinary load.  (Device-scope stores would go on to memory: 1.0 to 1.5 us.)
 //  - While the members are at work their compute units may have no room for other blocks, so a launch is kept to some milliseconds.
-//  - Every wait is bounded all the same: after kPolls polls, seconds, the members give up and set bit 31 of the status word.
+//  - The members' waits for each other are bounded all the same: after kPolls polls, seconds, they give up and set bit 31 of the
+//    status word.  (Before that a block waits for times that it sees pass itself, and for one that is between two stores.)
 #pragma once
 
 #include "dq_common.h"
 
 namespace dq {
 
-constexpr int kDies = 16;                        // (numbers that a die may have)
-constexpr long long kPickTicks = 3000, kJoinTicks = 500000;          // of the 100 MHz clock: 30 us, 5 ms
+constexpr long long kPickTicks = 3000;           // of the 100 MHz clock: 30 us
 constexpr int kPolls = 1 << 23;
 constexpr uint32_t kGaveUp = 0x80000000u;        // in the status word
 
 // In device memory; all zero before the launch.
 struct DieControl {
-    uint32_t home;                               // 1 + the die; with kPicked, it is not complete yet
+    uint32_t home;                               // 1 + the die; with kPicked and a lot, it is not complete yet
     uint32_t members;
     uint32_t joined[kDies];                      // top bit: closed
     uint32_t pad[34];                            // (the flags on cache lines that other dies' blocks do not touch)
@@ -75,42 +78,42 @@ __device__ __forceinline__ uint32_t die_number()
     return v & (kDies - 1);
 }
 
-// All threads of the block call it; sh: two words of LDS.
-__device__ __forceinline__ DieMember die_join(DieControl *ctl, uint32_t want, int *sh)
+// All threads of the block call it; sh: two words of LDS.  The die is closed after `patience` ticks (up to twice that, by lot), where
+// `enough` of the blocks are not there only after four times as many.
+__device__ __forceinline__ DieMember die_join(DieControl *ctl, uint32_t want, uint32_t enough, long long patience, int *sh)
 {
     if (threadIdx.x == 0) {
-        constexpr uint32_t kClosed = 0x80000000u, kPicked = 0x100u;
+        constexpr uint32_t kClosed = 0x80000000u, kPicked = 0x100u, kLotShift = 9, kLots = 8;
         const uint32_t die = die_number();
         int me = -1, count = 0;
         const auto swap_home = [&](uint32_t from, uint32_t to) {
             return __hip_atomic_compare_exchange_strong(&ctl->home, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
+        const auto picked_here = [&](uint32_t home) { return (home & ((1u << kLotShift) - 1u)) == ((die + 1) | kPicked); };
         const uint32_t ticket = __hip_atomic_fetch_add(&ctl->joined[die], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (ticket < want) {                             // (not closed, and not more than are wanted)
             // (a die whose blocks may have been told to end cannot become the one: `home` says another's number by then)
             const auto settle = [&] {
-                if (!swap_home(0u, die + 1) && !swap_home((die + 1) | kPicked, die + 1)) return;
+                if (!swap_home(0u, die + 1)) {
+                    const uint32_t home = load_fresh(&ctl->home);
+                    if (!picked_here(home) || !swap_home(home, die + 1)) return;
+                }
                 const uint32_t c = __hip_atomic_fetch_or(&ctl->joined[die], kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&ctl->members, min(c, want), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            };
-            const auto pick = [&] {
-                uint32_t best = die, most = 0;
-                for (uint32_t i = 0; i < kDies; ++i) {
-                    const uint32_t c = load_fresh(&ctl->joined[i]);
-                    if (c > most) {
-                        most = c;
-                        best = i;
-                    }
-                }
-                swap_home(0u, (best + 1) | kPicked);
             };
             if (ticket == want - 1) settle();
             const long long start = wall_clock64();
             uint32_t home;
-            while ((home = load_fresh(&ctl->home)) == 0 || home == ((die + 1) | kPicked)) {
-                const long long waited = wall_clock64() - start;
-                if (home == 0 && waited > kPickTicks) pick();
-                if (home != 0 && waited > kJoinTicks) settle();
+            while ((home = load_fresh(&ctl->home)) == 0 || picked_here(home)) {
+                const long long now = wall_clock64(), waited = now - start;
+                if (home == 0 && waited > kPickTicks) {
+                    const uint32_t lot = static_cast<uint32_t>(now), best = die_pick([&](uint32_t i) { return load_fresh(&ctl->joined[i]); }, die, lot);
+                    swap_home(0u, (best + 1) | kPicked | ((lot >> 3) % kLots) << kLotShift);
+                }
+                if (home != 0) {
+                    const long long limit = patience + (home >> kLotShift) * (patience / kLots);
+                    if (waited > limit && (load_fresh(&ctl->joined[die]) >= enough || waited > 4 * limit)) settle();
+                }
                 __builtin_amdgcn_s_sleep(1);
             }
             if (home == die + 1) {                       // (its members are counted by a block that is running)

@@ -141,6 +141,25 @@ inline bool csr_light_batches(int64_t B, int64_t n, int64_t entries, int in_flig
     return mean <= 1.2 * in_flight && mean * 1.125 <= cap;
 }
 
+// ------------------------------------------------------------------ blocks that work together on one die (die.h)
+constexpr uint32_t kDies = 16;                   // (numbers that a die may have; the part has eight)
+
+// The die where a launch has most blocks (count_of a number), `own` where it has none; of several with as many the first from number
+// lot % 8 on: launches that hold equal parts of all dies pick different ones, seven times of eight.
+template <typename CountOf>
+constexpr uint32_t die_pick(CountOf count_of, uint32_t own, uint32_t lot)
+{
+    uint32_t best = own, most = 0;
+    for (uint32_t i = 0; i < kDies; ++i) {
+        const uint32_t at = (i + lot % 8) % kDies, c = count_of(at);
+        if (c > most) {
+            most = c;
+            best = at;
+        }
+    }
+    return best;
+}
+
 // ------------------------------------------------------------------ rounds on one die, CSR features (csr_rounds.hip)
 constexpr int kDieUnits = 32;                    // compute units of a die
 constexpr int kRoundsRows = 128;                 // rows of a mini-batch: two a lane of the wavefront that lays them out

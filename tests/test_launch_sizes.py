@@ -142,3 +142,20 @@ def test_rounds_on_one_die_fit_the_workspace_and_the_chip(tmp_path):
         csr_rounds_shape(20958, 1000, 52000, 8, 129, 8, 8, s) || !csr_rounds_shape(20958, 1000, 52000, 8, 32, 8, 8, s)) std::printf("ends\\n");
     """)
     assert out == "", out[:2000]
+
+
+def test_launches_with_equal_parts_of_all_dies_pick_different_ones(tmp_path):
+    """Two launches that begin together hold as many blocks on every die: which one a launch keeps is by lot, over all of them.  One that
+    has more on a die keeps that one, and one without any its own."""
+    out = _sweep(tmp_path, """
+    int times[kDies] = {};
+    for (uint32_t lot = 0; lot < 800; ++lot) {
+        ++times[die_pick([](uint32_t i) { return i < 8 ? 16u : 0u; }, 3, lot)];
+        for (uint32_t most = 0; most < kDies; ++most)
+            if (die_pick([&](uint32_t i) { return i == most ? 17u : 16u; }, 3, lot) != most) std::printf("most %u lot %u\\n", most, lot);
+        if (die_pick([](uint32_t) { return 0u; }, 3, lot) != 3) std::printf("none, lot %u\\n", lot);
+    }
+    for (uint32_t i = 0; i < kDies; ++i)
+        if (times[i] != (i < 8 ? 100 : 0)) std::printf("die %u: %d\\n", i, times[i]);
+    """)
+    assert out == "", out[:2000]
