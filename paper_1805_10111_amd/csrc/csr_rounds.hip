@@ -29,7 +29,13 @@ namespace dq {
 constexpr int kNoRow = 0x7FFFFFFF;                        // where the rows past the last one begin
 
 static_assert(kBusyWaves == kCsrWaves - 1 && kBusy == kBusyWaves * kWave, "one wavefront waits at exchanges");
-static_assert(sizeof(DieControl) <= kRoundsControl, "room in the workspace");
+
+// In the workspace; zero before the launches.
+struct CsrRoundsControl {
+    DieControl first, second;
+    uint32_t slice[kDieUnits];                           // SHARED: the slices' largest magnitudes
+};
+static_assert(sizeof(CsrRoundsControl) <= kRoundsControl, "room in the workspace");
 
 struct CsrRoundsArgs {
     CsrView A;
@@ -48,7 +54,8 @@ struct CsrRoundsArgs {
     float *delta;
     uint32_t *status;
     float *rows; int64_t ld;                             // M gradients
-    DieControl *ctl; int want;                           // members
+    CsrRoundsControl *ctl;
+    int want, join;                                      // parts; members that the second kernel wants
 };
 
 struct CsrRoundsLds {
@@ -66,21 +73,21 @@ static_assert(sizeof(CsrRoundsLds) + 512 <= kRoundsFixedLds, "static LDS");
 // The arguments, read again wherever they are used: more of them than there are scalar registers to keep them in.
 typedef const CsrRoundsArgs __attribute__((address_space(4))) *CsrRoundsArgsPtr;
 
-// ALONE: one block does what the members would have done, one after the other, where they were too few (see csr_rounds).
-template <bool ACC, bool EACH, bool ALONE>
+// A round has `want` parts, a range of columns and at most one slice of a worker each.  A member has one of them and keeps the
+// state of its columns in registers.  SHARED: where the first kernel's members were too few, those that this one finds, one
+// or more, have every `count`-th part each, one after the other, and keep the state in memory.
+template <bool ACC, bool EACH, bool SHARED>
 __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRoundsArgs)
 {
     extern __shared__ __align__(16) float lds[];
     __shared__ CsrRoundsLds l;
     CsrRoundsArgsPtr a = (CsrRoundsArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    DieMember die{nullptr, 0, 1};
-    if constexpr (ALONE) {
-        if (load_fresh(&a->ctl->members) == static_cast<uint32_t>(a->want)) return;
-    } else {
-        constexpr long long kJoinTicks = 200000;         // (2 to 4 ms: kernels of other streams end meanwhile)
-        die = die_join(a->ctl, static_cast<uint32_t>(a->want), 0u, kJoinTicks, l.sh);
-        if (die.me < 0 || die.count != a->want) return;
-    }
+    if (SHARED && load_fresh(&a->ctl->first.members) == static_cast<uint32_t>(a->want)) return;
+    // (2 to 4 ms: kernels of other streams end meanwhile, and with the second kernel the rounds of a launch take as much longer)
+    constexpr long long kJoinTicks = 200000, kSharedTicks = 10000;
+    const DieMember die = SHARED ? die_join(&a->ctl->second, static_cast<uint32_t>(a->join), static_cast<uint32_t>(a->join + 1) / 2, kSharedTicks, l.sh)
+                                 : die_join(&a->ctl->first, static_cast<uint32_t>(a->want), 0u, kJoinTicks, l.sh);
+    if (die.me < 0 || (!SHARED && die.count != a->want)) return;
     int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const bool messenger = wave == kCsrWaves - 1, planner = wave == kCsrWaves - 2;
     int d = static_cast<int>(a->A.d), M = a->M, B = a->B, b_x = a->b_x, chunks = a->chunks, C = chunks * kChunk;
@@ -97,7 +104,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
         lane = t & (kWave - 1);
         C = chunks * kChunk;
     };
-    const int tasks = M * S, members = ALONE ? a->want : 1;
+    const int tasks = M * S, parts = SHARED ? a->want : die.me + 1, stride = SHARED ? die.count : 1;
     const int message_words = (d * b_x + 31) / 32, message_room = (message_words + 1 + 3) / 4 * 4, room = a->room;
     int *acc = reinterpret_cast<int *>(lds);                              // the slice's sums
     uint32_t *model = reinterpret_cast<uint32_t *>(lds + win);            // the model's message
@@ -247,7 +254,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
             }
         }
     };
-    if constexpr (!ALONE) load_state(die.me);
+    if constexpr (!SHARED) load_state(die.me);
 
     // the random words of a new model
     uint32_t word[kColumns];
@@ -260,20 +267,20 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
             word[n] = i & 2 ? (i & 1 ? w.w : w.z) : (i & 1 ? w.y : w.x);
         }
     };
-    if (a->flag_first || ALONE) draw_model_words(die.me, a->iter0 + 1u);
+    if (a->flag_first || SHARED) draw_model_words(die.me, a->iter0 + 1u);
     float *const rows = a->rows;
     const int64_t ld = a->ld;
     float delta_x = a->flag_first ? 0.0f : a->delta_x[0];
     const int units = M * chunks;                        // wavefront w takes chunk (worker, member's chunk) number w + 14 p
     const uint32_t per_chunk = (65536u + static_cast<uint32_t>(chunks) - 1u) / static_cast<uint32_t>(chunks);
     const auto worker_of = [&](int unit) { return static_cast<int>(static_cast<uint32_t>(unit) * per_chunk >> 16); };    // unit / chunks
-    const int first_round = !ALONE && !a->flag_first ? -1 : 0;           // (-1: only what round 0 needs beforehand)
+    const int first_round = !SHARED && !a->flag_first ? -1 : 0;           // (-1: only what round 0 needs beforehand)
     __syncthreads();
     for (int k = first_round; k < a->rounds; ++k) {
         const bool last = k == a->rounds - 1, flag = k == 0 && a->flag_first, active = k >= 0, gradients = active && !flag;
         forget();
         const uint32_t iter = a->iter0 + static_cast<uint32_t>(k);
-        const bool ahead = !ALONE && has_task && !last;  // the next round's mini-batch is laid out in this one
+        const bool ahead = !SHARED && has_task && !last;  // the next round's mini-batch is laid out in this one
         // ---- worker side: the slices of the gradients
         if (gradients && has_task) {                     // (the same for every thread)
             // the model's message, two pieces of a thread's together (past its end: zeros)
@@ -290,9 +297,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
         if (gradients && has_task) {
             const float inv_B = 1.0f / static_cast<float>(B);
 #pragma unroll 1
-            for (int task = die.me; task < (ALONE ? tasks : die.me + 1); ++task) {
-                const int m = ALONE ? task / S : my_m, c0 = (task - m * S) * win, c1 = min(d, c0 + win);
-                if constexpr (ALONE) {
+            for (int task = die.me; task < (SHARED ? tasks : die.me + 1); task += stride) {
+                const int m = SHARED ? task / S : my_m, c0 = (task - m * S) * win, c1 = min(d, c0 + win);
+                if constexpr (SHARED) {
                     __syncthreads();
                     if (planner) {
                         plan_rows(m, iter);
@@ -482,9 +489,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 wait_for_memory();
                 __syncthreads();
                 if (messenger && lane == 0) {
-                    l.slice[task] = l.slice_max;         // (in the member's own place: its value at the exchange)
+                    if constexpr (SHARED) a->ctl->slice[task] = l.slice_max;
+                    else l.slice[task] = l.slice_max;    // (in the member's own place: its value at the exchange)
                     l.poison = 0;
                 }
+                if (SHARED && messenger) wait_for_memory();
             }
         }
         // ---- master side
@@ -499,13 +508,13 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
             }
         };
         if (!exchange(gradients, has_task ? l.slice_max : 0u, [&] {
-                if (gradients) draw_words(die.me);
+                if (gradients && !SHARED) draw_words(die.me);
                 if (ahead && planner) {
                     if (k == first_round) plan_rows(my_m, iter + 1u);
                     leave_rows();
                 }
             }, [&](uint32_t v) {                         // the gradients' largest magnitudes
-                if (!ALONE && lane < tasks) l.slice[lane] = v;
+                if (lane < tasks) l.slice[lane] = SHARED ? load_fresh(a->ctl->slice + lane) : v;
                 uint32_t amax = 0;
 #pragma unroll
                 for (int n0 = 0; n0 < 16; n0 += 4) {
@@ -528,7 +537,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
             };
             Scale scale[kPasses];                         // (while the rows are on their way)
             if (gradients) {
-                load_rows(die.me);
+                if constexpr (!SHARED) load_rows(die.me);
                 const int b = a->b;
                 if (has_units) {
 #pragma unroll
@@ -543,8 +552,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 if (last && die.me == 0 && t < M) a->delta[t] = 0.0f;
             }
 #pragma unroll 1
-            for (int member = die.me; member < die.me + members; ++member) {
-                if constexpr (ALONE) {
+            for (int member = die.me; member < parts; member += stride) {
+                if constexpr (SHARED) {
                     __syncthreads();
                     load_state(member);
                     if (gradients) {
@@ -611,7 +620,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                         }
                     }
                     if constexpr (!EACH) apply(a->scale * mean + gs[n]);
-                    if (last || ALONE) {
+                    if (last || SHARED) {
                         a->x[i] = xv[n];
                         if constexpr (ACC) {
                             a->yv[i] = yv[n];
@@ -620,7 +629,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                     }
                     top = max(top, abs_bits(xv[n]));
                 }
-                if constexpr (ALONE) wait_for_memory();
+                if constexpr (SHARED) wait_for_memory();
             }
             for (int w = t; w < kMostChunks * kChunk * 16 / 32; w += kCsrThreads) l.message[w] = 0u;
             top = block_max(top);
@@ -641,7 +650,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 if (ms.bad) atomicOr(a->status, 1u);
             }
 #pragma unroll 1
-            for (int member = die.me; member < die.me + members; ++member) {
+            for (int member = die.me; member < parts; member += stride) {
                 if (member != die.me) {
                     __syncthreads();
                     for (int w = t; w < kMostChunks * kChunk * 16 / 32; w += kCsrThreads) l.message[w] = 0u;
@@ -653,7 +662,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                     const int j = t + n * kBusy, i = member * C + j;
                     if (n * kBusy >= C) break;
                     if (messenger || j >= C || i >= d) continue;
-                    const float x = ALONE ? load_fresh(a->x + i) : xv[n];
+                    const float x = SHARED ? load_fresh(a->x + i) : xv[n];
                     const int c = ms.inv_delta != 0.0f ? quantize_one(x, ms, word[n]) : 0;
                     if (b_x == 8) {
                         reinterpret_cast<uint8_t *>(l.message)[j] = static_cast<uint8_t>(c);
@@ -704,10 +713,10 @@ bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
     return csr_rounds_layout(prob, cfg, st, rounds, s);
 }
 
-template <bool ACC, bool EACH, bool ALONE>
+template <bool ACC, bool EACH, bool SHARED>
 static int csr_rounds_launch(const CsrRoundsArgs &a, size_t lds, hipStream_t stream)
 {
-    const auto kernel = csr_rounds_kernel<ACC, EACH, ALONE>;
+    const auto kernel = csr_rounds_kernel<ACC, EACH, SHARED>;
     static std::once_flag once;
     static hipError_t once_rc = hipSuccess;
     std::call_once(once, [&] {
@@ -715,13 +724,13 @@ static int csr_rounds_launch(const CsrRoundsArgs &a, size_t lds, hipStream_t str
                                       static_cast<int>(kRoundsLds));
     });
     DQ_HIP_TRY(once_rc);
-    kernel<<<dim3(ALONE ? 1u : 8u * static_cast<unsigned>(a.want)), dim3(kCsrThreads), lds, stream>>>(a);
+    kernel<<<dim3(8u * static_cast<unsigned>(SHARED ? a.join : a.want)), dim3(kCsrThreads), lds, stream>>>(a);
     DQ_LAUNCH_CHECK();
     return DQ_OK;
 }
 
 int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
-                   int64_t rounds, float eta, float theta, bool flag_first, hipStream_t stream)
+                   int64_t rounds, float eta, float theta, bool flag_first, int members, hipStream_t stream)
 {
     const bool acc = cfg->algo == DQ_ALGO_ACC;
     const void *quads[] = {st->x, st->x_snap, st->g_snap, acc ? st->y : nullptr, acc ? st->xsum : nullptr, st->ws};
@@ -734,7 +743,11 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
     // the M rows of a step, its slices' results, then what dq_run_rounds has for itself
     a.ld = pad4(prob->d);
     a.rows = static_cast<float *>(st->ws);
-    a.ctl = reinterpret_cast<DieControl *>(static_cast<char *>(st->ws) + csr_run_offset(prob->d, cfg->M));
+    a.ctl = reinterpret_cast<CsrRoundsControl *>(static_cast<char *>(st->ws) + csr_run_offset(prob->d, cfg->M));
+    // (32 find each other less often and take 12.1 us a round, 16 19.8, 8 35, one 245; nothing to do for 256 blocks is a wait for as many
+    // places where other work holds the part)
+    constexpr int kSharedMembers = 16;
+    a.join = std::min(members > 0 ? members : kSharedMembers, s.want);
     const size_t lds = static_cast<size_t>(s.lds);
     a.A = CsrView{prob->indptr, prob->indices, prob->values, prob->y, prob->n, prob->d};
     a.z_snap = st->z_snap;
@@ -751,11 +764,11 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
         a.iter0 = static_cast<uint32_t>(epoch * cfg->m + t0 + done);
         a.t0 = static_cast<int>((t0 + done) & 1); a.rounds = static_cast<int>(std::min(kMostRounds, rounds - done));
         a.flag_first = done == 0 && flag_first;
-        int rc = fill_u32(reinterpret_cast<uint32_t *>(a.ctl), sizeof(DieControl) / 4, 0u, stream);
+        int rc = fill_u32(reinterpret_cast<uint32_t *>(a.ctl), sizeof(CsrRoundsControl) / 4, 0u, stream);
         if (rc != DQ_OK) return rc;
         const auto launch = [&](auto with_acc, auto each) {
             constexpr bool ACC = decltype(with_acc)::value, EACH = decltype(each)::value;
-            const int one = csr_rounds_launch<ACC, EACH, false>(a, lds, stream);
+            const int one = members > 0 ? DQ_OK : csr_rounds_launch<ACC, EACH, false>(a, lds, stream);
             return one != DQ_OK ? one : csr_rounds_launch<ACC, EACH, true>(a, lds, stream);
         };
         const std::true_type yes;

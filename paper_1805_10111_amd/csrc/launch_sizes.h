@@ -172,7 +172,7 @@ constexpr int kPasses = 2;                       // chunks of all workers that a
 constexpr int64_t kFewRounds = 8;                // calls of fewer are not for one die
 constexpr int64_t kRoundsFixedLds = 13360;       // static arrays
 constexpr int64_t kRoundsLds = 160 * 1024 - kRoundsFixedLds;  // for the dynamic part
-constexpr int64_t kRoundsControl = 720;          // bytes of a run's workspace, from csr_run_offset on, for what the members share
+constexpr int64_t kRoundsControl = 1568;         // bytes of a run's workspace, from csr_run_offset on, for what the members share
 
 static_assert(kMostChunks * kChunk <= kColumns * kBusy, "every column has a thread");
 

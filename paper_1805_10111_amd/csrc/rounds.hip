@@ -6,9 +6,9 @@
 
 static inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
-extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st,
-                                 int64_t epoch, int64_t t0, int64_t rounds, float eta, float theta,
-                                 void **worker_events, void *stream)
+// members > 0: the call must be one that csr_rounds does (DQ_ERR_UNSUPPORTED if not), and does so with at most that many (see there).
+static int32_t run_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0, int64_t rounds,
+                          float eta, float theta, void **worker_events, int members, void *stream)
 {
     if (!prob || !cfg || !st || epoch < 0 || t0 < 0 || rounds < 0 || cfg->m <= 0 || t0 + rounds > cfg->m)
         return DQ_ERR_INVALID_ARG;
@@ -45,15 +45,18 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
     // Small dense problems, and CSR problems with mini-batches that a die has room for: everything in one launch (not when the
     // caller wants the worker kernels' own times).
     const bool small = rounds > 0 && !worker_events && dq::small_rounds_ok(prob, cfg, st);
-    if (small || (rounds > 0 && !worker_events && dq::csr_rounds_ok(prob, cfg, st, rounds))) {
+    const bool csr_one = rounds > 0 && !worker_events && dq::csr_rounds_ok(prob, cfg, st, rounds);
+    if (members > 0 && !csr_one) return DQ_ERR_UNSUPPORTED;
+    if (small || csr_one) {
         if (t0 == 0 && !start_is_snapshot) {             // as below
             const int32_t rc = dq_quantize_pack(st->x, prob->d, 1, prob->d, cfg->b_x, st->absmax_x, 0, cfg->seed,
                                                 static_cast<uint32_t>(epoch * cfg->m), DQ_TAG_MODEL, DQ_MASTER_ID, st->xq, xq_words,
                                                 st->delta_x, st->status, stream);
             if (rc != DQ_OK) return rc;
         }
-        return (small ? dq::small_rounds : dq::csr_rounds)(prob, cfg, st, epoch, t0, rounds, eta, theta, t0 == 0 && start_is_snapshot,
-                                                           as_stream(stream));
+        const bool flag_first = t0 == 0 && start_is_snapshot;
+        return small ? dq::small_rounds(prob, cfg, st, epoch, t0, rounds, eta, theta, flag_first, as_stream(stream))
+                     : dq::csr_rounds(prob, cfg, st, epoch, t0, rounds, eta, theta, flag_first, members, as_stream(stream));
     }
     // Alg. 1, master (i) without a launch of its own: between two rounds of one call the master kernel stops at the
     // update and ||x||_inf (spread over the chip), and the next round's row-streaming kernel quantizes the model in
@@ -186,6 +189,21 @@ extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cf
         if (rc != DQ_OK) return rc;
     }
     return DQ_OK;
+}
+
+extern "C" int32_t dq_run_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st,
+                                 int64_t epoch, int64_t t0, int64_t rounds, float eta, float theta,
+                                 void **worker_events, void *stream)
+{
+    return run_rounds(prob, cfg, st, epoch, t0, rounds, eta, theta, worker_events, 0, stream);
+}
+
+// For tests only (not declared in dq.h): what only happens where other work holds the part.
+extern "C" int32_t dq_test_run_rounds_shared(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch,
+                                             int64_t t0, int64_t rounds, float eta, float theta, int32_t members, void *stream)
+{
+    if (members < 1) return DQ_ERR_INVALID_ARG;
+    return run_rounds(prob, cfg, st, epoch, t0, rounds, eta, theta, nullptr, members, stream);
 }
 
 // Section 5.1 (parameters of Alg. 3 as used in the experiments): theta_s = 2/(s+2), eta_s = lr/theta_s, in float32.

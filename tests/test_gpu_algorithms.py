@@ -654,10 +654,31 @@ def _many_rounds_and_few(dq, d, M, B, algo, b, b_x, each, nnz, entries, m=19):
     return tuple(DoubleQuantTrainer(P, algo, M, B, b_x, b, m, 0.5, seed=3, each=each) for _ in range(2))
 
 
-@pytest.mark.parametrize("d,M,B,algo,b,b_x,each,nnz,entries", [
+ONE_DIE = [
     (5, 1, 1, "asylpg", 8, 8, False, 2.0, 0), (257, 1, 9, "acc", 2, 2, True, 9.0, 0), (4097, 28, 24, "asylpg", 4, 3, True, 30.0, 0),
     (7170, 14, 70, "acc", 8, 16, False, 30.0, 0), (20959, 8, 33, "acc", 4, 12, True, 30.0, 0), (20958, 8, 128, "asylpg", 8, 8, False, 30.0, 0),
-    (28415, 4, 25, "asylpg", 8, 4, False, 30.0, 0), (20958, 8, 64, "asylpg", 8, 8, False, 30.0, 500), (9001, 5, 128, "acc", 4, 8, False, 90.0, 500)])
+    (28415, 4, 25, "asylpg", 8, 4, False, 30.0, 0), (20958, 8, 64, "asylpg", 8, 8, False, 30.0, 500), (9001, 5, 128, "acc", 4, 8, False, 90.0, 500)]
+
+
+def _joined(tr):
+    """How many blocks the first and the second kernel of the trainer's last one-launch rounds found on their die."""
+    words = tr.M * ((tr.prob.d + 3) // 4 * 4) + tr.M * 16
+    control = tr.ws.view(torch.int32)[words:]
+    return int(control[1]), int(control[181])
+
+
+def _shared_rounds(dq, tr, t0, count, members):
+    """The rounds of a call that takes one launch, as if the blocks of its first kernel had not found room on a die: by the second, with at
+    most `members`."""
+    import ctypes as C
+    from paper_1805_10111_amd import api
+    f = api._lib.dq_test_run_rounds_shared
+    f.argtypes = [C.c_void_p] * 3 + [C.c_int64] * 3 + [C.c_float] * 2 + [C.c_int32, C.c_void_p]
+    assert f(tr.prob.ptr, C.byref(tr.cfg), C.byref(tr.state), tr.epoch_index, t0, count, tr.eta, tr.theta, members,
+             torch.cuda.current_stream().cuda_stream) == 0
+
+
+@pytest.mark.parametrize("d,M,B,algo,b,b_x,each,nnz,entries", ONE_DIE)
 def test_csr_rounds_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x, each, nnz, entries):
     """CSR features: a call of eight rounds or more does them in one launch on one die, a shorter one with launches for each.
     Everything must be identical: one member and one slice a worker and several, ragged last quads and chunks, fields that straddle
@@ -666,7 +687,30 @@ def test_csr_rounds_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x
     for epoch in range(2):
         many.epoch_prologue(); few.epoch_prologue()
         for t, n in ((0, 11), (11, 8)):
+            many.ws.view(torch.int32).fill_(-1)
             many.rounds(t, n)
+            assert _joined(many) == ({5: 1, 257: 2, 4097: 28, 7170: 29}.get(d, 32), 0), "the route, and every member on it"
+        for t, n in ((0, 5), (5, 5), (10, 1), (11, 5), (16, 3)):
+            few.rounds(t, n)
+        for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
+            assert torch.equal(getattr(many, name), getattr(few, name)), (epoch, name)
+        many.epoch_epilogue(); few.epoch_epilogue()
+    assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
+
+
+@pytest.mark.parametrize("members", [1, 2, 7, 27])
+@pytest.mark.parametrize("d,M,B,algo,b,b_x,each,nnz,entries", ONE_DIE)
+def test_csr_rounds_by_fewer_members_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x, each, nnz, entries, members):
+    """The same where fewer blocks find room on a die than there are parts of the work: they share them, from one block that does all to
+    a few short.  Everything must be identical again."""
+    many, few = _many_rounds_and_few(dq, d, M, B, algo, b, b_x, each, nnz, entries)
+    for epoch in range(2):
+        many.epoch_prologue(); few.epoch_prologue()
+        for t, n in ((0, 11), (11, 8)):
+            many.ws.view(torch.int32).fill_(-1)
+            _shared_rounds(dq, many, t, n, members)
+            first, second = _joined(many)
+            assert first == 0 and 1 <= second <= members
         for t, n in ((0, 5), (5, 5), (10, 1), (11, 5), (16, 3)):
             few.rounds(t, n)
         for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
@@ -690,11 +734,15 @@ def test_csr_rounds_without_a_status_word_are_not_done_in_one_launch(dq):
         assert torch.equal(getattr(many, name), getattr(few, name)), name
 
 
-def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq):
-    """A call of more rounds than one launch does, the model kept between the launches as between calls."""
+@pytest.mark.parametrize("members", [0, 3])
+def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq, members):
+    """A call of more rounds than one launch does, the model kept between the launches as between calls; also by fewer members."""
     many, few = _many_rounds_and_few(dq, 700, 2, 6, "acc", 8, 8, False, 9.0, 0, m=1050)
     many.epoch_prologue(); few.epoch_prologue()
-    many.rounds(0, 1050)
+    if members:
+        _shared_rounds(dq, many, 0, 1050, members)
+    else:
+        many.rounds(0, 1050)
     for t in range(0, 1050, 5):
         few.rounds(t, 5)
     for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status", "y", "xsum"):
