@@ -193,7 +193,9 @@ struct CsrRoundsShape {
 //    12,000 11.6, 12.7; M 32, d 6400 13.3, 14.0.
 //  - calls of eight rounds or more: the launches around it, and finding together, are 10 us a call.  M 8, d 20,958: two rounds
 //    12.5, 15.2; five 11.8, 12.0; eight 11.6, 11.2.
-//  - mini-batches that the busy threads hold in registers, as far as the caller's count of entries can tell.
+//  - mini-batches that the busy threads hold in registers, as far as the caller's count of entries can tell.  It cannot tell uneven
+//    rows, nor any where it is not given; larger batches are read in the round.  M 8, d 20,958, 64 rows of 50 entries in the mean,
+//    lognormal with sigma 1, 1.5 and 2: 14.8, 12.4; 21.2, 16.3; 31.2, 21.3; no count, 32 rows of 200 and of 1000: 26.4, 19.0; 86, 53.
 inline bool csr_rounds_shape(int64_t d, int64_t n, int64_t entries, int64_t M, int64_t B, int b_x, int64_t rounds, CsrRoundsShape &s)
 {
     const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
@@ -214,8 +216,12 @@ inline bool csr_rounds_shape(int64_t d, int64_t n, int64_t entries, int64_t M, i
     const int64_t room = most(M * chunks * (kChunk / 4), least(held, static_cast<int64_t>(1.5 * mean) + 256));
     s.room = static_cast<int>(ceil_div(room, 64) * 64);
     const int64_t message = pad4((d * b_x + 31) / 32 + 1);
-    const int64_t bytes = (s.win + message + s.room + pad4(d)) * 4;
+    int64_t bytes = (s.win + message + s.room + pad4(d)) * 4;
     if (bytes > kRoundsLds) return false;
+    // (what is left is for larger mini-batches than the mean's, as far as the threads hold them)
+    const int64_t more = least((kRoundsLds - bytes) / 256 * 64, most(0, held / 64 * 64 - s.room));
+    s.room += static_cast<int>(more);
+    bytes += more * 4;
     // (what makes up more than half of a compute unit's LDS: no two blocks on one)
     s.lds = most(bytes, 72 * 1024);
     return true;

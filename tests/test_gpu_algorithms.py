@@ -719,6 +719,39 @@ def test_csr_rounds_by_fewer_members_equal_calls_of_a_few(dq, d, M, B, algo, b, 
     assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
 
 
+def _problem_of_rows(lens, d, seed=6):
+    """CSR features with these numbers of entries in the rows."""
+    rng = np.random.default_rng(seed)
+    cols = np.concatenate([np.sort(rng.choice(d, k, replace=False)) for k in lens]).astype(np.int32)
+    values = (rng.standard_normal(cols.size) / 8).astype(np.float32)
+    return synth.Problem(n=len(lens), d=d, y=np.where(rng.random(len(lens)) < 0.5, -1.0, 1.0).astype(np.float32), l2=1e-3, l1=1e-6,
+                         indptr=np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), indices=cols, values=values)
+
+
+@pytest.mark.parametrize("members", [0, 1, 5])
+@pytest.mark.parametrize("d,M,B,algo", [(20958, 8, 24, "asylpg"), (20958, 4, 1, "acc"), (9500, 3, 128, "asylpg"), (12000, 14, 9, "acc")])
+def test_csr_rounds_of_uneven_rows_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, members):
+    """Mini-batches of more entries than the blocks hold are read in the round, in pieces of as many as there is room for: empty rows,
+    rows around a wavefront's width, rows longer than a piece and than a group of rows, few entries beside very many."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    lens = [0, 9000, 1, 63, 64, 65, 0, 0, 5056, 127, 128, 129, 7680, 3000, 6400, 2, 0, 8192, 700, 9001, 40, 4999, 8200, 0]
+    P = dq.DeviceProblem.from_host(_problem_of_rows(lens, d))
+    P._s.lda = 30 * len(lens)                              # (the rows are said to be short: else such calls keep their launches)
+    many, few = (DoubleQuantTrainer(P, algo, M, B, 8, 8, 12, 0.1, seed=3) for _ in range(2))
+    many.epoch_prologue(); few.epoch_prologue()
+    many.ws.view(torch.int32).fill_(-1)
+    if members:
+        _shared_rounds(dq, many, 0, 12, members)
+    else:
+        many.rounds(0, 12)
+    assert _joined(many)[0] == (0 if members else 32)
+    for t, n in ((0, 5), (5, 5), (10, 2)):
+        few.rounds(t, n)
+    for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
+        assert torch.equal(getattr(many, name), getattr(few, name)), name
+    assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
+
+
 def test_csr_rounds_without_a_status_word_are_not_done_in_one_launch(dq):
     """The status word is how a caller learns that the blocks of such a launch gave up waiting for each other.  Without one each round has
     launches of its own, with the same results."""
