@@ -771,10 +771,25 @@ static bool csr_rounds_layout(const dq_problem *prob, const dq_run_config *cfg, 
            st->ws_bytes >= csr_run_offset(prob->d, cfg->M) + kRoundsControl;
 }
 
-bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds)
+// A stream that may use a part of the compute units only (hipExtStreamCreateWithCUMask) need not have a whole die: with sixteen of each
+// die's 32 a call waits 2 to 4 ms for one and then does its rounds with what there is, 27 us each over 282 rounds; as launches 11.5.
+static bool whole_part(hipStream_t stream)
+{
+    uint32_t mask[32] = {};
+    int dev = 0, units = 0, in_mask = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipExtStreamGetCUMask(stream, sizeof(mask) / 4, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    for (const uint32_t word : mask) in_mask += __builtin_popcount(word);
+    return in_mask >= units;
+}
+
+bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds, hipStream_t stream)
 {
     CsrRoundsShape s;
-    return csr_rounds_layout(prob, cfg, st, rounds, s);
+    return csr_rounds_layout(prob, cfg, st, rounds, s) && whole_part(stream);
 }
 
 template <bool ACC, bool EACH, bool SHARED>

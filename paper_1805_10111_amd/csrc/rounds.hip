@@ -45,7 +45,7 @@ static int32_t run_rounds(const dq_problem *prob, const dq_run_config *cfg, cons
     // Small dense problems, and CSR problems with mini-batches that a die has room for: everything in one launch (not when the
     // caller wants the worker kernels' own times).
     const bool small = rounds > 0 && !worker_events && dq::small_rounds_ok(prob, cfg, st);
-    const bool csr_one = rounds > 0 && !worker_events && dq::csr_rounds_ok(prob, cfg, st, rounds);
+    const bool csr_one = rounds > 0 && !worker_events && dq::csr_rounds_ok(prob, cfg, st, rounds, as_stream(stream));
     if (members > 0 && !csr_one) return DQ_ERR_UNSUPPORTED;
     if (small || csr_one) {
         if (t0 == 0 && !start_is_snapshot) {             // as below

@@ -20,11 +20,11 @@ def gpu_available():
     return torch.cuda.is_available()
 
 
-def launches(call):
-    """How many kernels `call` enqueues: the nodes of a graph that captures it (nothing of it runs)."""
+def launches(call, side=None):
+    """How many kernels `call` enqueues: the nodes of a graph that captures it, on a stream of its own or `side` (nothing of it runs)."""
     import ctypes
     from paper_1805_10111_amd import api
-    g, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    g, side = torch.cuda.CUDAGraph(keep_graph=True), side or torch.cuda.Stream()
     with torch.cuda.stream(side):
         with torch.cuda.graph(g, stream=side):
             call()

@@ -767,6 +767,30 @@ def test_csr_rounds_without_a_status_word_are_not_done_in_one_launch(dq):
         assert torch.equal(getattr(many, name), getattr(few, name)), name
 
 
+def test_csr_rounds_on_part_of_the_compute_units_are_not_done_in_one_launch(dq):
+    """A stream with a mask of compute units need not have a whole die.  Each round has launches of its own there, with the same results."""
+    import ctypes as C
+    from paper_1805_10111_amd import api
+    many, few = _many_rounds_and_few(dq, 4097, 8, 24, "asylpg", 8, 8, False, 30.0, 0)
+    handle, units = C.c_void_p(), torch.cuda.get_device_properties(0).multi_processor_count
+    half = (C.c_uint32 * (units // 32))(*[0xFFFFFFFF] * (units // 64))
+    assert api._lib.hipExtStreamCreateWithCUMask(C.byref(handle), len(half), half) == 0
+    masked = torch.cuda.ExternalStream(handle.value)
+    for tr in (many, few):
+        tr.epoch_prologue()
+        tr.rounds(0, 11)
+    torch.cuda.synchronize()
+    assert launches(lambda: many.rounds(0, 11)) <= 3
+    assert launches(lambda: few.rounds(0, 11), masked) >= 22
+    many.rounds(11, 8)
+    with torch.cuda.stream(masked):
+        few.rounds(11, 8)
+    torch.cuda.synchronize()
+    for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status"):
+        assert torch.equal(getattr(many, name), getattr(few, name)), name
+    assert api._lib.hipStreamDestroy(handle) == 0
+
+
 @pytest.mark.parametrize("members", [0, 3])
 def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq, members):
     """A call of more rounds than one launch does, the model kept between the launches as between calls; also by fewer members."""
