@@ -752,6 +752,47 @@ def test_csr_rounds_of_uneven_rows_in_one_launch_equal_calls_of_a_few(dq, d, M, 
     assert host(many.x).any() and host(many.packed).any() and host(many.status)[0] == 0
 
 
+@pytest.mark.parametrize("members", [0, 3])
+@pytest.mark.parametrize("algo,each", [("asylpg", False), ("asylpg", True), ("acc", False)])
+@pytest.mark.parametrize("what", ["feature inf", "feature nan", "model", "margin", "long rows"])
+def test_csr_rounds_in_one_launch_on_what_is_not_finite(dq, what, algo, each, members):
+    """An infinity or NaN reaches the gradients (a feature of some rows, a cached margin; among more entries than the blocks hold) or comes
+    with the model: status, scales, messages and models are those of the separate rounds, NaNs where theirs are."""
+    from paper_1805_10111_amd.driver import DoubleQuantTrainer
+    d, M, B = 9500, 6, 8
+    long_rows = what == "long rows"
+    p = _problem_of_rows([40, 0, 9000, 5000, 700, 64, 9, 8200], d) if long_rows else synth.sparse_text_logistic(400, d, mean_nnz=30.0, seed=4)
+    if what.startswith("feature") or long_rows:
+        p.values = p.values.copy()
+        p.values[p.indptr[-2] if long_rows else slice(p.indptr[200], p.indptr[204])] = np.nan if "nan" in what else np.inf
+    P = dq.DeviceProblem.from_host(p)
+    if long_rows:
+        P._s.lda = 30 * p.n
+    many, few = (DoubleQuantTrainer(P, algo, M, B, 8, 8, 16, 0.1, seed=3, each=each) for _ in range(2))
+    for tr in (many, few):
+        tr.epoch_prologue()
+        tr.z_snap.nan_to_num_(0.0, 0.0, 0.0); tr.g_snap.nan_to_num_(0.0, 0.0, 0.0)         # (the rounds' own business only)
+        if what == "margin":
+            tr.z_snap[200:230] = float("nan")
+        tr.rounds(0, 3)
+        if what == "model":
+            tr.x[d - 1] = float("-inf")
+            if algo == "acc":
+                tr.y[d - 1] = float("-inf")
+    many.ws.view(torch.int32).fill_(-1)
+    if members:
+        _shared_rounds(dq, many, 3, 11, members)
+    else:
+        many.rounds(3, 11)
+    assert _joined(many)[0] == (0 if members else 32)
+    for t, n in ((3, 5), (8, 5), (13, 1)):
+        few.rounds(t, n)
+    for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
+        a, b = getattr(many, name), getattr(few, name)
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(), b.nan_to_num()), name
+    assert host(many.status)[0] == 1
+
+
 def test_csr_rounds_without_a_status_word_are_not_done_in_one_launch(dq):
     """The status word is how a caller learns that the blocks of such a launch gave up waiting for each other.  Without one each round has
     launches of its own, with the same results."""
