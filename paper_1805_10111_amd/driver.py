@@ -41,7 +41,9 @@ class DoubleQuantTrainer:
         self.xsum = torch.zeros(d, **f32)
         self.g_snap = torch.zeros(d, **f32)
         self.z_snap = torch.zeros(n, **f32) if cache_margins else None
-        self.obj = torch.zeros(1, dtype=torch.float64, device=dev)
+        # objective (a double) and status word side by side: one copy to the host tells both at the end of an epoch
+        self._report = torch.zeros(4, **i32)
+        self.obj, self.status = self._report[:2].view(torch.float64), self._report[2:3]
         self.xq_words = d if b_x == 32 else dq.packed_words(d, b_x)
         self.xq_stride = (self.xq_words + 3) // 4 * 4
         self.xq = torch.zeros((self.tau + 1) * self.xq_stride, **i32)     # ring of the last tau+1 model messages
@@ -52,7 +54,6 @@ class DoubleQuantTrainer:
         self.packed = torch.zeros((M, self.ld_words), **i32)
         self.delta = torch.zeros(M, **f32)
         self.nnz = torch.zeros((m, M), **i32)
-        self.status = torch.zeros(1, **i32)
         self.ws_full = dq.new_workspace(dq.OP_FULL_GRAD, prob)
         self.ws = dq.new_workspace(dq.OP_VR_GRAD, prob, M, B)
         self.epoch_index = 0
@@ -133,8 +134,9 @@ class DoubleQuantTrainer:
         """Objective at the epoch start and transmitted bits of the epoch (Section 3.1: 32 + b*d bits per
         quantized vector, 32*d unquantized; Section 4.2: position + value per nonzero of a sparsified one)."""
         d, M, m = self.prob.d, self.M, self.m
-        self.log.objectives.append(float(self.obj.item()))
-        self.check_status(scales=False)
+        report = self._report.cpu()
+        self.log.objectives.append(report[:2].view(torch.float64).item())
+        self.check_status(report[2:3], scales=False)
         self.log.rounds += m
         for flag in flags:
             self.log.bits_down += dq.dq_message_bits(dq.MSG_FLAG if flag else dq.MSG_DENSE, d, self.b_x)
@@ -151,10 +153,11 @@ class DoubleQuantTrainer:
         self.check_status()
         return self.log
 
-    def check_status(self, scales: bool = True) -> None:
-        """The status word's bits, each by its own name: bit 31 at the end of every epoch, since the epoch would go on from a
-        state that is not that of its rounds; bit 0 (`scales`) at the end of a run, whose numbers tell it anyway."""
-        bits = int(self.status.item()) & 0xFFFFFFFF
+    def check_status(self, word: Optional[torch.Tensor] = None, scales: bool = True) -> None:
+        """The status word's bits (`word`: a copy of it that the caller has), each by its own name: bit 31 at the end of every epoch,
+        since the next would go on from a state that is not that of its rounds; bit 0 (`scales`) at the end of a run, whose
+        numbers tell it anyway."""
+        bits = int((self.status if word is None else word).item()) & 0xFFFFFFFF
         if bits & 0x80000000:
             raise RuntimeError("dq_run_rounds: the blocks of a launch waited for each other for seconds and gave up; "
                                "the state is not that of the rounds asked for")

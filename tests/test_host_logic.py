@@ -228,6 +228,7 @@ def test_the_driver_names_what_the_status_word_says():
         for scales in (False, True):
             with pytest.raises(RuntimeError, match="gave up"):
                 tr.check_status(scales=scales)
-    tr.prob, tr.M, tr.m, tr.algo, tr.obj, tr.log = csr(), 2, 3, "asylpg", torch.zeros(1, dtype=torch.float64), RunLog()
+    tr.prob, tr.M, tr.m, tr.algo, tr.log = csr(), 2, 3, "asylpg", RunLog()
+    tr._report = torch.tensor([0, 0, -2 ** 31, 0], dtype=torch.int32)
     with pytest.raises(RuntimeError, match="gave up"):
         tr._account([False] * 3)
