@@ -2,7 +2,7 @@
 //
 // A round on bag-of-words rows moves little: 72,000 x 20,958, eight workers of 32 rows of 52 entries, 13,000 entries, a model and
 // eight gradients of 21,000 coordinates.  As launches (worker step, master) it is 11.4 us, of which the two launches and what each
-// needs to get under way are half; like this 9.6 us (284 rounds a call: 3234 us, now 2732).  The blocks stay, and a round is:
+// needs to get under way are half; like this 9.3 us (282 rounds a call: 3236 us, now 2680).  The blocks stay, and a round is:
 //   members that are worker m's slice s (the first M * S of them, see csr_worker_kernel's SLICED): the model's message into
 //     LDS, products, margins, coefficients, the slice's fixed-point sums, the slice of the gradient to memory (3.8 us)
 //   -- exchange, with the slices' maxima (1.2 us) -- every member for its columns, `chunks` * 256 of them, and all workers: quantize,
@@ -27,13 +27,13 @@
 namespace dq {
 
 constexpr int kNoRow = 0x7FFFFFFF;                        // where the rows past the last one begin
-constexpr int kReadAhead = 8;                             // entries that a thread has under way where it reads them in the round
+constexpr int kReadAhead = 4;                             // entries that a thread has under way where it reads them in the round
 
 static_assert(kBusyWaves == kCsrWaves - 1 && kBusy == kBusyWaves * kWave, "one wavefront waits at exchanges");
 
-// In the workspace; zero before the launches.
+// In the workspace; zero before the launch.
 struct CsrRoundsControl {
-    DieControl first, second;
+    DieControl die;
     uint32_t slice[kDieUnits];                           // SHARED: the slices' largest magnitudes
 };
 static_assert(sizeof(CsrRoundsControl) <= kRoundsControl, "room in the workspace");
@@ -56,7 +56,7 @@ struct CsrRoundsArgs {
     uint32_t *status;
     float *rows; int64_t ld;                             // M gradients
     CsrRoundsControl *ctl;
-    int want, join;                                      // parts; members that the second kernel wants
+    int want, join, shared;                              // parts; members wanted; SHARED whatever comes
 };
 
 struct CsrRoundsLds {
@@ -66,7 +66,7 @@ struct CsrRoundsLds {
     float amax[kDieUnits], delta[kDieUnits];             // of the workers' gradients: largest magnitude, scale
     uint32_t top[2][kCsrWaves];
     __align__(16) uint32_t message[kMostChunks * kChunk * 16 / 32];    // this member's part of the model's
-    int total, poison, dead, sh[2];
+    int total, poison, dead, sh[3];
     uint32_t slice_max, value;
 };
 static_assert(sizeof(CsrRoundsLds) + 512 <= kRoundsFixedLds, "static LDS");
@@ -74,21 +74,15 @@ static_assert(sizeof(CsrRoundsLds) + 512 <= kRoundsFixedLds, "static LDS");
 // The arguments, read again wherever they are used: more of them than there are scalar registers to keep them in.
 typedef const CsrRoundsArgs __attribute__((address_space(4))) *CsrRoundsArgsPtr;
 
+static __device__ uint32_t dies_taken[kDies];            // see die.h
+
 // A round has `want` parts, a range of columns and at most one slice of a worker each.  A member has one of them and keeps the
-// state of its columns in registers.  SHARED: where the first kernel's members were too few, those that this one finds, one
-// or more, have every `count`-th part each, one after the other, and keep the state in memory.
+// state of its columns in registers.  SHARED: where the members are too few, they have every `count`-th part each, one after the
+// other, and keep the state in memory.
 template <bool ACC, bool EACH, bool SHARED>
-__global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRoundsArgs)
+__device__ __forceinline__ void csr_rounds_of(int me, int count, CsrRoundsLds &l, float *lds, CsrRoundsArgsPtr a)
 {
-    extern __shared__ __align__(16) float lds[];
-    __shared__ CsrRoundsLds l;
-    CsrRoundsArgsPtr a = (CsrRoundsArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    if (SHARED && load_fresh(&a->ctl->first.members) == static_cast<uint32_t>(a->want)) return;
-    // (2 to 4 ms: kernels of other streams end meanwhile, and with the second kernel the rounds of a launch take as much longer)
-    constexpr long long kJoinTicks = 200000, kSharedTicks = 10000;
-    const DieMember die = SHARED ? die_join(&a->ctl->second, static_cast<uint32_t>(a->join), static_cast<uint32_t>(a->join + 1) / 2, kSharedTicks, l.sh)
-                                 : die_join(&a->ctl->first, static_cast<uint32_t>(a->want), 0u, kJoinTicks, l.sh);
-    if (die.me < 0 || (!SHARED && die.count != a->want)) return;
+    const DieMember die{&a->ctl->die, me, count};
     int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const bool messenger = wave == kCsrWaves - 1, planner = wave == kCsrWaves - 2;
     int d = static_cast<int>(a->A.d), M = a->M, B = a->B, b_x = a->b_x, chunks = a->chunks, C = chunks * kChunk;
@@ -397,7 +391,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 } else {
                     // ---- more entries than that: straight from memory, in the groups of rows that a step stages, by entries and not by
                     // rows, of which one can be most of the batch (a row a wavefront: 64 rows of lognormal length, sigma 2, 46.6 us a
-                    // round, now 21.3; 32 of 1000 entries 84, now 53)
+                    // round, now 20.2; 32 of 1000 entries 84, now 51)
                     const int row_ends[2] = {lane < B ? l.meta.pre[lane + 1] : kNoRow, lane + kWave < B ? l.meta.pre[lane + kWave + 1] : kNoRow};
 #pragma unroll 1
                     for (int g0 = 0, g1; g0 < B; g0 = g1) {
@@ -481,7 +475,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                                 if (beyond <= p0 || first >= p1 || first == beyond) continue;
                                 float sum_r = first < p0 ? part : 0.0f;
                                 const int to = min(beyond, p1) - p0;
-#pragma unroll 4
+#pragma unroll 2
                                 for (int e = max(first - p0, 0) + lane; e < to; e += kWave) sum_r += prod[e];
                                 if (beyond > p1) {
                                     part = sum_r;
@@ -757,7 +751,26 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
                 if (!planner || C > kBusy - kWave) draw_model_words(die.me, iter + 2u);
             }, [](uint32_t) {})) break;
     }
-    if (l.dead && t == 0) atomicOr(a->status, kGaveUp);
+    if (t == 0) {
+        if (l.dead) atomicOr(a->status, kGaveUp);
+        die_leave(dies_taken, l.sh);
+    }
+}
+
+template <bool ACC, bool EACH>
+__global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRoundsArgs)
+{
+    extern __shared__ __align__(16) float lds[];
+    __shared__ CsrRoundsLds l;
+    const CsrRoundsArgsPtr a = (CsrRoundsArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    // (2 to 4 ms: kernels of other streams end meanwhile, and with fewer members the rounds of a launch take as much longer: 20 us each
+    // with 16 to 31 of 32, 35 with 8, 65 with 4, 244 with one.  In the same kernel: as a second launch behind it, which mostly has nothing
+    // to do, it still had to wait for room on dies that other launches held)
+    constexpr long long kJoinTicks = 200000;
+    const DieMember die = die_join(&a->ctl->die, dies_taken, static_cast<uint32_t>(a->join), kJoinTicks, l.sh);
+    if (die.me < 0) return;
+    if (__builtin_expect(die.count == a->want && !a->shared, 1)) csr_rounds_of<ACC, EACH, false>(die.me, die.count, l, lds, a);
+    else csr_rounds_of<ACC, EACH, true>(die.me, die.count, l, lds, a);
 }
 
 // ------------------------------------------------------------------ host side
@@ -792,10 +805,17 @@ bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
     return csr_rounds_layout(prob, cfg, st, rounds, s) && whole_part(stream);
 }
 
-template <bool ACC, bool EACH, bool SHARED>
+// (for tests: no die is taken once all launches have ended)
+int32_t csr_rounds_dies_taken(uint32_t *host)
+{
+    DQ_HIP_TRY(hipMemcpyFromSymbol(host, HIP_SYMBOL(dies_taken), sizeof(dies_taken)));
+    return DQ_OK;
+}
+
+template <bool ACC, bool EACH>
 static int csr_rounds_launch(const CsrRoundsArgs &a, size_t lds, hipStream_t stream)
 {
-    const auto kernel = csr_rounds_kernel<ACC, EACH, SHARED>;
+    const auto kernel = csr_rounds_kernel<ACC, EACH>;
     static std::once_flag once;
     static hipError_t once_rc = hipSuccess;
     std::call_once(once, [&] {
@@ -803,7 +823,7 @@ static int csr_rounds_launch(const CsrRoundsArgs &a, size_t lds, hipStream_t str
                                       static_cast<int>(kRoundsLds));
     });
     DQ_HIP_TRY(once_rc);
-    kernel<<<dim3(8u * static_cast<unsigned>(SHARED ? a.join : a.want)), dim3(kCsrThreads), lds, stream>>>(a);
+    kernel<<<dim3(8u * static_cast<unsigned>(a.join)), dim3(kCsrThreads), lds, stream>>>(a);
     DQ_LAUNCH_CHECK();
     return DQ_OK;
 }
@@ -823,10 +843,8 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
     a.ld = pad4(prob->d);
     a.rows = static_cast<float *>(st->ws);
     a.ctl = reinterpret_cast<CsrRoundsControl *>(static_cast<char *>(st->ws) + csr_run_offset(prob->d, cfg->M));
-    // (32 find each other less often and take 12.1 us a round, 16 19.8, 8 35, one 245; nothing to do for 256 blocks is a wait for as many
-    // places where other work holds the part)
-    constexpr int kSharedMembers = 16;
-    a.join = std::min(members > 0 ? members : kSharedMembers, s.want);
+    a.join = members > 0 ? std::min(members, s.want) : s.want;
+    a.shared = members > 0;
     const size_t lds = static_cast<size_t>(s.lds);
     a.A = CsrView{prob->indptr, prob->indices, prob->values, prob->y, prob->n, prob->d};
     a.z_snap = st->z_snap;
@@ -847,8 +865,7 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
         if (rc != DQ_OK) return rc;
         const auto launch = [&](auto with_acc, auto each) {
             constexpr bool ACC = decltype(with_acc)::value, EACH = decltype(each)::value;
-            const int one = members > 0 ? DQ_OK : csr_rounds_launch<ACC, EACH, false>(a, lds, stream);
-            return one != DQ_OK ? one : csr_rounds_launch<ACC, EACH, true>(a, lds, stream);
+            return csr_rounds_launch<ACC, EACH>(a, lds, stream);
         };
         const std::true_type yes;
         const std::false_type no;

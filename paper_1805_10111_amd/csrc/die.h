@@ -9,13 +9,15 @@
 // What makes it sound:
 //  - Nobody waits without end for a block that may not have started.  A launch has `want` blocks for every die; each block
 //    adds itself to the count of the die that it finds itself on, the first die whose blocks are complete is the one, and all
-//    others end.  Two launches that begin together can each hold a part of every die: so after kPickTicks a launch picks the die
+//    others end.  Launches that begin together can each hold a part of every die: so after kPickTicks a launch picks the die
 //    where it has most blocks and gives up the others.  Where that one is not complete for `patience` either, because other
 //    work holds its compute units, it is closed with the blocks it has by then.  The members are running when the rounds begin,
-//    so whatever they wait for does happen; with fewer than it wants a kernel ends, and one behind it does the work with those
-//    that it finds.
-//  - Launches that hold equal parts pick among the dies by lot (two that always took the first would wait for each other, and
-//    neither be complete), and those that picked the same one all the same lose patience at different times, by lot again.
+//    so whatever they wait for does happen; where they are fewer than wanted they share the work.
+//  - A word a die, beside the library's code, says that a launch has picked it: others pick another one.  (Two with the same die would
+//    wait for each other, and neither be complete: four streams with calls of eight rounds took 25 to 35 us for a round of
+//    each, the same as launches 14.3, like this 14.4.)  The first member gives the die back.  A launch that finds all taken for
+//    `patience` picks one all the same; launches of several processes do not see each other's words: those that hold equal
+//    parts pick by lot, and those that picked the same one all the same lose patience at different times, by lot again.
 //  - Within a die the vector L1 caches write through to the die's L2: a store that has been waited for (vmcnt) is in L2, and
 //    a load with the sc1 bit, which does not look into L1, reads it there.  Data that one block leaves for another are
 //    read with load_fresh*, never with an ordinary load.  (Device-scope stores would go on to memory: 1.0 to 1.5 us.)
@@ -28,13 +30,13 @@
 
 namespace dq {
 
-constexpr long long kPickTicks = 3000;           // of the 100 MHz clock: 30 us
+constexpr long long kPickTicks = 1000;           // of the 100 MHz clock: 10 us (each call waits so long where several launches begin together)
 constexpr int kPolls = 1 << 23;
 constexpr uint32_t kGaveUp = 0x80000000u;        // in the status word
 
 // In device memory; all zero before the launch.
 struct DieControl {
-    uint32_t home;                               // 1 + the die; with kPicked and a lot, it is not complete yet
+    uint32_t home;                               // 1 + the die, whether the launch owns it; with kPicked and a lot: not complete yet
     uint32_t members;
     uint32_t joined[kDies];                      // top bit: closed
     uint32_t pad[34];                            // (the flags on cache lines that other dies' blocks do not touch)
@@ -78,25 +80,33 @@ __device__ __forceinline__ uint32_t die_number()
     return v & (kDies - 1);
 }
 
-// All threads of the block call it; sh: two words of LDS.  The die is closed after `patience` ticks (up to twice that, by lot), where
-// `enough` of the blocks are not there only after four times as many.
-__device__ __forceinline__ DieMember die_join(DieControl *ctl, uint32_t want, uint32_t enough, long long patience, int *sh)
+// All threads of the block call it; sh: three words of LDS, kept until die_leave; taken: a word a die, zero where no launch has picked it.  The die is
+// closed after `patience` ticks (up to twice that, by lot), where not even half of the blocks are there only after four times as many.
+__device__ __forceinline__ DieMember die_join(DieControl *ctl, uint32_t *taken, uint32_t want, long long patience, int *sh)
 {
+    constexpr uint32_t kClosed = 0x80000000u, kDieBits = 0xffu, kPicked = 0x100u, kOwned = 0x200u, kLotShift = 10, kLots = 8;
     if (threadIdx.x == 0) {
-        constexpr uint32_t kClosed = 0x80000000u, kPicked = 0x100u, kLotShift = 9, kLots = 8;
         const uint32_t die = die_number();
-        int me = -1, count = 0;
-        const auto swap_home = [&](uint32_t from, uint32_t to) {
-            return __hip_atomic_compare_exchange_strong(&ctl->home, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int me = -1, count = 0, owner = 0;
+        const auto swap = [&](uint32_t *p, uint32_t from, uint32_t to) {
+            return __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
-        const auto picked_here = [&](uint32_t home) { return (home & ((1u << kLotShift) - 1u)) == ((die + 1) | kPicked); };
+        const auto picked_here = [&](uint32_t home) { return (home & (kDieBits | kPicked)) == ((die + 1) | kPicked); };
+        // home = a die, if there is none yet; the first of the launches that want a die owns it
+        const auto claim = [&](uint32_t which, uint32_t more, bool owned_only) {
+            const bool own = swap(taken + which, 0u, 1u);
+            if (!own && owned_only) return false;
+            if (swap(&ctl->home, 0u, (which + 1) | more | (own ? kOwned : 0u))) return true;
+            if (own) __hip_atomic_store(taken + which, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        };
         const uint32_t ticket = __hip_atomic_fetch_add(&ctl->joined[die], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (ticket < want) {                             // (not closed, and not more than are wanted)
             // (a die whose blocks may have been told to end cannot become the one: `home` says another's number by then)
             const auto settle = [&] {
-                if (!swap_home(0u, die + 1)) {
+                if (!claim(die, 0u, false)) {
                     const uint32_t home = load_fresh(&ctl->home);
-                    if (!picked_here(home) || !swap_home(home, die + 1)) return;
+                    if (!picked_here(home) || !swap(&ctl->home, home, (die + 1) | (home & kOwned))) return;
                 }
                 const uint32_t c = __hip_atomic_fetch_or(&ctl->joined[die], kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&ctl->members, min(c, want), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -107,28 +117,37 @@ __device__ __forceinline__ DieMember die_join(DieControl *ctl, uint32_t want, ui
             while ((home = load_fresh(&ctl->home)) == 0 || picked_here(home)) {
                 const long long now = wall_clock64(), waited = now - start;
                 if (home == 0 && waited > kPickTicks) {
-                    const uint32_t lot = static_cast<uint32_t>(now), best = die_pick([&](uint32_t i) { return load_fresh(&ctl->joined[i]); }, die, lot);
-                    swap_home(0u, (best + 1) | kPicked | ((lot >> 3) % kLots) << kLotShift);
+                    const uint32_t lot = static_cast<uint32_t>(now);
+                    const uint32_t best = die_pick([&](uint32_t i) { return load_fresh(taken + i) ? 0u : load_fresh(&ctl->joined[i]); }, die, lot);
+                    claim(best, kPicked | ((lot >> 3) % kLots) << kLotShift, waited < patience);
                 }
                 if (home != 0) {
                     const long long limit = patience + (home >> kLotShift) * (patience / kLots);
-                    if (waited > limit && (load_fresh(&ctl->joined[die]) >= enough || waited > 4 * limit)) settle();
+                    if (waited > limit && (load_fresh(&ctl->joined[die]) >= (want + 1) / 2 || waited > 4 * limit)) settle();
                 }
                 __builtin_amdgcn_s_sleep(1);
             }
-            if (home == die + 1) {                       // (its members are counted by a block that is running)
+            if ((home & (kDieBits | kPicked)) == die + 1) {          // (its members are counted by a block that is running)
                 uint32_t n;
                 while ((n = load_fresh(&ctl->members)) == 0) __builtin_amdgcn_s_sleep(1);
                 me = static_cast<int>(ticket);           // (< n: it was counted, or home had been another die's)
                 count = static_cast<int>(n);
+                owner = ticket == 0 && (home & kOwned) != 0;
             }
         }
         sh[0] = me;
         sh[1] = count;
+        sh[2] = owner;
     }
     __syncthreads();
     // (the same for all: said so, or every loop over members is one whose lanes may part)
     return DieMember{ctl, __builtin_amdgcn_readfirstlane(sh[0]), __builtin_amdgcn_readfirstlane(sh[1])};
+}
+
+// At the end of a member, by one thread: the die is given back.
+__device__ __forceinline__ void die_leave(uint32_t *taken, const int *sh)
+{
+    if (sh[2]) __hip_atomic_store(taken + die_number(), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Every member has come this far, and what its wavefronts had stored and waited for (wait_for_memory) before this one's call can

@@ -129,10 +129,11 @@ bool small_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_
 int32_t small_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
                      int64_t rounds, float eta, float theta, bool flag_first, hipStream_t stream);
 
-// The same for CSR features (csr_rounds.hip).  members > 0: as if the first kernel had found too few, at most so many in the second.
+// The same for CSR features (csr_rounds.hip).  members > 0: as if no more of its blocks than that had found room on a die.
 bool csr_rounds_ok(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t rounds, hipStream_t stream);
 int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_run_state *st, int64_t epoch, int64_t t0,
                    int64_t rounds, float eta, float theta, bool flag_first, int members, hipStream_t stream);
+int32_t csr_rounds_dies_taken(uint32_t *host);
 
 // Quantizer and encoder of sparsified gradients in one launch (wire.hip), and the quads of a slice of them.
 int64_t sparse_parts_quads(int64_t d, int slices);

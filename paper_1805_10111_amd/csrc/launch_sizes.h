@@ -172,7 +172,7 @@ constexpr int kPasses = 2;                       // chunks of all workers that a
 constexpr int64_t kFewRounds = 8;                // calls of fewer are not for one die
 constexpr int64_t kRoundsFixedLds = 13360;       // static arrays
 constexpr int64_t kRoundsLds = 160 * 1024 - kRoundsFixedLds;  // for the dynamic part
-constexpr int64_t kRoundsControl = 1568;         // bytes of a run's workspace, from csr_run_offset on, for what the members share
+constexpr int64_t kRoundsControl = 848;          // bytes of a run's workspace, from csr_run_offset on, for what the members share
 
 static_assert(kMostChunks * kChunk <= kColumns * kBusy, "every column has a thread");
 
@@ -195,7 +195,7 @@ struct CsrRoundsShape {
 //    12.5, 15.2; five 11.8, 12.0; eight 11.6, 11.2.
 //  - mini-batches that the busy threads hold in registers, as far as the caller's count of entries can tell.  It cannot tell uneven
 //    rows, nor any where it is not given; larger batches are read in the round.  M 8, d 20,958, 64 rows of 50 entries in the mean,
-//    lognormal with sigma 1, 1.5 and 2: 14.8, 12.4; 21.2, 16.3; 31.2, 21.3; no count, 32 rows of 200 and of 1000: 26.4, 19.0; 86, 53.
+//    lognormal with sigma 1, 1.5 and 2: 14.8, 12.4; 20.7, 15.6; 29.5, 20.2; no count, 32 rows of 200 and of 1000: 26.6, 18.1; 87, 51.
 inline bool csr_rounds_shape(int64_t d, int64_t n, int64_t entries, int64_t M, int64_t B, int b_x, int64_t rounds, CsrRoundsShape &s)
 {
     const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };

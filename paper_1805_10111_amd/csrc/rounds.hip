@@ -205,6 +205,7 @@ extern "C" int32_t dq_test_run_rounds_shared(const dq_problem *prob, const dq_ru
     if (members < 1) return DQ_ERR_INVALID_ARG;
     return run_rounds(prob, cfg, st, epoch, t0, rounds, eta, theta, nullptr, members, stream);
 }
+extern "C" int32_t dq_test_dies_taken(uint32_t *host) { return dq::csr_rounds_dies_taken(host); }
 
 // Section 5.1 (parameters of Alg. 3 as used in the experiments): theta_s = 2/(s+2), eta_s = lr/theta_s, in float32.
 extern "C" int32_t dq_acc_params(float lr, int64_t s, float *theta_out, float *eta_out)

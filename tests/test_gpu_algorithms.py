@@ -661,15 +661,13 @@ ONE_DIE = [
 
 
 def _joined(tr):
-    """How many blocks the first and the second kernel of the trainer's last one-launch rounds found on their die."""
+    """How many blocks the trainer's last one-launch rounds found on their die."""
     words = tr.M * ((tr.prob.d + 3) // 4 * 4) + tr.M * 16
-    control = tr.ws.view(torch.int32)[words:]
-    return int(control[1]), int(control[181])
+    return int(tr.ws.view(torch.int32)[words + 1])
 
 
 def _shared_rounds(dq, tr, t0, count, members):
-    """The rounds of a call that takes one launch, as if the blocks of its first kernel had not found room on a die: by the second, with at
-    most `members`."""
+    """The rounds of a call that takes one launch, as if no more than `members` of its blocks had found room on a die."""
     import ctypes as C
     from paper_1805_10111_amd import api
     f = api._lib.dq_test_run_rounds_shared
@@ -689,7 +687,7 @@ def test_csr_rounds_in_one_launch_equal_calls_of_a_few(dq, d, M, B, algo, b, b_x
         for t, n in ((0, 11), (11, 8)):
             many.ws.view(torch.int32).fill_(-1)
             many.rounds(t, n)
-            assert _joined(many) == ({5: 1, 257: 2, 4097: 28, 7170: 29}.get(d, 32), 0), "the route, and every member on it"
+            assert _joined(many) == {5: 1, 257: 2, 4097: 28, 7170: 29}.get(d, 32), "the route, and every member on it"
         for t, n in ((0, 5), (5, 5), (10, 1), (11, 5), (16, 3)):
             few.rounds(t, n)
         for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
@@ -709,8 +707,7 @@ def test_csr_rounds_by_fewer_members_equal_calls_of_a_few(dq, d, M, B, algo, b, 
         for t, n in ((0, 11), (11, 8)):
             many.ws.view(torch.int32).fill_(-1)
             _shared_rounds(dq, many, t, n, members)
-            first, second = _joined(many)
-            assert first == 0 and 1 <= second <= members
+            assert 1 <= _joined(many) <= members
         for t, n in ((0, 5), (5, 5), (10, 1), (11, 5), (16, 3)):
             few.rounds(t, n)
         for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
@@ -744,7 +741,7 @@ def test_csr_rounds_of_uneven_rows_in_one_launch_equal_calls_of_a_few(dq, d, M, 
         _shared_rounds(dq, many, 0, 12, members)
     else:
         many.rounds(0, 12)
-    assert _joined(many)[0] == (0 if members else 32)
+    assert 1 <= _joined(many) <= members if members else _joined(many) == 32
     for t, n in ((0, 5), (5, 5), (10, 2)):
         few.rounds(t, n)
     for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
@@ -784,7 +781,7 @@ def test_csr_rounds_in_one_launch_on_what_is_not_finite(dq, what, algo, each, me
         _shared_rounds(dq, many, 3, 11, members)
     else:
         many.rounds(3, 11)
-    assert _joined(many)[0] == (0 if members else 32)
+    assert 1 <= _joined(many) <= members if members else _joined(many) == 32
     for t, n in ((3, 5), (8, 5), (13, 1)):
         few.rounds(t, n)
     for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status") + (("y", "xsum") if algo == "acc" else ()):
@@ -851,7 +848,9 @@ def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq, members):
 def test_csr_rounds_in_one_launch_on_several_streams_at_once(dq):
     """Three threads, a stream each, call at the same time, beside products that want the whole part: each of their launches finds a
     die, or waits for one, and the results are those of the separate rounds."""
+    import ctypes as C
     import threading
+    from paper_1805_10111_amd import api
     pairs = [_many_rounds_and_few(dq, d, M, 32, "asylpg", 8, 8, False, 30.0, 0, m=40) for d, M in ((20958, 8), (7000, 14), (4097, 20))]
     streams = [torch.cuda.Stream() for _ in range(len(pairs) + 1)]
     for many, few in pairs:
@@ -873,6 +872,8 @@ def test_csr_rounds_in_one_launch_on_several_streams_at_once(dq):
     for th in threads:
         th.join()
     torch.cuda.synchronize()
+    taken = np.full(16, 7, dtype=np.uint32)
+    assert api._lib.dq_test_dies_taken(taken.ctypes.data_as(C.c_void_p)) == 0 and not taken.any(), "every launch gives its die back"
     for many, few in pairs:
         for _ in range(5):
             for t in range(0, 40, 5):
