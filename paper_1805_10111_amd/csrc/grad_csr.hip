@@ -1097,8 +1097,8 @@ __global__ __launch_bounds__(kCsrThreads) void sparsify_parts_kernel(
 // rows of the chunk have theirs, one barrier gives the bound that fixes the unit of the fixed-point sums (FixedAcc),
 // and the same lanes add the rows' entries (from L2 now) to the columns.  A batch's first entries are requested before those
 // of the one before are used: a trip to memory less for each.  72,000 rows of 52 entries, 20,958
-// columns: 50.4 us with rows staged in LDS in groups of a hundred, five barrier-separated phases each; now 27.0 us;
-// 80,000 rows of 100 entries, 60,000 columns 236 -> 71 us; 40,000 rows of 20, 2000 columns 14.7 -> 13.4 us.
+// columns: 50.4 us with rows staged in LDS in groups of a hundred, five barrier-separated phases each; now 27.5 us by
+// itself and 29 inside epochs; 80,000 rows of 100 entries, 60,000 columns 236 -> 64 us; 40,000 rows of 20, 2000 columns 14.7 -> 13.4 us.
 constexpr int64_t kFullLds = 136 * 1024;                  // for the columns; 12.5 KB of static arrays beside them
 constexpr int kTogether = 256;                            // positions of a row up to here are its own lanes' work
 
