@@ -788,6 +788,8 @@ static bool csr_rounds_layout(const dq_problem *prob, const dq_run_config *cfg, 
 // die's 32 a call waits 2 to 4 ms for one and then does its rounds with what there is, 27 us each over 282 rounds; as launches 11.5.
 static bool whole_part(hipStream_t stream)
 {
+    // (default streams have no mask of their own; asked by this name for the legacy one's, the runtime crashes)
+    if (stream == hipStreamLegacy || stream == hipStreamPerThread) return true;
     uint32_t mask[32] = {};
     int dev = 0, units = 0, in_mask = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||

@@ -829,6 +829,27 @@ def test_csr_rounds_on_part_of_the_compute_units_are_not_done_in_one_launch(dq):
     assert api._lib.hipStreamDestroy(handle) == 0
 
 
+@pytest.mark.parametrize("stream", [0, 1, 2])
+def test_csr_rounds_on_the_default_streams(dq, stream):
+    """The null stream, hipStreamLegacy and hipStreamPerThread by their handles: one launch, as on any stream without a mask."""
+    import ctypes as C
+    from paper_1805_10111_amd import api
+    many, few = _many_rounds_and_few(dq, 4097, 8, 24, "asylpg", 8, 8, False, 30.0, 0)
+    for tr in (many, few):
+        tr.epoch_prologue()
+        tr.rounds(0, 1)
+    many.ws.view(torch.int32).fill_(-1)
+    torch.cuda.synchronize()
+    assert api._lib.dq_run_rounds(many.prob.ptr, C.byref(many.cfg), C.byref(many.state), C.c_int64(0), C.c_int64(1), C.c_int64(10),
+                                  C.c_float(many.eta), C.c_float(many.theta), None, C.c_void_p(stream)) == 0
+    torch.cuda.synchronize()
+    assert _joined(many) == 32
+    for t in (1, 6):
+        few.rounds(t, 5)
+    for name in ("packed", "delta", "x", "xq", "delta_x", "absmax_x", "status"):
+        assert torch.equal(getattr(many, name), getattr(few, name)), name
+
+
 @pytest.mark.parametrize("members", [0, 3])
 def test_csr_rounds_of_a_long_call_equal_calls_of_a_few(dq, members):
     """A call of more rounds than one launch does, the model kept between the launches as between calls; also by fewer members."""
