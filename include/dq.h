@@ -394,13 +394,14 @@ typedef struct dq_run_state {
  * hipEventElapsedTime over the pair is the kernel's own duration.  A flag-bit round leaves its pair
  * untouched; a pair of null handles makes that round's launch a plain one.  Pass null while `stream` is being
  * captured into a graph.
- * Rounds in few launches: on small dense problems, and on CSR features with mini-batches and a model that LDS has room for (Alg. 1 and 3,
- * eight rounds or more, with cached margins and a status word), a launch does many rounds, up to 512 on CSR features, without
- * worker_events.  On CSR features its blocks are one die's compute units, which have room for little else meanwhile: a kernel of another stream that has
- * blocks for that die ends only after them, up to 5 ms at 10 us a round.  Where other streams' work leaves no die free for 2 to 4 ms, the
- * rounds are done with the compute units that there are, 20 us each with 16 to 31 of a die's 32, 35 with 8.  Callers for whom
- * either is too long make calls of fewer than eight rounds.  Streams with a mask of compute units (hipExtStreamCreateWithCUMask)
- * have launches for each round; a graph takes what the stream of its capture does. */
+ * Rounds in few launches: on small dense problems, and on CSR features with mini-batches and a model that LDS has room for
+ * (Alg. 1 and 3, eight rounds or more, with cached margins and a status word), a launch does many rounds, up to 512 on CSR
+ * features, without worker_events.  On CSR features its blocks are one die's compute units, which have room for little else
+ * meanwhile: a kernel of another stream that has blocks for that die ends only after them, up to 5 ms at 10 us a round.  Where
+ * other streams' work leaves no die free for about as long as the rounds take, at most 2 to 4 ms, they are done with the
+ * compute units that there are, 20 us each with 16 to 31 of a die's 32, 35 with 8.  Callers for whom either is too long make
+ * calls of fewer than eight rounds.  Streams with a mask of compute units (hipExtStreamCreateWithCUMask) have launches for
+ * each round; a graph takes what the stream of its capture does. */
 int32_t dq_run_rounds(const dq_problem *prob /*host*/, const dq_run_config *cfg /*host*/, const dq_run_state *st /*host*/,
                       int64_t epoch, int64_t t0, int64_t rounds, float eta, float theta,
                       void **worker_events /*host*/, void *stream);

@@ -57,6 +57,7 @@ struct CsrRoundsArgs {
     float *rows; int64_t ld;                             // M gradients
     CsrRoundsControl *ctl;
     int want, join, shared;                              // parts; members wanted; SHARED whatever comes
+    int patience;                                        // see die_join
 };
 
 struct CsrRoundsLds {
@@ -763,11 +764,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rounds_kernel(const CsrRounds
     extern __shared__ __align__(16) float lds[];
     __shared__ CsrRoundsLds l;
     const CsrRoundsArgsPtr a = (CsrRoundsArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    // (2 to 4 ms: kernels of other streams end meanwhile, and with fewer members the rounds of a launch take as much longer: 20 us each
-    // with 16 to 31 of 32, 35 with 8, 65 with 4, 244 with one.  In the same kernel: as a second launch behind it, which mostly has nothing
-    // to do, it still had to wait for room on dies that other launches held)
-    constexpr long long kJoinTicks = 200000;
-    const DieMember die = die_join(&a->ctl->die, dies_taken, static_cast<uint32_t>(a->join), kJoinTicks, l.sh);
+    // (SHARED in the same kernel: as a second launch behind it, which mostly has nothing to do, it still had to wait for room on dies that
+    // other launches held)
+    const DieMember die = die_join(&a->ctl->die, dies_taken, static_cast<uint32_t>(a->join), a->patience, l.sh);
     if (die.me < 0) return;
     if (__builtin_expect(die.count == a->want && !a->shared, 1)) csr_rounds_of<ACC, EACH, false>(die.me, die.count, l, lds, a);
     else csr_rounds_of<ACC, EACH, true>(die.me, die.count, l, lds, a);
@@ -863,6 +862,10 @@ int32_t csr_rounds(const dq_problem *prob, const dq_run_config *cfg, const dq_ru
         a.iter0 = static_cast<uint32_t>(epoch * cfg->m + t0 + done);
         a.t0 = static_cast<int>((t0 + done) & 1); a.rounds = static_cast<int>(std::min(kMostRounds, rounds - done));
         a.flag_first = done == 0 && flag_first;
+        // About as long as the rounds take, 10 us each, at most 2 to 4 ms: kernels of other streams end meanwhile, and with fewer members
+        // the rounds take as much longer, 20 us each with 16 to 31 of 32, 35 with 8, 65 with 4, 244 with one.  (2 to 4 ms for calls of
+        // eight rounds too: four processes 17.6 us for a round of each, like this 14.5, as launches 14.0.)
+        a.patience = static_cast<int>(std::min<int64_t>(200000, 1000 * a.rounds));
         int rc = fill_u32(reinterpret_cast<uint32_t *>(a.ctl), sizeof(CsrRoundsControl) / 4, 0u, stream);
         if (rc != DQ_OK) return rc;
         const auto launch = [&](auto with_acc, auto each) {
